@@ -31,7 +31,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E bandwidth
 STAGES = {                      # kernels of one slim_decode call, in launch order, per variant
-    "generic": ["head_scores", "weighted_sum", "combine", "project"],
+    "generic": ["head_scores", "weighted_sum", "merge_project"],
+    "f32": ["f32_stream", "merge_project"],             # fp32 caches of up to 1024 columns and 32 heads, library's choice
     "fused": ["fused_stream", "project_mfma"],          # one launch when B <= 16: the second entry stays 0
     "fused_split": ["fused_stream", "project_mfma"],
 }
@@ -77,7 +78,7 @@ def calibration_copy(args, torch):
     del src, dst
 
 
-XCACHE_STAGES = ["q_tilde (head_scores on W_K)", "dense_scores", "weighted_sum", "combine", "project"]
+XCACHE_STAGES = ["q_tilde (head_scores on W_K)", "dense_scores", "weighted_sum", "merge_project"]
 XCACHE_MFMA_STAGES = ["xq_tilde", "xscores", "xweighted", "project_mfma"]     # two passes over X
 XCACHE_ONEPASS_STAGES = ["xq_tilde", "xfused", "project_mfma"]               # 512 <= d_model <= 1280
 
@@ -120,8 +121,8 @@ def bench_xcache(args, cfg, torch, binding, synth, emit=True):
         slim(i, stage_ms=stage)
         acc += np.array(list(stage))
     acc /= args.steps
-    # three launches: q~, the one-pass kernel, projection; four: two passes over X; five: the plain kernels
-    names = XCACHE_ONEPASS_STAGES if acc[3] == 0.0 else (XCACHE_MFMA_STAGES if acc[4] == 0.0 else XCACHE_STAGES)
+    # three launches: q~, the one-pass kernel, projection; four: two passes over X, or the plain kernels
+    names = XCACHE_ONEPASS_STAGES if acc[3] == 0.0 else (XCACHE_STAGES if args.variant == "generic" else XCACHE_MFMA_STAGES)
     dom = int(np.argmax(acc[:len(names)]))
     # dense contractions over all heads: priced against the bf16 MFMA peak with the method's own
     # flop counts (the hi + lo split of q~ doubles the MFMA work of the scores; not counted)
@@ -444,7 +445,7 @@ def bench_kcache(args, cfg, torch, binding, synth, with_cpu):
         vacc += vstage[0]
     vacc /= args.steps
 
-    names = list(STAGES[which])
+    names = list(STAGES["f32" if which == "generic" and acc[2] == 0.0 else which])
     k_bytes = float(lens.astype(np.int64).sum()) * d * es            # K-cache rows read once
     w_bytes = float(d) * d * es                                       # W_KV once per step
     one_launch = which == "fused" and acc[1] == 0.0                   # B <= 16: merge + projection inside
@@ -460,7 +461,7 @@ def bench_kcache(args, cfg, torch, binding, synth, with_cpu):
     if one_launch:
         names = ["fused_stream"]
     dom = int(np.argmax(acc[:len(names)]))
-    alg_bytes = {"project": w_bytes, "project_mfma": w_bytes}.get(names[dom], k_bytes + rope_bytes + (w_bytes if one_launch else 0.0))
+    alg_bytes = {"merge_project": w_bytes, "project_mfma": w_bytes}.get(names[dom], k_bytes + rope_bytes + (w_bytes if one_launch else 0.0))
     kern_s = acc[dom] * 1e-3
     achieved = alg_bytes / kern_s / 1e9
     roofline = {"bound": "hbm", "kernel": names[dom] + (" (one launch: stream + merge + projection)" if one_launch else ""),

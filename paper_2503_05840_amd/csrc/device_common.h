@@ -1,5 +1,5 @@
-// Device helpers shared by the kernel files (kernels_bf16.hip, kernels_xcache.hip, kernels_generic.hip): vector types,
-// the clamped sequence length, the in-register 8 x 8 transposition that turns a lane's block of a
+// Device helpers shared by the kernel files (kernels_bf16.hip, kernels_xcache.hip, kernels_f32.hip,
+// kernels_generic.hip): vector types, the clamped sequence length, a barrier for LDS exchanges, the in-register 8 x 8 transposition that turns a lane's block of a
 // row-major tile into MFMA operands, and loop helpers whose register buffers are picked at compile time.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -20,6 +20,34 @@ __device__ __forceinline__ int seq_len_of(const int32_t* lens, int b, int T) {
   if (!lens) return T;
   const int n = lens[b];
   return n < 0 ? 0 : (n > T ? T : n);
+}
+
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for its
+// global loads (__syncthreads() would also drain the tiles that are being prefetched from HBM).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// v + (v of the lane selected by a DPP control inside the 16-lane row); one v_add_f32_dpp
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+
+// max over the 32 lanes that share lane / 32: four DPP steps inside the 16-lane row (lane ^ 1, lane ^ 2,
+// the other quad of the 8-lane half, the other half of the row), then the row 16 lanes away by a register swap
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ float max_over_32(float v) {
+  v = dpp_max<0xB1>(v);
+  v = dpp_max<0x4E>(v);
+  v = dpp_max<0x141>(v);
+  v = dpp_max<0x140>(v);
+  const unsigned u = __float_as_uint(v);
+  const auto sw = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
 // 8 rows x 8 bf16 columns per lane  ->  8 operands (one per column), each 8 rows of that column.

@@ -43,12 +43,6 @@ constexpr float LOG2E = 1.4426950408889634f;
 __device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
 
-// v + (v of the lane selected by a DPP control inside the 16-lane row); one v_add_f32_dpp
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-
 // max over the four lanes l, l^16, l^32, l^48 (the same column group in the four row groups).
 // Register swaps (v_permlane32_swap / v_permlane16_swap), no LDS traffic.
 __device__ __forceinline__ float max_over_row_groups(float v) {

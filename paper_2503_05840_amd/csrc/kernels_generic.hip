@@ -6,8 +6,8 @@
 //   head_scores   : softmax arguments q_i K_i^T / sqrt(d_k)                 (eq. 2)
 //   weighted_sum  : [softmax(.) K], the full-width weighted sum of K rows   (eq. 7, option 2)
 //                   per split of the context, with a local max (flash-decoding style)
-//   combine       : log-sum-exp merge of the splits and the 1/l normalisation
-//   project       : ... W_KV,i per head                                     (eq. 7, option 2)
+//   merge_project : log-sum-exp merge of the splits, 1/l, and ... W_KV,i per head   (eq. 7, option 2)
+//   project       : a plain product with a weight matrix                    (eq. 1, 3-5 for one row)
 //   vanilla_*     : softmax(.) V_i reading both caches                      (eq. 2; Table 2 "Vanilla")
 //   dense_scores  : (q_i W_K,i^T) X^T for the X-cache scheme                (non-square section, Fig. 4)
 #include "slim_kernels.h"
@@ -34,6 +34,7 @@ struct F32 {
     v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
   }
   static __device__ __forceinline__ float one(const elem* p) { return *p; }
+  static __device__ __forceinline__ void four(const elem* p, float (&v)[4]) { load(p, v); }
   static __device__ __forceinline__ void two(const elem* p, float& a, float& b) {
     const float2 x = *reinterpret_cast<const float2*>(p);
     a = x.x; b = x.y;
@@ -64,6 +65,11 @@ struct BF16 {
   static __device__ __forceinline__ float one(const elem* p) {
     return __uint_as_float(((uint32_t)*p) << 16);
   }
+  static __device__ __forceinline__ void four(const elem* p, float (&v)[4]) {
+    const uint2 x = *reinterpret_cast<const uint2*>(p);
+    v[0] = __uint_as_float(x.x << 16); v[1] = __uint_as_float(x.x & 0xffff0000u);
+    v[2] = __uint_as_float(x.y << 16); v[3] = __uint_as_float(x.y & 0xffff0000u);
+  }
   static __device__ __forceinline__ void two(const elem* p, float& a, float& b) {
     const uint32_t x = *reinterpret_cast<const uint32_t*>(p);
     a = __uint_as_float(x << 16); b = __uint_as_float(x & 0xffff0000u);
@@ -85,7 +91,8 @@ template <class ET>
 __global__ __launch_bounds__(256) void head_scores_kernel(
     const float* __restrict__ q, long q_bstride, const typename ET::elem* __restrict__ M,
     long m_bstride, long row_pitch, const int32_t* __restrict__ rows_per_b, int rows, int e, int H,
-    int d_k, float scale, float* __restrict__ S, long s_bstride, const float* __restrict__ rope) {
+    int d_k, float scale, float* __restrict__ S, long s_bstride, const float* __restrict__ rope, int* counters,
+    int ncounters) {
   extern __shared__ float smem[];
   constexpr int VEC = ET::VEC;
   const int nvec = e / VEC;
@@ -95,6 +102,9 @@ __global__ __launch_bounds__(256) void head_scores_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nrows = seq_len_of(rows_per_b, b, rows);
   const int r0 = blockIdx.x * HS_ROWS;
+  // (the arrival counters of the projection that ends this call start at 0)
+  if (blockIdx.x == 0 && b == 0)
+    for (int i = tid; i < ncounters; i += 256) counters[i] = 0;
   if (r0 >= nrows) return;
   for (int i = tid; i < e; i += 256) q_s[i] = q[b * q_bstride + i];
   __syncthreads();
@@ -293,52 +303,179 @@ __global__ __launch_bounds__(256) void weighted_sum_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// combine: merge the splits (log-sum-exp weights) and normalise.
+// merge + projection on the vector ALU:  out[b][h d_k + j] = sum_c C[b][h][c] W[c][h d_k + j] with C merged from
+// the context splits (log-sum-exp weights, 1 / l) on the fly.
+// One workgroup (4 waves) per (head and block of 64 of its columns, row split of W, 4 sequences): per 64 rows c it
+// requests its 64 x 64 block of W, merges C of its 4 sequences x 64 rows (a lane per row, the splits dealt to the
+// waves in fours) while W travels, and multiplies from LDS; row groups and waves are summed in a fixed order, row splits by
+// the last workgroup to arrive (as in the MFMA projection: write-through stores, agent-scope loads).
+// Bound by the length of this chain, not by bytes: the row splits are what fills the chip (one kernel that merged
+// to memory and one with a workgroup per 64 columns took 7.4 + 40.3 us for 4 sequences x 16 heads x 1024 rows with
+// up to 12 splits each; this one 13.2 us with up to 47, most of it round trips).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ Cpart,
-                                                      const float* __restrict__ mpart,
-                                                      const float* __restrict__ lpart, int nsplit,
-                                                      int H, int width, float* __restrict__ Cn) {
-  const int b = blockIdx.y;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long)H * width) return;
-  const int h = (int)(i / width);
-  const int c = (int)(i % width);
-  float m = NEG_INF;
-  for (int s = 0; s < nsplit; ++s) m = fmaxf(m, mpart[((long)b * nsplit + s) * H + h]);
-  float num = 0.f, den = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const long pb = ((long)b * nsplit + s) * H + h;
-    const float ms = mpart[pb];
-    const float w = (ms == NEG_INF) ? 0.f : __expf(ms - m);
-    num = fmaf(w, Cpart[pb * width + c], num);
-    den = fmaf(w, lpart[pb], den);
+constexpr int MP_ROWS = 64, MP_COLS = 64, MP_NB = 4, MP_SPLITS = 4;
+
+template <class ET>
+__global__ __launch_bounds__(256) void merge_project_kernel(
+    const float* __restrict__ Cpart, const float* __restrict__ mpart, const float* __restrict__ lpart, int nsplit,
+    int own_splits, const int32_t* __restrict__ seq_lens, int T, const typename ET::elem* __restrict__ W, int rows, int e,
+    int H, int d_k, float* __restrict__ out, float* outpart, int row_splits, int crows, int* counters, int B) {
+  __shared__ float wgt[MP_NB][MERGE_MAX_SPLITS];
+  __shared__ int nsp[MP_NB];
+  __shared__ float cs[MP_NB][MP_ROWS];
+  __shared__ float red[4][MP_NB][MP_COLS];
+  __shared__ int is_last;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int ncb = (d_k + MP_COLS - 1) / MP_COLS;
+  const int h = blockIdx.x / ncb, j0 = (blockIdx.x - h * ncb) * MP_COLS;
+  const int b0 = blockIdx.z * MP_NB, nb = min(MP_NB, B - b0);
+  const int c_lo = blockIdx.y * crows, c_hi = min(rows, c_lo + crows);
+  const int idx = tid & 15, rg = tid >> 4;              // four columns of rows rg + 16 i
+  const bool col_ok = j0 + idx * 4 < d_k;               // (d_k is a multiple of 4)
+  const typename ET::elem* Wc = W + (size_t)h * d_k + j0 + (col_ok ? idx * 4 : 0);
+  float wv[4][4];
+  auto load_w = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ET::four(Wc + (size_t)min(c0 + rg + 16 * i, rows - 1) * e, wv[i]);
+  };
+  // splits of the four sequences (wave-uniform)
+  int ns4[MP_NB];
+#pragma unroll
+  for (int q = 0; q < MP_NB; ++q) {
+    ns4[q] = nsplit;
+    if (own_splits) {
+      const int len = seq_len_of(seq_lens, min(b0 + q, B - 1), T), per = f32_rows_per_split(len, nsplit);
+      ns4[q] = per > 0 ? (len + per - 1) / per : 0;
+    }
+    if (q >= nb) ns4[q] = 0;
   }
-  Cn[((long)b * H + h) * width + c] = num / den;
+  load_w(c_lo);                                         // in flight while the weights of the splits are built
+
+  {                                                     // one wave per sequence, a lane per split
+    const int b = min(b0 + w, B - 1);
+    const int ns = w == 0 ? ns4[0] : w == 1 ? ns4[1] : w == 2 ? ns4[2] : ns4[3];
+    float mp = NEG_INF, lp = 0.f;
+    if (lane < ns) {
+      mp = mpart[((size_t)b * nsplit + lane) * H + h];
+      lp = lpart[((size_t)b * nsplit + lane) * H + h];
+    }
+    float M = mp;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o));
+    const float wg = (mp == NEG_INF) ? 0.f : __expf(mp - M);
+    float L = wg * lp;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) L += __shfl_xor(L, o);
+    wgt[w][lane] = wg / L;
+    if (lane == 0) nsp[w] = ns;
+  }
+  __syncthreads();
+
+  float acc[MP_NB][4];
+#pragma unroll
+  for (int q = 0; q < MP_NB; ++q)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[q][c] = 0.f;
+  for (int c0 = c_lo; c0 < c_hi; c0 += MP_ROWS) {
+    // C of row c0 + lane: this wave's share of every sequence's splits, four splits of four sequences per round trip
+    // (wave-uniform bases and clamped split indices: one load instruction each, no branches)
+    float cv[MP_NB];
+#pragma unroll
+    for (int q = 0; q < MP_NB; ++q) cv[q] = 0.f;
+    const int cl = min(c0 + lane, rows - 1);
+    for (int s0 = wu * MP_SPLITS; s0 < nsplit; s0 += 4 * MP_SPLITS) {
+      float x[MP_NB][MP_SPLITS];
+#pragma unroll
+      for (int q = 0; q < MP_NB; ++q)
+#pragma unroll
+        for (int u = 0; u < MP_SPLITS; ++u)
+          x[q][u] = Cpart[((size_t)(min(b0 + q, B - 1) * nsplit + min(s0 + u, max(ns4[q] - 1, 0))) * H + h) * rows + cl];
+#pragma unroll
+      for (int q = 0; q < MP_NB; ++q)
+#pragma unroll
+        for (int u = 0; u < MP_SPLITS; ++u) cv[q] = s0 + u < ns4[q] ? fmaf(wgt[q][s0 + u], x[q][u], cv[q]) : cv[q];
+    }
+#pragma unroll
+    for (int q = 0; q < MP_NB; ++q) red[w][q][lane] = cv[q];
+    __syncthreads();
+    {
+      const float sum = red[0][w][lane] + red[1][w][lane] + red[2][w][lane] + red[3][w][lane];
+      cs[w][lane] = c0 + lane < c_hi ? (nsp[w] > 0 ? sum : NAN) : 0.f;      // (no row at all: 0 / 0)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < MP_NB; ++q) {
+        const float x = cs[q][rg + 16 * i];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[q][c] = fmaf(x, wv[i][c], acc[q][c]);
+      }
+    if (c0 + MP_ROWS < c_hi) load_w(c0 + MP_ROWS);
+    __syncthreads();
+  }
+  // the four row groups of a wave, then the waves
+#pragma unroll
+  for (int q = 0; q < MP_NB; ++q)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float v = acc[q][c];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lane < 16) red[w][q][idx * 4 + c] = v;
+    }
+  __syncthreads();
+  const bool mine = w < nb && j0 + lane < d_k;           // sequence b0 + w, column j0 + lane of the head
+  const size_t col = (size_t)(b0 + w) * e + (size_t)h * d_k + j0 + lane;
+  const float sum = red[0][w][lane] + red[1][w][lane] + red[2][w][lane] + red[3][w][lane];
+  if (row_splits == 1) {
+    if (mine) out[col] = sum;
+    return;
+  }
+  if (mine) {
+    float* dst = outpart + (size_t)blockIdx.y * B * e + col;
+    asm volatile("global_store_dword %0, %1, off sc0 sc1" : : "v"(dst), "v"(sum) : "memory");
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  int* const counter = counters + blockIdx.z * gridDim.x + blockIdx.x;
+  if (tid == 0) is_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == row_splits - 1;
+  __syncthreads();
+  if (!is_last) return;
+  float total = 0.f;
+  if (mine)
+    for (int s0 = 0; s0 < row_splits; s0 += 8) {
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        x[u] = __hip_atomic_load(outpart + (size_t)min(s0 + u, row_splits - 1) * B * e + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) total += s0 + u < row_splits ? x[u] : 0.f;
+    }
+  if (mine) out[col] = total;
 }
 
 // ------------------------------------------------------------------------------------------------
-// project: out[b][n] = sum_c Cn[b][n/d_k][c] W[c][n].  Workgroup = 64 output columns x 4 batch
+// project: out[b][n] = sum_c x[b][c] W[c][n] (the products either side of the decode step).  Workgroup = 64 output columns x 4 batch
 // rows; its 16 waves interleave over c, eight rows of W in flight per wave, and are summed through
 // LDS in a fixed order.
 // ------------------------------------------------------------------------------------------------
 constexpr int PROJ_WAVES = 16, PROJ_UNROLL = 8;
 
 template <class ET>
-__global__ __launch_bounds__(PROJ_WAVES * 64) void project_kernel(const float* __restrict__ Cn,
+__global__ __launch_bounds__(PROJ_WAVES * 64) void project_kernel(const float* __restrict__ x,
                                                                  const typename ET::elem* __restrict__ W,
-                                                                 int rows, int e, int H, int d_k,
-                                                                 float* __restrict__ out, int B) {
+                                                                 int rows, int e, float* __restrict__ out, int B) {
   __shared__ float red[PROJ_WAVES][4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + lane;
   const int b0 = blockIdx.y * 4;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   if (n < e) {
-    const int h = n / d_k;
     const float* cp[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cp[j] = Cn + ((long)min(b0 + j, B - 1) * H + h) * rows;
+    for (int j = 0; j < 4; ++j) cp[j] = x + (long)min(b0 + j, B - 1) * rows;
     const typename ET::elem* wn = W + n;
     int c = wave;
     const bool one_row = b0 + 1 >= B;                  // (a single sequence: no loads for the three rows that repeat it)
@@ -720,18 +857,19 @@ __global__ __launch_bounds__(256) void vanilla_combine_kernel(const float* __res
 // ------------------------------------------------------------------------------------------------
 void launch_head_scores(int dtype, const float* q, long q_bstride, const void* M, long m_bstride,
                         long row_pitch, const int32_t* rows_per_b, int rows, int e, int H, int d_k,
-                        float scale, float* S, long s_bstride, const float* rope, int B, hipStream_t st) {
+                        float scale, float* S, long s_bstride, const float* rope, int* counters, int ncounters, int B,
+                        hipStream_t st) {
   dim3 grid((rows + HS_ROWS - 1) / HS_ROWS, B);
   const int nvec = e / vec_elems(dtype);
   const size_t smem = sizeof(float) * ((size_t)e + 4 * (size_t)nvec);
   if (dtype == DT_BF16) {
     (void)hipFuncSetAttribute((const void*)head_scores_kernel<BF16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     hipLaunchKernelGGL(head_scores_kernel<BF16>, grid, dim3(256), smem, st, q, q_bstride,
-                       (const uint16_t*)M, m_bstride, row_pitch, rows_per_b, rows, e, H, d_k, scale, S, s_bstride, rope);
+                       (const uint16_t*)M, m_bstride, row_pitch, rows_per_b, rows, e, H, d_k, scale, S, s_bstride, rope, counters, ncounters);
   } else {
     (void)hipFuncSetAttribute((const void*)head_scores_kernel<F32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     hipLaunchKernelGGL(head_scores_kernel<F32>, grid, dim3(256), smem, st, q, q_bstride,
-                       (const float*)M, m_bstride, row_pitch, rows_per_b, rows, e, H, d_k, scale, S, s_bstride, rope);
+                       (const float*)M, m_bstride, row_pitch, rows_per_b, rows, e, H, d_k, scale, S, s_bstride, rope, counters, ncounters);
   }
 }
 
@@ -761,19 +899,41 @@ void launch_weighted_sum(int dtype, const float* S, const void* M, long m_bstrid
                        m_bstride, width, seq_lens, T, H, nsplit, ncolblk, Cpart, mpart, lpart);
 }
 
-void launch_combine(const float* Cpart, const float* mpart, const float* lpart, int nsplit, int H,
-                    int width, float* Cn, int B, hipStream_t st) {
-  dim3 grid((unsigned)(((long)H * width + 255) / 256), B);
-  hipLaunchKernelGGL(combine_kernel, grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, H, width, Cn);
+// Workgroups of a launch before the rows of W are split = arrival counters of the launch.
+long merge_counters(int H, int d_k, int B) { return (long)H * ((d_k + MP_COLS - 1) / MP_COLS) * ((B + MP_NB - 1) / MP_NB); }
+
+// Row splits: up to two workgroups per compute unit, 64 rows each at least; none where the arrivals would not fit
+// the counters.
+int merge_row_splits(int H, int d_k, int rows, int B, int max_counters) {
+  const long per = merge_counters(H, d_k, B);
+  if (per > max_counters) return 1;
+  int rs = (int)(512 / per);
+  const int most = (rows + MP_ROWS - 1) / MP_ROWS;
+  if (rs > most) rs = most;
+  if (rs < 1) rs = 1;
+  const int crows = ((rows + rs - 1) / rs + MP_ROWS - 1) / MP_ROWS * MP_ROWS;
+  return (rows + crows - 1) / crows;
 }
 
-void launch_project(int dtype, const float* Cn, const void* W, int rows, int e, int H, int d_k,
-                    float* out, int B, hipStream_t st) {
+void launch_merge_project(int dtype, const float* Cpart, const float* mpart, const float* lpart, int nsplit, bool own_splits,
+                          const int32_t* seq_lens, int T, const void* W, int rows, int e, int H, int d_k, float* out,
+                          float* outpart, int row_splits, int* counters, int B, hipStream_t st) {
+  const int crows = ((rows + row_splits - 1) / row_splits + MP_ROWS - 1) / MP_ROWS * MP_ROWS;
+  dim3 grid(H * ((d_k + MP_COLS - 1) / MP_COLS), row_splits, (B + MP_NB - 1) / MP_NB);
+  if (dtype == DT_BF16)
+    hipLaunchKernelGGL(merge_project_kernel<BF16>, grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, (int)own_splits, seq_lens, T,
+                       (const uint16_t*)W, rows, e, H, d_k, out, outpart, row_splits, crows, counters, B);
+  else
+    hipLaunchKernelGGL(merge_project_kernel<F32>, grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, (int)own_splits, seq_lens, T,
+                       (const float*)W, rows, e, H, d_k, out, outpart, row_splits, crows, counters, B);
+}
+
+void launch_project(int dtype, const float* x, const void* W, int rows, int e, float* out, int B, hipStream_t st) {
   dim3 grid((e + 63) / 64, (B + 3) / 4);
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(project_kernel<BF16>, grid, dim3(PROJ_WAVES * 64), 0, st, Cn, (const uint16_t*)W, rows, e, H, d_k, out, B);
+    hipLaunchKernelGGL(project_kernel<BF16>, grid, dim3(PROJ_WAVES * 64), 0, st, x, (const uint16_t*)W, rows, e, out, B);
   else
-    hipLaunchKernelGGL(project_kernel<F32>, grid, dim3(PROJ_WAVES * 64), 0, st, Cn, (const float*)W, rows, e, H, d_k, out, B);
+    hipLaunchKernelGGL(project_kernel<F32>, grid, dim3(PROJ_WAVES * 64), 0, st, x, (const float*)W, rows, e, out, B);
 }
 
 void launch_append(int dtype, const float* knew, const float* vnew, void* K, void* V, long bstride,

@@ -27,12 +27,6 @@ __device__ __forceinline__ void split_hi_lo(const float (&x)[8], bf16x8& hi, bf1
   }
 }
 
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for its
-// global loads (__syncthreads() would also drain the tiles that are being prefetched from HBM).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Workgroup i of a one-dimensional launch -> (unit, inner): a unit is a set of `ninner` workgroups that read
 // the same data (a sequence's q~ or scores, the same rows of X).  Workgroups are dealt to the 8 XCDs round
 // robin, each with an L2 of its own, so with `colocate` a unit's workgroups are the ones with the same
@@ -501,22 +495,6 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
 // heads (d_model <= 1280: three waves on two of the four SIMDs, hence 168 registers, which hold half
 // the accumulators and the hi halves of q~; the lo halves wait in LDS).
 // ------------------------------------------------------------------------------------------------
-// max over the 32 lanes that share lane / 32: four DPP steps inside the 16-lane row (lane ^ 1, lane ^ 2,
-// the other quad of the 8-lane half, the other half of the row), then the row 16 lanes away by a register swap
-template <int CTRL>
-__device__ __forceinline__ float dpp_max(float v) {
-  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true)));
-}
-__device__ __forceinline__ float max_over_32(float v) {
-  v = dpp_max<0xB1>(v);
-  v = dpp_max<0x4E>(v);
-  v = dpp_max<0x141>(v);
-  v = dpp_max<0x140>(v);
-  const unsigned u = __float_as_uint(v);
-  const auto sw = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-}
-
 constexpr int XF_PITCH = 272;            // bytes per parked row: 256 + 16 of padding
 constexpr int XF_RED_HS = 36;            // floats per head row of a wave's partial scores (32 rows + padding that keeps 16-byte stores)
 constexpr int XF_P_HS = 40;              // bf16 per head row of the numerators (32 rows + padding)

@@ -22,13 +22,15 @@ struct Plan {
   int nsplit_v = 1;    // context splits of the vanilla kernel
   int nsplit_x = 1;    // context splits of the X-cache MFMA path (two passes over X)
   int nsplit_xf = 0;   // context splits of the one-pass X-cache kernel (0: the shape does not take it)
-  size_t off_S = 0, off_Cpart = 0, off_m = 0, off_l = 0, off_Cn = 0, off_qt = 0;
+  size_t off_S = 0, off_Cpart = 0, off_m = 0, off_l = 0, off_qt = 0;
   size_t off_vacc = 0, off_vm = 0, off_vl = 0;
   size_t off_exch = 0, off_outpart = 0, off_ctrl = 0;   // bf16 fast path
   bool fused_ok = false;
   FusedGeom geom{};
   int csw = 1;         // row splits of W_KV in the MFMA projection (its own launch)
   int csw_f = 0;       // same, when the stream kernel's workgroups do the projection (0: not possible)
+  int nsplit_f = 1;    // context splits of the fp32 stream kernel
+  int rsplit = 1;      // row splits of W_KV in the vector-ALU merge + projection
   size_t total = 0;
 };
 
@@ -38,7 +40,8 @@ constexpr int CTRL_INTS = 4096;
 
 int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-Plan make_plan(int B, int H, int T, int width, int e) {
+// `lean`: no more partials than the other kernels of the shape need anyway, one row split (see make_plan).
+Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
   Plan p;
   const int ncolblk = (width + 511) / 512, nhb = (H + 31) / 32;
   const long per_split = (long)B * ncolblk * nhb;
@@ -57,6 +60,11 @@ Plan make_plan(int B, int H, int T, int width, int e) {
   if ((size_t)B * p.nsplit_xf > nparts) nparts = (size_t)B * p.nsplit_xf;
   if (p.fused_ok && (size_t)p.geom.nparts > nparts) nparts = p.geom.nparts;
   if (p.fused_ok && (size_t)B * 4 > nparts && fused_by_sequence(p.geom, B, false)) nparts = (size_t)B * 4;
+  p.nsplit_f = f32_stream_splits(B, T);
+  const int d_k = e >= H ? e / H : 1;                  // (sizes are asked for with any arguments)
+  p.rsplit = lean ? 1 : merge_row_splits(H, d_k, width, B, CTRL_INTS / 2);
+  if (lean && (size_t)B * p.nsplit_f > nparts) p.nsplit_f = (int)(nparts / B);
+  if (f32_stream_ok(DT_F32, H, width, d_k) && (size_t)B * p.nsplit_f > nparts) nparts = (size_t)B * p.nsplit_f;
   p.csw = proj_row_splits(H, width, e, B);
   if (p.fused_ok && B <= 16 && p.geom.grid >= H) {
     const int tiles_w = (width + TILE_ROWS - 1) / TILE_ROWS;
@@ -66,13 +74,14 @@ Plan make_plan(int B, int H, int T, int width, int e) {
   p.off_Cpart = o;  o += up(sizeof(float) * nparts * H * width);
   p.off_m = o;      o += up(sizeof(float) * nparts * H);
   p.off_l = o;      o += up(sizeof(float) * nparts * H);
-  p.off_Cn = o;     o += up(sizeof(float) * (size_t)B * H * width);
   p.off_qt = o;     o += up(sizeof(float) * (size_t)B * ((H + 15) / 16 * 16) * width);   // (whole tiles of 16 heads)
   p.off_vacc = o;   o += up(sizeof(float) * (size_t)B * p.nsplit_v * e);
   p.off_vm = o;     o += up(sizeof(float) * (size_t)B * p.nsplit_v * H);
   p.off_vl = o;     o += up(sizeof(float) * (size_t)B * p.nsplit_v * H);
   if (p.fused_ok) { p.off_exch = o; o += up(fused_exch_bytes(p.geom)); }
-  p.off_outpart = o; o += up(sizeof(float) * (size_t)(p.csw > p.csw_f ? p.csw : p.csw_f) * B * e);
+  int parts = p.csw > p.csw_f ? p.csw : p.csw_f;
+  if (p.rsplit > parts) parts = p.rsplit;
+  p.off_outpart = o; o += up(sizeof(float) * (size_t)parts * B * e);
   p.total = o;
   return p;
 }
@@ -82,6 +91,14 @@ Plan make_plan(int B, int H, int T, int width, int e) {
 // from hipGetSymbolAddress at set-up (device_state) and is what kernels, copies and queries are given.
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)SLIM_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
+
+// The lean plan where only that one fits the static scratch: every shape it can hold stays accepted.
+Plan make_plan(int B, int H, int T, int width, int e) {
+  const Plan p = make_plan_at(B, H, T, width, e, false);
+  if (p.total <= STATIC_SCRATCH_BYTES) return p;
+  const Plan lean = make_plan_at(B, H, T, width, e, true);
+  return lean.total <= STATIC_SCRATCH_BYTES ? lean : p;
+}
 
 // Per-device set-up, done once (slim_init, else the first call that needs it) under a lock: the
 // address of the static scratch, the compute-unit count, whether workgroup i of a launch runs on XCD
@@ -313,7 +330,6 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   float* Cpart = (float*)(ws + p.off_Cpart);
   float* mpart = (float*)(ws + p.off_m);
   float* lpart = (float*)(ws + p.off_l);
-  float* Cn = (float*)(ws + p.off_Cn);
   const long kb = t_stride * d;
 
   StageTimer tm(o, st);
@@ -380,33 +396,43 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     tm.finish();
     return launch_status();
   }
-  launch_head_scores(dtype, (const float*)q, d, Kcache, kb, d, lens, T, d, H, d_k, scale, S,
-                     (long)H * T, rope, B, st);
-  tm.mark();
-  launch_weighted_sum(dtype, S, Kcache, kb, d, lens, T, H, p.nsplit, Cpart, mpart, lpart, B, st);
-  tm.mark();
-  // Shapes the stream kernel does not take (more than 32 heads, very large batches) still get the MFMA
-  // merge + projection when the head width allows it; an explicit request for the plain kernels keeps
-  // every step on the vector ALU.
   const int requested = o ? o->variant : SLIM_VARIANT_AUTO;
-  if (dtype == SLIM_BF16 && requested != SLIM_VARIANT_GENERIC && d_k % 8 == 0 && d_k <= 128 &&
-      (long)H * ((B + 15) / 16) < CTRL_INTS / 2) {
-    int* ctrl = (int*)(ws + p.off_ctrl);
-    launch_zero_ints(ctrl, CTRL_INTS / 2, st);
-    ProjArgs pa{};
-    pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_KV;
-    pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
-    pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.nsplit = p.nsplit; pa.mode = 1; pa.mscale = 1.4426950408889634f;      // natural-log maxima
-    pa.csw = p.csw;
-    launch_project_mfma(pa, st);
+  int* const ctrl = (int*)(ws + p.off_ctrl);
+  float* const outpart = (float*)(ws + p.off_outpart);
+  const int arrivals = p.rsplit > 1 ? (int)merge_counters(H, d_k, B) : 0;
+  if (requested != SLIM_VARIANT_GENERIC && f32_stream_ok(dtype, H, d, d_k)) {
+    // fp32: one kernel to the partials, one to the result (an explicit request for the plain kernels gets those)
+    launch_f32_stream((const float*)q, (const float*)Kcache, kb, lens, T, H, d, d_k, p.nsplit_f, scale, rope, Cpart, mpart, lpart,
+                      ctrl, arrivals, B, st);
+    tm.mark();
+    launch_merge_project(dtype, Cpart, mpart, lpart, p.nsplit_f, true, lens, T, W_KV, d, d, H, d_k, (float*)out, outpart, p.rsplit,
+                         ctrl, B, st);
     tm.mark();
     tm.finish();
     return launch_status();
   }
-  launch_combine(Cpart, mpart, lpart, p.nsplit, H, d, Cn, B, st);
+  // Shapes the stream kernel does not take (more than 32 heads, very large batches) still get the MFMA
+  // merge + projection when the head width allows it; an explicit request for the plain kernels keeps
+  // every step on the vector ALU.
+  const bool mfma_projection = dtype == SLIM_BF16 && requested != SLIM_VARIANT_GENERIC && d_k % 8 == 0 && d_k <= 128 &&
+                               (long)H * ((B + 15) / 16) < CTRL_INTS / 2;
+  launch_head_scores(dtype, (const float*)q, d, Kcache, kb, d, lens, T, d, H, d_k, scale, S,
+                     (long)H * T, rope, ctrl, mfma_projection ? H * ((B + 15) / 16) : arrivals, B, st);
   tm.mark();
-  launch_project(dtype, Cn, W_KV, d, d, H, d_k, (float*)out, B, st);
+  launch_weighted_sum(dtype, S, Kcache, kb, d, lens, T, H, p.nsplit, Cpart, mpart, lpart, B, st);
+  tm.mark();
+  if (mfma_projection) {
+    ProjArgs pa{};
+    pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_KV;
+    pa.out = (float*)out; pa.outpart = outpart; pa.counters = ctrl;
+    pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
+    pa.nsplit = p.nsplit; pa.mode = 1; pa.mscale = 1.4426950408889634f;      // natural-log maxima
+    pa.csw = p.csw;
+    launch_project_mfma(pa, st);
+  } else {
+    launch_merge_project(dtype, Cpart, mpart, lpart, p.nsplit, false, lens, T, W_KV, d, d, H, d_k, (float*)out, outpart, p.rsplit,
+                         ctrl, B, st);
+  }
   tm.mark();
   tm.finish();
   return launch_status();
@@ -506,7 +532,6 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
   float* Cpart = (float*)(ws + p.off_Cpart);
   float* mpart = (float*)(ws + p.off_m);
   float* lpart = (float*)(ws + p.off_l);
-  float* Cn = (float*)(ws + p.off_Cn);
   float* qt = (float*)(ws + p.off_qt);
   const long xb = t_stride * d_model;
 
@@ -545,16 +570,16 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     return launch_status();
   }
   // qt[b][h][c] = sum_j q[b][h d_k + j] W_K[c][h d_k + j]   ("rows" of W_K scored against q)
+  int* const ctrl = (int*)(ws + p.off_ctrl);
   launch_head_scores(dtype, (const float*)q, e, W_K, 0, e, nullptr, d_model, e, H, d_k, 1.0f, qt,
-                     (long)H * d_model, nullptr, B, st);
+                     (long)H * d_model, nullptr, ctrl, p.rsplit > 1 ? (int)merge_counters(H, d_k, B) : 0, B, st);
   tm.mark();
   launch_dense_scores(dtype, qt, X, xb, d_model, lens, T, H, scale, S, B, st);
   tm.mark();
   launch_weighted_sum(dtype, S, X, xb, d_model, lens, T, H, p.nsplit, Cpart, mpart, lpart, B, st);
   tm.mark();
-  launch_combine(Cpart, mpart, lpart, p.nsplit, H, d_model, Cn, B, st);
-  tm.mark();
-  launch_project(dtype, Cn, W_V, d_model, e, H, d_k, (float*)out, B, st);
+  launch_merge_project(dtype, Cpart, mpart, lpart, p.nsplit, false, lens, T, W_V, d_model, e, H, d_k, (float*)out,
+                       (float*)(ws + p.off_outpart), p.rsplit, ctrl, B, st);
   tm.mark();
   tm.finish();
   return launch_status();
@@ -642,9 +667,9 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
     pa.rope = rope; pa.rotate_k = slim_path ? 0 : 1;
     launch_dense_mfma(pa, st);
   } else {
-    launch_project(dtype, (const float*)c.x, c.W_Q, d, d, 1, d, q, B, st);      // one "head" as wide as the matrix
-    launch_project(dtype, (const float*)c.x, c.W_K, d, d, 1, d, knew, B, st);
-    if (!slim_path) launch_project(dtype, (const float*)c.x, c.W_V, d, d, 1, d, vnew, B, st);
+    launch_project(dtype, (const float*)c.x, c.W_Q, d, d, q, B, st);
+    launch_project(dtype, (const float*)c.x, c.W_K, d, d, knew, B, st);
+    if (!slim_path) launch_project(dtype, (const float*)c.x, c.W_V, d, d, vnew, B, st);
     launch_append(dtype, knew, slim_path ? nullptr : vnew, c.Kcache, slim_path ? nullptr : c.Vcache,
                   t_stride * d, lens, T, d, d_k, rope, q, slim_path ? 0 : 1, B, st);
   }
@@ -670,7 +695,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
     pa.Wm[0] = (const uint16_t*)c.W_O; pa.outm[0] = (float*)c.y; pa.role[0] = 0;
     launch_dense_mfma(pa, st);
   } else {
-    launch_project(dtype, attn, c.W_O, d, d, 1, d, (float*)c.y, B, st);
+    launch_project(dtype, attn, c.W_O, d, d, (float*)c.y, B, st);
   }
   tm.mark();
   tm.finish();

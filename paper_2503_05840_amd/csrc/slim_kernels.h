@@ -17,10 +17,11 @@ inline int elem_bytes(int dtype) { return dtype == DT_BF16 ? 2 : 4; }
 // S[b][h][r] = scale * sum_j q[b][h*d_k + j] * M[b][r][h*d_k + j]   for r < rows_b
 // (attention scores against a K-cache, eq. 2; also q_h W_K,h^T for the X-cache scheme with
 //  M := W_K, rows := d_model, m_bstride := 0).  rope: nullable [rows][d_k/2] {cos, sin}; when set,
-// row r is rotated by position r before the dot product (RoPE appendix, option 1).
+// row r is rotated by position r before the dot product (RoPE appendix, option 1).  Zeroes `ncounters` counters.
 void launch_head_scores(int dtype, const float* q, long q_bstride, const void* M, long m_bstride,
                         long row_pitch, const int32_t* rows_per_b, int rows, int e, int H, int d_k,
-                        float scale, float* S, long s_bstride, const float* rope, int B, hipStream_t st);
+                        float scale, float* S, long s_bstride, const float* rope, int* counters, int ncounters, int B,
+                        hipStream_t st);
 
 // S[b][h][t] = scale * sum_c qt[b][h][c] * X[b][t][c]   (X-cache scores, Fig. 4)
 void launch_dense_scores(int dtype, const float* qt, const void* X, long x_bstride, int d_model,
@@ -32,13 +33,31 @@ void launch_weighted_sum(int dtype, const float* S, const void* M, long m_bstrid
                          const int32_t* seq_lens, int T, int H, int nsplit, float* Cpart,
                          float* mpart, float* lpart, int B, hipStream_t st);
 
-// Cn[b][h][c] = sum_s e^{m_s - m} Cpart_s[h][c] / sum_s e^{m_s - m} l_s
-void launch_combine(const float* Cpart, const float* mpart, const float* lpart, int nsplit,
-                    int H, int width, float* Cn, int B, hipStream_t st);
+// Splits of one sequence that one wave of the merge looks after (a lane per split).
+constexpr int MERGE_MAX_SPLITS = 64;
 
-// out[b][n] = sum_c Cn[b][n / d_k][c] * W[c][n],  W row-major [rows][e]
-void launch_project(int dtype, const float* Cn, const void* W, int rows, int e, int H, int d_k,
-                    float* out, int B, hipStream_t st);
+// Merge + projection:  C[b][h] = sum_s e^{m_s - m} Cpart[b][s][h] / sum_s e^{m_s - m} l_s,
+// out[b][n] = sum_c C[b][n / d_k][c] W[c][n],  W row-major [rows][e].  own_splits: sequence b has
+// ceil(len_b / f32_rows_per_split(len_b)) splits (kernels_f32.hip), else nsplit.  The rows of W are shared by
+// row_splits workgroups (merge_row_splits); with more than one, outpart [row_splits][B][e] and
+// merge_counters(...) counters that are 0 on entry.
+long merge_counters(int H, int d_k, int B);
+int merge_row_splits(int H, int d_k, int rows, int B, int max_counters);
+void launch_merge_project(int dtype, const float* Cpart, const float* mpart, const float* lpart, int nsplit, bool own_splits,
+                          const int32_t* seq_lens, int T, const void* W, int rows, int e, int H, int d_k, float* out,
+                          float* outpart, int row_splits, int* counters, int B, hipStream_t st);
+
+// out[b][n] = sum_c x[b][c] W[c][n],  W row-major [rows][e]
+void launch_project(int dtype, const float* x, const void* W, int rows, int e, float* out, int B, hipStream_t st);
+
+// ---- fp32 caches of up to 1024 columns (kernels_f32.hip) ---------------------------------------
+// Partials as launch_weighted_sum's (natural logarithms) from one kernel; zeroes `ncounters` counters.
+bool f32_stream_ok(int dtype, int H, int d, int d_k);
+int f32_stream_splits(int B, int T);
+__host__ __device__ inline int f32_rows_per_split(int len, int nsplit) { return ((len + nsplit - 1) / nsplit + 31) / 32 * 32; }
+void launch_f32_stream(const float* q, const float* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int d_k,
+                       int nsplit, float scale, const float* rope, float* Cpart, float* mpart, float* lpart, int* counters,
+                       int ncounters, int B, hipStream_t st);
 
 // New token rows into the caches at row len_b - 1: K <- knew (rotated to that position when rope and
 // rotate_k), V <- vnew (nullable: no V-cache); with rope, q [B][d] is rotated in place as well.
