@@ -299,17 +299,25 @@ __global__ __launch_bounds__(512) void xscores_kernel(const uint16_t* qt, const 
 // ------------------------------------------------------------------------------------------------
 constexpr float XW_SLACK = 6.0f;
 
+// NT: head tiles of 16 per workgroup.  FULL: the weights enter the matrix product as three bf16 terms (8 + 8 + 8
+// bits: exactly the fp32 value) and their sum is taken in fp32 on the vector ALU -- the wide K-cache path, whose
+// weights are fp32; otherwise rounded to bf16 once.  (FULL is 3 MFMAs where there was one; the matrix cores are idle
+// most of the time here.)  At 40 heads x 5120 columns, 6503 rows: 28.0 us, K coming from the memory-side cache, where
+// the vector-ALU kernel took 99.8; the whole step 197.8 -> 59.8 us.
+template <int NT, bool FULL>
 __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const uint16_t* X, long x_bstride,
                                                         const int32_t* seq_lens, int T, int B, int H, int dm, int nsplit,
                                                         float* Cpart, float* mpart, float* lpart, int colocate) {
-  constexpr int NT = 2, NW = 8;
-  __shared__ float red[NW][NT][4][8][64];              // [wave][head tile][r][i][lane]: 128 KB
+  constexpr int NW = 8;
+  constexpr int TP = NT <= 2 ? NT : 1;                 // head tiles merged at once: 64 KB of LDS each
+  static_assert(NT <= 3, "registers");
+  __shared__ float red[NW][TP][4][8][64];              // [wave][head tile][r][i][lane]
   __shared__ float msh[NW][NT * 16], lsh[NW][NT * 16];
   // unit = (sequence, context split): its workgroups read the same rows of X (one column block each, for
   // every head group) and the same scores (one head group each, for every column block)
   const int ncb = dm / 128;
   int unit, inner;
-  if (!unit_of_workgroup(blockIdx.x, ((H + 31) / 32) * ncb, B * nsplit, colocate != 0, unit, inner)) return;
+  if (!unit_of_workgroup(blockIdx.x, ((H + NT * 16 - 1) / (NT * 16)) * ncb, B * nsplit, colocate != 0, unit, inner)) return;
   const int b = unit / nsplit, s = unit - b * nsplit;
   const int cbk = inner % ncb, hg = inner / ncb;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -325,7 +333,7 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
   auto row_of = [&](int k) { return r_lo + 32 * (w + NW * k); };
 
   float m[NT];
-  f32x4 acc[8][NT], accl[NT];
+  f32x4 acc[8][NT], accl[NT];                          // (FULL: accl[t][0] is this lane's share of the sum)
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     m[t] = NEG_INF;
@@ -352,7 +360,7 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
     const int row = r0 + kg * 8;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int h = min(hg * 32 + t * 16 + n, H - 1);
+      const int h = min(hg * (NT * 16) + t * 16 + n, H - 1);
       const float* src = S + ((size_t)b * H + h) * Tp + row;
       x[t][0] = *reinterpret_cast<const f32x4*>(src);
       x[t][1] = *reinterpret_cast<const f32x4*>(src + 4);
@@ -362,7 +370,8 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
   // compile-time index).  A step's work is short next to the latency of a load, so what it needs must
   // have been requested several steps earlier.  Loads past the end re-read the last tile (unused) so that
   // every step issues the same loads and the compiler can wait for exactly the ones a step needs.
-  constexpr int D = 2, DS = 2, UN = 2;                 // X sets, score sets, steps per unrolled group (a common multiple)
+  // Three head tiles leave registers for one set of each; a step is long enough there (2000 cycles a wave).
+  constexpr int D = NT <= 2 ? 2 : 1, DS = D, UN = 2;   // X sets, score sets, steps per unrolled group (a common multiple)
   u32x4 xt[D][8];
   f32x4 sc[DS][NT][2];
   if (ntile > 0) {
@@ -371,51 +380,91 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
 #pragma unroll
     for (int j = 0; j < D; ++j) load_tile(xt[j], row_of(min(j, ntile - 1)));
   }
+  // weights of head tile t from its scores (first row of the lane: row), the state of its softmax moved on
+  auto weights = [&](int t, const f32x4 (&sx)[2], int row, u32x4 (&pb)[FULL ? 3 : 1]) {
+    const int live = (hg * (NT * 16) + t * 16 + n < H) ? r_hi - row : 0;   // rows of this lane that count
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = j < live ? sx[j >> 2][j & 3] : NEG_INF;
+    float tmax = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    // The reference the weights are taken against moves only when the maximum has grown by more than
+    // XW_SLACK (log2 domain): weights stay below 2^XW_SLACK, which costs bf16 and the fp32 sums nothing,
+    // and the accumulators are rescaled rarely instead of at nearly every tile.
+    const float mn = (tmax > m[t] + XW_SLACK) ? tmax : m[t];
+    const float ref = (mn == NEG_INF) ? 0.f : mn;
+    const float alpha = __builtin_amdgcn_exp2f(m[t] - ref);
+    float psum = 0.f;
+    if constexpr (FULL) {
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(x[j] - ref), p1 = __builtin_amdgcn_exp2f(x[j + 1] - ref);
+        psum += p0 + p1;
+        unsigned u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+        pb[0][j / 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);          // the upper halves: the value truncated to 8 bits
+        const float q0 = p0 - __uint_as_float(u0 & 0xffff0000u), q1 = p1 - __uint_as_float(u1 & 0xffff0000u);
+        u0 = __float_as_uint(q0); u1 = __float_as_uint(q1);
+        pb[1][j / 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+        const float o0 = q0 - __uint_as_float(u0 & 0xffff0000u), o1 = q1 - __uint_as_float(u1 & 0xffff0000u);
+        pb[2][j / 2] = __builtin_amdgcn_perm(__float_as_uint(o1), __float_as_uint(o0), 0x07060302u);   // (8 bits are left)
+      }
+    } else {
+      bf16x8 pv;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pv[j] = (__bf16)__builtin_amdgcn_exp2f(x[j] - ref);
+      pb[0] = __builtin_bit_cast(u32x4, pv);
+    }
+    m[t] = mn;
+    if (__any(alpha != 1.f)) {
+      accl[t] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i][t] *= alpha;
+    }
+    if constexpr (FULL) accl[t][0] += psum;
+  };
   auto step = [&](int k, auto SI) {
     constexpr int si = decltype(SI)::value;
     u32x4 (&cur)[8] = xt[si % D];
     f32x4 (&sx)[NT][2] = sc[si % DS];
     const int row = row_of(k) + kg * 8;
-    bf16x8 pb[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int live = (hg * 32 + t * 16 + n < H) ? r_hi - row : 0;   // rows of this lane that count
-      float x[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = j < live ? sx[t][j >> 2][j & 3] : NEG_INF;
-      float tmax = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-      // The reference the weights are taken against moves only when the maximum has grown by more than
-      // XW_SLACK (log2 domain): weights stay below 2^XW_SLACK, which costs bf16 and the fp32 sums nothing,
-      // and the accumulators are rescaled rarely instead of at nearly every tile.
-      const float mn = (tmax > m[t] + XW_SLACK) ? tmax : m[t];
-      const float ref = (mn == NEG_INF) ? 0.f : mn;
-      const float alpha = __builtin_amdgcn_exp2f(m[t] - ref);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pb[t][j] = (__bf16)__builtin_amdgcn_exp2f(x[j] - ref);
-      m[t] = mn;
-      if (__any(alpha != 1.f)) {
-        accl[t] *= alpha;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i][t] *= alpha;
-      }
-    }
     u32x4 am[8];
-    transpose8x8(cur, am);
-    // both sets are free again: the scores of the wave's tile k + DS first, then X of its tile k + D
-    load_scores(sx, row_of(min(k + DS, ntile - 1)));
-    load_tile(cur, row_of(min(k + D, ntile - 1)));
-    const u32x4 ones_bits = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+    if constexpr (FULL) {
+      // one head tile after the other: only its own terms of the weights are live
+      transpose8x8(cur, am);
+      load_tile(cur, row_of(min(k + D, ntile - 1)));
 #pragma unroll
-    for (int t = 0; t < NT; ++t) accl[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[t], accl[t], 0, 0, 0);
+      for (int t = 0; t < NT; ++t) {
+        u32x4 pb[3];
+        weights(t, sx[t], row, pb);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
+        for (int o = 2; o >= 0; --o)                      // (the smallest terms first)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, am[i]), __builtin_bit_cast(bf16x8, pb[o]),
+                                                                acc[i][t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      load_scores(sx, row_of(min(k + DS, ntile - 1)));
+    } else {
+      u32x4 pb[NT][1];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) weights(t, sx[t], row, pb[t]);
+      transpose8x8(cur, am);
+      // both sets are free again: the scores of the wave's tile k + DS first, then X of its tile k + D
+      load_scores(sx, row_of(min(k + DS, ntile - 1)));
+      load_tile(cur, row_of(min(k + D, ntile - 1)));
+      const u32x4 ones_bits = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+      const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
 #pragma unroll
       for (int t = 0; t < NT; ++t)
-        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pb[t], acc[i][t], 0, 0, 0);
+        accl[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pb[t][0]), accl[t], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, am[i]), __builtin_bit_cast(bf16x8, pb[t][0]),
+                                                              acc[i][t], 0, 0, 0);
     }
   };
   int k = 0;
@@ -429,42 +478,55 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
     for (int t = 0; t < NT; ++t) msh[w][t * 16 + n] = m[t];
   }
   __syncthreads();
-  float mall[NT];
+  float mall[NT], wsc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     float mm = NEG_INF;
 #pragma unroll
     for (int ww = 0; ww < NW; ++ww) mm = fmaxf(mm, msh[ww][t * 16 + n]);
     mall[t] = mm;
-    const float sc = (m[t] == NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(m[t] - mm);
-    if (kg == 0) lsh[w][t * 16 + n] = accl[t][0] * sc;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[w][t][r][i][lane] = acc[i][t][r] * sc;
+    wsc[t] = (m[t] == NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(m[t] - mm);
+    float lw = accl[t][0] * wsc[t];
+    if constexpr (FULL) {                               // the four row groups' shares
+      lw += __shfl_xor(lw, 16);
+      lw += __shfl_xor(lw, 32);
+    }
+    if (kg == 0) lsh[w][t * 16 + n] = lw;
   }
-  __syncthreads();
-  // thread (t, r, lane): columns col0 + (rg*4 + r)*8 .. +7 of head hg*32 + t*16 + n
-  {
-    const int t = w >> 2, r = w & 3;
-    const int h = hg * 32 + t * 16 + n;
-    float o[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+  for (int t0 = 0; t0 < NT; t0 += TP) {
+    if (t0 > 0) __syncthreads();                        // (the tiles before have been read)
+#pragma unroll
+    for (int tt = 0; tt < TP; ++tt)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[w][tt][r][i][lane] = acc[i][t0 + tt][r] * wsc[t0 + tt];
+    __syncthreads();
+    // thread (tt, r, lane): columns col0 + (rg*4 + r)*8 .. +7 of head tile t0 + tt, head n; with one tile at a time the
+    // two halves of the waves take four of the eight columns each
+    constexpr int IC = TP == 2 ? 8 : 4;
+    const int tt = TP == 2 ? w >> 2 : 0, i0 = TP == 2 ? 0 : (w >> 2) * 4, r = w & 3;
+    const int h = hg * (NT * 16) + (t0 + tt) * 16 + n;
+    float o[IC];
+#pragma unroll
+    for (int i = 0; i < IC; ++i) {
       float sum = 0.f;
 #pragma unroll
-      for (int ww = 0; ww < NW; ++ww) sum += red[ww][t][r][i][lane];
+      for (int ww = 0; ww < NW; ++ww) sum += red[ww][tt][r][i0 + i][lane];
       o[i] = sum;
     }
     if (h < H) {
-      float* dst = Cpart + ((size_t)pid * H + h) * dm + col0 + (rg * 4 + r) * 8;
+      float* dst = Cpart + ((size_t)pid * H + h) * dm + col0 + (rg * 4 + r) * 8 + i0;
       *reinterpret_cast<f32x4*>(dst) = f32x4{o[0], o[1], o[2], o[3]};
-      *reinterpret_cast<f32x4*>(dst + 4) = f32x4{o[4], o[5], o[6], o[7]};
-      if (cbk == 0 && r == 0 && kg == 0) {
-        float l = 0.f;
+      if constexpr (IC == 8) *reinterpret_cast<f32x4*>(dst + 4) = f32x4{o[4], o[5], o[6], o[7]};
+      if (cbk == 0 && r == 0 && kg == 0 && i0 == 0) {
+        float l = 0.f, mh = NEG_INF;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) l += lsh[ww][t * 16 + n];
-        mpart[(size_t)pid * H + h] = mall[t];
+        for (int ww = 0; ww < NW; ++ww) l += lsh[ww][(t0 + tt) * 16 + n];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) mh = t == t0 + tt ? mall[t] : mh;
+        mpart[(size_t)pid * H + h] = mh;
         lpart[(size_t)pid * H + h] = l;
       }
     }
@@ -804,8 +866,39 @@ void launch_xweighted(const float* S, const void* X, long x_bstride, const int32
                       int d_model, int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
   const int ninner = ((H + 31) / 32) * (d_model / 128), colocate = colocate_units(B * nsplit);
   dim3 grid(unit_grid(B * nsplit, ninner, colocate));
-  hipLaunchKernelGGL(xweighted_kernel, grid, dim3(512), 0, st, S, (const uint16_t*)X, x_bstride, seq_lens, T, B, H,
+  hipLaunchKernelGGL((xweighted_kernel<2, false>), grid, dim3(512), 0, st, S, (const uint16_t*)X, x_bstride, seq_lens, T, B, H,
                      d_model, nsplit, Cpart, mpart, lpart, colocate);
+}
+
+// The wide K-cache path: head tiles per workgroup.  Three where that saves a pass over K (33..48, 65..96 heads, ...),
+// else two, which leaves registers for a second tile in flight.
+static int kweighted_tiles(int H) {
+  const int tiles = (H + 15) / 16;
+  return (tiles + 2) / 3 < (tiles + 1) / 2 ? 3 : 2;
+}
+
+// One round of workgroups (one per compute unit: 8 waves of 256 registers), eight tiles of rows each at least.
+int kweighted_splits(int B, int H, int T, int d) {
+  const int nt = kweighted_tiles(H);
+  const long per = (long)B * ((H + nt * 16 - 1) / (nt * 16)) * (d / 128 > 0 ? d / 128 : 1);
+  int s = (int)(256 / per);
+  const int cap = (T + 255) / 256;
+  if (s > cap) s = cap;
+  if (s > PROJ_MAX_PARTS) s = PROJ_MAX_PARTS;
+  return s < 1 ? 1 : s;
+}
+
+void launch_kweighted(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
+                      float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
+  const int nt = kweighted_tiles(H);
+  const int ninner = ((H + nt * 16 - 1) / (nt * 16)) * (d / 128), colocate = colocate_units(B * nsplit);
+  dim3 grid(unit_grid(B * nsplit, ninner, colocate));
+  if (nt == 3)
+    hipLaunchKernelGGL((xweighted_kernel<3, true>), grid, dim3(512), 0, st, S, (const uint16_t*)K, k_bstride, seq_lens, T, B, H, d,
+                       nsplit, Cpart, mpart, lpart, colocate);
+  else
+    hipLaunchKernelGGL((xweighted_kernel<2, true>), grid, dim3(512), 0, st, S, (const uint16_t*)K, k_bstride, seq_lens, T, B, H, d,
+                       nsplit, Cpart, mpart, lpart, colocate);
 }
 
 }  // namespace slim

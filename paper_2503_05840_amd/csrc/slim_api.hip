@@ -30,6 +30,7 @@ struct Plan {
   int csw = 1;         // row splits of W_KV in the MFMA projection (its own launch)
   int csw_f = 0;       // same, when the stream kernel's workgroups do the projection (0: not possible)
   int nsplit_f = 1;    // context splits of the fp32 stream kernel
+  int nsplit_k = 1;    // context splits of the wide K-cache path's weighted sum
   int rsplit = 1;      // row splits of W_KV in the vector-ALU merge + projection
   size_t total = 0;
 };
@@ -60,6 +61,8 @@ Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
   if ((size_t)B * p.nsplit_xf > nparts) nparts = (size_t)B * p.nsplit_xf;
   if (p.fused_ok && (size_t)p.geom.nparts > nparts) nparts = p.geom.nparts;
   if (p.fused_ok && (size_t)B * 4 > nparts && fused_by_sequence(p.geom, B, false)) nparts = (size_t)B * 4;
+  p.nsplit_k = kweighted_splits(B, H, T, width);
+  if ((size_t)B * p.nsplit_k > nparts) p.nsplit_k = (int)(nparts / B);       // (the plain kernels' partials are more)
   p.nsplit_f = f32_stream_splits(B, T);
   const int d_k = e >= H ? e / H : 1;                  // (sizes are asked for with any arguments)
   p.rsplit = lean ? 1 : merge_row_splits(H, d_k, width, B, CTRL_INTS / 2);
@@ -412,21 +415,30 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     return launch_status();
   }
   // Shapes the stream kernel does not take (more than 32 heads, very large batches) still get the MFMA
-  // merge + projection when the head width allows it; an explicit request for the plain kernels keeps
-  // every step on the vector ALU.
+  // merge + projection when the head width allows it, and scores and weighted sum at the memory's rate when the
+  // rows are whole 128-column blocks; an explicit request for the plain kernels keeps every step on the vector ALU.
   const bool mfma_projection = dtype == SLIM_BF16 && requested != SLIM_VARIANT_GENERIC && d_k % 8 == 0 && d_k <= 128 &&
                                (long)H * ((B + 15) / 16) < CTRL_INTS / 2;
-  launch_head_scores(dtype, (const float*)q, d, Kcache, kb, d, lens, T, d, H, d_k, scale, S,
-                     (long)H * T, rope, ctrl, mfma_projection ? H * ((B + 15) / 16) : arrivals, B, st);
-  tm.mark();
-  launch_weighted_sum(dtype, S, Kcache, kb, d, lens, T, H, p.nsplit, Cpart, mpart, lpart, B, st);
+  const int arrivals_mfma = H * ((B + 15) / 16);
+  const bool wide = mfma_projection && wide_ok(dtype, T, d, d_k);
+  if (wide) {
+    launch_kscores((const float*)q, Kcache, kb, lens, T, H, d, d_k, scale * 1.4426950408889634f, rope, S, ctrl, arrivals_mfma, B, st);
+    tm.mark();
+    launch_kweighted(S, Kcache, kb, lens, T, H, d, p.nsplit_k, Cpart, mpart, lpart, B, st);
+  } else {
+    launch_head_scores(dtype, (const float*)q, d, Kcache, kb, d, lens, T, d, H, d_k, scale, S,
+                       (long)H * T, rope, ctrl, mfma_projection ? arrivals_mfma : arrivals, B, st);
+    tm.mark();
+    launch_weighted_sum(dtype, S, Kcache, kb, d, lens, T, H, p.nsplit, Cpart, mpart, lpart, B, st);
+  }
   tm.mark();
   if (mfma_projection) {
     ProjArgs pa{};
     pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_KV;
     pa.out = (float*)out; pa.outpart = outpart; pa.counters = ctrl;
     pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.nsplit = p.nsplit; pa.mode = 1; pa.mscale = 1.4426950408889634f;      // natural-log maxima
+    pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
+    pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
     pa.csw = p.csw;
     launch_project_mfma(pa, st);
   } else {

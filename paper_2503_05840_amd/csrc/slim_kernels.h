@@ -167,4 +167,14 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
 void launch_xweighted(const float* S, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
                       int d_model, int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 
+// ---- bf16 K-caches the stream kernel does not take (kernels_wide.hip; weighted sum in kernels_xcache.hip) ----
+// Scores in the log2 domain, [B][H][T padded to 32] (scale_log2 = log2(e) / sqrt(d_k)), then per split the weighted
+// sum with fp32 weights; partials laid out [b][nsplit], maxima in the log2 domain.
+bool wide_ok(int dtype, int T, int d, int d_k);
+int kweighted_splits(int B, int H, int T, int d);
+void launch_kscores(const float* q, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int d_k,
+                    float scale_log2, const float* rope, float* S, int* counters, int ncounters, int B, hipStream_t st);
+void launch_kweighted(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
+                      float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
+
 }  // namespace slim
