@@ -547,31 +547,34 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
 //   1. park the slice in LDS (row-padded), transpose it in registers for step 3, request the next tile,
 //      read the slice back in A-operand order, partial scores of the group's heads over the wave's
 //      columns on MFMA (query hi + lo), partials to LDS;  -- barrier --
-//   2. waves 0..7 sum the partials of their heads over the column owners (lane = row), keep those
-//      heads' running reference and sum of weights, write bf16 numerators and the rescale factors;
-//      -- barrier --
+//   2. the first eight waves (four, if there are fewer than eight) sum the partials of their heads over the column
+//      owners (lane = row), keep those heads' running reference and sum of weights, write bf16 numerators and, when a
+//      reference moved, the rescale factors;  -- barrier --
 //   3. every wave rescales if a reference moved and adds P^T X on MFMA.
 // Rows are not split over the waves, so nothing is merged at the end.  A one-dimensional launch: the head
 // groups of a (sequence, context split) read the same rows and are mapped to one XCD (unit_of_workgroup).
-// Two shapes: 8 waves x 32 heads (d_model <= 1024; 32 + 16 MFMAs per wave and tile) and 10 waves x 16
-// heads (d_model <= 1280: three waves on two of the four SIMDs, hence 168 registers, which hold half
-// the accumulators and the hi halves of q~; the lo halves wait in LDS).
+// Shapes: 4, 6 or 8 waves x 16 or 32 heads for d_model <= 512, 768, 1024 and 10 waves x 16 heads beyond (three waves
+// on two of the four SIMDs, hence 168 registers, which hold half the accumulators and the hi halves of q~; the lo
+// halves wait in LDS).  (Four waves that score tile k + 1 beside four that sum tile k, both MFMA phases in one barrier
+// interval: 51 us instead of 46 at 8 sequences x 128 heads x 4096 rows x 1024 columns -- the tile then crosses LDS twice
+// and its 64 KB through the L1, at 64 bytes a cycle, stand between the barriers.)
 // ------------------------------------------------------------------------------------------------
 constexpr int XF_PITCH = 272;            // bytes per parked row: 256 + 16 of padding
 constexpr int XF_RED_HS = 36;            // floats per head row of a wave's partial scores (32 rows + padding that keeps 16-byte stores)
 constexpr int XF_P_HS = 40;              // bf16 per head row of the numerators (32 rows + padding)
 
-// NW waves, each the owner of 128 columns (d_model <= 128 NW); NT head tiles of 16 per group.  Two shapes are
-// built: 8 waves x 32 heads (two waves per SIMD, 256 registers each) and 10 waves x 16 heads for rows of up to
-// 1280 columns (three waves on two of the SIMDs: 168 registers, which half the accumulators and half the
-// resident q~ fit).  The softmax state of the group's heads is looked after by waves 0..7, HG / 8 heads each.
+// NW waves, each the owner of 128 columns (d_model <= 128 NW); NT head tiles of 16 per group.
+// Workgroups a compute unit holds at once: two waves of 256 registers per SIMD.  (Two of 6 waves would need 168: spills.)
+constexpr int xfused_per_cu(int NW) { return NW == 4 ? 2 : 1; }
+
 template <int NW, int NT>
-__global__ __launch_bounds__(NW * 64) void xfused_kernel(const uint16_t* qt, const uint16_t* X, long x_bstride,
+__global__ __launch_bounds__(NW * 64, 2) void xfused_kernel(const uint16_t* qt, const uint16_t* X, long x_bstride,
                                                          const int32_t* seq_lens, int T, int B, int H, int dm, int nsplit,
                                                          float* Cpart, float* mpart, float* lpart, int colocate) {
   constexpr int HG = 16 * NT;                          // heads per group
-  constexpr int HPL = HG / 16;                         // heads per lane of an owner wave (lane = (row, half): 2 x 32 lanes)
-  static_assert(NW >= 8 && (NT == 1 || NT == 2), "owners are waves 0..7");
+  constexpr int OWN = NW >= 8 ? 8 : 4;                 // waves that make the numerators
+  constexpr int HPL = HG / (2 * OWN);                  // heads per lane of an owner wave (lane = (row, half): 2 x 32 lanes)
+  static_assert(NT == 1 || NT == 2, "registers");
   __shared__ __align__(16) unsigned char slot[NW][32 * XF_PITCH];
   __shared__ __align__(16) float red[NW][HG][XF_RED_HS];
   __shared__ __align__(16) uint16_t P_s[HG][XF_P_HS];
@@ -583,7 +586,8 @@ __global__ __launch_bounds__(NW * 64) void xfused_kernel(const uint16_t* qt, con
   // unit = (sequence, context split): its head groups read the same rows of X, from one XCD's L2
   int unit, hg;
   if (!unit_of_workgroup(blockIdx.x, (H + HG - 1) / HG, B * nsplit, colocate != 0, unit, hg)) return;
-  const int b = unit / nsplit, s = unit - b * nsplit;
+  const int s = unit / B, b = unit - s * B;            // (sequences fastest: with B a multiple of 8 the splits of a sequence, which
+                                                       //  read the same q~, share an XCD as well: 49.8 -> 47 us at B = 8)
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int idx = lane & 15, rg = lane >> 4;           // column group / row group of the register tile
   const int n = idx, kg = rg;                          // MFMA: N index (head) or M index (row), k group
@@ -627,11 +631,11 @@ __global__ __launch_bounds__(NW * 64) void xfused_kernel(const uint16_t* qt, con
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // softmax state of the heads this wave owns (waves 0..7): lane (r = lane % 32, hp = lane / 32) looks after
+  // softmax state of the heads this wave owns (the first OWN waves): lane (r = lane % 32, hp = lane / 32) looks after
   // row r of heads (2 w + hp) HPL + {0 .. HPL - 1} of the group; m is the same in all 32 lanes, l is the
   // lane's own share
   const int r = lane & 31, hp = lane >> 5;
-  const bool owner = w < 8;
+  const bool owner = w < OWN;
   float m[HPL], l[HPL];
 #pragma unroll
   for (int i = 0; i < HPL; ++i) { m[i] = NEG_INF; l[i] = 0.f; }
@@ -677,34 +681,50 @@ __global__ __launch_bounds__(NW * 64) void xfused_kernel(const uint16_t* qt, con
     }
   };
   // 2. this wave's four heads: sum over the column owners, reference, numerators
+  bool moved_before = true;                            // alpha_s of this wave's heads may not be all ones (wave-uniform)
   auto numerators = [&](int k) {
     if (!owner) return;
     const int r0 = r_lo + 32 * k;
+    float x[HPL];
+    bool over = false;
 #pragma unroll
     for (int i = 0; i < HPL; ++i) {
       const int hl = (2 * w + hp) * HPL + i;
       float sc = 0.f;
 #pragma unroll
       for (int w0 = 0; w0 < NW; w0 += 8) {             // (the reads of a batch are issued before the first is used)
-        float part[8];
+        constexpr int NR = NW < 8 ? NW : 8;
+        float part[NR];
 #pragma unroll
-        for (int ws = 0; ws < 8; ++ws)                 // (waves without columns leave their block unwritten: read, not used)
+        for (int ws = 0; ws < NR; ++ws)                // (waves without columns leave their block unwritten: read, not used)
           part[ws] = red[min(w0 + ws, NW - 1)][hl][r];
 #pragma unroll
-        for (int ws = 0; ws < 8; ++ws) sc += w0 + ws < ncb ? part[ws] : 0.f;
+        for (int ws = 0; ws < NR; ++ws) sc += w0 + ws < ncb ? part[ws] : 0.f;
       }
       const bool live = (hg * HG + hl < H) && (r0 + r < r_hi);
-      const float x = live ? sc : NEG_INF;
-      const float tmax = max_over_32(x);
-      // (the reference moves only when the maximum has grown by more than XW_SLACK, as in xweighted_kernel)
-      const float mn = (tmax > m[i] + XW_SLACK) ? tmax : m[i];
-      const float ref = (mn == NEG_INF) ? 0.f : mn;
-      const float alpha = (m[i] == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f(m[i] - ref);   // (nothing accumulated yet: nothing to rescale)
-      const __bf16 pw = (__bf16)__builtin_amdgcn_exp2f(x - ref);
-      l[i] = l[i] * alpha + (float)pw;                 // the weight as the MFMA will see it
-      m[i] = mn;
-      P_s[hl][r] = __builtin_bit_cast(uint16_t, pw);
-      if (r == 0) alpha_s[hl] = alpha;
+      x[i] = live ? sc : NEG_INF;
+      over |= x[i] > m[i] + XW_SLACK;
+    }
+    // The reference moves only when the maximum has grown by more than XW_SLACK, as in xweighted_kernel: rarely, so the
+    // maximum over the rows is taken only then.
+    const bool moved = __any(over);
+    if (moved || moved_before) {
+#pragma unroll
+      for (int i = 0; i < HPL; ++i) {
+        const float tmax = max_over_32(x[i]);
+        const float mn = (tmax > m[i] + XW_SLACK) ? tmax : m[i];
+        const float alpha = (m[i] == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f(m[i] - mn);   // (nothing accumulated yet: nothing to rescale)
+        l[i] *= alpha;
+        m[i] = mn;
+        if (r == 0) alpha_s[(2 * w + hp) * HPL + i] = alpha;
+      }
+    }
+    moved_before = moved;
+#pragma unroll
+    for (int i = 0; i < HPL; ++i) {
+      const __bf16 pw = (__bf16)__builtin_amdgcn_exp2f(x[i] - (m[i] == NEG_INF ? 0.f : m[i]));
+      l[i] += (float)pw;                               // the weight as the MFMA will see it
+      P_s[(2 * w + hp) * HPL + i][r] = __builtin_bit_cast(uint16_t, pw);
     }
   };
   // 3. rescale where a reference moved; P^T X for this wave's columns (the tile in am, its numerators in LDS)
@@ -808,18 +828,27 @@ int xcache_splits(int B, int H, int T, int d_model) {
 
 bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_model <= 1280; }
 
-// heads per workgroup of the one-pass kernel: 32 with 8 column owners, 16 with 10 (rows wider than 1024)
-static int xfused_head_group(int d_model) { return d_model <= 1024 ? 32 : 16; }
+// Shape of the one-pass kernel: waves, and head tiles per workgroup
+static int xfused_waves(int d_model) { return d_model <= 512 ? 4 : d_model <= 768 ? 6 : d_model <= 1024 ? 8 : 10; }
+static int xfused_tiles(int H, int d_model) { return d_model <= 1024 && H > 16 ? 2 : 1; }
 
 int xfused_splits(int B, int H, int T, int d_model) {
-  // one workgroup per (split, head group, sequence): split the context as far as it takes to fill the chip
-  const int hg = xfused_head_group(d_model);
-  const int per = B * ((H + hg - 1) / hg);
-  int s = (256 + per - 1) / per;
-  const int cap = (T + 255) / 256;
-  if (s > cap) s = cap;
-  if (s > PROJ_MAX_PARTS) s = PROJ_MAX_PARTS;
-  return s < 1 ? 1 : s;
+  // One workgroup per (split, head group, sequence): the split count whose rounds of workgroups over the 256 compute
+  // units take the fewest steps of 32 rows, where starting a workgroup, its first tile and its partial cost about four
+  // steps.  (Filling the chip with ceil(256 / units) splits made 288 workgroups of 24 sequences x 2 head groups x 6
+  // splits, two rounds of 8 steps: 50.8 us; 5 splits take one round of 10: 33.6 us.)
+  const int hg = 16 * xfused_tiles(H, d_model);
+  const long per = (long)B * ((H + hg - 1) / hg), slots = 256 * xfused_per_cu(xfused_waves(d_model));
+  const int tiles = (T + 31) / 32;
+  int most = (T + 255) / 256;
+  if (most > PROJ_MAX_PARTS) most = PROJ_MAX_PARTS;
+  int best = 1;
+  long best_cost = 0;
+  for (int s = 1; s <= most; ++s) {
+    const long rounds = (per * s + slots - 1) / slots, cost = rounds * ((tiles + s - 1) / s + 4);
+    if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
+  }
+  return best;
 }
 
 // Units dealt to the 8 XCDs (unit_of_workgroup): only when they spread evenly, within a quarter
@@ -830,15 +859,26 @@ static unsigned unit_grid(int nunits, int ninner, int colocate) {
 
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
                    int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
-  const int hg = xfused_head_group(d_model);
+  const int nt = xfused_tiles(H, d_model), hg = 16 * nt;
   const int colocate = colocate_units(B * nsplit);
   dim3 grid(unit_grid(B * nsplit, (H + hg - 1) / hg, colocate));
-  if (hg == 32)
-    hipLaunchKernelGGL((xfused_kernel<8, 2>), grid, dim3(512), 0, st, (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H,
-                       d_model, nsplit, Cpart, mpart, lpart, colocate);
-  else
-    hipLaunchKernelGGL((xfused_kernel<10, 1>), grid, dim3(640), 0, st, (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H,
-                       d_model, nsplit, Cpart, mpart, lpart, colocate);
+  auto go = [&](auto nw, auto tiles) {
+    hipLaunchKernelGGL((xfused_kernel<decltype(nw)::value, decltype(tiles)::value>), grid, dim3(decltype(nw)::value * 64), 0, st,
+                       (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H, d_model, nsplit, Cpart, mpart, lpart,
+                       colocate);
+  };
+  using N1 = std::integral_constant<int, 1>;
+  using N2 = std::integral_constant<int, 2>;
+  auto either = [&](auto nw) {
+    if (nt == 2) go(nw, N2{});
+    else go(nw, N1{});
+  };
+  switch (xfused_waves(d_model)) {
+    case 4: either(std::integral_constant<int, 4>{}); break;
+    case 6: either(std::integral_constant<int, 6>{}); break;
+    case 8: either(std::integral_constant<int, 8>{}); break;
+    default: go(std::integral_constant<int, 10>{}, N1{}); break;
+  }
 }
 
 void launch_xq_tilde(const float* q, const void* Wk, float* qt, int B, int H, int d_k, int d_model, int e,
