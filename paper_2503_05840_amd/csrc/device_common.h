@@ -50,6 +50,26 @@ __device__ __forceinline__ float max_over_32(float v) {
   return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
+// max / sum over the whole wave, the same in every lane: DPP inside the 16-lane rows, register swaps across them (a
+// __shfl_xor butterfly goes through LDS six times, a tenth of a microsecond each)
+__device__ __forceinline__ float max_over_wave(float v) {
+  v = max_over_32(v);
+  const unsigned u = __float_as_uint(v);
+  const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+}
+__device__ __forceinline__ float sum_over_wave(float v) {
+  v = dpp_add<0xB1>(v);
+  v = dpp_add<0x4E>(v);
+  v = dpp_add<0x141>(v);
+  v = dpp_add<0x140>(v);
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // 8 rows x 8 bf16 columns per lane  ->  8 operands (one per column), each 8 rows of that column.
 __device__ __forceinline__ void transpose8x8(const u32x4 (&kt)[8], u32x4 (&a)[8]) {
 #pragma unroll

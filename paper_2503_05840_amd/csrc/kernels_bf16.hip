@@ -123,7 +123,14 @@ __device__ void build_tile_prefix(int* prefix, int* lens_s, const int32_t* lens,
 // One workgroup (8 waves) per (head h, row split cs of W, batch chunk bz of 16*NBT sequences).  The
 // wave tile is the same 32 x 128 register tile as above (rows = c, columns = the head's output
 // columns), A = W tile transposed, B = merged, normalised C^T split in bf16 hi + lo.
-// COH: the partials come from other workgroups of the same launch (loads at agent scope).
+// What bounds it is the chain of dependent round trips around its bytes, so everything that can be asked for at once
+// is: two tiles of W per wave, then the maxima and sums of all partials.
+// COH: the partials come from other workgroups of the same launch (loads at agent scope, each a trip to the memory
+// side): they are asked for together with their maxima and sums, a lane four consecutive rows c of one sequence and
+// eight loads in flight, and the merged C goes to LDS in B-operand order (up to 1024 / NBT rows at a time, in the place
+// of the cross-wave sum).  Merged per tile in operand layout instead, as a launch of its own does it, that is a trip per
+// tile more: 13 us instead of 10 from the last arrival to the end at 16 sequences x 4096 columns.  (As a launch of its own
+// the staged form takes longer, 13.6 against 12.3 us at 64 sequences x 1280 columns with 3 partials each.)
 // ------------------------------------------------------------------------------------------------
 template <int NBT>
 struct ProjShared {
@@ -143,8 +150,26 @@ __device__ __forceinline__ int ld_err(const int* p) {
   if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else return *p;
 }
+// a pointer the compiler can keep in scalar registers (it is the same in every lane, which it cannot always see)
+__device__ __forceinline__ const float* uniform_ptr(const float* p) {
+  const unsigned long long u = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u), hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
+  return (const float*)(((unsigned long long)hi << 32) | lo);
+}
+// eight 16-byte loads in flight together, p[q] wave-uniform, byte offsets o0 for the first four and o1 for the others, at
+// agent scope: loads and their wait in one asm block
+__device__ __forceinline__ void ld_part8(const float* const (&p)[8], unsigned o0, unsigned o1, f32x4 (&x)[8]) {
+  asm volatile("global_load_dwordx4 %0, %8, %10 sc1\n\tglobal_load_dwordx4 %1, %8, %11 sc1\n\t"
+                 "global_load_dwordx4 %2, %8, %12 sc1\n\tglobal_load_dwordx4 %3, %8, %13 sc1\n\t"
+                 "global_load_dwordx4 %4, %9, %14 sc1\n\tglobal_load_dwordx4 %5, %9, %15 sc1\n\t"
+                 "global_load_dwordx4 %6, %9, %16 sc1\n\tglobal_load_dwordx4 %7, %9, %17 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                 : "v"(o0), "v"(o1), "s"(p[0]), "s"(p[1]), "s"(p[2]), "s"(p[3]), "s"(p[4]), "s"(p[5]), "s"(p[6]), "s"(p[7])
+                 : "memory");
+}
 
-// `red`: 64 KB of LDS for the cross-wave sum.
+// `red`: 64 KB of LDS: the merged C, later the cross-wave sum.
 // `after_w_issue` runs (all threads) once the first tile of W is in flight and before any partial
 // is read: the place to build the tile prefix, or to wait for the other workgroups' partials.
 // DENSE: plain products out_m = x W_m for up to three matrices that share x (ProjArgs::Wm); hx counts
@@ -168,8 +193,6 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   const int nhx = DENSE ? a.H * a.nmat : a.H;          // arrival counters per batch chunk
   const int lph = a.d_k / 8;
   const bool col_active = idx < lph;
-  // partial p of head h starts at ((p * H) + h) * rows; DENSE has one row of x per sequence for all heads
-  const int hmul = DENSE ? 1 : a.H, hadd = DENSE ? 0 : h;
   const uint16_t* Wh = Wmat + (size_t)h * a.d_k + idx * 8;
   const int c_lo = cs * a.crows, c_hi = min(a.rows, c_lo + a.crows);
   const int ntile = (c_hi - c_lo + TILE_ROWS - 1) / TILE_ROWS;
@@ -197,44 +220,136 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   if (w < ntile) load_w(wt, w);                      // in flight while the merge weights are built
   if (w + NW < ntile) load_w(wn, w + NW);
 
-  after_w_issue();
-
-  // ---- which partials belong to which sequence, and their merge weights for head h ------------
-  for (int bl = w; bl < nb; bl += NW) {              // one wave per sequence, one lane per partial
-    const int b = bbase + bl;
-    int p0, np;
-    if constexpr (DENSE) {                           // "partial" b is row b of x, weight 1
-      if (lane == 0) { sm.wpid[bl][0] = 1.f; sm.pid0s[bl] = b; sm.nps[bl] = 1; }
-      continue;
-    }
-    if (a.mode == 0) {
+  // Which partials belong to which sequence: in mode 1 nsplit each; in mode 0 from the tile prefix, looked up once and
+  // kept in LDS (single-launch mode: before the wait for the other workgroups, whose barrier it shares).
+  auto look_up = [&]() {
+    if (w == 0) {                                     // (16 NBT <= 64 sequences: one wave)
+      const int b = bbase + min(lane, nb - 1);
       const int VT = prefix[a.B];
       const int Qt = (VT + a.NG - 1) / a.NG;
       const int gf = prefix[b] / Qt, gl = (prefix[b + 1] - 1) / Qt;
-      p0 = b + gf;
-      np = gl - gf + 1;
-    } else {
-      p0 = b * a.nsplit;
-      np = a.nsplit;
+      const int np = min(gl - gf + 1, PROJ_MAX_PARTS);
+      if (lane < nb) {
+        sm.pid0s[lane] = min(b + gf, a.B + a.NG - 2);  // (a sequence without rows has no partial)
+        sm.nps[lane] = np;
+      }
     }
-    np = min(np, PROJ_MAX_PARTS);
-    float mp = NEG_INF, lp = 0.f;
-    if (lane < np) {
-      mp = ld_part<COH>(a.mpart + (size_t)(p0 + lane) * a.H + h);
-      lp = ld_part<COH>(a.lpart + (size_t)(p0 + lane) * a.H + h);
+  };
+  if constexpr (COH && !DENSE) look_up();
+  after_w_issue();
+  const bool even = a.mode == 1;
+  if constexpr (!COH && !DENSE) {
+    if (!even) {
+      look_up();
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
-    float M = mp;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o));
-    const float wgt = (mp == NEG_INF) ? 0.f : exp2f((mp - M) * a.mscale);
-    float L = wgt * lp;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) L += __shfl_xor(L, o);
-    if (lane < np) sm.wpid[bl][lane] = wgt / L;
-    if (lane == 0) { sm.pid0s[bl] = p0; sm.nps[bl] = np; }
   }
-  // (a barrier for the weights in LDS only: __syncthreads() would also wait for the tiles of W in flight)
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // (bl: wave-uniform)
+  auto first_part = [&](int bl) { return even ? (bbase + bl) * a.nsplit : __builtin_amdgcn_readfirstlane(sm.pid0s[bl]); };
+  auto num_parts = [&](int bl) { return even ? min(a.nsplit, PROJ_MAX_PARTS) : __builtin_amdgcn_readfirstlane(sm.nps[bl]); };
+
+  // The merged C in LDS: 8 rows of 16 NBT sequences after the other, a sequence's 8 values as 16 bytes; hi halves, then lo
+  constexpr int CH = 1024 / NBT;                      // rows at a time
+  uint16_t* const cs_hi = reinterpret_cast<uint16_t*>(red);
+  uint16_t* const cs_lo = cs_hi + CH * 16 * NBT;
+  const int c_pad = c_lo + ntile * TILE_ROWS;
+  // A wave merges whole sequences, a lane four consecutive rows c: 8 / wps sequences at a time, each by wps waves (all in
+  // shifts and wave-uniform addresses: this code is a good part of what stands between the partials and the product).
+  // One round trip takes RI x 256 rows of a wave and 8 / RI of a sequence's partials.
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int lg = nb >= 5 ? 0 : nb >= 3 ? 1 : nb == 2 ? 2 : 3;     // log2(wps)
+  const int seq0 = wu >> lg, lane0 = (wu & ((1 << lg) - 1)) * 64;
+  f32x4 px[8];
+  auto fetch = [&](auto RI_, int c0, int bl, int v, int pb) {
+    constexpr int RI = decltype(RI_)::value, Q = 8 / RI;
+    const int p0 = first_part(bl), np = num_parts(bl);
+    const float* p[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      p[q] = uniform_ptr(a.Cpart + ((size_t)(p0 + min(pb + q % Q, max(np - 1, 0))) * a.H + h) * a.rows + c0);
+    const int top = a.rows - 4 - c0;
+    ld_part8(p, (unsigned)min((v + lane) * 4, top) * 4u, (unsigned)min((v + lane + (RI == 2 ? 64 << lg : 0)) * 4, top) * 4u, px);
+  };
+  auto merge_chunk = [&](auto RI_, int c0, bool fetched) {
+    constexpr int RI = decltype(RI_)::value, Q = 8 / RI;
+    const int rows4 = min(CH, c_pad - c0) / 4;
+    for (int bl = seq0; bl < nb; bl += 8 >> lg) {
+      const int np = num_parts(bl);
+      for (int v = lane0; v < rows4; v += (64 << lg) * RI) {
+        f32x4 cn[RI];
+#pragma unroll
+        for (int i = 0; i < RI; ++i) cn[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int pb = 0; pb < np; pb += Q) {
+          if (!(fetched && bl == seq0 && v == lane0 && pb == 0)) fetch(RI_, c0, bl, v, pb);
+#pragma unroll
+          for (int pq = 0; pq < Q; ++pq)
+            if (pb + pq < np) {
+              const float wgt = sm.wpid[bl][pb + pq];
+#pragma unroll
+              for (int i = 0; i < RI; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) cn[i][j] = fmaf(wgt, px[i * Q + pq][j], cn[i][j]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RI; ++i) {
+          const int ve = v + lane + i * (64 << lg), r = ve * 4;
+          if (ve < rows4) {
+            if (c0 + r >= c_hi) cn[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (rows of the last tile past the end of W)
+            unsigned hw[2], lw[2];
+#pragma unroll
+            for (int j = 0; j < 4; j += 2) {
+              const __bf16 h0 = (__bf16)cn[i][j], h1 = (__bf16)cn[i][j + 1];
+              const bf16x2 hv = {h0, h1}, lv = {(__bf16)(cn[i][j] - (float)h0), (__bf16)(cn[i][j + 1] - (float)h1)};
+              hw[j / 2] = __builtin_bit_cast(unsigned, hv);
+              lw[j / 2] = __builtin_bit_cast(unsigned, lv);
+            }
+            const int at = ((r >> 3) * (16 * NBT) + bl) * 8 + (r & 7);
+            *reinterpret_cast<uint2*>(cs_hi + at) = make_uint2(hw[0], hw[1]);
+            *reinterpret_cast<uint2*>(cs_lo + at) = make_uint2(lw[0], lw[1]);
+          }
+        }
+      }
+    }
+  };
+  // (few sequences: their rows are spread over several waves and one round trip takes eight partials)
+  auto with_rows = [&](auto&& f) {
+    if (lg > 0) f(std::integral_constant<int, 1>{});
+    else f(std::integral_constant<int, 2>{});
+  };
+  if constexpr (!DENSE) {
+    // ---- merge weights for head h: one wave per sequence, one lane per partial; the first partials
+    //      themselves are asked for behind the maxima and sums ----------------------------------------
+    constexpr int SW = 2 * NBT;                       // sequences per wave
+    float mp[SW], lp[SW];
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {
+      const int bl = wu + NW * i;
+      mp[i] = NEG_INF; lp[i] = 0.f;
+      if (bl < nb && lane < num_parts(bl)) {
+        mp[i] = ld_part<COH>(a.mpart + (size_t)(first_part(bl) + lane) * a.H + h);
+        lp[i] = ld_part<COH>(a.lpart + (size_t)(first_part(bl) + lane) * a.H + h);
+      }
+    }
+    const bool fetched = COH && seq0 < nb && lane0 < min(CH, c_pad - c_lo) / 4;
+    if constexpr (COH)
+      if (fetched) with_rows([&](auto RI_) { fetch(RI_, c_lo, seq0, lane0, 0); });
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {
+      const int bl = wu + NW * i;
+      if (bl >= nb) break;
+      const float M = max_over_wave(mp[i]);
+      const float wgt = (mp[i] == NEG_INF) ? 0.f : exp2f((mp[i] - M) * a.mscale);
+      const float L = sum_over_wave(wgt * lp[i]);
+      if (lane < num_parts(bl)) sm.wpid[bl][lane] = wgt / L;
+    }
+    // (barriers for LDS only: __syncthreads() would also wait for the tiles of W in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if constexpr (COH) {
+      with_rows([&](auto RI_) { merge_chunk(RI_, c_lo, fetched); });
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+  }
 
   f32x4 acc[8][NBT];
 #pragma unroll
@@ -242,116 +357,121 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 #pragma unroll
     for (int t = 0; t < NBT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int ct = w; ct < ntile; ct += NW) {
-    const int c0 = c_lo + ct * TILE_ROWS;
-    const bool more = ct + NW < ntile;
-    // B operand: merged C for (b = bt*16 + n, rows c0 + kg*8 .. +8)
-    bf16x8 bhi[NBT], blo[NBT];
-    const int c = c0 + kg * 8;
-    if constexpr (DENSE) load_x(xn, min(ct + NW, ntile - 1));
-#pragma unroll
-    for (int t = 0; t < NBT; ++t) {
-      float cn[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) cn[j] = 0.f;
-      const int bl = t * 16 + n;
+  constexpr int TC = CH / TILE_ROWS;                  // tiles per merged chunk
+  for (int tc = 0; tc < ntile; tc += COH ? TC : ntile) {
+    if (COH && tc > 0) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (every wave is done with the chunk before)
+      with_rows([&](auto RI_) { merge_chunk(RI_, c_lo + tc * TILE_ROWS, false); });
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    const int ct_end = COH ? min(ntile, tc + TC) : ntile;
+    for (int ct = tc + w; ct < ct_end; ct += NW) {    // (TC is a multiple of the waves: w + NW i throughout)
+      const int c0 = c_lo + ct * TILE_ROWS;
+      const bool more = ct + NW < ntile;
+      // B operand: merged C for (b = bt*16 + n, rows c0 + kg*8 .. +8)
+      bf16x8 bhi[NBT], blo[NBT];
       if constexpr (DENSE) {
-        if (bl < nb && c < c_hi) {
+        const int c = c0 + kg * 8;
+        load_x(xn, min(ct + NW, ntile - 1));
 #pragma unroll
-          for (int j = 0; j < 4; ++j) { cn[j] = xc[t][0][j]; cn[4 + j] = xc[t][1][j]; }
-        }
-      } else if (bl < nb && c < c_hi) {
-        const int p0 = sm.pid0s[bl], np = sm.nps[bl];
-        if constexpr (COH) {
-          // eight partials per round trip: agent-scope loads, one wait
-          for (int pb = 0; pb < np; pb += 8) {
-            f32x4 x[8][2];
+        for (int t = 0; t < NBT; ++t) {
+          const bool live = t * 16 + n < nb && c < c_hi;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const int pp = min(pb + q, np - 1);
-              const float* src = a.Cpart + ((size_t)(p0 + pp) * hmul + hadd) * a.rows + c;
-              asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(x[q][0]) : "v"(src) : "memory");
-              asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(x[q][1]) : "v"(src + 4) : "memory");
-            }
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(x[0][0]), "+v"(x[0][1]), "+v"(x[1][0]), "+v"(x[1][1]),
-                         "+v"(x[2][0]), "+v"(x[2][1]), "+v"(x[3][0]), "+v"(x[3][1]) : : "memory");
-            asm volatile("" : "+v"(x[4][0]), "+v"(x[4][1]), "+v"(x[5][0]), "+v"(x[5][1]),
-                         "+v"(x[6][0]), "+v"(x[6][1]), "+v"(x[7][0]), "+v"(x[7][1]) : : "memory");
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float wgt = (pb + q < np) ? sm.wpid[bl][min(pb + q, np - 1)] : 0.f;
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                cn[j] = fmaf(wgt, x[q][0][j], cn[j]);
-                cn[4 + j] = fmaf(wgt, x[q][1][j], cn[4 + j]);
-              }
-            }
-          }
-        } else {
-          for (int p = 0; p < np; ++p) {
-            const float wgt = sm.wpid[bl][p];
-            const float* src = a.Cpart + ((size_t)(p0 + p) * hmul + hadd) * a.rows + c;
-            const float4 x0 = *reinterpret_cast<const float4*>(src);
-            const float4 x1 = *reinterpret_cast<const float4*>(src + 4);
-            cn[0] = fmaf(wgt, x0.x, cn[0]); cn[1] = fmaf(wgt, x0.y, cn[1]);
-            cn[2] = fmaf(wgt, x0.z, cn[2]); cn[3] = fmaf(wgt, x0.w, cn[3]);
-            cn[4] = fmaf(wgt, x1.x, cn[4]); cn[5] = fmaf(wgt, x1.y, cn[5]);
-            cn[6] = fmaf(wgt, x1.z, cn[6]); cn[7] = fmaf(wgt, x1.w, cn[7]);
+          for (int j = 0; j < 8; ++j) {
+            const float v = live ? xc[t][j >> 2][j & 3] : 0.f;
+            const __bf16 hi = (__bf16)v;
+            bhi[t][j] = hi;
+            blo[t][j] = (__bf16)(v - (float)hi);
           }
         }
+      } else if constexpr (COH) {
+#pragma unroll
+        for (int t = 0; t < NBT; ++t) {                // (columns of sequences past the last one: any values, never used)
+          const int at = (((ct - tc) * 4 + kg) * (16 * NBT) + t * 16 + n) * 8;
+          bhi[t] = *reinterpret_cast<const bf16x8*>(cs_hi + at);
+          blo[t] = *reinterpret_cast<const bf16x8*>(cs_lo + at);
+        }
+      } else {
+        const int c = c0 + kg * 8;
+#pragma unroll
+        for (int t = 0; t < NBT; ++t) {
+          float cn[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) cn[j] = 0.f;
+          const int bl = t * 16 + n;
+          if (bl < nb && c < c_hi) {
+            const int p0 = even ? (bbase + bl) * a.nsplit : sm.pid0s[bl], np = even ? min(a.nsplit, PROJ_MAX_PARTS) : sm.nps[bl];
+            for (int p = 0; p < np; ++p) {
+              const float wgt = sm.wpid[bl][p];
+              const float* src = a.Cpart + ((size_t)(p0 + p) * a.H + h) * a.rows + c;
+              const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) { cn[j] = fmaf(wgt, x0[j], cn[j]); cn[4 + j] = fmaf(wgt, x1[j], cn[4 + j]); }
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const __bf16 hi = (__bf16)cn[j];
+            bhi[t][j] = hi;
+            blo[t][j] = (__bf16)(cn[j] - (float)hi);
+          }
+        }
       }
+      u32x4 am[8];
+      transpose8x8(wt, am);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const __bf16 hi = (__bf16)cn[j];
-        bhi[t][j] = hi;
-        blo[t][j] = (__bf16)(cn[j] - (float)hi);
+      for (int i = 0; i < 8; ++i) {
+        const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
+#pragma unroll
+        for (int t = 0; t < NBT; ++t) {
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[t], acc[i][t], 0, 0, 0);
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[t], acc[i][t], 0, 0, 0);
+        }
       }
-    }
-    u32x4 am[8];
-    transpose8x8(wt, am);
+      if (more) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
-#pragma unroll
-      for (int t = 0; t < NBT; ++t) {
-        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[t], acc[i][t], 0, 0, 0);
-        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[t], acc[i][t], 0, 0, 0);
+        for (int j = 0; j < 8; ++j) wt[j] = wn[j];
+        if (ct + 2 * NW < ntile) load_w(wn, ct + 2 * NW);
       }
-    }
-    if (more) {
+      if constexpr (DENSE) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) wt[j] = wn[j];
-      if (ct + 2 * NW < ntile) load_w(wn, ct + 2 * NW);
-    }
-    if constexpr (DENSE) {
-#pragma unroll
-      for (int t = 0; t < NBT; ++t) { xc[t][0] = xn[t][0]; xc[t][1] = xn[t][1]; }
+        for (int t = 0; t < NBT; ++t) { xc[t][0] = xn[t][0]; xc[t][1] = xn[t][1]; }
+      }
     }
   }
+  if constexpr (COH) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the merged C gives way to the sum)
 
-  // ---- sum the 8 waves: sm.obuf[b][j], IPR of the 8 accumulator columns per pass through LDS -----
+  // ---- sum the 8 waves, IPR of the 8 accumulator columns per pass through LDS: thread (ei, lane) ends up with
+  //      accumulator element i0 + ei / NBT of batch tile ei % NBT as that lane of a wave held it ----------------
   constexpr int IPR = 8 / NBT;
+  f32x4* const red4 = reinterpret_cast<f32x4*>(red);
+  f32x4 osum[NBT];                                     // per pass: columns (kg*4 + r)*8 + i of sequence n of the batch tile
 #pragma unroll
-  for (int i0 = 0; i0 < 8; i0 += IPR) {
+  for (int ps = 0; ps < NBT; ++ps) {
 #pragma unroll
     for (int ii = 0; ii < IPR; ++ii)
 #pragma unroll
-      for (int t = 0; t < NBT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[((w * IPR + ii) * (NBT * 4) + t * 4 + r) * 64 + lane] = acc[i0 + ii][t][r];
+      for (int t = 0; t < NBT; ++t) red4[(w * 8 + ii * NBT + t) * 64 + lane] = acc[ps * IPR + ii][t];
     __syncthreads();
-    for (int v = tid; v < IPR * NBT * 4 * 64; v += NTHR) {
-      const int ln = v & 63, reg = (v >> 6) % (NBT * 4), ii = (v >> 6) / (NBT * 4);
-      float sum = 0.f;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ww = 0; ww < NW; ++ww) sum += red[((ww * IPR + ii) * (NBT * 4) + reg) * 64 + ln];
-      const int t = reg >> 2, r = reg & 3;
-      const int bl = t * 16 + (ln & 15);
-      const int mi = (ln >> 4) * 4 + r;
-      if (mi < lph) sm.obuf[bl][mi * 8 + i0 + ii] = sum;
+    for (int ww = 0; ww < NW; ++ww) sum += red4[(ww * 8 + w) * 64 + lane];
+    osum[ps] = sum;
+    if (ps + 1 < NBT) __syncthreads();
+  }
+  const int obl = (w % NBT) * 16 + n, omi = kg * 4;    // this thread's sequence and first column group
+  auto oi = [&](int ps) { return ps * IPR + w / NBT; };
+  const bool mine = obl < nb && omi < lph;
+  auto to_obuf = [&]() {
+    if (obl < nb) {
+#pragma unroll
+      for (int ps = 0; ps < NBT; ++ps)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (omi + r < lph) sm.obuf[obl][(omi + r) * 8 + oi(ps)] = osum[ps][r];
     }
     __syncthreads();
-  }
+  };
 
   // One finished output element (sequence bbase + bl, column j of the head); `other` is column j ^ 1.
   auto emit = [&](int bl, int j, float val, float other, bool bad) {
@@ -382,6 +502,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 
   if (a.csw == 1) {
     const bool bad = a.err && ld_err<COH>(a.err) == (int)a.launch_id;      // the stream kernel gave up waiting
+    to_obuf();
     for (int v = tid; v < nb * a.d_k; v += NTHR) {
       const int bl = v / a.d_k, j = v % a.d_k;
       emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
@@ -389,45 +510,64 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     return;
   }
   // ---- several workgroups share the rows of W: last one to arrive adds the partial sums ---------
-  // No cache-wide fences: the partial sums are stored write-through and waited for (so they are
-  // visible device-wide) before this workgroup's arrival is counted, and the last workgroup reads
-  // them with device-coherent loads.
-  for (int v = tid; v < nb * a.d_k; v += NTHR) {
-    const int bl = v / a.d_k, j = v % a.d_k;
-    float* dst = &outpart[((size_t)cs * a.B + bbase + bl) * a.e + h * a.d_k + j];
-    asm volatile("global_store_dword %0, %1, off sc0 sc1" : : "v"(dst), "v"(sm.obuf[bl][j]) : "memory");
+  // No cache-wide fences: the partial sums are stored and waited for before this workgroup's arrival is counted, and
+  // the last workgroup reads them past its L1.  Where the workgroups of a head share an XCD (xcd_local: checked by the
+  // host) its L2 is their meeting point -- plain stores, an atomic that the L2 executes; otherwise the stores are
+  // written through and the atomic has device scope: three round trips to the memory side instead of to the L2.
+  // The partial sums of a head lie in accumulator order, [element i][column group], so that they leave and come back
+  // 16 bytes at a time (where the head has whole fours of column groups).
+  const bool xl = a.xcd_local != 0, fours = (lph & 3) == 0;
+  auto part_at = [&](int sp, int ps) { return outpart + ((size_t)sp * a.B + bbase + obl) * a.e + h * a.d_k + oi(ps) * lph + omi; };
+  if (mine) {
+#pragma unroll
+    for (int ps = 0; ps < NBT; ++ps) {
+      if (fours) st_result4(part_at(cs, ps), osum[ps], !xl);
+      else
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (omi + r < lph) st_result(part_at(cs, ps) + r, osum[ps][r], !xl);
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    const int old = __hip_atomic_fetch_add(&a.counters[bz * nhx + hx], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int* const counter = &a.counters[bz * nhx + hx];
+    const int old = xl ? __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                       : __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     sm.is_last = (old == a.csw - 1);
   }
   __syncthreads();
   if (!sm.is_last) return;
   // (the error word travels with the partial sums: requested here, looked at behind their wait)
   const int errv = a.err ? __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-  for (int v0 = 0; v0 < nb * a.d_k; v0 += NTHR) {
-    if (v0 + (tid & ~63) >= nb * a.d_k) break;           // (whole waves: the columns of a pair sit in neighbour lanes)
-    const int v = min(v0 + tid, nb * a.d_k - 1);
-    const int bl = v / a.d_k, j = v % a.d_k;
-    float sum = 0.f;
-    for (int s0 = 0; s0 < a.csw; s0 += 8) {
-      float part[8];
+  if (mine) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int sp = min(s0 + q, a.csw - 1);
-        const float* src = &outpart[((size_t)sp * a.B + bbase + bl) * a.e + h * a.d_k + j];
-        asm volatile("global_load_dword %0, %1, off sc1" : "=v"(part[q]) : "v"(src) : "memory");
+    for (int ps = 0; ps < NBT; ++ps) {
+      osum[ps] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int s0 = 0; s0 < a.csw; s0 += 8) {
+        if (fours) {
+          const float* src[8];
+          f32x4 part[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) src[q] = uniform_ptr(outpart + (size_t)min(s0 + q, a.csw - 1) * a.B * a.e);
+          const unsigned at = (unsigned)(part_at(0, ps) - outpart) * 4u;
+          ld_part8(src, at, at, part);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) if (s0 + q < a.csw) osum[ps] += part[q];
+        } else {
+          for (int q = s0; q < min(s0 + 8, a.csw); ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (omi + r < lph) osum[ps][r] += ld_part<true>(part_at(q, ps) + r);
+        }
       }
-      asm volatile("s_waitcnt vmcnt(0)" : "+v"(part[0]), "+v"(part[1]), "+v"(part[2]), "+v"(part[3]),
-                   "+v"(part[4]), "+v"(part[5]), "+v"(part[6]), "+v"(part[7]) : : "memory");
-#pragma unroll
-      for (int q = 0; q < 8; ++q) if (s0 + q < a.csw) sum += part[q];
     }
-    const float other = DENSE ? __shfl_xor(sum, 1) : 0.f;
-    const bool bad = a.err && errv == (int)a.launch_id;
-    if (v0 + tid < nb * a.d_k) emit(bl, j, sum, other, bad);               // NaN: the stream kernel gave up waiting
+  }
+  to_obuf();
+  const bool bad = a.err && errv == (int)a.launch_id;                      // NaN: the stream kernel gave up waiting
+  for (int v = tid; v < nb * a.d_k; v += NTHR) {
+    const int bl = v / a.d_k, j = v % a.d_k;
+    emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
   }
   if (tid == 0) a.counters[bz * nhx + hx] = 0;
 }
@@ -436,8 +576,12 @@ template <int NBT, bool DENSE>
 __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   __shared__ int prefix[FUSED_MAX_B + 1];
   __shared__ ProjShared<NBT> sm;
-  __shared__ float red[8 * 8 * 4 * 64];
-  project_work<NBT, false, DENSE>(a, blockIdx.x, blockIdx.y, blockIdx.z, prefix, sm, red, [&]() {
+  __shared__ __align__(16) float red[8 * 8 * 4 * 64];
+  // unit = (head, batch chunk), for which csw workgroups share the rows of W: dealt to the XCDs so that they meet in one L2
+  const int nhx = DENSE ? a.H * a.nmat : a.H;
+  const int slot = blockIdx.x >> 3, unit = (slot / a.csw) * 8 + (blockIdx.x & 7);
+  if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
+  project_work<NBT, false, DENSE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);
   });
 }
@@ -518,8 +662,12 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   const int p = wu;                                 // this wave's team: wave p of every workgroup of the group
 
   const bool fuse = !BYSEQ && a.fuse != 0;
-  if (blockIdx.x == 0 && a.counters)                // the projection's arrival counters start at 0
-    for (int i = tid; i < a.ncounters; i += NTHR) st_result(a.counters + i, 0, fuse);
+  // the projection's arrival counters start at 0 (single-launch mode: a head's counter is cleared from the XCD that counts)
+  if (fuse) {
+    if (blockIdx.x < a.H && tid == 0) st_result(a.counters + blockIdx.x, 0, !a.proj.xcd_local);
+  } else if (blockIdx.x == 0 && a.counters) {
+    for (int i = tid; i < a.ncounters; i += NTHR) a.counters[i] = 0;
+  }
 
   build_tile_prefix(prefix, lens_s, a.seq_lens, a.B, a.T);     // (ends with a workgroup barrier)
   const int VT = prefix[a.B];
@@ -1133,11 +1281,12 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) st_result(reinterpret_cast<int*>(a.flags) + blockIdx.x, (int)a.launch_id, true);
-  const int wg = blockIdx.x;
-  if (wg >= a.proj.H * a.proj.csw) return;
+  // (head, row split): a head's workgroups on one XCD, as in project_mfma_kernel
+  const int slot = blockIdx.x >> 3, phead = (slot / a.proj.csw) * 8 + (blockIdx.x & 7);
+  if (phead >= a.proj.H) return;
   // (everything of the stream phase is over in this workgroup: its LDS is reused)
   ProjShared<1>& psm = *reinterpret_cast<ProjShared<1>*>(sbuf);
-  project_work<1, true, false>(a.proj, wg / a.proj.csw, wg % a.proj.csw, 0, prefix, psm, red, [&]() {
+  project_work<1, true, false>(a.proj, phead, slot % a.proj.csw, 0, prefix, psm, red, [&]() {
     // every workgroup's partials must be out: all arrival flags carry this launch's id
     if (wu == 0) {
       unsigned long long since = ~0ull;
@@ -1300,16 +1449,20 @@ int proj_batch_tiles(int B, int rows, int e, int H) {
   return B <= 32 ? 2 : 4;
 }
 
+// Row splits of `units` (head, batch chunk) pairs: a unit's workgroups share an XCD, which holds 32 of them at once
+// (one per compute unit: a single round).
+int proj_splits_per_unit(int units) {
+  const int c = 32 / ((units + 7) / 8);
+  return c < 1 ? 1 : c;
+}
+
 int proj_row_splits(int H, int rows, int e, int B) {
   // one 32-row tile of W per wave (8 waves = 256 rows per workgroup) unless that makes more
   // workgroups than CUs
   const int per = 16 * proj_batch_tiles(B, rows, e, H);
   const int zb = (B + per - 1) / per;
-  int csw = (rows + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS);
-  const int cap = 256 / (H * zb);                     // one workgroup per CU: a single round
-  if (csw > cap) csw = cap;
-  if (csw < 1) csw = 1;
-  return csw;
+  const int csw = (rows + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), cap = proj_splits_per_unit(H * zb);
+  return csw > cap ? cap : csw;
 }
 
 int proj_rows_per_split(int rows, int csw) {
@@ -1319,7 +1472,7 @@ int proj_rows_per_split(int rows, int csw) {
 void launch_project_mfma(ProjArgs a, hipStream_t st) {
   const int nbt = proj_batch_tiles(a.B, a.rows, a.e, a.H);
   a.crows = proj_rows_per_split(a.rows, a.csw);
-  dim3 grid(a.H, a.csw, (a.B + 16 * nbt - 1) / (16 * nbt)), block(512);
+  dim3 grid(8u * a.csw * (((unsigned)a.H * ((a.B + 16 * nbt - 1) / (16 * nbt)) + 7) / 8)), block(512);
   if (nbt == 1) hipLaunchKernelGGL((project_mfma_kernel<1, false>), grid, block, 0, st, a);
   else if (nbt == 2) hipLaunchKernelGGL((project_mfma_kernel<2, false>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((project_mfma_kernel<4, false>), grid, block, 0, st, a);
@@ -1330,7 +1483,7 @@ void launch_dense_mfma(ProjArgs a, hipStream_t st) {
   const int nbt = proj_batch_tiles(a.B, a.rows, a.e, a.H * a.nmat);
   a.crows = proj_rows_per_split(a.rows, a.csw);
   a.mode = 2;
-  dim3 grid(a.H * a.nmat, a.csw, (a.B + 16 * nbt - 1) / (16 * nbt)), block(512);
+  dim3 grid(8u * a.csw * (((unsigned)a.H * a.nmat * ((a.B + 16 * nbt - 1) / (16 * nbt)) + 7) / 8)), block(512);
   if (nbt == 1) hipLaunchKernelGGL((project_mfma_kernel<1, true>), grid, block, 0, st, a);
   else if (nbt == 2) hipLaunchKernelGGL((project_mfma_kernel<2, true>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((project_mfma_kernel<4, true>), grid, block, 0, st, a);

@@ -360,13 +360,9 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
       mp = mpart[((size_t)b * nsplit + lane) * H + h];
       lp = lpart[((size_t)b * nsplit + lane) * H + h];
     }
-    float M = mp;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o));
+    const float M = max_over_wave(mp);
     const float wg = (mp == NEG_INF) ? 0.f : __expf(mp - M);
-    float L = wg * lp;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) L += __shfl_xor(L, o);
+    const float L = sum_over_wave(wg * lp);
     wgt[w][lane] = wg / L;
     if (lane == 0) nsp[w] = ns;
   }

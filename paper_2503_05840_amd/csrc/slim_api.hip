@@ -70,8 +70,8 @@ Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
   if (f32_stream_ok(DT_F32, H, width, d_k) && (size_t)B * p.nsplit_f > nparts) nparts = (size_t)B * p.nsplit_f;
   p.csw = proj_row_splits(H, width, e, B);
   if (p.fused_ok && B <= 16 && p.geom.grid >= H) {
-    const int tiles_w = (width + TILE_ROWS - 1) / TILE_ROWS;
-    p.csw_f = p.geom.grid / H < tiles_w ? p.geom.grid / H : tiles_w;
+    const int tiles_w = (width + TILE_ROWS - 1) / TILE_ROWS, c = proj_splits_per_unit(H);
+    p.csw_f = c < tiles_w ? c : tiles_w;
   }
   p.off_S = o;      o += up(sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32));   // (rows padded to 32 scores)
   p.off_Cpart = o;  o += up(sizeof(float) * nparts * H * width);
@@ -133,6 +133,15 @@ DeviceState* device_state() {
   if (hipEventCreateWithFlags(&s.order_ev, hipEventDisableTiming) != hipSuccess) { s.order_ev = nullptr; (void)hipGetLastError(); }
   s.ready = true;
   return &s;
+}
+
+// Whether workgroup i of a launch is known to run on XCD i % 8: after slim_init or a call that needed the set-up; without
+// it the callers' kernels meet at the memory side.  (Never sets anything up itself: the set-up waits for the device.)
+bool xcd_round_robin_known() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return false; }
+  std::lock_guard<std::mutex> lk(g_dev_mu);
+  return g_dev[dev].ready && g_dev[dev].xcd_round_robin;
 }
 
 // Library-owned scratch: one allocation per device, grown on demand, kept until exit.
@@ -377,7 +386,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw;
+    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcd_local = dev->xcd_round_robin;
     if (const int shares = fused_by_sequence(g, B, lens != nullptr)) {
       fa.by_sequence = shares;
       pa.mode = 1; pa.nsplit = shares;               // partials laid out [sequence][share]
@@ -439,7 +448,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
     pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
     pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
-    pa.csw = p.csw;
+    pa.csw = p.csw; pa.xcd_local = xcd_round_robin_known();
     launch_project_mfma(pa, st);
   } else {
     launch_merge_project(dtype, Cpart, mpart, lpart, p.nsplit, false, lens, T, W_KV, d, d, H, d_k, (float*)out, outpart, p.rsplit,
@@ -575,7 +584,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     pa.err = nullptr; pa.launch_id = 0; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d_model; pa.e = e;
     pa.NG = 0; pa.nsplit = nsplit; pa.mode = 1; pa.mscale = 1.0f;
-    pa.csw = proj_row_splits(H, d_model, e, B);
+    pa.csw = proj_row_splits(H, d_model, e, B); pa.xcd_local = xcd_round_robin_known();
     launch_project_mfma(pa, st);
     tm.mark();
     tm.finish();
@@ -664,7 +673,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   ProjArgs pa{};
   pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = (int*)(ws + p.off_ctrl);
   pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-  pa.nsplit = 1; pa.mscale = 1.0f;
+  pa.nsplit = 1; pa.mscale = 1.0f; pa.xcd_local = xcd_round_robin_known();
 
   StageTimer tm(o, st);
   if (fast) {

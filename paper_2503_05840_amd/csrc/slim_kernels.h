@@ -100,6 +100,7 @@ struct ProjArgs {
   int NG, nsplit, mode;               // mode 0: partials laid out by the stream kernel; 1: [b][nsplit]
   float mscale;                       // 1 for log2-domain maxima, log2(e) for natural-log ones
   int csw, crows;                     // row splits of W across workgroups, rows per split
+  int xcd_local;                      // workgroup i runs on XCD i % 8 (checked): the row splits of a head meet in its L2
   // Dense products (launch_dense_mfma): Cpart = x [B][rows], out_m = x W_m for nmat matrices.
   // role 0: fp32 result.  The new token's rows (it sits at row / position seq_lens[b] - 1):
   // role 1: query, fp32, rotated to that position when rope is set; role 2: key row into Kc (rotated
@@ -147,6 +148,7 @@ bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
 int fused_blocks_per_cu(const FusedGeom& g, bool rope);
 void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st);
 int proj_batch_tiles(int B, int rows, int e, int H);
+int proj_splits_per_unit(int units);
 int proj_row_splits(int H, int rows, int e, int B);
 int proj_rows_per_split(int rows, int csw);
 void launch_project_mfma(ProjArgs a, hipStream_t st);
