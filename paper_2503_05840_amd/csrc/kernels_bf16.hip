@@ -357,15 +357,8 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 #pragma unroll
     for (int t = 0; t < NBT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  constexpr int TC = CH / TILE_ROWS;                  // tiles per merged chunk
-  for (int tc = 0; tc < ntile; tc += COH ? TC : ntile) {
-    if (COH && tc > 0) {
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (every wave is done with the chunk before)
-      with_rows([&](auto RI_) { merge_chunk(RI_, c_lo + tc * TILE_ROWS, false); });
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    }
-    const int ct_end = COH ? min(ntile, tc + TC) : ntile;
-    for (int ct = tc + w; ct < ct_end; ct += NW) {    // (TC is a multiple of the waves: w + NW i throughout)
+  auto tiles = [&](int tc, int ct_end) {
+    for (int ct = tc + w; ct < ct_end; ct += NW) {
       const int c0 = c_lo + ct * TILE_ROWS;
       const bool more = ct + NW < ntile;
       // B operand: merged C for (b = bt*16 + n, rows c0 + kg*8 .. +8)
@@ -438,6 +431,19 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         for (int t = 0; t < NBT; ++t) { xc[t][0] = xn[t][0]; xc[t][1] = xn[t][1]; }
       }
     }
+  };
+  if constexpr (COH) {
+    constexpr int TC = CH / TILE_ROWS;                // tiles per merged chunk (a multiple of the waves: w + NW i throughout)
+    for (int tc = 0; tc < ntile; tc += TC) {
+      if (tc > 0) {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (every wave is done with the chunk before)
+        with_rows([&](auto RI_) { merge_chunk(RI_, c_lo + tc * TILE_ROWS, false); });
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      }
+      tiles(tc, min(ntile, tc + TC));
+    }
+  } else {
+    tiles(0, ntile);
   }
   if constexpr (COH) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the merged C gives way to the sum)
 
@@ -516,9 +522,18 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   // written through and the atomic has device scope: three round trips to the memory side instead of to the L2.
   // The partial sums of a head lie in accumulator order, [element i][column group], so that they leave and come back
   // 16 bytes at a time (where the head has whole fours of column groups).
+  // Dense products of up to 512 elements (a few sequences) keep their columns in order instead, an element a thread: they
+  // are finished from where they are read, without another pass through LDS (4 x 4096 x 4096: 12.0 against 12.8 us).
   const bool xl = a.xcd_local != 0, fours = (lph & 3) == 0;
+  const bool in_order = DENSE && nb * a.d_k <= NTHR;
+  const int ebl = tid / a.d_k, ej = tid - ebl * a.d_k;  // in_order: this thread's element
+  const bool eok = tid < nb * a.d_k;
+  auto elem_at = [&](int sp) { return outpart + ((size_t)sp * a.B + bbase + ebl) * a.e + h * a.d_k + ej; };
   auto part_at = [&](int sp, int ps) { return outpart + ((size_t)sp * a.B + bbase + obl) * a.e + h * a.d_k + oi(ps) * lph + omi; };
-  if (mine) {
+  if (in_order) {
+    to_obuf();
+    if (eok) st_result(elem_at(cs), sm.obuf[ebl][ej], !xl);
+  } else if (mine) {
 #pragma unroll
     for (int ps = 0; ps < NBT; ++ps) {
       if (fours) st_result4(part_at(cs, ps), osum[ps], !xl);
@@ -540,6 +555,21 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   if (!sm.is_last) return;
   // (the error word travels with the partial sums: requested here, looked at behind their wait)
   const int errv = a.err ? __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  if (in_order) {
+    float sum = 0.f;
+    if (eok)
+      for (int s0 = 0; s0 < a.csw; s0 += 8) {
+        float part[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) part[q] = ld_part<true>(elem_at(min(s0 + q, a.csw - 1)));
+#pragma unroll
+        for (int q = 0; q < 8; ++q) if (s0 + q < a.csw) sum += part[q];
+      }
+    const float other = __shfl_xor(sum, 1);              // (a pair's columns sit in neighbour lanes)
+    if (eok) emit(ebl, ej, sum, other, a.err && errv == (int)a.launch_id);
+    if (tid == 0) a.counters[bz * nhx + hx] = 0;
+    return;
+  }
   if (mine) {
 #pragma unroll
     for (int ps = 0; ps < NBT; ++ps) {
