@@ -765,14 +765,14 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (blockIdx.x == 0 && tid == 0) st_result(a.err - 1, (int)a.launch_id, true);   // the launch the error word speaks of
 
   // The work of this wave as a list of segments (a sequence or a share of one); tile k of a segment is
-  // row tile t0 + k * stride of sequence b.  Two partitions:
+  // row tile t0 + k * stride (less `lead` from the second tile on) of sequence b.  Two partitions:
   //  * by context (default): the group's range of tiles [v0, v1) is cut at sequence boundaries and
-  //    the waves take the tiles of a share round-robin; the waves' results are merged at the
+  //    the waves take the tiles of a share round-robin, waves 0..3 with a tile's lead; the waves' results are merged at the
   //    end of each share and the groups' partials by the projection.  Balanced for any lengths.
   //  * by sequence: every sequence is cut into a.by_sequence equal shares and wave slot g * NP + p
   //    takes shares round-robin; no merge inside the workgroup, one partial per share.  For batches
   //    whose shares fill the slots evenly (many short sequences).
-  struct Seg { int b, t0, stride, ntl, len, pid; unsigned it0; const uint16_t* Kb; };   // it0: tiles of earlier segments
+  struct Seg { int b, t0, stride, lead, ntl, len, pid; unsigned it0; const uint16_t* Kb; };   // it0: tiles of earlier segments
   constexpr bool by_seq = BYSEQ;
   int seg_b = by_seq ? g * NP + p : 0;
   unsigned seg_it = 0;                              // tiles this wave has been through so far
@@ -785,7 +785,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       const int q = seg_b, b = q / shares, j = q - b * shares;
       seg_b += a.NG * NP;
       const int tiles_b = prefix[b + 1] - prefix[b], per = (tiles_b + shares - 1) / shares;
-      sg.b = b; sg.t0 = j * per; sg.stride = 1; sg.pid = q;
+      sg.b = b; sg.t0 = j * per; sg.stride = 1; sg.lead = 0; sg.pid = q;
       sg.len = lens_s[b];
       sg.Kb = a.K + (size_t)b * a.k_bstride;
       sg.ntl = max(0, min(per, tiles_b - j * per));
@@ -799,10 +799,17 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       const int s1 = min(v1, prefix[b + 1]) - prefix[b];
       if (s0 >= s1) continue;
       sg.b = b; sg.pid = b + g;
-      sg.t0 = s0 + p; sg.stride = NP;                 // this wave's tiles are s0+p, s0+p+NP, ...
+      // The first four tiles of a share go to waves 0..3, the rest to all eight in turn: every SIMD holds one of the first
+      // four waves and one of the others, whose first tiles arrive about one and a half steps later (requested at 9 us
+      // after the launch, not 4: the first burst is the memory's) and which so ended 5 us later with as many tiles.
+      // 52.6 -> 52.0 us at 16384 rows x 4096 columns, 67.5 -> 66.8 on the ragged rotary batch.  (Shares of less than four
+      // tiles per wave are over before that: there two tiles behind one another on half of the waves would be the longer.)
+      const int ahead = s1 - s0 >= 4 * NP ? NP / 2 : 0;
+      sg.stride = NP; sg.lead = p < ahead ? NP - ahead : 0;
+      sg.t0 = s0 + p + (p < ahead ? 0 : ahead);        // (without the lead: s0 + p, s0 + p + NP, ...)
       sg.len = lens_s[b];
       sg.Kb = a.K + (size_t)b * a.k_bstride;
-      sg.ntl = max(0, (s1 - s0 - p + NP - 1) / NP);
+      sg.ntl = (p < ahead ? 1 : 0) + max(0, (s1 - s0 - ahead - p + NP - 1) / NP);
       sg.it0 = seg_it;                                // tile k carries tag tag_base + it0 + k + 1
       seg_it += (unsigned)sg.ntl;
       ++seg_b;
@@ -891,7 +898,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       // where all rows collapse onto the last one and nobody uses the result): the compiler's s_waitcnt
       // for the next tile's registers is then exact.
       auto load_tile = [&](u32x4 (&t)[8], f32x4 (&r)[2], int k) {
-        const int st = __builtin_amdgcn_readfirstlane(sg.t0 + k * sg.stride);
+        const int st = __builtin_amdgcn_readfirstlane(sg.t0 + k * sg.stride - (k > 0 ? sg.lead : 0));
         if constexpr (ROPE) {
           const int row = min(st * TILE_ROWS + rg * 8, a.T - 1);
           const f32x4* rp = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(rope_lane) + (size_t)row * rope_pitch);
@@ -941,7 +948,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       // ---- softmax numerators of the unit's heads from the 8 scores of a lane (row of score jj given by
       //      row_of), against the head's running maximum
       auto numerators = [&](int k, float (&sc)[8], unsigned (&pw)[4], auto&& row_of) {
-        const int st = sg.t0 + k * sg.stride;
+        const int st = sg.t0 + k * sg.stride - (k > 0 ? sg.lead : 0);
         if ((st + 1) * TILE_ROWS > len) {             // last, partial tile: rows past the end weigh nothing
 #pragma unroll
           for (int j = 0; j < 8; ++j) sc[j] = (st * TILE_ROWS + row_of(j) < len) ? sc[j] : NEG_INF;

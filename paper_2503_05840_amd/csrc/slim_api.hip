@@ -58,6 +58,7 @@ Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
   p.nsplit_x = xcache_splits(B, H, T, width);
   p.nsplit_xf = xfused_ok(width) ? xfused_splits(B, H, T, width) : 0;
   size_t nparts = (size_t)B * (p.nsplit > p.nsplit_x ? p.nsplit : p.nsplit_x);
+  if (lean && (size_t)B * p.nsplit_xf > nparts) p.nsplit_xf = (int)(nparts / B);
   if ((size_t)B * p.nsplit_xf > nparts) nparts = (size_t)B * p.nsplit_xf;
   if (p.fused_ok && (size_t)p.geom.nparts > nparts) nparts = p.geom.nparts;
   if (p.fused_ok && (size_t)B * 4 > nparts && fused_by_sequence(p.geom, B, false)) nparts = (size_t)B * 4;
