@@ -71,8 +71,9 @@ Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
   if (f32_stream_ok(DT_F32, H, width, d_k) && (size_t)B * p.nsplit_f > nparts) nparts = (size_t)B * p.nsplit_f;
   p.csw = proj_row_splits(H, width, e, B);
   if (p.fused_ok && B <= 16 && p.geom.grid >= H) {
-    const int tiles_w = (width + TILE_ROWS - 1) / TILE_ROWS, c = proj_splits_per_unit(H);
-    p.csw_f = c < tiles_w ? c : tiles_w;
+    // a tile of W for every wave (8 waves x 32 rows) before another workgroup: what is split finer has more to hand over
+    const int most = (width + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), c = proj_splits_per_unit(H);
+    p.csw_f = c < most ? c : most;
   }
   p.off_S = o;      o += up(sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32));   // (rows padded to 32 scores)
   p.off_Cpart = o;  o += up(sizeof(float) * nparts * H * width);
