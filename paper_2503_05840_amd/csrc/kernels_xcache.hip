@@ -811,8 +811,10 @@ static int head_tiles_in_flight(int H) {
   while (p < nht && p < 8) p *= 2;
   return p;
 }
+// (heads of at most 128 columns: q~ holds four k-steps of a head's columns, the projection a head's output block in one
+// tile of 128)
 bool xcache_fast_ok(int dtype, int H, int d_model, int d_k) {
-  return dtype == DT_BF16 && d_model % 128 == 0 && d_k % 32 == 0 && d_k >= 32 && H >= 1 && d_model < (1 << 22);
+  return dtype == DT_BF16 && d_model % 128 == 0 && d_k % 32 == 0 && d_k >= 32 && d_k <= 128 && H >= 1 && d_model < (1 << 22);
 }
 
 int xcache_splits(int B, int H, int T, int d_model) {

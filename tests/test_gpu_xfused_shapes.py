@@ -27,3 +27,14 @@ def test_one_pass_xcache_shapes_match_oracle(i):
     say(f"  rel err {e:.3e}")
     assert e <= TOL["bf16"]
     assert np.array_equal(a, x.run())
+
+
+@pytest.mark.parametrize("d_k", [96, 128, 160, 256])
+def test_xcache_heads_on_either_side_of_128_columns_match_oracle(d_k):
+    # 128 columns are the widest head of the MFMA path; wider ones take the plain kernels
+    cfg = synth.scaled(synth.CONFIGS[4], B=2, H=3, d=512, d_k=d_k, T=70)
+    say(f"[case] X-cache, heads of {d_k} columns: B=2 H=3 d_model=512 T=70")
+    x = XCase(cfg, lens=[70, 33])
+    e = x.err(x.run())
+    say(f"  rel err {e:.3e}")
+    assert e <= TOL["bf16"]
