@@ -20,7 +20,9 @@
  *     aborts.  Argument errors are detected on the host before anything is launched.
  *   - Waits between workgroups inside the kernels are bounded in real time; if one ever runs out
  *     (the launch's workgroups were not all resident together), the outputs of that call are
- *     written as NaN instead of the kernel hanging, and slim_status reports SLIM_ERR_TIMEOUT.
+ *     written as NaN instead of the kernel hanging, and slim_status reports SLIM_ERR_TIMEOUT.  The
+ *     same happens to results whose workgroups do not run on the XCD that slim_init found for
+ *     them, so that they cannot meet in its L2.
  *   - q is the already projected, un-scaled query (the library applies 1/sqrt(d_k)); out is
  *     concat(head_1..head_H) before W_O (eq. 5).  Attention runs over exactly the cached
  *     rows handed in (the caller appends the new token's key first if it wants it attended).
@@ -46,7 +48,8 @@ extern "C" {
 #define SLIM_ERR_ILLCOND    -7   /* result written, but rcond(W_K) < 1e-12: do not trust it   */
 #define SLIM_ERR_LAUNCH     -8   /* HIP reported an error at allocation or launch             */
 #define SLIM_ERR_SEQLEN     -9   /* a host-side sequence length is < 1 or > T                 */
-#define SLIM_ERR_TIMEOUT   -10   /* slim_status: a wait between workgroups ran out (outputs NaN) */
+#define SLIM_ERR_TIMEOUT   -10   /* slim_status: a wait between workgroups ran out, or workgroups could
+                                    not meet where they were expected to (outputs NaN)            */
 #define SLIM_ERR_LAYOUT    -11   /* opts->k_layout: rows per sequence not a multiple of 32, or a shape or
                                     dtype whose kernels read row-major caches only              */
 
@@ -157,6 +160,12 @@ typedef struct slim_opts {
 #define SLIM_VARIANT_FUSED     3   /* bf16, H <= 32, d_k <= 128: single pass over K with the weighted
                                       sum and the projection on MFMA (one launch when B <= 16, else
                                       two); falls back to GENERIC when the shape does not qualify */
+/* For tests, added to any of these: workgroups that share a result meet at the memory side even where
+ * slim_init has found that they can meet in an XCD's L2 (same sums in the same order); and, with the
+ * meeting in the L2, every workgroup expects to run on another XCD than its own, as if the hardware had
+ * placed it elsewhere (outputs NaN, SLIM_ERR_TIMEOUT from slim_status). */
+#define SLIM_VARIANT_VIA_MEMORY  0x100
+#define SLIM_VARIANT_MISPLACED   0x200
 
 /* Per-device set-up for the current device, idempotent and thread-safe: looks up the address of the
  * library's static device array, counts the compute units, checks with one probe launch on the null stream (plus a
@@ -166,11 +175,13 @@ typedef struct slim_opts {
  * of the first decode call, e.g. before a stream capture starts.  SLIM_ERR_LAUNCH when HIP fails. */
 int slim_init(void);
 
-/* Whether the waits between workgroups of the latest bf16 fast-path launch that used this workspace
- * ended normally.  The decode calls are asynchronous and return before their kernels have run, so a
+/* Whether the workgroups of the latest bf16 fast-path call that used this workspace (K-cache, X-cache or
+ * attention block) could work together: whether their waits for each other ended normally, and whether
+ * those that meet in an XCD's L2 ran there.  The decode calls are asynchronous and return before their kernels have run, so a
  * wait that runs out inside a kernel (the chip could not keep the launch's workgroups resident
  * together within opts->wait_budget_us, e.g. because other work held compute units) cannot be reported
- * by the call itself: the kernel raises an error word in the workspace and writes NaN outputs.  This
+ * by the call itself: the kernel raises an error word in the workspace and writes NaN outputs (the new
+ * token's cache rows among them, in an attention block whose projections were concerned).  This
  * query waits for `stream` (hipStream_t, null => the null stream), reads the word back and returns
  * SLIM_ERR_TIMEOUT or SLIM_OK.  The fast path needs the chip free of other kernels while it runs.
  *   workspace: the device scratch the call was given; NULL => the library-owned scratch of the

@@ -91,6 +91,10 @@ __device__ __forceinline__ void st_result4(float* p, f32x4 v, bool write_through
   else *reinterpret_cast<f32x4*>(p) = v;
 }
 
+// Whether this workgroup runs elsewhere than where workgroups with its i % 8 are expected (see ProjArgs::xcc_map).
+__device__ __forceinline__ unsigned my_xcc() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xf; }   // HW_REG_XCC_ID
+__device__ __forceinline__ bool misplaced(unsigned xcc_map) { return my_xcc() != ((xcc_map >> ((blockIdx.x & 7) * 4)) & 0xf); }
+
 // Tiles of 32 rows: prefix[b] = number of tiles of sequences 0..b-1; lens_s[b] (if given) = rows of
 // sequence b.  The first wave takes 64 sequences at a time, one per lane (one memory round trip per 64
 // sequences instead of one per sequence), and adds them up with a scan over the lanes.
@@ -215,10 +219,13 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
       x[t][1] = *reinterpret_cast<const f32x4*>(src + 4);
     }
   };
+  // (raised by an earlier launch; the single launch reads the word when its own waits are over)
+  const int err_early = !COH && a.err_before ? ld_err<true>(a.err) : 0;
   if constexpr (DENSE) load_x(xc, min(w, max(ntile - 1, 0)));
   u32x4 wt[8], wn[8];
   if (w < ntile) load_w(wt, w);                      // in flight while the merge weights are built
   if (w + NW < ntile) load_w(wn, w + NW);
+  const bool astray = a.xcc_map != 0 && misplaced(a.xcc_map);      // (used at the hand-over; looked up while W travels)
 
   // Which partials belong to which sequence: in mode 1 nsplit each; in mode 0 from the tile prefix, looked up once and
   // kept in LDS (single-launch mode: before the wait for the other workgroups, whose barrier it shares).
@@ -483,8 +490,9 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   auto emit = [&](int bl, int j, float val, float other, bool bad) {
     const size_t b = (size_t)(bbase + bl);
     const int col = h * a.d_k + j;
+    if (bad) val = other = NAN;
     if constexpr (!DENSE) {
-      outp[b * a.e + col] = bad ? NAN : val;
+      outp[b * a.e + col] = val;
     } else {
       const int role = a.role[mtx];
       if (role == 0) { outp[b * a.e + col] = val; return; }
@@ -507,7 +515,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   };
 
   if (a.csw == 1) {
-    const bool bad = a.err && ld_err<COH>(a.err) == (int)a.launch_id;      // the stream kernel gave up waiting
+    const bool bad = a.err_before && (COH ? ld_err<true>(a.err) : err_early) == (int)a.launch_id;
     to_obuf();
     for (int v = tid; v < nb * a.d_k; v += NTHR) {
       const int bl = v / a.d_k, j = v % a.d_k;
@@ -517,14 +525,21 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   // ---- several workgroups share the rows of W: last one to arrive adds the partial sums ---------
   // No cache-wide fences: the partial sums are stored and waited for before this workgroup's arrival is counted, and
-  // the last workgroup reads them past its L1.  Where the workgroups of a head share an XCD (xcd_local: checked by the
-  // host) its L2 is their meeting point -- plain stores, an atomic that the L2 executes; otherwise the stores are
+  // the last workgroup reads them past its L1.  Where the workgroups of a head share an XCD (xcc_map != 0: checked by
+  // the host) its L2 is their meeting point -- plain stores, an atomic that the L2 executes; otherwise the stores are
   // written through and the atomic has device scope: three round trips to the memory side instead of to the L2.
+  // Every workgroup looks where it runs before it relies on that: one that is elsewhere counts nowhere, so that its unit
+  // has no last arriver, and itself writes the unit's result, NaN, and raises the error word.
   // The partial sums of a head lie in accumulator order, [element i][column group], so that they leave and come back
   // 16 bytes at a time (where the head has whole fours of column groups).
   // Dense products of up to 512 elements (a few sequences) keep their columns in order instead, an element a thread: they
   // are finished from where they are read, without another pass through LDS (4 x 4096 x 4096: 12.0 against 12.8 us).
-  const bool xl = a.xcd_local != 0, fours = (lph & 3) == 0;
+  const bool xl = a.xcc_map != 0, fours = (lph & 3) == 0;
+  if (astray) {
+    if (tid == 0 && a.err) st_result(a.err, (int)a.launch_id, true);
+    for (int v = tid; v < nb * a.d_k; v += NTHR) emit(v / a.d_k, v % a.d_k, NAN, NAN, true);
+    return;
+  }
   const bool in_order = DENSE && nb * a.d_k <= NTHR;
   const int ebl = tid / a.d_k, ej = tid - ebl * a.d_k;  // in_order: this thread's element
   const bool eok = tid < nb * a.d_k;
@@ -553,8 +568,8 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   __syncthreads();
   if (!sm.is_last) return;
-  // (the error word travels with the partial sums: requested here, looked at behind their wait)
-  const int errv = a.err ? __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  // (single launch: the error word travels with the partial sums, requested here, looked at behind their wait)
+  const int errv = COH ? ld_err<true>(a.err) : err_early;
   if (in_order) {
     float sum = 0.f;
     if (eok)
@@ -566,7 +581,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         for (int q = 0; q < 8; ++q) if (s0 + q < a.csw) sum += part[q];
       }
     const float other = __shfl_xor(sum, 1);              // (a pair's columns sit in neighbour lanes)
-    if (eok) emit(ebl, ej, sum, other, a.err && errv == (int)a.launch_id);
+    if (eok) emit(ebl, ej, sum, other, a.err_before && errv == (int)a.launch_id);
     if (tid == 0) a.counters[bz * nhx + hx] = 0;
     return;
   }
@@ -594,7 +609,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     }
   }
   to_obuf();
-  const bool bad = a.err && errv == (int)a.launch_id;                      // NaN: the stream kernel gave up waiting
+  const bool bad = a.err_before && errv == (int)a.launch_id;              // NaN: the stream kernel gave up waiting
   for (int v = tid; v < nb * a.d_k; v += NTHR) {
     const int bl = v / a.d_k, j = v % a.d_k;
     emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
@@ -610,6 +625,8 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   // unit = (head, batch chunk), for which csw workgroups share the rows of W: dealt to the XCDs so that they meet in one L2
   const int nhx = DENSE ? a.H * a.nmat : a.H;
   const int slot = blockIdx.x >> 3, unit = (slot / a.csw) * 8 + (blockIdx.x & 7);
+  // (the launch the error word speaks of; an earlier launch of the call has written it already)
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.err && !a.err_before) st_result(a.err - 1, (int)a.launch_id, true);
   if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
   project_work<NBT, false, DENSE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);
@@ -692,9 +709,21 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   const int p = wu;                                 // this wave's team: wave p of every workgroup of the group
 
   const bool fuse = !BYSEQ && a.fuse != 0;
-  // the projection's arrival counters start at 0 (single-launch mode: a head's counter is cleared from the XCD that counts)
+  // Single launch: this workgroup's (head, row split) of the projection, a head's workgroups on one XCD as in
+  // project_mfma_kernel.  The arrival counters start at 0, a head's cleared by its first workgroup, in the L2 that counts.
+  auto projection_share = [&](int& phead, int& psplit) {
+    int i = blockIdx.x;
+    asm volatile("" : "+s"(i));                       // (computed where it is used: not kept in registers through the stream)
+    const int slot = i >> 3;
+    phead = (slot / a.proj.csw) * 8 + (i & 7);
+    psplit = slot % a.proj.csw;
+  };
   if (fuse) {
-    if (blockIdx.x < a.H && tid == 0) st_result(a.counters + blockIdx.x, 0, !a.proj.xcd_local);
+    if (wu == NP - 1) {                               // (while the first wave builds the tile prefix)
+      int phead, psplit;
+      projection_share(phead, psplit);
+      if (phead < a.proj.H && psplit == 0 && lane == 0) st_result(a.counters + phead, 0, a.proj.xcc_map == 0);
+    }
   } else if (blockIdx.x == 0 && a.counters) {
     for (int i = tid; i < a.ncounters; i += NTHR) a.counters[i] = 0;
   }
@@ -1314,16 +1343,19 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (!fuse) return;
 
   // ========================= single-launch mode: merge + projection ===============================
-  // This workgroup's partials are out (write-through stores, waited for) before its arrival flag.
+  // This workgroup's partials are out (write-through stores, waited for) before its arrival flag, and so is the error word
+  // if it may have cleared a counter in another L2 than its head's.  (Looked up here, where it costs nothing beside the
+  // stores' way out; at the kernel's start it was 0.3 us of every launch.)
+  if (wu == NP - 1 && a.proj.xcc_map != 0 && misplaced(a.proj.xcc_map) && lane == 0) st_result(a.err, (int)a.launch_id, true);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) st_result(reinterpret_cast<int*>(a.flags) + blockIdx.x, (int)a.launch_id, true);
-  // (head, row split): a head's workgroups on one XCD, as in project_mfma_kernel
-  const int slot = blockIdx.x >> 3, phead = (slot / a.proj.csw) * 8 + (blockIdx.x & 7);
+  int phead, psplit;
+  projection_share(phead, psplit);
   if (phead >= a.proj.H) return;
   // (everything of the stream phase is over in this workgroup: its LDS is reused)
   ProjShared<1>& psm = *reinterpret_cast<ProjShared<1>*>(sbuf);
-  project_work<1, true, false>(a.proj, phead, slot % a.proj.csw, 0, prefix, psm, red, [&]() {
+  project_work<1, true, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
     // every workgroup's partials must be out: all arrival flags carry this launch's id
     if (wu == 0) {
       unsigned long long since = ~0ull;
@@ -1346,8 +1378,8 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
 
 // Records which XCD each workgroup of a 256-workgroup launch runs on.
 __global__ __launch_bounds__(512) void xcc_probe_kernel(unsigned* out) {
-  const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20);   // HW_REG_XCC_ID
-  if (threadIdx.x == 0) out[blockIdx.x] = xcc & 0xf;
+  const unsigned xcc = my_xcc();
+  if (threadIdx.x == 0) out[blockIdx.x] = xcc;
   for (int i = 0; i < 200; ++i) __builtin_amdgcn_s_sleep(10);        // stay resident while the rest start
 }
 
@@ -1384,10 +1416,10 @@ bool fused_geometry(int B, int H, int T, int d, FusedGeom* g) {
   return true;
 }
 
-// True when workgroups i and j of a 256-workgroup launch share an XCD whenever i % 8 == j % 8: a probe
-// launch on `st` that records each workgroup's XCD into `dev_buf` (device memory, 256 unsigned), read
-// back with a blocking copy.  The caller caches the answer per device.
-bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
+// The XCC ids (four bits each, see ProjArgs::xcc_map) when workgroups i and j of a 256-workgroup launch share an XCD
+// exactly where i % 8 == j % 8, else 0: a probe launch on `st` that records each workgroup's XCD into `dev_buf`
+// (device memory, 256 unsigned), read back with a blocking copy.  The caller caches the answer per device.
+unsigned probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
   unsigned h[256];
   hipLaunchKernelGGL(xcc_probe_kernel, dim3(256), dim3(512), 0, st, dev_buf);
   bool ok = hipMemcpyAsync(h, dev_buf, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
@@ -1398,7 +1430,9 @@ bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
     for (int i = 1; i < 8 && ok; ++i)
       for (int j = 0; j < i; ++j) ok = ok && h[i] != h[j];
   (void)hipGetLastError();
-  return ok;
+  unsigned map = 0;
+  for (int i = 0; i < 8 && ok; ++i) map |= h[i] << (4 * i);
+  return map;                                          // (eight different ids: never 0)
 }
 
 // Workgroups of the stream kernel one compute unit can hold at once (0 on error): the launch is only

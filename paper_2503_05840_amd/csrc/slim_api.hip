@@ -110,7 +110,8 @@ Plan make_plan(int B, int H, int T, int width, int e) {
 // i % 8 (a probe launch on the null stream and a blocking read-back, no allocation: it writes into
 // the static scratch), and the event used to order stream-kernel launches of different streams.
 struct DeviceState {
-  bool ready = false, xcd_round_robin = false;
+  bool ready = false;
+  unsigned xcc_map = 0;                       // see ProjArgs; 0: workgroups are not dealt to the XCDs round robin
   int cus = 0;
   void* static_scratch = nullptr;
   hipEvent_t order_ev = nullptr;
@@ -131,19 +132,27 @@ DeviceState* device_state() {
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) { (void)hipGetLastError(); return nullptr; }
   s.static_scratch = ptr;
   if (hipDeviceGetAttribute(&s.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) { (void)hipGetLastError(); s.cus = 0; }
-  s.xcd_round_robin = s.cus >= 256 && probe_xcd_round_robin((unsigned*)ptr, nullptr);
+  s.xcc_map = s.cus >= 256 ? probe_xcd_round_robin((unsigned*)ptr, nullptr) : 0;
   if (hipEventCreateWithFlags(&s.order_ev, hipEventDisableTiming) != hipSuccess) { s.order_ev = nullptr; (void)hipGetLastError(); }
   s.ready = true;
   return &s;
 }
 
-// Whether workgroup i of a launch is known to run on XCD i % 8: after slim_init or a call that needed the set-up; without
+// Where workgroup i of a launch is known to run (ProjArgs::xcc_map): after slim_init or a call that needed the set-up; without
 // it the callers' kernels meet at the memory side.  (Never sets anything up itself: the set-up waits for the device.)
-bool xcd_round_robin_known() {
+unsigned known_xcc_map() {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return false; }
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return 0; }
   std::lock_guard<std::mutex> lk(g_dev_mu);
-  return g_dev[dev].ready && g_dev[dev].xcd_round_robin;
+  return g_dev[dev].ready ? g_dev[dev].xcc_map : 0;
+}
+
+// opts->variant: which implementation, and two switches for tests
+int variant_of(const slim_opts* o) { return o ? o->variant & 0xff : SLIM_VARIANT_AUTO; }
+unsigned call_xcc_map(unsigned map, const slim_opts* o) {
+  const int v = o ? o->variant : 0;
+  if (v & SLIM_VARIANT_VIA_MEMORY) return 0;
+  return (v & SLIM_VARIANT_MISPLACED) ? (map << 4) | (map >> 28) : map;       // (every workgroup's neighbour's XCD)
 }
 
 // Library-owned scratch: one allocation per device, grown on demand, kept until exit.
@@ -263,7 +272,7 @@ extern "C" const char* slim_strerror(int code) {
     case SLIM_ERR_LAUNCH: return "HIP allocation or launch error";
     case SLIM_ERR_SEQLEN: return "sequence length outside [1, T]";
     case SLIM_ERR_LAYOUT: return "banded K-cache: rows per sequence not a multiple of 32, or no kernel reads that layout for this shape / dtype / call";
-    case SLIM_ERR_TIMEOUT: return "a wait between workgroups ran out in the latest stream-kernel launch on this workspace; its outputs are NaN";
+    case SLIM_ERR_TIMEOUT: return "a wait between workgroups ran out in the latest fast-path call on this workspace, or they did not run where they were to meet; its outputs are NaN";
     default: return "unknown slim status";
   }
 }
@@ -295,6 +304,10 @@ std::atomic<unsigned> g_tag{(unsigned)std::chrono::steady_clock::now().time_sinc
 // Launch ids (arrival flags, error word) start at a random point as well: a fresh workspace may hold
 // anything, small integers included.
 std::atomic<unsigned> g_launch{((unsigned)std::chrono::steady_clock::now().time_since_epoch().count() * 2246822519u) | 1u};
+unsigned next_launch_id() {
+  const unsigned id = g_launch.fetch_add(1);
+  return id ? id : g_launch.fetch_add(1);
+}
 
 extern "C" int slim_variant_for(int B, int H, int T, int d, int dtype) {
   if (B < 1 || H < 1 || T < 1 || d < 1 || d % H != 0) return 0;
@@ -318,9 +331,10 @@ extern "C" size_t slim_workspace_bytes_xcache(int B, int H, int T, int d_model, 
 namespace {
 
 // slim_decode and slim_decode_static: the same validation, plan and launches; `fixed_ws` (non-null for
-// the static scratch) replaces the workspace lookup.
+// the static scratch) replaces the workspace lookup.  block_id: the launch id of an attention block's earlier launches on
+// this workspace (0: none), so that what they could not do shows in this step's result as well.
 int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, int B, int H, int T, int d,
-                const slim_opts* o, char* fixed_ws, size_t fixed_ws_bytes) {
+                const slim_opts* o, char* fixed_ws, size_t fixed_ws_bytes, unsigned block_id) {
   if (!q || !Kcache || !W_KV || !out) return SLIM_ERR_ARG;
   if (H < 1 || d < 1 || d % H != 0) return SLIM_ERR_SHAPE;
   const int d_k = d / H;
@@ -347,7 +361,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   const long kb = t_stride * d;
 
   StageTimer tm(o, st);
-  int variant = pick_variant(o ? o->variant : SLIM_VARIANT_AUTO, B, H, T, d, dtype);
+  int variant = pick_variant(variant_of(o), B, H, T, d, dtype);
   DeviceState* dev = nullptr;
   if (variant == SLIM_VARIANT_FUSED || variant == SLIM_VARIANT_FUSED_SPLIT) {
     // the stream kernel needs this device's set-up, and all of its workgroups resident together
@@ -373,22 +387,21 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     fa.exch = (unsigned long long*)(ws + p.off_exch);
     const unsigned tiles = (unsigned)B * (unsigned)((T + TILE_ROWS - 1) / TILE_ROWS) + (unsigned)B + 64u;
     fa.tag_base = g_tag.fetch_add(tiles);
-    unsigned lid = g_launch.fetch_add(1);
-    if (lid == 0) lid = g_launch.fetch_add(1);
+    const unsigned lid = block_id ? block_id : next_launch_id(), map = call_xcc_map(dev->xcc_map, o);
     fa.launch_id = lid;
     // every wait for another workgroup: 20 ms of real time (100 MHz ticks) unless the caller says otherwise
     const long long budget_us = (o && o->wait_budget_us) ? (long long)o->wait_budget_us : 20000;
     fa.wait_ticks = budget_us < 0 ? 0ull : (unsigned long long)budget_us * 100ull;
-    fa.xcd_local = (g.gpx > 0 && dev->xcd_round_robin) ? 1 : 0;
+    fa.xcd_local = (g.gpx > 0 && map != 0) ? 1 : 0;
     fa.rope = rope;
     fa.Cpart = Cpart; fa.mpart = mpart; fa.lpart = lpart;
     fa.err = ctrl + CTRL_INTS - 1; fa.counters = ctrl; fa.ncounters = H * zb;
     ProjArgs pa{};
     pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_KV;
     pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
-    pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.seq_lens = lens;
+    pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.err_before = 1; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcd_local = dev->xcd_round_robin;
+    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcc_map = map;
     if (const int shares = fused_by_sequence(g, B, lens != nullptr)) {
       fa.by_sequence = shares;
       pa.mode = 1; pa.nsplit = shares;               // partials laid out [sequence][share]
@@ -410,7 +423,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     tm.finish();
     return launch_status();
   }
-  const int requested = o ? o->variant : SLIM_VARIANT_AUTO;
+  const int requested = variant_of(o);
   int* const ctrl = (int*)(ws + p.off_ctrl);
   float* const outpart = (float*)(ws + p.off_outpart);
   const int arrivals = p.rsplit > 1 ? (int)merge_counters(H, d_k, B) : 0;
@@ -450,7 +463,8 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
     pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
     pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
-    pa.csw = p.csw; pa.xcd_local = xcd_round_robin_known();
+    pa.csw = p.csw; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
+    pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = block_id ? block_id : next_launch_id(); pa.err_before = block_id != 0;
     launch_project_mfma(pa, st);
   } else {
     launch_merge_project(dtype, Cpart, mpart, lpart, p.nsplit, false, lens, T, W_KV, d, d, H, d_k, (float*)out, outpart, p.rsplit,
@@ -465,7 +479,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
 
 extern "C" int slim_decode(const void* q, const void* Kcache, const void* W_KV, void* out, int B,
                            int H, int T, int d, const slim_opts* o) {
-  return decode_core(q, Kcache, W_KV, out, B, H, T, d, o, nullptr, 0);
+  return decode_core(q, Kcache, W_KV, out, B, H, T, d, o, nullptr, 0, 0);
 }
 
 extern "C" int slim_init(void) { return device_state() ? SLIM_OK : SLIM_ERR_LAUNCH; }
@@ -477,7 +491,7 @@ extern "C" int slim_decode_static(const void* q, const void* Kcache, const void*
   if (o && (o->workspace || o->stage_ms)) return SLIM_ERR_ARG;     // brings its own scratch; timing events allocate
   DeviceState* dev = device_state();
   if (!dev) return SLIM_ERR_LAUNCH;
-  return decode_core(q, Kcache, W_KV, out, B, H, T, d, o, (char*)dev->static_scratch, STATIC_SCRATCH_BYTES);
+  return decode_core(q, Kcache, W_KV, out, B, H, T, d, o, (char*)dev->static_scratch, STATIC_SCRATCH_BYTES, 0);
 }
 
 extern "C" int slim_status(const void* workspace, void* stream) {
@@ -559,14 +573,15 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
   const long xb = t_stride * d_model;
 
   StageTimer tm(o, st);
-  const int req = o ? o->variant : SLIM_VARIANT_AUTO;
+  const int req = variant_of(o);
   if (req != SLIM_VARIANT_GENERIC && xcache_fast_ok(dtype, H, d_model, d_k) && H < CTRL_INTS / 2 &&
       (size_t)T * d_model * 2 < ((size_t)1 << 32)) {      // (the kernels address a sequence's rows with 32-bit offsets)
     // MFMA path: q~, scores (log2 domain), weighted sum per context split, merge + projection
     int* ctrl = (int*)(ws + p.off_ctrl);
     const int per = 16 * proj_batch_tiles(B, d_model, e, H);
     const int zb = (B + per - 1) / per;
-    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, ctrl, H * zb, st);
+    const int csw = proj_row_splits(H, d_model, e, B);
+    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, ctrl, csw > 1 ? H * zb : 0, st);
     tm.mark();
     int nsplit = p.nsplit_x;
     if (p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT) {
@@ -583,10 +598,10 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     ProjArgs pa{};
     pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_V;
     pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
-    pa.err = nullptr; pa.launch_id = 0; pa.seq_lens = lens;
+    pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = next_launch_id(); pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d_model; pa.e = e;
     pa.NG = 0; pa.nsplit = nsplit; pa.mode = 1; pa.mscale = 1.0f;
-    pa.csw = proj_row_splits(H, d_model, e, B); pa.xcd_local = xcd_round_robin_known();
+    pa.csw = csw; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
     launch_project_mfma(pa, st);
     tm.mark();
     tm.finish();
@@ -659,7 +674,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   float* knew = (float*)(ws + bb.off_k);
   float* vnew = (float*)(ws + bb.off_v);
   float* attn = (float*)(ws + bb.off_attn);
-  const int variant = pick_variant(o ? o->variant : SLIM_VARIANT_AUTO, B, H, T, d, dtype);
+  const int variant = pick_variant(variant_of(o), B, H, T, d, dtype);
   // the MFMA products count arrivals per (matrix, head, batch chunk)
   const int zb = (B + 15) / 16;
   const int nmat = slim_path ? 2 : 3;
@@ -675,7 +690,9 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   ProjArgs pa{};
   pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = (int*)(ws + p.off_ctrl);
   pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-  pa.nsplit = 1; pa.mscale = 1.0f; pa.xcd_local = xcd_round_robin_known();
+  pa.nsplit = 1; pa.mscale = 1.0f; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
+  const unsigned id = fast ? next_launch_id() : 0;     // one for all launches of the call
+  pa.err = (int*)(ws + p.off_ctrl) + CTRL_INTS - 1; pa.launch_id = id;
 
   StageTimer tm(o, st);
   if (fast) {
@@ -706,7 +723,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   inner.stage_ms = nullptr;
   int rc;
   if (slim_path) {
-    rc = slim_decode(q, c.Kcache, c.W_second, attn, B, H, T, d, &inner);
+    rc = decode_core(q, c.Kcache, c.W_second, attn, B, H, T, d, &inner, nullptr, 0, id);
   } else {
     inner.rope_table = nullptr;                       // the cache already holds the rotated keys
     rc = vanilla_kv_decode(q, c.Kcache, c.Vcache, attn, B, H, T, d, &inner);
@@ -714,7 +731,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   if (rc) return rc;
   tm.mark();
   if (fast) {
-    pa.Cpart = attn; pa.nmat = 1; pa.csw = dense_row_splits(H, 1, d, d, B);
+    pa.Cpart = attn; pa.nmat = 1; pa.csw = dense_row_splits(H, 1, d, d, B); pa.err_before = 1;
     pa.Wm[0] = (const uint16_t*)c.W_O; pa.outm[0] = (float*)c.y; pa.role[0] = 0;
     launch_dense_mfma(pa, st);
   } else {

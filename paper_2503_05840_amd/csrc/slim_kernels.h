@@ -94,13 +94,16 @@ struct ProjArgs {
   const float* Cpart; const float* mpart; const float* lpart;
   const uint16_t* W;                  // [rows][e] bf16
   float* out; float* outpart;         // [B][e], [csw][B][e]
-  int* counters; const int* err; unsigned launch_id;
+  int* counters; int* err; unsigned launch_id;    // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
+  int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
   const int32_t* seq_lens;
   int B, T, H, d_k, rows, e;
   int NG, nsplit, mode;               // mode 0: partials laid out by the stream kernel; 1: [b][nsplit]
   float mscale;                       // 1 for log2-domain maxima, log2(e) for natural-log ones
   int csw, crows;                     // row splits of W across workgroups, rows per split
-  int xcd_local;                      // workgroup i runs on XCD i % 8 (checked): the row splits of a head meet in its L2
+  // The XCC id of XCD slot i % 8 in bits 4 (i % 8) .. + 3 where workgroup i of a launch runs there (checked at set-up, and by
+  // every workgroup for itself): the row splits of a head meet in its L2.  0: not known, they meet at the memory side.
+  unsigned xcc_map;
   // Dense products (launch_dense_mfma): Cpart = x [B][rows], out_m = x W_m for nmat matrices.
   // role 0: fp32 result.  The new token's rows (it sits at row / position seq_lens[b] - 1):
   // role 1: query, fp32, rotated to that position when rope is set; role 2: key row into Kc (rotated
@@ -144,7 +147,7 @@ struct FusedArgs {
 bool fused_geometry(int B, int H, int T, int d, FusedGeom* g);
 int fused_by_sequence(const FusedGeom& g, int B, bool ragged);
 size_t fused_exch_bytes(const FusedGeom& g);
-bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
+unsigned probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
 int fused_blocks_per_cu(const FusedGeom& g, bool rope);
 void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st);
 int proj_batch_tiles(int B, int rows, int e, int H);
