@@ -21,8 +21,7 @@
  *   - Waits between workgroups inside the kernels are bounded in real time; if one ever runs out
  *     (the launch's workgroups were not all resident together), the outputs of that call are
  *     written as NaN instead of the kernel hanging, and slim_status reports SLIM_ERR_TIMEOUT.  The
- *     same happens to results whose workgroups do not run on the XCD that slim_init found for
- *     them, so that they cannot meet in its L2.
+ *     same happens to results whose workgroups do not share the XCD in whose L2 they are to meet.
  *   - q is the already projected, un-scaled query (the library applies 1/sqrt(d_k)); out is
  *     concat(head_1..head_H) before W_O (eq. 5).  Attention runs over exactly the cached
  *     rows handed in (the caller appends the new token's key first if it wants it attended).
@@ -162,10 +161,10 @@ typedef struct slim_opts {
                                       two); falls back to GENERIC when the shape does not qualify */
 /* For tests, added to any of these: workgroups that share a result meet at the memory side even where
  * slim_init has found that they can meet in an XCD's L2 (same sums in the same order); and, with the
- * meeting in the L2, every workgroup expects to run on another XCD than its own, as if the hardware had
- * placed it elsewhere (outputs NaN, SLIM_ERR_TIMEOUT from slim_status). */
+ * meeting in the L2, every second of them behaves as if the hardware had placed it on another XCD (outputs
+ * NaN, SLIM_ERR_TIMEOUT from slim_status). */
 #define SLIM_VARIANT_VIA_MEMORY  0x100
-#define SLIM_VARIANT_MISPLACED   0x200
+#define SLIM_VARIANT_APART   0x200
 
 /* Per-device set-up for the current device, idempotent and thread-safe: looks up the address of the
  * library's static device array, counts the compute units, checks with one probe launch on the null stream (plus a
@@ -177,7 +176,7 @@ int slim_init(void);
 
 /* Whether the workgroups of the latest bf16 fast-path call that used this workspace (K-cache, X-cache or
  * attention block) could work together: whether their waits for each other ended normally, and whether
- * those that meet in an XCD's L2 ran there.  The decode calls are asynchronous and return before their kernels have run, so a
+ * those that meet in an XCD's L2 shared that XCD.  The decode calls are asynchronous and return before their kernels have run, so a
  * wait that runs out inside a kernel (the chip could not keep the launch's workgroups resident
  * together within opts->wait_budget_us, e.g. because other work held compute units) cannot be reported
  * by the call itself: the kernel raises an error word in the workspace and writes NaN outputs (the new

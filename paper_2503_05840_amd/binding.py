@@ -17,7 +17,7 @@ LIB_PATH = os.environ.get("SLIM_ATTENTION_LIB") or os.path.join(_PKG, "libslim_a
 SLIM_OK = 0
 SLIM_F32, SLIM_BF16 = 0, 1
 VARIANT_AUTO, VARIANT_GENERIC, VARIANT_FUSED_SPLIT, VARIANT_FUSED = 0, 1, 2, 3
-VARIANT_VIA_MEMORY, VARIANT_MISPLACED = 0x100, 0x200      # for tests, added to a variant
+VARIANT_VIA_MEMORY, VARIANT_APART = 0x100, 0x200      # for tests, added to a variant
 K_ROWMAJOR, K_BANDED = 0, 1       # slim_opts.k_layout
 DTYPES = {"f32": SLIM_F32, "bf16": SLIM_BF16}
 

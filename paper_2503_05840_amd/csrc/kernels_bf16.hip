@@ -91,9 +91,7 @@ __device__ __forceinline__ void st_result4(float* p, f32x4 v, bool write_through
   else *reinterpret_cast<f32x4*>(p) = v;
 }
 
-// Whether this workgroup runs elsewhere than where workgroups with its i % 8 are expected (see ProjArgs::xcc_map).
-__device__ __forceinline__ unsigned my_xcc() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xf; }   // HW_REG_XCC_ID
-__device__ __forceinline__ bool misplaced(unsigned xcc_map) { return my_xcc() != ((xcc_map >> ((blockIdx.x & 7) * 4)) & 0xf); }
+__device__ __forceinline__ unsigned my_xcc() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 7; }   // HW_REG_XCC_ID
 
 // Tiles of 32 rows: prefix[b] = number of tiles of sequences 0..b-1; lens_s[b] (if given) = rows of
 // sequence b.  The first wave takes 64 sequences at a time, one per lane (one memory round trip per 64
@@ -175,7 +173,8 @@ __device__ __forceinline__ void ld_part8(const float* const (&p)[8], unsigned o0
 
 // `red`: 64 KB of LDS: the merged C, later the cross-wave sum.
 // `after_w_issue` runs (all threads) once the first tile of W is in flight and before any partial
-// is read: the place to build the tile prefix, or to wait for the other workgroups' partials.
+// is read: the place to build the tile prefix, or to wait for the other workgroups' partials (false: this one has no part
+// in a result, which is NaN).
 // DENSE: plain products out_m = x W_m for up to three matrices that share x (ProjArgs::Wm); hx counts
 // (matrix, head) column blocks.  The result leaves as fp32, or -- the new token's rows -- rotated to
 // the append position and/or stored into the caches (ProjArgs::role).
@@ -194,7 +193,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   const int idx = lane & 15, rg = lane >> 4;
   const int n = idx, kg = rg;
 
-  const int nhx = DENSE ? a.H * a.nmat : a.H;          // arrival counters per batch chunk
+  const int nhx = DENSE ? a.H * a.nmat : a.H;          // units per batch chunk
   const int lph = a.d_k / 8;
   const bool col_active = idx < lph;
   const uint16_t* Wh = Wmat + (size_t)h * a.d_k + idx * 8;
@@ -225,7 +224,6 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   u32x4 wt[8], wn[8];
   if (w < ntile) load_w(wt, w);                      // in flight while the merge weights are built
   if (w + NW < ntile) load_w(wn, w + NW);
-  const bool astray = a.xcc_map != 0 && misplaced(a.xcc_map);      // (used at the hand-over; looked up while W travels)
 
   // Which partials belong to which sequence: in mode 1 nsplit each; in mode 0 from the tile prefix, looked up once and
   // kept in LDS (single-launch mode: before the wait for the other workgroups, whose barrier it shares).
@@ -243,7 +241,51 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     }
   };
   if constexpr (COH && !DENSE) look_up();
-  after_w_issue();
+  const bool all_well = after_w_issue();
+
+  // One finished output element (sequence bbase + bl, column j of the head); `other` is column j ^ 1.
+  auto emit = [&](int bl, int j, float val, float other, bool bad) {
+    const size_t b = (size_t)(bbase + bl);
+    const int col = h * a.d_k + j;
+    if (bad) val = other = NAN;
+    if constexpr (!DENSE) {
+      outp[b * a.e + col] = val;
+    } else {
+      const int role = a.role[mtx];
+      if (role == 0) { outp[b * a.e + col] = val; return; }
+      // the new token of sequence b sits at row / position len_b - 1
+      const int pos = seq_len_of(a.seq_lens, (int)b, a.T) - 1;
+      if (pos < 0) return;
+      float r = val;
+      if (a.rope && (role == 1 || (role == 2 && a.rotate_k))) {
+        const float* cs = a.rope + ((size_t)pos * (a.d_k / 2) + j / 2) * 2;
+        r = (j & 1) ? fmaf(val, cs[0], -other * cs[1]) : fmaf(val, cs[0], other * cs[1]);
+      }
+      if (role == 1) { outp[b * a.e + col] = r; return; }
+      // (banded K-cache: bands of 32 rows, a head's 32 x d_k block contiguous inside its band)
+      const size_t at = (role == 2 && a.k_banded)
+                            ? ((size_t)(pos >> 5) * a.H + h) * (32 * (size_t)a.d_k) + (size_t)(pos & 31) * a.d_k + j
+                            : (size_t)pos * a.e + col;
+      uint16_t* dst = (role == 2 ? a.Kc : a.Vc) + b * a.c_bstride + at;
+      *dst = __builtin_bit_cast(uint16_t, (__bf16)r);
+    }
+  };
+  auto no_result = [&]() {
+    for (int v = tid; v < nb * a.d_k; v += NTHR) emit(v / a.d_k, v % a.d_k, NAN, NAN, true);
+  };
+  if (COH && !all_well) {                              // (the unit's workgroups are apart: all of them know)
+    if (tid == 0) st_result(a.err, (int)a.launch_id, true);
+    no_result();
+    return;
+  }
+  // In a launch of its own: who takes part in this unit, and where (see the hand-over), at the memory side, used there, on its
+  // way while W and the partials travel.
+  const bool xl = a.xcd_local != 0;
+  unsigned long long* const place = reinterpret_cast<unsigned long long*>(a.counters + PROJ_MAX_UNITS) + (bz * nhx + hx);
+  const unsigned long long my_place = COH ? 0 : 1ull << (8 * (my_xcc() ^ (a.apart ? cs & 1 : 0)));
+  unsigned long long places = 0;
+  if (!COH && xl && a.csw > 1 && tid == 0) places = __hip_atomic_fetch_add(place, my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
+
   const bool even = a.mode == 1;
   if constexpr (!COH && !DENSE) {
     if (!even) {
@@ -486,34 +528,6 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     __syncthreads();
   };
 
-  // One finished output element (sequence bbase + bl, column j of the head); `other` is column j ^ 1.
-  auto emit = [&](int bl, int j, float val, float other, bool bad) {
-    const size_t b = (size_t)(bbase + bl);
-    const int col = h * a.d_k + j;
-    if (bad) val = other = NAN;
-    if constexpr (!DENSE) {
-      outp[b * a.e + col] = val;
-    } else {
-      const int role = a.role[mtx];
-      if (role == 0) { outp[b * a.e + col] = val; return; }
-      // the new token of sequence b sits at row / position len_b - 1
-      const int pos = seq_len_of(a.seq_lens, (int)b, a.T) - 1;
-      if (pos < 0) return;
-      float r = val;
-      if (a.rope && (role == 1 || (role == 2 && a.rotate_k))) {
-        const float* cs = a.rope + ((size_t)pos * (a.d_k / 2) + j / 2) * 2;
-        r = (j & 1) ? fmaf(val, cs[0], -other * cs[1]) : fmaf(val, cs[0], other * cs[1]);
-      }
-      if (role == 1) { outp[b * a.e + col] = r; return; }
-      // (banded K-cache: bands of 32 rows, a head's 32 x d_k block contiguous inside its band)
-      const size_t at = (role == 2 && a.k_banded)
-                            ? ((size_t)(pos >> 5) * a.H + h) * (32 * (size_t)a.d_k) + (size_t)(pos & 31) * a.d_k + j
-                            : (size_t)pos * a.e + col;
-      uint16_t* dst = (role == 2 ? a.Kc : a.Vc) + b * a.c_bstride + at;
-      *dst = __builtin_bit_cast(uint16_t, (__bf16)r);
-    }
-  };
-
   if (a.csw == 1) {
     const bool bad = a.err_before && (COH ? ld_err<true>(a.err) : err_early) == (int)a.launch_id;
     to_obuf();
@@ -525,21 +539,22 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   // ---- several workgroups share the rows of W: last one to arrive adds the partial sums ---------
   // No cache-wide fences: the partial sums are stored and waited for before this workgroup's arrival is counted, and
-  // the last workgroup reads them past its L1.  Where the workgroups of a head share an XCD (xcc_map != 0: checked by
-  // the host) its L2 is their meeting point -- plain stores, an atomic that the L2 executes; otherwise the stores are
+  // the last workgroup reads them past its L1.  Where the workgroups of a head share an XCD (xcd_local: found by
+  // the host at set-up) its L2 is their meeting point -- plain stores, an atomic that the L2 executes; otherwise the stores are
   // written through and the atomic has device scope: three round trips to the memory side instead of to the L2.
-  // Every workgroup looks where it runs before it relies on that: one that is elsewhere counts nowhere, so that its unit
-  // has no last arriver, and itself writes the unit's result, NaN, and raises the error word.
+  // Whether they do share it they find out themselves on every launch.  In the single launch the arrival flags carry the XCD
+  // of every workgroup.  In a launch of its own each adds its XCD to the unit's word, and the last one to do so sees them all:
+  // if they are apart, none of the counts becomes complete, so that nobody else writes the result; it writes NaN and raises
+  // the error word.  (The XCD that workgroup 0 runs on differs from queue to queue: the host has nothing to compare with.)
   // The partial sums of a head lie in accumulator order, [element i][column group], so that they leave and come back
   // 16 bytes at a time (where the head has whole fours of column groups).
   // Dense products of up to 512 elements (a few sequences) keep their columns in order instead, an element a thread: they
   // are finished from where they are read, without another pass through LDS (4 x 4096 x 4096: 12.0 against 12.8 us).
-  const bool xl = a.xcc_map != 0, fours = (lph & 3) == 0;
-  if (astray) {
-    if (tid == 0 && a.err) st_result(a.err, (int)a.launch_id, true);
-    for (int v = tid; v < nb * a.d_k; v += NTHR) emit(v / a.d_k, v % a.d_k, NAN, NAN, true);
+  if (!COH && a.err_before && err_early == (int)a.launch_id) {             // (then the control words may not be 0 either)
+    no_result();
     return;
   }
+  const bool fours = (lph & 3) == 0;
   const bool in_order = DENSE && nb * a.d_k <= NTHR;
   const int ebl = tid / a.d_k, ej = tid - ebl * a.d_k;  // in_order: this thread's element
   const bool eok = tid < nb * a.d_k;
@@ -562,14 +577,28 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   __syncthreads();
   if (tid == 0) {
     int* const counter = &a.counters[bz * nhx + hx];
-    const int old = xl ? __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
-                       : __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sm.is_last = (old == a.csw - 1);
+    // (the sum of the bytes: how many had added themselves by then)
+    const bool last_apart = !COH && (int)((places * 0x0101010101010101ull) >> 56) == a.csw && places != (unsigned long long)a.csw * my_place;      // (and apart)
+    int old = -1;
+    if (!xl) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else if (COH || !(a.apart && (cs & 1))) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    sm.is_last = xl && last_apart ? 2 : (old == a.csw - 1);
   }
   __syncthreads();
   if (!sm.is_last) return;
+  if (!COH && sm.is_last == 2) {                               // the last of a unit whose workgroups are apart
+    if (tid == 0) st_result(a.err, (int)a.launch_id, true);
+    no_result();
+    return;
+  }
   // (single launch: the error word travels with the partial sums, requested here, looked at behind their wait)
   const int errv = COH ? ld_err<true>(a.err) : err_early;
+  auto reset = [&]() {                                 // for the next launch on these control words
+    if (tid == 0) {
+      a.counters[bz * nhx + hx] = 0;
+      if (!COH && xl) __hip_atomic_store(place, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
   if (in_order) {
     float sum = 0.f;
     if (eok)
@@ -582,7 +611,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
       }
     const float other = __shfl_xor(sum, 1);              // (a pair's columns sit in neighbour lanes)
     if (eok) emit(ebl, ej, sum, other, a.err_before && errv == (int)a.launch_id);
-    if (tid == 0) a.counters[bz * nhx + hx] = 0;
+    reset();
     return;
   }
   if (mine) {
@@ -614,7 +643,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     const int bl = v / a.d_k, j = v % a.d_k;
     emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
   }
-  if (tid == 0) a.counters[bz * nhx + hx] = 0;
+  reset();
 }
 
 template <int NBT, bool DENSE>
@@ -630,6 +659,7 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
   project_work<NBT, false, DENSE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);
+    return true;
   });
 }
 
@@ -722,7 +752,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
     if (wu == NP - 1) {                               // (while the first wave builds the tile prefix)
       int phead, psplit;
       projection_share(phead, psplit);
-      if (phead < a.proj.H && psplit == 0 && lane == 0) st_result(a.counters + phead, 0, a.proj.xcc_map == 0);
+      if (phead < a.proj.H && psplit == 0 && lane == 0) st_result(a.counters + phead, 0, a.proj.xcd_local == 0);
     }
   } else if (blockIdx.x == 0 && a.counters) {
     for (int i = tid; i < a.ncounters; i += NTHR) a.counters[i] = 0;
@@ -1343,20 +1373,21 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (!fuse) return;
 
   // ========================= single-launch mode: merge + projection ===============================
-  // This workgroup's partials are out (write-through stores, waited for) before its arrival flag, and so is the error word
-  // if it may have cleared a counter in another L2 than its head's.  (Looked up here, where it costs nothing beside the
-  // stores' way out; at the kernel's start it was 0.3 us of every launch.)
-  if (wu == NP - 1 && a.proj.xcc_map != 0 && misplaced(a.proj.xcc_map) && lane == 0) st_result(a.err, (int)a.launch_id, true);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) st_result(reinterpret_cast<int*>(a.flags) + blockIdx.x, (int)a.launch_id, true);
+  // This workgroup's partials are out (write-through stores, waited for) before its arrival flag: the launch's id, and in the
+  // three lowest bits the XCD it runs on.
   int phead, psplit;
   projection_share(phead, psplit);
+  const unsigned flag_id = a.launch_id << 3, xcc = my_xcc() ^ (a.proj.apart ? psplit & 1 : 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) st_result(reinterpret_cast<int*>(a.flags) + blockIdx.x, (int)(flag_id | xcc), true);
   if (phead >= a.proj.H) return;
   // (everything of the stream phase is over in this workgroup: its LDS is reused)
   ProjShared<1>& psm = *reinterpret_cast<ProjShared<1>*>(sbuf);
   project_work<1, true, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
-    // every workgroup's partials must be out: all arrival flags carry this launch's id
+    // Every workgroup's partials must be out: all arrival flags carry this launch's id.  False: the workgroups of this head
+    // are to meet in an XCD's L2, and do not run on one XCD.
+    bool together = true;
     if (wu == 0) {
       unsigned long long since = ~0ull;
       for (;;) {
@@ -1365,14 +1396,25 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           seen[j] = __hip_atomic_load(a.flags + min(lane + 64 * j, (int)gridDim.x - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool ok = seen[0] == a.launch_id && seen[1] == a.launch_id && seen[2] == a.launch_id && seen[3] == a.launch_id;
+        const unsigned other = (seen[0] ^ flag_id) | (seen[1] ^ flag_id) | (seen[2] ^ flag_id) | (seen[3] ^ flag_id);
         static_assert(FUSED_MAX_GRID <= 256, "four flags per lane cover the grid");
-        if (__all(ok)) break;
+        if (__all(other < 8)) {
+          // (this head's workgroups: i % 8 as here, i / 8 in the csw slots of the head)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int i = lane + 64 * j, s0 = (int)(blockIdx.x >> 3) - psplit;
+            if ((i & 7) == (int)(blockIdx.x & 7) && (unsigned)((i >> 3) - s0) < (unsigned)a.proj.csw) together &= (seen[j] & 7) == xcc;
+          }
+          together = __all(together) || a.proj.xcd_local == 0 || a.proj.csw == 1;
+          break;
+        }
         if (dead || out_of_time(since)) { give_up(); break; }
         __builtin_amdgcn_s_sleep(4);
       }
+      if (lane == 0) psm.is_last = together;
     }
     __syncthreads();
+    return psm.is_last != 0;
   });
 }
 
@@ -1416,10 +1458,10 @@ bool fused_geometry(int B, int H, int T, int d, FusedGeom* g) {
   return true;
 }
 
-// The XCC ids (four bits each, see ProjArgs::xcc_map) when workgroups i and j of a 256-workgroup launch share an XCD
-// exactly where i % 8 == j % 8, else 0: a probe launch on `st` that records each workgroup's XCD into `dev_buf`
-// (device memory, 256 unsigned), read back with a blocking copy.  The caller caches the answer per device.
-unsigned probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
+// True when workgroups i and j of a 256-workgroup launch share an XCD exactly where i % 8 == j % 8: a probe
+// launch on `st` that records each workgroup's XCD into `dev_buf` (device memory, 256 unsigned), read
+// back with a blocking copy.  The caller caches the answer per device.
+bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
   unsigned h[256];
   hipLaunchKernelGGL(xcc_probe_kernel, dim3(256), dim3(512), 0, st, dev_buf);
   bool ok = hipMemcpyAsync(h, dev_buf, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
@@ -1430,9 +1472,7 @@ unsigned probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st) {
     for (int i = 1; i < 8 && ok; ++i)
       for (int j = 0; j < i; ++j) ok = ok && h[i] != h[j];
   (void)hipGetLastError();
-  unsigned map = 0;
-  for (int i = 0; i < 8 && ok; ++i) map |= h[i] << (4 * i);
-  return map;                                          // (eight different ids: never 0)
+  return ok;
 }
 
 // Workgroups of the stream kernel one compute unit can hold at once (0 on error): the launch is only

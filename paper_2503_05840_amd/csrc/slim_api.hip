@@ -110,8 +110,7 @@ Plan make_plan(int B, int H, int T, int width, int e) {
 // i % 8 (a probe launch on the null stream and a blocking read-back, no allocation: it writes into
 // the static scratch), and the event used to order stream-kernel launches of different streams.
 struct DeviceState {
-  bool ready = false;
-  unsigned xcc_map = 0;                       // see ProjArgs; 0: workgroups are not dealt to the XCDs round robin
+  bool ready = false, xcd_round_robin = false;
   int cus = 0;
   void* static_scratch = nullptr;
   hipEvent_t order_ev = nullptr;
@@ -132,28 +131,24 @@ DeviceState* device_state() {
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) { (void)hipGetLastError(); return nullptr; }
   s.static_scratch = ptr;
   if (hipDeviceGetAttribute(&s.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) { (void)hipGetLastError(); s.cus = 0; }
-  s.xcc_map = s.cus >= 256 ? probe_xcd_round_robin((unsigned*)ptr, nullptr) : 0;
+  s.xcd_round_robin = s.cus >= 256 && probe_xcd_round_robin((unsigned*)ptr, nullptr);
   if (hipEventCreateWithFlags(&s.order_ev, hipEventDisableTiming) != hipSuccess) { s.order_ev = nullptr; (void)hipGetLastError(); }
   s.ready = true;
   return &s;
 }
 
-// Where workgroup i of a launch is known to run (ProjArgs::xcc_map): after slim_init or a call that needed the set-up; without
+// Whether workgroups i and j of a launch are known to share an XCD where i % 8 == j % 8: after slim_init or a call that needed the set-up; without
 // it the callers' kernels meet at the memory side.  (Never sets anything up itself: the set-up waits for the device.)
-unsigned known_xcc_map() {
+bool xcd_round_robin_known() {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return 0; }
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return false; }
   std::lock_guard<std::mutex> lk(g_dev_mu);
-  return g_dev[dev].ready ? g_dev[dev].xcc_map : 0;
+  return g_dev[dev].ready && g_dev[dev].xcd_round_robin;
 }
 
 // opts->variant: which implementation, and two switches for tests
 int variant_of(const slim_opts* o) { return o ? o->variant & 0xff : SLIM_VARIANT_AUTO; }
-unsigned call_xcc_map(unsigned map, const slim_opts* o) {
-  const int v = o ? o->variant : 0;
-  if (v & SLIM_VARIANT_VIA_MEMORY) return 0;
-  return (v & SLIM_VARIANT_MISPLACED) ? (map << 4) | (map >> 28) : map;       // (every workgroup's neighbour's XCD)
-}
+bool flag_of(const slim_opts* o, int flag) { return o && (o->variant & flag); }
 
 // Library-owned scratch: one allocation per device, grown on demand, kept until exit.
 struct OwnedScratch { void* ptr = nullptr; size_t bytes = 0; };
@@ -376,8 +371,6 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   if (variant == SLIM_VARIANT_FUSED || variant == SLIM_VARIANT_FUSED_SPLIT) {
     const FusedGeom& g = p.geom;
     int* ctrl = (int*)(ws + p.off_ctrl);
-    const int per = 16 * proj_batch_tiles(B, d, d, H);
-    const int zb = (B + per - 1) / per;
     FusedArgs fa{};
     fa.q = (const float*)q; fa.K = (const uint16_t*)Kcache; fa.k_bstride = kb; fa.seq_lens = lens;
     fa.k_banded = k_layout == SLIM_K_BANDED;
@@ -387,25 +380,28 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     fa.exch = (unsigned long long*)(ws + p.off_exch);
     const unsigned tiles = (unsigned)B * (unsigned)((T + TILE_ROWS - 1) / TILE_ROWS) + (unsigned)B + 64u;
     fa.tag_base = g_tag.fetch_add(tiles);
-    const unsigned lid = block_id ? block_id : next_launch_id(), map = call_xcc_map(dev->xcc_map, o);
+    const unsigned lid = block_id ? block_id : next_launch_id();
+    const bool xcd_local = dev->xcd_round_robin && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
     fa.launch_id = lid;
     // every wait for another workgroup: 20 ms of real time (100 MHz ticks) unless the caller says otherwise
     const long long budget_us = (o && o->wait_budget_us) ? (long long)o->wait_budget_us : 20000;
     fa.wait_ticks = budget_us < 0 ? 0ull : (unsigned long long)budget_us * 100ull;
-    fa.xcd_local = (g.gpx > 0 && map != 0) ? 1 : 0;
+    fa.xcd_local = (g.gpx > 0 && xcd_local) ? 1 : 0;
     fa.rope = rope;
     fa.Cpart = Cpart; fa.mpart = mpart; fa.lpart = lpart;
-    fa.err = ctrl + CTRL_INTS - 1; fa.counters = ctrl; fa.ncounters = H * zb;
+    fa.err = ctrl + CTRL_INTS - 1; fa.counters = ctrl;
     ProjArgs pa{};
     pa.Cpart = Cpart; pa.mpart = mpart; pa.lpart = lpart; pa.W = (const uint16_t*)W_KV;
     pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.err_before = 1; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcc_map = map;
+    pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcd_local = xcd_local;
+    pa.apart = flag_of(o, SLIM_VARIANT_APART);
     if (const int shares = fused_by_sequence(g, B, lens != nullptr)) {
       fa.by_sequence = shares;
       pa.mode = 1; pa.nsplit = shares;               // partials laid out [sequence][share]
     }
+    fa.ncounters = p.csw > 1 ? PROJ_CTRL_INTS : 0;
     const bool one_launch = variant == SLIM_VARIANT_FUSED && p.csw_f > 0 && !fa.by_sequence;
     if (one_launch) {
       // the stream kernel's workgroups also merge and project (flags after the counters)
@@ -443,7 +439,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   // rows are whole 128-column blocks; an explicit request for the plain kernels keeps every step on the vector ALU.
   const bool mfma_projection = dtype == SLIM_BF16 && requested != SLIM_VARIANT_GENERIC && d_k % 8 == 0 && d_k <= 128 &&
                                (long)H * ((B + 15) / 16) < CTRL_INTS / 2;
-  const int arrivals_mfma = H * ((B + 15) / 16);
+  const int arrivals_mfma = p.csw > 1 ? PROJ_CTRL_INTS : 0;
   const bool wide = mfma_projection && wide_ok(dtype, T, d, d_k);
   if (wide) {
     launch_kscores((const float*)q, Kcache, kb, lens, T, H, d, d_k, scale * 1.4426950408889634f, rope, S, ctrl, arrivals_mfma, B, st);
@@ -463,7 +459,8 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
     pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
     pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
-    pa.csw = p.csw; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
+    pa.csw = p.csw; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART);
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = block_id ? block_id : next_launch_id(); pa.err_before = block_id != 0;
     launch_project_mfma(pa, st);
   } else {
@@ -578,10 +575,9 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
       (size_t)T * d_model * 2 < ((size_t)1 << 32)) {      // (the kernels address a sequence's rows with 32-bit offsets)
     // MFMA path: q~, scores (log2 domain), weighted sum per context split, merge + projection
     int* ctrl = (int*)(ws + p.off_ctrl);
-    const int per = 16 * proj_batch_tiles(B, d_model, e, H);
-    const int zb = (B + per - 1) / per;
     const int csw = proj_row_splits(H, d_model, e, B);
-    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, ctrl, csw > 1 ? H * zb : 0, st);
+    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, ctrl,
+                    csw > 1 ? PROJ_CTRL_INTS : 0, st);
     tm.mark();
     int nsplit = p.nsplit_x;
     if (p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT) {
@@ -601,7 +597,8 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = next_launch_id(); pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d_model; pa.e = e;
     pa.NG = 0; pa.nsplit = nsplit; pa.mode = 1; pa.mscale = 1.0f;
-    pa.csw = csw; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
+    pa.csw = csw; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART);
     launch_project_mfma(pa, st);
     tm.mark();
     tm.finish();
@@ -690,14 +687,15 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   ProjArgs pa{};
   pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = (int*)(ws + p.off_ctrl);
   pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-  pa.nsplit = 1; pa.mscale = 1.0f; pa.xcc_map = call_xcc_map(known_xcc_map(), o);
+  pa.nsplit = 1; pa.mscale = 1.0f; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART);
   const unsigned id = fast ? next_launch_id() : 0;     // one for all launches of the call
   pa.err = (int*)(ws + p.off_ctrl) + CTRL_INTS - 1; pa.launch_id = id;
 
   StageTimer tm(o, st);
   if (fast) {
     // q, k (and v) in one launch; the new rows go straight into the caches
-    launch_zero_ints(pa.counters, CTRL_INTS / 2, st);
+    launch_zero_ints(pa.counters, PROJ_CTRL_INTS, st);
     pa.nmat = nmat; pa.csw = dense_row_splits(H, nmat, d, d, B);
     pa.Wm[0] = (const uint16_t*)c.W_Q; pa.outm[0] = q; pa.role[0] = 1;
     pa.Wm[1] = (const uint16_t*)c.W_K; pa.outm[1] = nullptr; pa.role[1] = 2;

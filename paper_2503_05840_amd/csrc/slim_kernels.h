@@ -83,6 +83,10 @@ constexpr int FUSED_WAVES = 8;       // waves per workgroup of the stream kernel
 constexpr int FUSED_SLOTS = 2;       // LDS landing slots (8 KB tiles) per wave
 constexpr int FUSED_AHEAD = 2;       // register sets of a wave: one tile being scored, the other in flight
 constexpr int PROJ_MAX_PARTS = 64;   // partials per sequence the projection merges
+// Control words of a projection whose rows of W are split, all 0 on entry: per (head, batch chunk) unit an arrival counter,
+// then a 64-bit word of who takes part, a byte per XCD.  More units than this have no row splits (proj_splits_per_unit).
+constexpr int PROJ_MAX_UNITS = 128;
+constexpr int PROJ_CTRL_INTS = 3 * PROJ_MAX_UNITS;
 
 struct FusedGeom {
   int lph, lphp, hpu;   // active lanes per head (d_k/8), lanes reserved per head, heads per unit
@@ -94,16 +98,18 @@ struct ProjArgs {
   const float* Cpart; const float* mpart; const float* lpart;
   const uint16_t* W;                  // [rows][e] bf16
   float* out; float* outpart;         // [B][e], [csw][B][e]
-  int* counters; int* err; unsigned launch_id;    // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
+  int* counters;                      // [PROJ_CTRL_INTS]
+  int* err; unsigned launch_id;       // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
   int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
   const int32_t* seq_lens;
   int B, T, H, d_k, rows, e;
   int NG, nsplit, mode;               // mode 0: partials laid out by the stream kernel; 1: [b][nsplit]
   float mscale;                       // 1 for log2-domain maxima, log2(e) for natural-log ones
   int csw, crows;                     // row splits of W across workgroups, rows per split
-  // The XCC id of XCD slot i % 8 in bits 4 (i % 8) .. + 3 where workgroup i of a launch runs there (checked at set-up, and by
-  // every workgroup for itself): the row splits of a head meet in its L2.  0: not known, they meet at the memory side.
-  unsigned xcc_map;
+  // Workgroups i and j of a launch share an XCD where i % 8 == j % 8 (checked at set-up, and by the workgroups of a unit on
+  // every launch): the row splits of a head meet in its L2.  0: not known, they meet at the memory side.
+  int xcd_local;
+  int apart;                          // (for tests: with xcd_local, every second row split behaves as if on another XCD)
   // Dense products (launch_dense_mfma): Cpart = x [B][rows], out_m = x W_m for nmat matrices.
   // role 0: fp32 result.  The new token's rows (it sits at row / position seq_lens[b] - 1):
   // role 1: query, fp32, rotated to that position when rope is set; role 2: key row into Kc (rotated
@@ -147,7 +153,7 @@ struct FusedArgs {
 bool fused_geometry(int B, int H, int T, int d, FusedGeom* g);
 int fused_by_sequence(const FusedGeom& g, int B, bool ragged);
 size_t fused_exch_bytes(const FusedGeom& g);
-unsigned probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
+bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
 int fused_blocks_per_cu(const FusedGeom& g, bool rope);
 void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st);
 int proj_batch_tiles(int B, int rows, int e, int H);
