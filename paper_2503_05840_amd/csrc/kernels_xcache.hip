@@ -14,6 +14,8 @@
 
 #include "device_common.h"
 
+#include <algorithm>
+
 namespace slim {
 namespace {
 
@@ -834,16 +836,28 @@ bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_m
 static int xfused_waves(int d_model) { return d_model <= 512 ? 4 : d_model <= 768 ? 6 : d_model <= 1024 ? 8 : 10; }
 static int xfused_tiles(int H, int d_model) { return d_model <= 1024 && H > 16 ? 2 : 1; }
 
-int xfused_splits(int B, int H, int T, int d_model) {
-  // One workgroup per (split, head group, sequence): the split count whose rounds of workgroups over the 256 compute
-  // units take the fewest steps of 32 rows, where starting a workgroup, its first tile and its partial cost about four
-  // steps.  (Filling the chip with ceil(256 / units) splits made 288 workgroups of 24 sequences x 2 head groups x 6
-  // splits, two rounds of 8 steps: 50.8 us; 5 splits take one round of 10: 33.6 us.)
+// Context splits of the one-pass kernel: one workgroup per (split, head group, sequence).
+static long xfused_units(int B, int H, int d_model) {
   const int hg = 16 * xfused_tiles(H, d_model);
-  const long per = (long)B * ((H + hg - 1) / hg), slots = 256 * xfused_per_cu(xfused_waves(d_model));
-  const int tiles = (T + 31) / 32;
-  int most = (T + 255) / 256;
-  if (most > PROJ_MAX_PARTS) most = PROJ_MAX_PARTS;
+  return (long)B * ((H + hg - 1) / hg);
+}
+static long xfused_slots(int d_model) { return 256 * xfused_per_cu(xfused_waves(d_model)); }
+
+// At most: eight tiles of rows each, what the projection merges, and six more than fill the chip once (beyond that 0.5 %
+// of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials without bound).  Grows with T.
+int xfused_most_splits(int B, int H, int T, int d_model) {
+  const long units = xfused_units(B, H, d_model), fill = (xfused_slots(d_model) + units - 1) / units + 6;
+  const int most = (T + 255) / 256;
+  return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
+}
+
+// The count whose rounds of workgroups over the 256 compute units take the fewest steps of 32 rows, where starting a
+// workgroup, its first tile and its partial cost about four steps.  (Filling the chip with ceil(256 / units) splits made
+// 288 workgroups of 24 sequences x 2 head groups x 6 splits, two rounds of 8 steps: 50.8 us; 5 splits take one round of
+// 10: 33.6 us.)
+int xfused_splits(int B, int H, int T, int d_model) {
+  const long per = xfused_units(B, H, d_model), slots = xfused_slots(d_model);
+  const int tiles = (T + 31) / 32, most = xfused_most_splits(B, H, T, d_model);
   int best = 1;
   long best_cost = 0;
   for (int s = 1; s <= most; ++s) {

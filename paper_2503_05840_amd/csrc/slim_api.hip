@@ -41,52 +41,66 @@ constexpr int CTRL_INTS = 4096;
 
 int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// `lean`: no more partials than the other kernels of the shape need anyway, one row split (see make_plan).
-Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
+// Every term of the total is the same or grows with T, so that a workspace sized for a cache's capacity serves every shorter
+// context; what a launch then uses of it (context splits above all) may go up and down with T inside that bound.
+// A K-cache call (slim_decode, vanilla_kv_decode, the blocks; width == e) and an X-cache call need different parts.
+Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
   Plan p;
   const int ncolblk = (width + 511) / 512, nhb = (H + 31) / 32;
   const long per_split = (long)B * ncolblk * nhb;
   p.nsplit = clampi((int)((1024 + per_split - 1) / per_split), 1, clampi((T + 127) / 128, 1, 64));
-  // vanilla kernel: workgroups of four waves, a wave per group of heads; about eight workgroups per
-  // compute unit, splits of at least 256 rows
-  const int hpw = vanilla_heads_per_wave(DT_BF16, e / H);      // (the packing of the bf16 kernel; harmless for fp32)
-  const long per_split_v = (long)B * (((H + (hpw ? hpw : 1) - 1) / (hpw ? hpw : 1) + 3) / 4);
-  p.nsplit_v = clampi((int)((2048 + per_split_v - 1) / per_split_v), 1, clampi(T / 256, 1, 256));
-  size_t o = 0;
-  p.off_ctrl = o;    o += up(sizeof(int) * CTRL_INTS);
-  p.fused_ok = (width == e) && fused_geometry(B, H, T, width, &p.geom);
-  p.nsplit_x = xcache_splits(B, H, T, width);
-  p.nsplit_xf = xfused_ok(width) ? xfused_splits(B, H, T, width) : 0;
-  size_t nparts = (size_t)B * (p.nsplit > p.nsplit_x ? p.nsplit : p.nsplit_x);
-  if (lean && (size_t)B * p.nsplit_xf > nparts) p.nsplit_xf = (int)(nparts / B);
-  if ((size_t)B * p.nsplit_xf > nparts) nparts = (size_t)B * p.nsplit_xf;
-  if (p.fused_ok && (size_t)p.geom.nparts > nparts) nparts = p.geom.nparts;
-  if (p.fused_ok && (size_t)B * 4 > nparts && fused_by_sequence(p.geom, B, false)) nparts = (size_t)B * 4;
-  p.nsplit_k = kweighted_splits(B, H, T, width);
-  if ((size_t)B * p.nsplit_k > nparts) p.nsplit_k = (int)(nparts / B);       // (the plain kernels' partials are more)
-  p.nsplit_f = f32_stream_splits(B, T);
   const int d_k = e >= H ? e / H : 1;                  // (sizes are asked for with any arguments)
-  p.rsplit = lean ? 1 : merge_row_splits(H, d_k, width, B, CTRL_INTS / 2);
-  if (lean && (size_t)B * p.nsplit_f > nparts) p.nsplit_f = (int)(nparts / B);
-  if (f32_stream_ok(DT_F32, H, width, d_k) && (size_t)B * p.nsplit_f > nparts) nparts = (size_t)B * p.nsplit_f;
+  p.rsplit = merge_row_splits(H, d_k, width, B, CTRL_INTS / 2);
   p.csw = proj_row_splits(H, width, e, B);
-  if (p.fused_ok && B <= 16 && p.geom.grid >= H) {
-    // a tile of W for every wave (8 waves x 32 rows) before another workgroup: what is split finer has more to hand over
-    const int most = (width + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), c = proj_splits_per_unit(H);
-    p.csw_f = c < most ? c : most;
+  int parts = p.csw > p.rsplit ? p.csw : p.rsplit;     // partial results of the projection
+  size_t nparts = (size_t)B * p.nsplit;                // partial weighted sums
+  auto at_least = [&](size_t n) { if (n > nparts) nparts = n; };
+  if (xcache) {
+    p.nsplit_x = xcache_splits(B, H, T, width);
+    at_least((size_t)B * p.nsplit_x);
+    if (xfused_ok(width)) {
+      p.nsplit_xf = xfused_splits(B, H, T, width);
+      at_least((size_t)B * xfused_most_splits(B, H, T, width));
+    }
+  } else {
+    // vanilla kernel: workgroups of four waves, a wave per group of heads; about eight workgroups per
+    // compute unit, splits of at least 256 rows
+    const int hpw = vanilla_heads_per_wave(DT_BF16, e / H);    // (the packing of the bf16 kernel; harmless for fp32)
+    const long per_split_v = (long)B * (((H + (hpw ? hpw : 1) - 1) / (hpw ? hpw : 1) + 3) / 4);
+    p.nsplit_v = clampi((int)((2048 + per_split_v - 1) / per_split_v), 1, clampi(T / 256, 1, 256));
+    p.fused_ok = fused_geometry(B, H, T, width, &p.geom);
+    if (p.fused_ok) {
+      at_least((size_t)p.geom.nparts);
+      if (fused_by_sequence(p.geom, B, false)) at_least((size_t)B * 4);
+      if (B <= 16 && p.geom.grid >= H) {
+        // a tile of W for every wave (8 waves x 32 rows) before another workgroup: what is split finer has more to hand over
+        const int most = (width + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), c = proj_splits_per_unit(H);
+        p.csw_f = c < most ? c : most;
+        if (p.csw_f > parts) parts = p.csw_f;
+      }
+    }
+    p.nsplit_f = f32_stream_splits(B, T);
+    if (f32_stream_ok(DT_F32, H, width, d_k)) at_least((size_t)B * p.nsplit_f);
+    p.nsplit_k = kweighted_splits(B, H, T, width);
+    if ((size_t)B * p.nsplit_k > nparts) p.nsplit_k = (int)(nparts / B);     // (the plain kernels' partials are more)
   }
-  p.off_S = o;      o += up(sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32));   // (rows padded to 32 scores)
-  p.off_Cpart = o;  o += up(sizeof(float) * nparts * H * width);
-  p.off_m = o;      o += up(sizeof(float) * nparts * H);
-  p.off_l = o;      o += up(sizeof(float) * nparts * H);
-  p.off_qt = o;     o += up(sizeof(float) * (size_t)B * ((H + 15) / 16 * 16) * width);   // (whole tiles of 16 heads)
-  p.off_vacc = o;   o += up(sizeof(float) * (size_t)B * p.nsplit_v * e);
-  p.off_vm = o;     o += up(sizeof(float) * (size_t)B * p.nsplit_v * H);
-  p.off_vl = o;     o += up(sizeof(float) * (size_t)B * p.nsplit_v * H);
-  if (p.fused_ok) { p.off_exch = o; o += up(fused_exch_bytes(p.geom)); }
-  int parts = p.csw > p.csw_f ? p.csw : p.csw_f;
-  if (p.rsplit > parts) parts = p.rsplit;
-  p.off_outpart = o; o += up(sizeof(float) * (size_t)parts * B * e);
+  size_t o = 0;
+  auto take = [&](size_t bytes) { const size_t at = o; o += up(bytes); return at; };
+  p.off_ctrl = take(sizeof(int) * CTRL_INTS);
+  // The scores (rows padded to 32) have been used when the projection's partial results are written, which take their place.
+  const size_t scores = sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32), outparts = sizeof(float) * (size_t)parts * B * e;
+  p.off_S = p.off_outpart = take(scores > outparts ? scores : outparts);
+  p.off_Cpart = take(sizeof(float) * nparts * H * width);
+  p.off_m = take(sizeof(float) * nparts * H);
+  p.off_l = take(sizeof(float) * nparts * H);
+  if (xcache) {
+    p.off_qt = take(sizeof(float) * (size_t)B * ((H + 15) / 16 * 16) * width);   // (whole tiles of 16 heads)
+  } else {
+    p.off_vacc = take(sizeof(float) * (size_t)B * p.nsplit_v * e);
+    p.off_vm = take(sizeof(float) * (size_t)B * p.nsplit_v * H);
+    p.off_vl = take(sizeof(float) * (size_t)B * p.nsplit_v * H);
+    if (p.fused_ok) p.off_exch = take(fused_exch_bytes(p.geom));
+  }
   p.total = o;
   return p;
 }
@@ -96,14 +110,6 @@ Plan make_plan_at(int B, int H, int T, int width, int e, bool lean) {
 // from hipGetSymbolAddress at set-up (device_state) and is what kernels, copies and queries are given.
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)SLIM_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
-
-// The lean plan where only that one fits the static scratch: every shape it can hold stays accepted.
-Plan make_plan(int B, int H, int T, int width, int e) {
-  const Plan p = make_plan_at(B, H, T, width, e, false);
-  if (p.total <= STATIC_SCRATCH_BYTES) return p;
-  const Plan lean = make_plan_at(B, H, T, width, e, true);
-  return lean.total <= STATIC_SCRATCH_BYTES ? lean : p;
-}
 
 // Per-device set-up, done once (slim_init, else the first call that needs it) under a lock: the
 // address of the static scratch, the compute-unit count, whether workgroup i of a launch runs on XCD
@@ -313,14 +319,13 @@ extern "C" int slim_variant_for(int B, int H, int T, int d, int dtype) {
 extern "C" size_t slim_workspace_bytes(int B, int H, int T, int d, int dtype) {
   if (B < 1 || H < 1 || T < 1 || d < 1) return 0;
   (void)dtype;
-  // d is the cached row width; the vanilla partials are sized for e = d (K-cache case).
-  return make_plan(B, H, T, d, d).total;
+  return make_plan(B, H, T, d, d, false).total;
 }
 
 extern "C" size_t slim_workspace_bytes_xcache(int B, int H, int T, int d_model, int d_k, int dtype) {
   if (B < 1 || H < 1 || T < 1 || d_model < 1 || d_k < 1) return 0;
   (void)dtype;
-  return make_plan(B, H, T, d_model, H * d_k).total;
+  return make_plan(B, H, T, d_model, H * d_k, true).total;
 }
 
 namespace {
@@ -339,7 +344,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   const float* rope = o ? o->rope_table : nullptr;
   if (rope && (d_k & 1)) return SLIM_ERR_SHAPE;
   if (rope && misaligned(rope)) return SLIM_ERR_ALIGN;
-  const Plan p = make_plan(B, H, T, d, d);
+  const Plan p = make_plan(B, H, T, d, d, false);
   char* ws = fixed_ws;
   if (fixed_ws) {
     if (p.total > fixed_ws_bytes) return SLIM_ERR_WORKSPACE;
@@ -531,7 +536,7 @@ extern "C" int vanilla_kv_decode(const void* q, const void* Kcache, const void* 
   if (int rc = check_common(B, H, T, d, d_k, d, o, &dtype, &t_stride)) return rc;
   if (d_k / vec_elems(dtype) > 32) return SLIM_ERR_SHAPE;
   if (misaligned(q) || misaligned(Kcache) || misaligned(Vcache) || misaligned(out)) return SLIM_ERR_ALIGN;
-  const Plan p = make_plan(B, H, T, d, d);
+  const Plan p = make_plan(B, H, T, d, d, false);
   char* ws;
   if (int rc = get_workspace(o, p.total, &ws)) return rc;
   hipStream_t st = o ? (hipStream_t)o->stream : nullptr;
@@ -556,7 +561,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
   if (int rc = check_common(B, H, T, e, d_k, d_model, o, &dtype, &t_stride)) return rc;
   if (misaligned(q) || misaligned(X) || misaligned(W_K) || misaligned(W_V) || misaligned(out))
     return SLIM_ERR_ALIGN;
-  const Plan p = make_plan(B, H, T, d_model, e);
+  const Plan p = make_plan(B, H, T, d_model, e, true);
   char* ws;
   if (int rc = get_workspace(o, p.total, &ws)) return rc;
   hipStream_t st = o ? (hipStream_t)o->stream : nullptr;
@@ -581,7 +586,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     tm.mark();
     int nsplit = p.nsplit_x;
     if (p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT) {
-      // d_model <= 1024: scores, numerators and weighted sum in one pass over X
+      // d_model 512..1280: scores, numerators and weighted sum in one pass over X
       nsplit = p.nsplit_xf;
       launch_xfused(qt, X, xb, lens, T, H, d_model, nsplit, Cpart, mpart, lpart, B, st);
       tm.mark();
@@ -660,7 +665,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   if (!slim_path && d_k / vec_elems(dtype) > 32) return SLIM_ERR_SHAPE;
   const void* ptrs[] = {c.x, c.W_Q, c.W_K, c.W_V, c.W_second, c.W_O, c.Kcache, c.Vcache, c.y, o ? o->rope_table : nullptr};
   for (const void* q : ptrs) if (q && misaligned(q)) return SLIM_ERR_ALIGN;
-  const Plan p = make_plan(B, H, T, d, d);
+  const Plan p = make_plan(B, H, T, d, d, false);
   const BlockBufs bb = block_layout(p, B, H, d);
   char* ws;
   if (int rc = get_workspace(o, bb.total, &ws)) return rc;
@@ -745,7 +750,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
 extern "C" size_t slim_workspace_bytes_block(int B, int H, int T, int d, int dtype) {
   if (B < 1 || H < 1 || T < 1 || d < 1) return 0;
   (void)dtype;
-  return block_layout(make_plan(B, H, T, d, d), B, H, d).total;
+  return block_layout(make_plan(B, H, T, d, d, false), B, H, d).total;
 }
 
 extern "C" int slim_attention_block(const void* x, const void* W_Q, const void* W_K, const void* W_KV,
