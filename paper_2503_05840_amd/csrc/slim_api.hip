@@ -4,6 +4,7 @@
 #include "slim_kernels.h"
 
 #include <math.h>
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <mutex>
@@ -52,7 +53,6 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
   const int d_k = e >= H ? e / H : 1;                  // (sizes are asked for with any arguments)
   p.rsplit = merge_row_splits(H, d_k, width, B, CTRL_INTS / 2);
   p.csw = proj_row_splits(H, width, e, B);
-  int parts = p.csw > p.rsplit ? p.csw : p.rsplit;     // partial results of the projection
   size_t nparts = (size_t)B * p.nsplit;                // partial weighted sums
   auto at_least = [&](size_t n) { if (n > nparts) nparts = n; };
   if (xcache) {
@@ -76,7 +76,6 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
         // a tile of W for every wave (8 waves x 32 rows) before another workgroup: what is split finer has more to hand over
         const int most = (width + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), c = proj_splits_per_unit(H);
         p.csw_f = c < most ? c : most;
-        if (p.csw_f > parts) parts = p.csw_f;
       }
     }
     p.nsplit_f = f32_stream_splits(B, T);
@@ -88,8 +87,10 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
   auto take = [&](size_t bytes) { const size_t at = o; o += up(bytes); return at; };
   p.off_ctrl = take(sizeof(int) * CTRL_INTS);
   // The scores (rows padded to 32) have been used when the projection's partial results are written, which take their place.
-  const size_t scores = sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32), outparts = sizeof(float) * (size_t)parts * B * e;
-  p.off_S = p.off_outpart = take(scores > outparts ? scores : outparts);
+  const size_t scores = sizeof(float) * (size_t)B * H * ((T + 31) / 32 * 32);
+  const size_t mfma = sizeof(float) * (size_t)(p.csw > p.csw_f ? p.csw : p.csw_f) * B * proj_part_row(H, d_k);
+  const size_t valu = sizeof(float) * (size_t)p.rsplit * B * e;
+  p.off_S = p.off_outpart = take(std::max(scores, std::max(mfma, valu)));
   p.off_Cpart = take(sizeof(float) * nparts * H * width);
   p.off_m = take(sizeof(float) * nparts * H);
   p.off_l = take(sizeof(float) * nparts * H);
@@ -638,13 +639,13 @@ BlockBufs block_layout(const Plan& p, int B, int H, int d) {
   b.off_k = o; o += row;
   b.off_v = o; o += row;
   b.off_attn = o; o += row;
-  // partial sums of the dense products: [matrix][row split][B][d] for one, two or three matrices
+  // partial sums of the dense products: [matrix][row split][B][proj_part_row] for one, two or three matrices
   size_t parts = 1;
   for (int nmat = 1; nmat <= 3; ++nmat) {
     const size_t n = (size_t)nmat * dense_row_splits(H, nmat, d, d, B);
     if (n > parts) parts = n;
   }
-  b.off_dpart = o; o += up(sizeof(float) * parts * B * d);
+  b.off_dpart = o; o += up(sizeof(float) * parts * B * proj_part_row(H, d / H));
   b.total = o;
   return b;
 }

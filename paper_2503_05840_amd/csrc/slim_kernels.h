@@ -97,7 +97,7 @@ struct FusedGeom {
 struct ProjArgs {
   const float* Cpart; const float* mpart; const float* lpart;
   const uint16_t* W;                  // [rows][e] bf16
-  float* out; float* outpart;         // [B][e], [csw][B][e]
+  float* out; float* outpart;         // [B][e], [csw][B][proj_part_row]
   int* counters;                      // [PROJ_CTRL_INTS]
   int* err; unsigned launch_id;       // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
   int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
@@ -159,6 +159,7 @@ void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st)
 int proj_batch_tiles(int B, int rows, int e, int H);
 int proj_splits_per_unit(int units);
 int proj_row_splits(int H, int rows, int e, int B);
+int proj_part_row(int H, int d_k);
 int proj_rows_per_split(int rows, int csw);
 void launch_project_mfma(ProjArgs a, hipStream_t st);
 int dense_row_splits(int H, int nmat, int rows, int e, int B);
