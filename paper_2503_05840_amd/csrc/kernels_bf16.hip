@@ -733,8 +733,18 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
     int i = blockIdx.x;
     asm volatile("" : "+s"(i));                       // (computed where it is used: not kept in registers through the stream)
     const int slot = i >> 3;
-    phead = (slot / a.proj.csw) * 8 + (i & 7);
     psplit = slot % a.proj.csw;
+    // Heads wider than a cache line whose rows of W are no whole lines share lines with their neighbours, so neighbours share
+    // an XCD: dealt round robin, every XCD fetches those lines for itself (1 x 500..3000 rows x 32 heads x 96 columns: 23.7,
+    // 25.4 and 26.1 us against 22.7, 24.3 and 24.9).  The others are dealt round robin, which is the faster one there
+    // (128 columns: 25.5 against 25.9; 16..32 columns, a small W: up to 0.7 us).
+    if (a.d_k > 64 && a.d_k % 64 != 0) {
+      const int x = i & 7;
+      phead = x * a.H / 8 + slot / a.proj.csw;
+      if (phead >= (x + 1) * a.H / 8) phead = a.H;
+    } else {
+      phead = (slot / a.proj.csw) * 8 + (i & 7);
+    }
   };
   if (fuse) {
     if (wu == NP - 1) {                               // (while the first wave builds the tile prefix)
