@@ -676,8 +676,10 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
 // following seven rows advance by the one-position rotation (table row 1), kept in registers.
 constexpr float SOFTMAX_SLACK = 6.0f;
 
-// LPHP: lanes reserved per head as a compile-time constant (16 or 8: heads of 128 or 64 columns), or 0
-// for the run-time value.  BYSEQ: the by-sequence partition (a.by_sequence != 0), which has no merge of the
+// LPHP: lanes reserved per head: 16, 8, 4 or 2 (heads of up to 128, 64, 32 or 16 columns).  At compile time, because the
+// divisions by it and what follows from them cost registers: with a run-time value for the two narrow classes, layers of 17
+// to 32 such heads had 84 bytes of scratch per lane (108 with rotary keys) where the others have 56..60 (80..88), and took
+// 26.2 us at 1 x 4096 rows x 32 heads x 32 (now 25.8), 40.3 at 4 x 5000 with rotary keys (now 38.1).  BYSEQ: the by-sequence partition (a.by_sequence != 0), which has no merge of the
 // waves and never runs the projection; an instantiation of its own keeps each partition's code out of the
 // other's registers.
 template <int NT, bool ROPE, int LPHP, bool BYSEQ>
@@ -764,7 +766,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (!has_work && !fuse) return;
 
   // ---- lane -> column mapping inside the unit --------------------------------------------------
-  const int lphp = LPHP ? LPHP : a.lphp;
+  constexpr int lphp = LPHP;
   const int hh = idx / lphp, li = idx % lphp;
   const int myhead = u * a.hpu + hh;
   const bool col_active = (li < a.lph) && (hh < a.hpu) && (myhead < a.H);
@@ -1488,7 +1490,8 @@ int fused_blocks_per_cu(const FusedGeom& g, bool rope) {
   auto with_lphp = [&](auto nt, auto rp) {
     if (g.lphp == 16) ask(nt, rp, std::integral_constant<int, 16>{});
     else if (g.lphp == 8) ask(nt, rp, std::integral_constant<int, 8>{});
-    else ask(nt, rp, std::integral_constant<int, 0>{});
+    else if (g.lphp == 4) ask(nt, rp, std::integral_constant<int, 4>{});
+    else ask(nt, rp, std::integral_constant<int, 2>{});
   };
   auto with_rope = [&](auto nt) {
     if (rope) with_lphp(nt, std::true_type{});
@@ -1531,7 +1534,8 @@ void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st)
   auto with_lphp = [&](auto nt, auto rope) {
     if (g.lphp == 16) go(nt, rope, std::integral_constant<int, 16>{});
     else if (g.lphp == 8) go(nt, rope, std::integral_constant<int, 8>{});
-    else go(nt, rope, std::integral_constant<int, 0>{});
+    else if (g.lphp == 4) go(nt, rope, std::integral_constant<int, 4>{});
+    else go(nt, rope, std::integral_constant<int, 2>{});
   };
   auto with_rope = [&](auto nt) {
     if (a.rope) with_lphp(nt, std::true_type{});

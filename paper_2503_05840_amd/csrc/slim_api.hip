@@ -123,7 +123,7 @@ struct DeviceState {
   hipEvent_t order_ev = nullptr;
   hipStream_t last_stream = nullptr;
   bool any_launch = false;
-  signed char blocks_per_cu[2][2][3] = {};    // [NT - 1][rope][lphp class]: 0 unknown, else 1 + blocks
+  signed char blocks_per_cu[2][2][4] = {};    // [NT - 1][rope][lphp class]: 0 unknown, else 1 + blocks
 };
 DeviceState g_dev[64];
 std::mutex g_dev_mu;
@@ -201,7 +201,7 @@ void order_after_previous_stream_kernel(DeviceState& d, hipStream_t st) {
 // All workgroups of a stream-kernel launch must be resident at once (they wait for each other): the
 // device must hold `grid` of them, by its own occupancy figure for this instantiation.
 bool stream_kernel_fits(DeviceState& d, const FusedGeom& g, bool rope) {
-  const int lc = g.lphp == 16 ? 0 : (g.lphp == 8 ? 1 : 2);
+  const int lc = g.lphp == 16 ? 0 : g.lphp == 8 ? 1 : g.lphp == 4 ? 2 : 3;
   signed char& slot = d.blocks_per_cu[g.NT - 1][rope ? 1 : 0][lc];
   {
     std::lock_guard<std::mutex> lk(g_dev_mu);
@@ -381,7 +381,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     fa.q = (const float*)q; fa.K = (const uint16_t*)Kcache; fa.k_bstride = kb; fa.seq_lens = lens;
     fa.k_banded = k_layout == SLIM_K_BANDED;
     fa.T = T; fa.B = B; fa.H = H; fa.d = d; fa.d_k = d_k;
-    fa.G = g.G; fa.NG = g.NG; fa.gpx = g.gpx; fa.lph = g.lph; fa.lphp = g.lphp; fa.hpu = g.hpu;
+    fa.G = g.G; fa.NG = g.NG; fa.gpx = g.gpx; fa.lph = g.lph; fa.hpu = g.hpu;
     fa.qscale = scale * 1.4426950408889634f;
     fa.exch = (unsigned long long*)(ws + p.off_exch);
     const unsigned tiles = (unsigned)B * (unsigned)((T + TILE_ROWS - 1) / TILE_ROWS) + (unsigned)B + 64u;

@@ -128,7 +128,7 @@ struct FusedArgs {
   int k_banded;                       // 0: [t][d] row-major per sequence; 1: [t / 32][H][32][d_k] (32-row bands, head-major)
   const int32_t* seq_lens;
   int T, B, H, d, d_k;
-  int G, NG, gpx, lph, lphp, hpu;
+  int G, NG, gpx, lph, hpu;
   float qscale;                       // log2(e) / sqrt(d_k): scores live in the log2 domain
   unsigned long long* exch;           // [NG][NP][EXCH_SLOTS][2][16*NT][4] 16-byte words {tag, max, 4 bf16 weights}
   unsigned tag_base, launch_id;
