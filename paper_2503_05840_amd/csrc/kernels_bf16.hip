@@ -129,7 +129,7 @@ __device__ void build_tile_prefix(int* prefix, int* lens_s, const int32_t* lens,
 // is: two tiles of W per wave, then the maxima and sums of all partials.
 // COH: the partials come from other workgroups of the same launch (loads at agent scope, each a trip to the memory
 // side): they are asked for together with their maxima and sums, a lane four consecutive rows c of one sequence and
-// eight loads in flight, and the merged C goes to LDS in B-operand order (up to 1024 / NBT rows at a time, in the place
+// eight loads in flight, and the merged C goes to LDS in B-operand order (up to PROJ_STAGED_ROWS rows, in the place
 // of the cross-wave sum).  Merged per tile in operand layout instead, as a launch of its own does it, that is a trip per
 // tile more: 13 us instead of 10 from the last arrival to the end at 16 sequences x 4096 columns.  (As a launch of its own
 // the staged form takes longer, 13.6 against 12.3 us at 64 sequences x 1280 columns with 3 partials each.)
@@ -298,11 +298,11 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   auto first_part = [&](int bl) { return even ? (bbase + bl) * a.nsplit : __builtin_amdgcn_readfirstlane(sm.pid0s[bl]); };
   auto num_parts = [&](int bl) { return even ? min(a.nsplit, PROJ_MAX_PARTS) : __builtin_amdgcn_readfirstlane(sm.nps[bl]); };
 
-  // The merged C in LDS: 8 rows of 16 NBT sequences after the other, a sequence's 8 values as 16 bytes; hi halves, then lo
-  constexpr int CH = 1024 / NBT;                      // rows at a time
+  // The merged C in LDS: 8 rows of 16 sequences after the other, a sequence's 8 values as 16 bytes; hi halves, then lo
+  static_assert(!COH || NBT == 1, "the single launch has at most 16 sequences");
   uint16_t* const cs_hi = reinterpret_cast<uint16_t*>(red);
-  uint16_t* const cs_lo = cs_hi + CH * 16 * NBT;
-  const int c_pad = c_lo + ntile * TILE_ROWS;
+  uint16_t* const cs_lo = cs_hi + PROJ_STAGED_ROWS * 16;
+  const int rows4 = ntile * TILE_ROWS / 4;            // (crows <= PROJ_STAGED_ROWS: checked on the host)
   // A wave merges whole sequences, a lane four consecutive rows c: 8 / wps sequences at a time, each by wps waves (all in
   // shifts and wave-uniform addresses: this code is a good part of what stands between the partials and the product).
   // One round trip takes RI x 256 rows of a wave and 8 / RI of a sequence's partials.
@@ -310,19 +310,18 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   const int lg = nb >= 5 ? 0 : nb >= 3 ? 1 : nb == 2 ? 2 : 3;     // log2(wps)
   const int seq0 = wu >> lg, lane0 = (wu & ((1 << lg) - 1)) * 64;
   f32x4 px[8];
-  auto fetch = [&](auto RI_, int c0, int bl, int v, int pb) {
+  auto fetch = [&](auto RI_, int bl, int v, int pb) {
     constexpr int RI = decltype(RI_)::value, Q = 8 / RI;
     const int p0 = first_part(bl), np = num_parts(bl);
     const float* p[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q)
-      p[q] = uniform_ptr(a.Cpart + ((size_t)(p0 + min(pb + q % Q, max(np - 1, 0))) * a.H + h) * a.rows + c0);
-    const int top = a.rows - 4 - c0;
+      p[q] = uniform_ptr(a.Cpart + ((size_t)(p0 + min(pb + q % Q, max(np - 1, 0))) * a.H + h) * a.rows + c_lo);
+    const int top = a.rows - 4 - c_lo;
     ld_part8(p, (unsigned)min((v + lane) * 4, top) * 4u, (unsigned)min((v + lane + (RI == 2 ? 64 << lg : 0)) * 4, top) * 4u, px);
   };
-  auto merge_chunk = [&](auto RI_, int c0, bool fetched) {
+  auto merge = [&](auto RI_, bool fetched) {
     constexpr int RI = decltype(RI_)::value, Q = 8 / RI;
-    const int rows4 = min(CH, c_pad - c0) / 4;
     for (int bl = seq0; bl < nb; bl += 8 >> lg) {
       const int np = num_parts(bl);
       for (int v = lane0; v < rows4; v += (64 << lg) * RI) {
@@ -330,7 +329,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 #pragma unroll
         for (int i = 0; i < RI; ++i) cn[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int pb = 0; pb < np; pb += Q) {
-          if (!(fetched && bl == seq0 && v == lane0 && pb == 0)) fetch(RI_, c0, bl, v, pb);
+          if (!(fetched && bl == seq0 && v == lane0 && pb == 0)) fetch(RI_, bl, v, pb);
 #pragma unroll
           for (int pq = 0; pq < Q; ++pq)
             if (pb + pq < np) {
@@ -345,7 +344,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         for (int i = 0; i < RI; ++i) {
           const int ve = v + lane + i * (64 << lg), r = ve * 4;
           if (ve < rows4) {
-            if (c0 + r >= c_hi) cn[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (rows of the last tile past the end of W)
+            if (c_lo + r >= c_hi) cn[i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (rows of the last tile past the end of W)
             unsigned hw[2], lw[2];
 #pragma unroll
             for (int j = 0; j < 4; j += 2) {
@@ -354,7 +353,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
               hw[j / 2] = __builtin_bit_cast(unsigned, hv);
               lw[j / 2] = __builtin_bit_cast(unsigned, lv);
             }
-            const int at = ((r >> 3) * (16 * NBT) + bl) * 8 + (r & 7);
+            const int at = ((r >> 3) * 16 + bl) * 8 + (r & 7);
             *reinterpret_cast<uint2*>(cs_hi + at) = make_uint2(hw[0], hw[1]);
             *reinterpret_cast<uint2*>(cs_lo + at) = make_uint2(lw[0], lw[1]);
           }
@@ -381,9 +380,9 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         lp[i] = ld_part<COH>(a.lpart + (size_t)(first_part(bl) + lane) * a.H + h);
       }
     }
-    const bool fetched = COH && seq0 < nb && lane0 < min(CH, c_pad - c_lo) / 4;
+    const bool fetched = COH && seq0 < nb && lane0 < rows4;
     if constexpr (COH)
-      if (fetched) with_rows([&](auto RI_) { fetch(RI_, c_lo, seq0, lane0, 0); });
+      if (fetched) with_rows([&](auto RI_) { fetch(RI_, seq0, lane0, 0); });
 #pragma unroll
     for (int i = 0; i < SW; ++i) {
       const int bl = wu + NW * i;
@@ -396,7 +395,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     // (barriers for LDS only: __syncthreads() would also wait for the tiles of W in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if constexpr (COH) {
-      with_rows([&](auto RI_) { merge_chunk(RI_, c_lo, fetched); });
+      with_rows([&](auto RI_) { merge(RI_, fetched); });
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
   }
@@ -407,93 +406,78 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 #pragma unroll
     for (int t = 0; t < NBT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto tiles = [&](int tc, int ct_end) {
-    for (int ct = tc + w; ct < ct_end; ct += NW) {
-      const int c0 = c_lo + ct * TILE_ROWS;
-      const bool more = ct + NW < ntile;
-      // B operand: merged C for (b = bt*16 + n, rows c0 + kg*8 .. +8)
-      bf16x8 bhi[NBT], blo[NBT];
-      if constexpr (DENSE) {
-        const int c = c0 + kg * 8;
-        load_x(xn, min(ct + NW, ntile - 1));
+  for (int ct = w; ct < ntile; ct += NW) {
+    const int c0 = c_lo + ct * TILE_ROWS;
+    const bool more = ct + NW < ntile;
+    // B operand: merged C for (b = bt*16 + n, rows c0 + kg*8 .. +8)
+    bf16x8 bhi[NBT], blo[NBT];
+    if constexpr (DENSE) {
+      const int c = c0 + kg * 8;
+      load_x(xn, min(ct + NW, ntile - 1));
 #pragma unroll
-        for (int t = 0; t < NBT; ++t) {
-          const bool live = t * 16 + n < nb && c < c_hi;
+      for (int t = 0; t < NBT; ++t) {
+        const bool live = t * 16 + n < nb && c < c_hi;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float v = live ? xc[t][j >> 2][j & 3] : 0.f;
-            const __bf16 hi = (__bf16)v;
-            bhi[t][j] = hi;
-            blo[t][j] = (__bf16)(v - (float)hi);
-          }
-        }
-      } else if constexpr (COH) {
-#pragma unroll
-        for (int t = 0; t < NBT; ++t) {                // (columns of sequences past the last one: any values, never used)
-          const int at = (((ct - tc) * 4 + kg) * (16 * NBT) + t * 16 + n) * 8;
-          bhi[t] = *reinterpret_cast<const bf16x8*>(cs_hi + at);
-          blo[t] = *reinterpret_cast<const bf16x8*>(cs_lo + at);
-        }
-      } else {
-        const int c = c0 + kg * 8;
-#pragma unroll
-        for (int t = 0; t < NBT; ++t) {
-          float cn[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) cn[j] = 0.f;
-          const int bl = t * 16 + n;
-          if (bl < nb && c < c_hi) {
-            const int p0 = even ? (bbase + bl) * a.nsplit : sm.pid0s[bl], np = even ? min(a.nsplit, PROJ_MAX_PARTS) : sm.nps[bl];
-            for (int p = 0; p < np; ++p) {
-              const float wgt = sm.wpid[bl][p];
-              const float* src = a.Cpart + ((size_t)(p0 + p) * a.H + h) * a.rows + c;
-              const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
-#pragma unroll
-              for (int j = 0; j < 4; ++j) { cn[j] = fmaf(wgt, x0[j], cn[j]); cn[4 + j] = fmaf(wgt, x1[j], cn[4 + j]); }
-            }
-          }
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const __bf16 hi = (__bf16)cn[j];
-            bhi[t][j] = hi;
-            blo[t][j] = (__bf16)(cn[j] - (float)hi);
-          }
+        for (int j = 0; j < 8; ++j) {
+          const float v = live ? xc[t][j >> 2][j & 3] : 0.f;
+          const __bf16 hi = (__bf16)v;
+          bhi[t][j] = hi;
+          blo[t][j] = (__bf16)(v - (float)hi);
         }
       }
-      u32x4 am[8];
-      transpose8x8(wt, am);
+    } else if constexpr (COH) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
+      for (int t = 0; t < NBT; ++t) {                // (columns of sequences past the last one: any values, never used)
+        const int at = ((ct * 4 + kg) * 16 + n) * 8;
+        bhi[t] = *reinterpret_cast<const bf16x8*>(cs_hi + at);
+        blo[t] = *reinterpret_cast<const bf16x8*>(cs_lo + at);
+      }
+    } else {
+      const int c = c0 + kg * 8;
 #pragma unroll
-        for (int t = 0; t < NBT; ++t) {
-          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[t], acc[i][t], 0, 0, 0);
-          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[t], acc[i][t], 0, 0, 0);
+      for (int t = 0; t < NBT; ++t) {
+        float cn[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) cn[j] = 0.f;
+        const int bl = t * 16 + n;
+        if (bl < nb && c < c_hi) {
+          const int p0 = even ? (bbase + bl) * a.nsplit : sm.pid0s[bl], np = even ? min(a.nsplit, PROJ_MAX_PARTS) : sm.nps[bl];
+          for (int p = 0; p < np; ++p) {
+            const float wgt = sm.wpid[bl][p];
+            const float* src = a.Cpart + ((size_t)(p0 + p) * a.H + h) * a.rows + c;
+            const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { cn[j] = fmaf(wgt, x0[j], cn[j]); cn[4 + j] = fmaf(wgt, x1[j], cn[4 + j]); }
+          }
         }
-      }
-      if (more) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) wt[j] = wn[j];
-        if (ct + 2 * NW < ntile) load_w(wn, ct + 2 * NW);
-      }
-      if constexpr (DENSE) {
-#pragma unroll
-        for (int t = 0; t < NBT; ++t) { xc[t][0] = xn[t][0]; xc[t][1] = xn[t][1]; }
+        for (int j = 0; j < 8; ++j) {
+          const __bf16 hi = (__bf16)cn[j];
+          bhi[t][j] = hi;
+          blo[t][j] = (__bf16)(cn[j] - (float)hi);
+        }
       }
     }
-  };
-  if constexpr (COH) {
-    constexpr int TC = CH / TILE_ROWS;                // tiles per merged chunk (a multiple of the waves: w + NW i throughout)
-    for (int tc = 0; tc < ntile; tc += TC) {
-      if (tc > 0) {
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (every wave is done with the chunk before)
-        with_rows([&](auto RI_) { merge_chunk(RI_, c_lo + tc * TILE_ROWS, false); });
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    u32x4 am[8];
+    transpose8x8(wt, am);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
+#pragma unroll
+      for (int t = 0; t < NBT; ++t) {
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bhi[t], acc[i][t], 0, 0, 0);
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, blo[t], acc[i][t], 0, 0, 0);
       }
-      tiles(tc, min(ntile, tc + TC));
     }
-  } else {
-    tiles(0, ntile);
+    if (more) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) wt[j] = wn[j];
+      if (ct + 2 * NW < ntile) load_w(wn, ct + 2 * NW);
+    }
+    if constexpr (DENSE) {
+#pragma unroll
+      for (int t = 0; t < NBT; ++t) { xc[t][0] = xn[t][0]; xc[t][1] = xn[t][1]; }
+    }
   }
   if constexpr (COH) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the merged C gives way to the sum)
 

@@ -76,6 +76,7 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
         // a tile of W for every wave (8 waves x 32 rows) before another workgroup: what is split finer has more to hand over
         const int most = (width + 8 * TILE_ROWS - 1) / (8 * TILE_ROWS), c = proj_splits_per_unit(H);
         p.csw_f = c < most ? c : most;
+        if (proj_rows_per_split(width, p.csw_f) > PROJ_STAGED_ROWS) p.csw_f = 0;    // (never: 4096 rows at most, eight splits of 32 heads)
       }
     }
     p.nsplit_f = f32_stream_splits(B, T);

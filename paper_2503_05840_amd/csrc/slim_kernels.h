@@ -83,6 +83,7 @@ constexpr int FUSED_WAVES = 8;       // waves per workgroup of the stream kernel
 constexpr int FUSED_SLOTS = 2;       // LDS landing slots (8 KB tiles) per wave
 constexpr int FUSED_AHEAD = 2;       // register sets of a wave: one tile being scored, the other in flight
 constexpr int PROJ_MAX_PARTS = 64;   // partials per sequence the projection merges
+constexpr int PROJ_STAGED_ROWS = 1024;   // rows of W per workgroup of the single launch at most
 // Control words of a projection whose rows of W are split, all 0 on entry: per (head, batch chunk) unit an arrival counter,
 // then a 64-bit word of who takes part, a byte per XCD.  More units than this have no row splits (proj_splits_per_unit).
 constexpr int PROJ_MAX_UNITS = 128;
