@@ -230,7 +230,11 @@ int slim_decode(const void* q, const void* Kcache, const void* W_KV, void* out,
  *     slim_static_scratch_bytes()) are refused with SLIM_ERR_WORKSPACE before anything is launched.
  *   - Every call on a GPU shares that GPU's array: calls that overlap on one GPU (different streams
  *     or threads) race.  Nothing needs clearing between calls: the kernels zero their own counters
- *     and tell fresh exchange words from stale ones by per-launch tags. */
+ *     and tell fresh exchange words from stale ones by per-launch tags.
+ * Under stream capture (any decode call, with a workspace of its own or this one): call slim_init before.
+ * The tags are recorded with the launch, so a recorded stream-kernel launch is preceded by two that clear
+ * the words of the replay before.  Replays are not ordered against other launches of the stream kernel by
+ * the library (see opts->workspace): the caller keeps them from overlapping. */
 #define SLIM_STATIC_SCRATCH_BYTES (64u << 20)
 size_t slim_static_scratch_bytes(void);
 int slim_decode_static(const void* q, const void* Kcache, const void* W_KV, void* out,

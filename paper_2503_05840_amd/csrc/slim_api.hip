@@ -199,6 +199,15 @@ void order_after_previous_stream_kernel(DeviceState& d, hipStream_t st) {
   d.any_launch = true;
 }
 
+// Whether calls on this stream are being recorded into a graph.  The ids and tags by which the stream kernel tells this
+// launch's words from an earlier one's are part of what is recorded, so a replay would take the words of the replay before
+// for its own: a recorded launch has them cleared first.
+bool recording(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (!st || hipStreamIsCapturing(st, &s) != hipSuccess) { if (st) (void)hipGetLastError(); return false; }
+  return s == hipStreamCaptureStatusActive;
+}
+
 // All workgroups of a stream-kernel launch must be resident at once (they wait for each other): the
 // device must hold `grid` of them, by its own occupancy figure for this instantiation.
 bool stream_kernel_fits(DeviceState& d, const FusedGeom& g, bool rope) {
@@ -309,7 +318,7 @@ std::atomic<unsigned> g_tag{(unsigned)std::chrono::steady_clock::now().time_sinc
 std::atomic<unsigned> g_launch{((unsigned)std::chrono::steady_clock::now().time_since_epoch().count() * 2246822519u) | 1u};
 unsigned next_launch_id() {
   const unsigned id = g_launch.fetch_add(1);
-  return id ? id : g_launch.fetch_add(1);
+  return (id << 3) != 0 ? id : next_launch_id();       // (the arrival flags carry the lower 29 bits)
 }
 
 extern "C" int slim_variant_for(int B, int H, int T, int d, int dtype) {
@@ -386,7 +395,8 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     fa.qscale = scale * 1.4426950408889634f;
     fa.exch = (unsigned long long*)(ws + p.off_exch);
     const unsigned tiles = (unsigned)B * (unsigned)((T + TILE_ROWS - 1) / TILE_ROWS) + (unsigned)B + 64u;
-    fa.tag_base = g_tag.fetch_add(tiles);
+    do fa.tag_base = g_tag.fetch_add(tiles);
+    while (fa.tag_base + tiles < tiles);               // (no tag is 0, what cleared words hold)
     const unsigned lid = block_id ? block_id : next_launch_id();
     const bool xcd_local = dev->xcd_round_robin && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
     fa.launch_id = lid;
@@ -416,7 +426,13 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
       pa.crows = proj_rows_per_split(d, p.csw_f);
       fa.fuse = 1; fa.flags = (unsigned*)(ctrl + CTRL_INTS / 2); fa.proj = pa;
     }
-    order_after_previous_stream_kernel(*dev, st);
+    if (recording(st)) {
+      // (arrival flags and error words lie in the upper half of the control block; a block has cleared its error words before)
+      launch_zero_ints(ctrl + CTRL_INTS / 2, CTRL_INTS / 2 - (block_id ? 2 : 0), st);
+      launch_zero_ints((int*)(ws + p.off_exch), (int)(fused_exch_bytes(g) / sizeof(int)), st);
+    } else {
+      order_after_previous_stream_kernel(*dev, st);    // (a graph's launches are ordered by whoever launches the graph)
+    }
     launch_fused_stream(g, fa, st);
     tm.mark();
     if (!one_launch) {
@@ -702,7 +718,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   StageTimer tm(o, st);
   if (fast) {
     // q, k (and v) in one launch; the new rows go straight into the caches
-    launch_zero_ints(pa.counters, PROJ_CTRL_INTS, st);
+    launch_zero_ints(pa.counters, CTRL_INTS, st);
     pa.nmat = nmat; pa.csw = dense_row_splits(H, nmat, d, d, B);
     pa.Wm[0] = (const uint16_t*)c.W_Q; pa.outm[0] = q; pa.role[0] = 1;
     pa.Wm[1] = (const uint16_t*)c.W_K; pa.outm[1] = nullptr; pa.role[1] = 2;
