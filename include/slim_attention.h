@@ -152,7 +152,8 @@ typedef struct slim_opts {
 #define SLIM_MAX_STAGES 8
 
 #define SLIM_VARIANT_AUTO      0
-#define SLIM_VARIANT_GENERIC   1   /* plain vector-ALU kernels, any supported shape            */
+#define SLIM_VARIANT_GENERIC   1   /* plain vector-ALU kernels, any supported shape (slower than AUTO
+                                      wherever another kernel takes the shape)                 */
 #define SLIM_VARIANT_FUSED_SPLIT 2 /* as FUSED, but the merge + projection always runs as a launch of
                                       its own; slim_decode_xcache: scores and weighted sum as two
                                       passes over X even where the one-pass kernel applies     */
@@ -188,8 +189,11 @@ int slim_init(void);
 #define SLIM_STATIC_SCRATCH ((const void*)(uintptr_t)1)
 int slim_status(const void* workspace, void* stream);
 
-/* The implementation SLIM_VARIANT_AUTO resolves to for a K-cache decode of this shape
- * (one of the SLIM_VARIANT_* values above, never AUTO); 0 on invalid arguments. */
+/* Whether SLIM_VARIANT_AUTO takes the bf16 stream kernel for a K-cache decode of this shape: SLIM_VARIANT_FUSED
+ * if so, SLIM_VARIANT_GENERIC for everything else, never AUTO; 0 on invalid arguments.  GENERIC as an answer
+ * only says "not the stream kernel": fp32 caches of up to 1024 columns and bf16 layers of more than 32 heads
+ * have kernels of their own, which a call reaches with SLIM_VARIANT_AUTO -- asking such a call for
+ * SLIM_VARIANT_GENERIC gets the plain vector-ALU kernels, three to five times slower there. */
 int slim_variant_for(int B, int H, int T, int d, int dtype);
 
 /* Upper bound of the device scratch slim_decode / vanilla_kv_decode need for this shape.  None of the

@@ -194,7 +194,7 @@ def slim_workspace_bytes_block(B, H, T, d, dtype: str) -> int:
 
 
 def auto_variant_name(B, H, T, d, dtype: str) -> str:
-    """Which implementation SLIM_VARIANT_AUTO resolves to for this shape."""
+    """'fused' where SLIM_VARIANT_AUTO takes the bf16 stream kernel for this shape, else 'generic'."""
     return VARIANT_NAMES[int(load().slim_variant_for(B, H, T, d, DTYPES[dtype]))]
 
 

@@ -91,7 +91,8 @@ __global__ __launch_bounds__(KS_WAVES * 64) void kscores_kernel(const float* __r
 }  // namespace
 
 // Whole 128-column blocks for the weighted sum, heads of whole 16-byte pieces up to 128 columns, and a sequence's
-// rows within 32-bit byte offsets.
+// rows within 32-bit byte offsets.  (Rows that end inside a block take the plain kernels, at three times the time:
+// 1 x 2000 rows x 36 heads x 80 = 2880 columns 108 us.  The weighted sum has no masked column block.)
 bool wide_ok(int dtype, int T, int d, int d_k) {
   return dtype == DT_BF16 && d % 128 == 0 && d < (1 << 22) && d_k % 8 == 0 && d_k <= 128 && T < (1 << 24) &&
          (size_t)T * d * 2 < ((size_t)1 << 32);

@@ -372,7 +372,8 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
   // compile-time index).  A step's work is short next to the latency of a load, so what it needs must
   // have been requested several steps earlier.  Loads past the end re-read the last tile (unused) so that
   // every step issues the same loads and the compiler can wait for exactly the ones a step needs.
-  // Three head tiles leave registers for one set of each; a step is long enough there (2000 cycles a wave).
+  // Three head tiles leave registers for one set of each; a step is long enough there (2000 cycles a wave).  With three
+  // terms per weight both tile counts are past the 256 registers by ten (44 bytes of scratch per lane).
   constexpr int D = NT <= 2 ? 2 : 1, DS = D, UN = 2;   // X sets, score sets, steps per unrolled group (a common multiple)
   u32x4 xt[D][8];
   f32x4 sc[DS][NT][2];
