@@ -282,10 +282,9 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   // In a launch of its own: who takes part in this unit, and where (see the hand-over), at the memory side, used there, on its
   // way while W and the partials travel.
   const bool xl = a.xcd_local != 0;
-  unsigned long long* const place = reinterpret_cast<unsigned long long*>(a.counters + PROJ_MAX_UNITS) + (bz * nhx + hx);
   const unsigned long long my_place = COH ? 0 : 1ull << (8 * (my_xcc() ^ (a.apart ? cs & 1 : 0)));
   unsigned long long places = 0;
-  if (!COH && xl && a.csw > 1 && tid == 0) places = __hip_atomic_fetch_add(place, my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
+  if (!COH && xl && a.csw > 1 && tid == 0) places = __hip_atomic_fetch_add(a.places + (bz * nhx + hx), my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
 
   const bool even = a.mode == 1;
   if constexpr (!COH && !DENSE) {
@@ -572,12 +571,6 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   // (single launch: the error word travels with the partial sums, requested here, looked at behind their wait)
   const int errv = COH ? ld_err<true>(a.err) : err_early;
-  auto reset = [&]() {                                 // for the next launch on these control words
-    if (tid == 0) {
-      a.counters[bz * nhx + hx] = 0;
-      if (!COH && xl) __hip_atomic_store(place, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  };
   if (in_order) {
     float sum = 0.f;
     if (eok)
@@ -590,7 +583,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
       }
     const float other = __shfl_xor(sum, 1);              // (a pair's columns sit in neighbour lanes)
     if (eok) emit(ebl, ej, sum, other, a.err_before && errv == (int)a.launch_id);
-    reset();
+    if (tid == 0) a.counters[bz * nhx + hx] = 0;
     return;
   }
   if (mine) {
@@ -615,7 +608,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     const int bl = v / a.d_k, j = v % a.d_k;
     emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
   }
-  reset();
+  if (tid == 0) a.counters[bz * nhx + hx] = 0;
 }
 
 template <int NBT, bool DENSE>

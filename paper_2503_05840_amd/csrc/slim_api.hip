@@ -36,6 +36,11 @@ struct Plan {
   size_t total = 0;
 };
 
+// Sets of words in which the workgroups of a unit note where they run (PROJ_CTRL_INTS): first or second launch of a call.
+unsigned long long* unit_words(int* ctrl, bool second) {
+  return (unsigned long long*)(ctrl + (second ? PROJ_SECOND_WORDS : PROJ_MAX_UNITS));
+}
+
 // Control block at the start of every workspace: arrival counters, arrival flags, and in its last two
 // ints the id of the latest stream-kernel launch and the error word (= that id when a wait ran out).
 constexpr int CTRL_INTS = 4096;
@@ -413,7 +418,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.err_before = 1; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
     pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcd_local = xcd_local;
-    pa.apart = flag_of(o, SLIM_VARIANT_APART);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     if (const int shares = fused_by_sequence(g, B, lens != nullptr)) {
       fa.by_sequence = shares;
       pa.mode = 1; pa.nsplit = shares;               // partials laid out [sequence][share]
@@ -483,7 +488,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
     pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
     pa.csw = p.csw; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
-    pa.apart = flag_of(o, SLIM_VARIANT_APART);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = block_id ? block_id : next_launch_id(); pa.err_before = block_id != 0;
     launch_project_mfma(pa, st);
   } else {
@@ -621,7 +626,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d_model; pa.e = e;
     pa.NG = 0; pa.nsplit = nsplit; pa.mode = 1; pa.mscale = 1.0f;
     pa.csw = csw; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
-    pa.apart = flag_of(o, SLIM_VARIANT_APART);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     launch_project_mfma(pa, st);
     tm.mark();
     tm.finish();
@@ -707,13 +712,14 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
     DeviceState* dev = device_state();
     if (!fast || t_stride % 32 != 0 || !dev || !stream_kernel_fits(*dev, p.geom, rope != nullptr)) return SLIM_ERR_LAYOUT;
   }
+  int* const ctrl = (int*)(ws + p.off_ctrl);
   ProjArgs pa{};
-  pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = (int*)(ws + p.off_ctrl);
+  pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = ctrl;
   pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
   pa.nsplit = 1; pa.mscale = 1.0f; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
-    pa.apart = flag_of(o, SLIM_VARIANT_APART);
+    pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
   const unsigned id = fast ? next_launch_id() : 0;     // one for all launches of the call
-  pa.err = (int*)(ws + p.off_ctrl) + CTRL_INTS - 1; pa.launch_id = id;
+  pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = id;
 
   StageTimer tm(o, st);
   if (fast) {
@@ -752,7 +758,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   if (rc) return rc;
   tm.mark();
   if (fast) {
-    pa.Cpart = attn; pa.nmat = 1; pa.csw = dense_row_splits(H, 1, d, d, B); pa.err_before = 1;
+    pa.Cpart = attn; pa.nmat = 1; pa.csw = dense_row_splits(H, 1, d, d, B); pa.err_before = 1; pa.places = unit_words(ctrl, true);
     pa.Wm[0] = (const uint16_t*)c.W_O; pa.outm[0] = (float*)c.y; pa.role[0] = 0;
     launch_dense_mfma(pa, st);
   } else {

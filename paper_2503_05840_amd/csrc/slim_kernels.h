@@ -85,9 +85,12 @@ constexpr int FUSED_AHEAD = 2;       // register sets of a wave: one tile being 
 constexpr int PROJ_MAX_PARTS = 64;   // partials per sequence the projection merges
 constexpr int PROJ_STAGED_ROWS = 1024;   // rows of W per workgroup of the single launch at most
 // Control words of a projection whose rows of W are split, all 0 on entry: per (head, batch chunk) unit an arrival counter,
-// then a 64-bit word of who takes part, a byte per XCD.  More units than this have no row splits (proj_splits_per_unit).
+// which the last arriver leaves at 0, and in a launch of its own a 64-bit word of who takes part, a byte per XCD, which is
+// used once (a block's second launch has a second set; leaving it at 0 as well, at the memory side, was 0.2 us of a launch).
+// More units than this have no row splits (proj_splits_per_unit).
 constexpr int PROJ_MAX_UNITS = 128;
-constexpr int PROJ_CTRL_INTS = 3 * PROJ_MAX_UNITS;
+constexpr int PROJ_CTRL_INTS = 3 * PROJ_MAX_UNITS;             // counters, words
+constexpr int PROJ_SECOND_WORDS = PROJ_CTRL_INTS;              // (int offset of the second set, cleared with the whole block)
 
 struct FusedGeom {
   int lph, lphp, hpu;   // active lanes per head (d_k/8), lanes reserved per head, heads per unit
@@ -99,7 +102,7 @@ struct ProjArgs {
   const float* Cpart; const float* mpart; const float* lpart;
   const uint16_t* W;                  // [rows][e] bf16
   float* out; float* outpart;         // [B][e], [csw][B][proj_part_row]
-  int* counters;                      // [PROJ_CTRL_INTS]
+  int* counters; unsigned long long* places;       // [PROJ_MAX_UNITS] each
   int* err; unsigned launch_id;       // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
   int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
   const int32_t* seq_lens;
