@@ -165,7 +165,7 @@ typedef struct slim_opts {
  * meeting in the L2, every second of them behaves as if the hardware had placed it on another XCD (outputs
  * NaN, SLIM_ERR_TIMEOUT from slim_status). */
 #define SLIM_VARIANT_VIA_MEMORY  0x100
-#define SLIM_VARIANT_APART   0x200
+#define SLIM_VARIANT_APART       0x200
 
 /* Per-device set-up for the current device, idempotent and thread-safe: looks up the address of the
  * library's static device array, counts the compute units, checks with one probe launch on the null stream (plus a
@@ -177,7 +177,8 @@ int slim_init(void);
 
 /* Whether the workgroups of the latest bf16 fast-path call that used this workspace (K-cache, X-cache or
  * attention block) could work together: whether their waits for each other ended normally, and whether
- * those that meet in an XCD's L2 shared that XCD.  The decode calls are asynchronous and return before their kernels have run, so a
+ * those that meet in an XCD's L2 shared that XCD.
+ * The decode calls are asynchronous and return before their kernels have run, so a
  * wait that runs out inside a kernel (the chip could not keep the launch's workgroups resident
  * together within opts->wait_budget_us, e.g. because other work held compute units) cannot be reported
  * by the call itself: the kernel raises an error word in the workspace and writes NaN outputs (the new

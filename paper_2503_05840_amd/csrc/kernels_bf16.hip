@@ -279,12 +279,13 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     no_result();
     return;
   }
-  // In a launch of its own: who takes part in this unit, and where (see the hand-over), at the memory side, used there, on its
-  // way while W and the partials travel.
+  // In a launch of its own: who takes part in this unit, and where (see the hand-over); on its way to the memory side and
+  // back while W and the partials travel.
   const bool xl = a.xcd_local != 0;
   const unsigned long long my_place = COH ? 0 : 1ull << (8 * (my_xcc() ^ (a.apart ? cs & 1 : 0)));
   unsigned long long places = 0;
-  if (!COH && xl && a.csw > 1 && tid == 0) places = __hip_atomic_fetch_add(a.places + (bz * nhx + hx), my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
+  if (!COH && xl && a.csw > 1 && tid == 0)
+    places = __hip_atomic_fetch_add(a.places + (bz * nhx + hx), my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
 
   const bool even = a.mode == 1;
   if constexpr (!COH && !DENSE) {
@@ -556,7 +557,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   if (tid == 0) {
     int* const counter = &a.counters[bz * nhx + hx];
     // (the sum of the bytes: how many had added themselves by then)
-    const bool last_apart = !COH && (int)((places * 0x0101010101010101ull) >> 56) == a.csw && places != (unsigned long long)a.csw * my_place;      // (and apart)
+    const bool last_apart = !COH && (int)((places * 0x0101010101010101ull) >> 56) == a.csw && places != (unsigned long long)a.csw * my_place;
     int old = -1;
     if (!xl) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else if (COH || !(a.apart && (cs & 1))) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -564,7 +565,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   __syncthreads();
   if (!sm.is_last) return;
-  if (!COH && sm.is_last == 2) {                               // the last of a unit whose workgroups are apart
+  if (!COH && sm.is_last == 2) {                       // the last of a unit whose workgroups are apart
     if (tid == 0) st_result(a.err, (int)a.launch_id, true);
     no_result();
     return;

@@ -41,8 +41,9 @@ unsigned long long* unit_words(int* ctrl, bool second) {
   return (unsigned long long*)(ctrl + (second ? PROJ_SECOND_WORDS : PROJ_MAX_UNITS));
 }
 
-// Control block at the start of every workspace: arrival counters, arrival flags, and in its last two
-// ints the id of the latest stream-kernel launch and the error word (= that id when a wait ran out).
+// Control block at the start of every workspace: a projection's control words (PROJ_CTRL_INTS, twice the words), arrival
+// flags from the middle on, and in its last two ints the id of the latest fast-path call and the error word (= that id when a
+// wait ran out or workgroups could not meet).
 constexpr int CTRL_INTS = 4096;
 
 int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -150,8 +151,8 @@ DeviceState* device_state() {
   return &s;
 }
 
-// Whether workgroups i and j of a launch are known to share an XCD where i % 8 == j % 8: after slim_init or a call that needed the set-up; without
-// it the callers' kernels meet at the memory side.  (Never sets anything up itself: the set-up waits for the device.)
+// Whether workgroups i and j of a launch are known to share an XCD where i % 8 == j % 8: after slim_init or a call that
+// needed the set-up; without it the callers' kernels meet at the memory side.  (Never sets anything up itself: the set-up waits for the device.)
 bool xcd_round_robin_known() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return false; }
@@ -159,9 +160,12 @@ bool xcd_round_robin_known() {
   return g_dev[dev].ready && g_dev[dev].xcd_round_robin;
 }
 
-// opts->variant: which implementation, and two switches for tests
-int variant_of(const slim_opts* o) { return o ? o->variant & 0xff : SLIM_VARIANT_AUTO; }
-bool flag_of(const slim_opts* o, int flag) { return o && (o->variant & flag); }
+// opts->variant: which implementation, and two switches for tests (a value that is no variant with or without these is the
+// library's choice)
+constexpr int VARIANT_SWITCHES = SLIM_VARIANT_VIA_MEMORY | SLIM_VARIANT_APART;
+bool has_switches(const slim_opts* o) { return o && (o->variant & ~(VARIANT_SWITCHES | 3)) == 0; }
+int variant_of(const slim_opts* o) { return !o ? SLIM_VARIANT_AUTO : has_switches(o) ? o->variant & 3 : o->variant; }
+bool flag_of(const slim_opts* o, int flag) { return has_switches(o) && (o->variant & flag); }
 
 // Library-owned scratch: one allocation per device, grown on demand, kept until exit.
 struct OwnedScratch { void* ptr = nullptr; size_t bytes = 0; };
