@@ -534,20 +534,31 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   // The partial sums of a head lie in accumulator order, [element i][column group], padded to whole fours of column groups,
   // so that they leave and come back 16 bytes at a time.  (Heads of 80 columns without the padding, one dword after the
   // other: 24.9 instead of 21.4 us at 1 x 300 rows x 32 heads.)
-  // Dense products of up to 512 elements (a few sequences) keep their columns in order instead, an element a thread: they
-  // are finished from where they are read, without another pass through LDS (4 x 4096 x 4096: 12.0 against 12.8 us).
+  // Dense products of up to 1024 elements (a few sequences) keep their columns in order instead, an element or two a thread:
+  // they are finished from where they are read, without another pass through LDS (4 x 4096 x 4096: 12.0 against 12.8 us; two
+  // elements: vanilla block of 12 x 300 rows x 20 heads x 64 43.5 against 44.6 us, of 8 x 500 x 32 x 128 74.1 against 74.8).
   if (!COH && a.err_before && err_early == (int)a.launch_id) {             // (then the control words may not be 0 either)
     no_result();
     return;
   }
-  const bool in_order = DENSE && nb * a.d_k <= NTHR;
-  const int ebl = tid / a.d_k, ej = tid - ebl * a.d_k;  // in_order: this thread's element
-  const bool eok = tid < nb * a.d_k;
-  auto elem_at = [&](int sp) { return outpart + ((size_t)sp * a.B + bbase + ebl) * part_row + h * lph4 * 8 + ej; };
+  const int nel = nb * a.d_k;
+  constexpr int IN_ORDER = NBT == 1 ? 2 : 1;            // elements per thread at most (more batch tiles: registers)
+  const bool in_order = DENSE && nel <= IN_ORDER * NTHR;
+  // (thread tid: elements tid and tid + NTHR, the second one in f<2> only)
+  auto per_thread = [&](auto&& f) {
+    if (IN_ORDER == 1 || nel <= NTHR) f(std::integral_constant<int, 1>{});
+    else f(std::integral_constant<int, IN_ORDER>{});
+  };
   auto part_at = [&](int sp, int ps) { return outpart + ((size_t)sp * a.B + bbase + obl) * part_row + (h * 8 + oi(ps)) * lph4 + omi; };
   if (in_order) {
     to_obuf();
-    if (eok) st_result(elem_at(cs), sm.obuf[ebl][ej], !xl);
+    per_thread([&](auto NE) {
+#pragma unroll
+      for (int u = 0; u < decltype(NE)::value; ++u) {
+        const int v = tid + u * NTHR, bl = v / a.d_k, j = v - bl * a.d_k;
+        if (v < nel) st_result(outpart + ((size_t)cs * a.B + bbase + bl) * part_row + h * lph4 * 8 + j, sm.obuf[bl][j], !xl);
+      }
+    });
   } else if (mine) {
 #pragma unroll
     for (int ps = 0; ps < NBT; ++ps) st_result4(part_at(cs, ps), osum[ps], !xl);
@@ -573,17 +584,34 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   // (single launch: the error word travels with the partial sums, requested here, looked at behind their wait)
   const int errv = COH ? ld_err<true>(a.err) : err_early;
   if (in_order) {
-    float sum = 0.f;
-    if (eok)
-      for (int s0 = 0; s0 < a.csw; s0 += 8) {
-        float part[8];
+    per_thread([&](auto NE) {
+      constexpr int N = decltype(NE)::value;
+      int bl[N], col[N];
+      const float* src[N];
+      float sum[N];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) part[q] = ld_part<true>(elem_at(min(s0 + q, a.csw - 1)));
-#pragma unroll
-        for (int q = 0; q < 8; ++q) if (s0 + q < a.csw) sum += part[q];
+      for (int u = 0; u < N; ++u) {
+        const int v = min(tid + u * NTHR, nel - 1);
+        bl[u] = v / a.d_k; col[u] = v - bl[u] * a.d_k; sum[u] = 0.f;
+        src[u] = outpart + ((size_t)bbase + bl[u]) * part_row + h * lph4 * 8 + col[u];
       }
-    const float other = __shfl_xor(sum, 1);              // (a pair's columns sit in neighbour lanes)
-    if (eok) emit(ebl, ej, sum, other, a.err_before && errv == (int)a.launch_id);
+      for (int s0 = 0; s0 < a.csw; s0 += 8) {
+        float part[N][8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int u = 0; u < N; ++u) part[u][q] = ld_part<true>(src[u] + (size_t)min(s0 + q, a.csw - 1) * a.B * part_row);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int u = 0; u < N; ++u) if (s0 + q < a.csw) sum[u] += part[u][q];
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const float other = __shfl_xor(sum[u], 1);       // (a pair's columns sit in neighbour lanes)
+        if (tid + u * NTHR < nel) emit(bl[u], col[u], sum[u], other, false);
+      }
+    });
     if (tid == 0) a.counters[bz * nhx + hx] = 0;
     return;
   }

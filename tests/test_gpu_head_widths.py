@@ -24,8 +24,9 @@ def test_head_widths_match_oracle(d_k):
         assert np.array_equal(a, k.run_slim(variant=binding.VARIANT_VIA_MEMORY))
 
 
-@pytest.mark.parametrize("d_k", [16, 48, 80, 112])
-@pytest.mark.parametrize("B", [2, 9])
+# (a workgroup's B x d_k elements: up to 512 and up to 1024 in column order, one and two a thread, more in the padded order)
+@pytest.mark.parametrize("d_k", [16, 48, 64, 80, 112])
+@pytest.mark.parametrize("B", [2, 8, 9, 16])
 def test_blocks_of_these_widths_match_oracle(d_k, B):
     H = 7 if d_k >= 72 else 19
     say(f"[case] block, head width {d_k}: B={B} H={H} T=50")
