@@ -83,6 +83,23 @@ __device__ __forceinline__ void transpose8x8(const u32x4 (&kt)[8], u32x4 (&a)[8]
   }
 }
 
+// Workgroup i of a one-dimensional launch -> (unit, inner): a unit is a set of `ninner` workgroups that read
+// the same data (a sequence's q~ or scores, the same rows of X).  Workgroups are dealt to the 8 XCDs round
+// robin, each with an L2 of its own, so with `colocate` a unit's workgroups are the ones with the same
+// i % 8 and consecutive i / 8: what they share is fetched into one L2 instead of up to eight.  (Where the
+// dealing differs the mapping is still a bijection: only the sharing is lost.)  False: no such unit.
+__device__ __forceinline__ bool unit_of_workgroup(int i, int ninner, int nunits, bool colocate, int& unit, int& inner) {
+  if (colocate) {
+    const int slot = i >> 3;
+    unit = (slot / ninner) * 8 + (i & 7);
+    inner = slot % ninner;
+  } else {
+    unit = i / ninner;
+    inner = i % ninner;
+  }
+  return unit < nunits;
+}
+
 // f(k + I, integral_constant<I>) for I = 0 .. N-1 while k + I < end: loop bodies whose register
 // buffers are chosen by a compile-time index.
 template <int I, int N, class F>

@@ -29,23 +29,6 @@ __device__ __forceinline__ void split_hi_lo(const float (&x)[8], bf16x8& hi, bf1
   }
 }
 
-// Workgroup i of a one-dimensional launch -> (unit, inner): a unit is a set of `ninner` workgroups that read
-// the same data (a sequence's q~ or scores, the same rows of X).  Workgroups are dealt to the 8 XCDs round
-// robin, each with an L2 of its own, so with `colocate` a unit's workgroups are the ones with the same
-// i % 8 and consecutive i / 8: what they share is fetched into one L2 instead of up to eight.  (Where the
-// dealing differs the mapping is still a bijection: only the sharing is lost.)  False: no such unit.
-__device__ __forceinline__ bool unit_of_workgroup(int i, int ninner, int nunits, bool colocate, int& unit, int& inner) {
-  if (colocate) {
-    const int slot = i >> 3;
-    unit = (slot / ninner) * 8 + (i & 7);
-    inner = slot % ninner;
-  } else {
-    unit = i / ninner;
-    inner = i % ninner;
-  }
-  return unit < nunits;
-}
-
 // ------------------------------------------------------------------------------------------------
 // q~[b][h][c] = scale * sum_j q[b][h d_k + j] W_K[c][h d_k + j]   (scale = log2(e) / sqrt(d_k)), written
 // as two bf16 arrays, hi = bf16(q~) and lo = bf16(q~ - hi), in the order the scores kernel's MFMA B operands
@@ -302,8 +285,8 @@ __global__ __launch_bounds__(512) void xscores_kernel(const uint16_t* qt, const 
 constexpr float XW_SLACK = 6.0f;
 
 // NT: head tiles of 16 per workgroup.  FULL: the weights enter the matrix product as three bf16 terms (8 + 8 + 8
-// bits: exactly the fp32 value) and their sum is taken in fp32 on the vector ALU -- the wide K-cache path, whose
-// weights are fp32; otherwise rounded to bf16 once.  (FULL is 3 MFMAs where there was one; the matrix cores are idle
+// bits: exactly the fp32 value) and their sum is taken in fp32 on the vector ALU -- K-caches whose weights are fp32, where
+// the scratch has no room for what kweighted_kernel (kernels_wide.hip) needs; otherwise rounded to bf16 once.  (FULL is 3 MFMAs where there was one; the matrix cores are idle
 // most of the time here.)  At 40 heads x 5120 columns, 6503 rows: 28.0 us, K coming from the memory-side cache, where
 // the vector-ALU kernel took 99.8; the whole step 197.8 -> 59.8 us.
 template <int NT, bool FULL>
@@ -868,12 +851,6 @@ int xfused_splits(int B, int H, int T, int d_model) {
   return best;
 }
 
-// Units dealt to the 8 XCDs (unit_of_workgroup): only when they spread evenly, within a quarter
-static int colocate_units(int nunits) { return (nunits % 8 == 0 || nunits >= 32) ? 1 : 0; }
-static unsigned unit_grid(int nunits, int ninner, int colocate) {
-  return colocate ? 8u * (unsigned)ninner * (unsigned)((nunits + 7) / 8) : (unsigned)nunits * (unsigned)ninner;
-}
-
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
                    int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
   const int nt = xfused_tiles(H, d_model), hg = 16 * nt;
@@ -927,26 +904,8 @@ void launch_xweighted(const float* S, const void* X, long x_bstride, const int32
                      d_model, nsplit, Cpart, mpart, lpart, colocate);
 }
 
-// The wide K-cache path: head tiles per workgroup.  Three where that saves a pass over K (33..48, 65..96 heads, ...),
-// else two, which leaves registers for a second tile in flight.
-static int kweighted_tiles(int H) {
-  const int tiles = (H + 15) / 16;
-  return (tiles + 2) / 3 < (tiles + 1) / 2 ? 3 : 2;
-}
-
-// One round of workgroups (one per compute unit: 8 waves of 256 registers), eight tiles of rows each at least.
-int kweighted_splits(int B, int H, int T, int d) {
-  const int nt = kweighted_tiles(H);
-  const long per = (long)B * ((H + nt * 16 - 1) / (nt * 16)) * (d / 128 > 0 ? d / 128 : 1);
-  int s = (int)(256 / per);
-  const int cap = (T + 255) / 256;
-  if (s > cap) s = cap;
-  if (s > PROJ_MAX_PARTS) s = PROJ_MAX_PARTS;
-  return s < 1 ? 1 : s;
-}
-
-void launch_kweighted(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
-                      float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
+void launch_xweighted_full(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
+                           float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
   const int nt = kweighted_tiles(H);
   const int ninner = ((H + nt * 16 - 1) / (nt * 16)) * (d / 128), colocate = colocate_units(B * nsplit);
   dim3 grid(unit_grid(B * nsplit, ninner, colocate));

@@ -25,6 +25,7 @@ struct Plan {
   int nsplit_xf = 0;   // context splits of the one-pass X-cache kernel (0: the shape does not take it)
   size_t off_S = 0, off_Cpart = 0, off_m = 0, off_l = 0, off_qt = 0;
   size_t off_vacc = 0, off_vm = 0, off_vl = 0;
+  size_t vanilla_floats = 0;    // floats from off_vacc to the end of the vanilla kernel's part
   size_t off_exch = 0, off_outpart = 0, off_ctrl = 0;   // bf16 fast path
   bool fused_ok = false;
   FusedGeom geom{};
@@ -107,6 +108,7 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
     p.off_vacc = take(sizeof(float) * (size_t)B * p.nsplit_v * e);
     p.off_vm = take(sizeof(float) * (size_t)B * p.nsplit_v * H);
     p.off_vl = take(sizeof(float) * (size_t)B * p.nsplit_v * H);
+    p.vanilla_floats = (o - p.off_vacc) / sizeof(float);
     if (p.fused_ok) p.off_exch = take(fused_exch_bytes(p.geom));
   }
   p.total = o;
@@ -474,9 +476,12 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
   const int arrivals_mfma = p.csw > 1 ? PROJ_CTRL_INTS : 0;
   const bool wide = mfma_projection && wide_ok(dtype, T, d, d_k);
   if (wide) {
-    launch_kscores((const float*)q, Kcache, kb, lens, T, H, d, d_k, scale * 1.4426950408889634f, rope, S, ctrl, arrivals_mfma, B, st);
+    // (the blocks' references and sums take the vanilla kernel's place, which all but huge batches of long contexts have)
+    float* const blocks = kscores_block_floats(B, H, T) <= p.vanilla_floats ? (float*)(ws + p.off_vacc) : nullptr;
+    launch_kscores((const float*)q, Kcache, kb, lens, T, H, d, d_k, scale * 1.4426950408889634f, rope, S, blocks, ctrl, arrivals_mfma, B, st);
     tm.mark();
-    launch_kweighted(S, Kcache, kb, lens, T, H, d, p.nsplit_k, Cpart, mpart, lpart, B, st);
+    if (blocks) launch_kweighted(S, blocks, Kcache, kb, lens, T, H, d, p.nsplit_k, Cpart, mpart, lpart, B, st);
+    else launch_xweighted_full(S, Kcache, kb, lens, T, H, d, p.nsplit_k, Cpart, mpart, lpart, B, st);
   } else {
     launch_head_scores(dtype, (const float*)q, d, Kcache, kb, d, lens, T, d, H, d_k, scale, S,
                        (long)H * T, rope, ctrl, mfma_projection ? arrivals_mfma : arrivals, B, st);

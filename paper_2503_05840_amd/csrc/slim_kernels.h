@@ -184,14 +184,27 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
 void launch_xweighted(const float* S, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
                       int d_model, int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 
+// ---- launches whose units of workgroups share what they read (unit_of_workgroup) -----------------------
+// Units dealt to the 8 XCDs (unit_of_workgroup): only when they spread evenly, within a quarter
+inline int colocate_units(int nunits) { return (nunits % 8 == 0 || nunits >= 32) ? 1 : 0; }
+inline unsigned unit_grid(int nunits, int ninner, int colocate) {
+  return colocate ? 8u * (unsigned)ninner * (unsigned)((nunits + 7) / 8) : (unsigned)nunits * (unsigned)ninner;
+}
+
 // ---- bf16 K-caches the stream kernel does not take (kernels_wide.hip; weighted sum in kernels_xcache.hip) ----
-// Scores in the log2 domain, [B][H][T padded to 32] (scale_log2 = log2(e) / sqrt(d_k)), then per split the weighted
-// sum with fp32 weights; partials laid out [b][nsplit], maxima in the log2 domain.
+// [B][H][T padded to 32]: with `blocks` (kscores_block_floats) softmax numerators against a reference per head and 64
+// rows, else scores in the log2 domain (scale_log2 = log2(e) / sqrt(d_k)); then per split the weighted sum with fp32
+// weights, partials laid out [b][nsplit], maxima in the log2 domain.
 bool wide_ok(int dtype, int T, int d, int d_k);
+int kweighted_tiles(int H);
 int kweighted_splits(int B, int H, int T, int d);
+size_t kscores_block_floats(int B, int H, int T);
 void launch_kscores(const float* q, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int d_k,
-                    float scale_log2, const float* rope, float* S, int* counters, int ncounters, int B, hipStream_t st);
-void launch_kweighted(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
-                      float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
+                    float scale_log2, const float* rope, float* S, float* blocks, int* counters, int ncounters, int B, hipStream_t st);
+void launch_kweighted(const float* P, const float* blocks, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d,
+                      int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
+// the same from scores, the numerators taken by every workgroup for itself
+void launch_xweighted_full(const float* S, const void* K, long k_bstride, const int32_t* seq_lens, int T, int H, int d, int nsplit,
+                           float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 
 }  // namespace slim
