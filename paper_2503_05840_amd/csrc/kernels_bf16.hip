@@ -178,7 +178,8 @@ __device__ __forceinline__ void ld_part8(const float* const (&p)[8], unsigned o0
 // DENSE: plain products out_m = x W_m for up to three matrices that share x (ProjArgs::Wm); hx counts
 // (matrix, head) column blocks.  The result leaves as fp32, or -- the new token's rows -- rotated to
 // the append position and/or stored into the caches (ProjArgs::role).
-template <int NBT, bool COH, bool DENSE, class Hook>
+// ONCE: W is read once per launch and is large: its loads ask to be let go of first (nontemporal).
+template <int NBT, bool COH, bool DENSE, bool ONCE, class Hook>
 __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, int bz, const int* prefix,
                                              ProjShared<NBT>& sm, float* red, Hook&& after_w_issue) {
   const int mtx = DENSE ? hx / a.H : 0;
@@ -205,7 +206,9 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int r = min(c0 + rg * 8 + j, a.rows - 1);
-      wt[j] = col_active ? *reinterpret_cast<const u32x4*>(Wh + (size_t)r * a.e) : u32x4{0u, 0u, 0u, 0u};
+      const u32x4* const src = reinterpret_cast<const u32x4*>(Wh + (size_t)r * a.e);
+      if constexpr (ONCE) wt[j] = col_active ? __builtin_nontemporal_load(src) : u32x4{0u, 0u, 0u, 0u};
+      else wt[j] = col_active ? *src : u32x4{0u, 0u, 0u, 0u};
     }
   };
   // DENSE: the B operand is a slice of x, known from the start: requested first, one tile ahead.
@@ -640,7 +643,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   if (tid == 0) a.counters[bz * nhx + hx] = 0;
 }
 
-template <int NBT, bool DENSE>
+template <int NBT, bool DENSE, bool ONCE>
 __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   __shared__ int prefix[FUSED_MAX_B + 1];
   __shared__ ProjShared<NBT> sm;
@@ -651,7 +654,7 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   // (the launch the error word speaks of; an earlier launch of the call has written it already)
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.err && !a.err_before) st_result(a.err - 1, (int)a.launch_id, true);
   if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
-  project_work<NBT, false, DENSE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
+  project_work<NBT, false, DENSE, ONCE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);
     return true;
   });
@@ -1390,7 +1393,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (phead >= a.proj.H) return;
   // (everything of the stream phase is over in this workgroup: its LDS is reused)
   ProjShared<1>& psm = *reinterpret_cast<ProjShared<1>*>(sbuf);
-  project_work<1, true, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
+  project_work<1, true, false, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
     // Every workgroup's partials must be out: all arrival flags carry this launch's id.  False: the workgroups of this head
     // are to meet in an XCD's L2, and do not run on one XCD.
     bool together = true;
@@ -1591,13 +1594,34 @@ int proj_rows_per_split(int rows, int csw) {
   return ((rows + csw - 1) / csw + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
 }
 
+// Whether a launch's loads of W are nontemporal: a matrix of at least 16 MB that one batch chunk reads, in a call that reads
+// `call_bytes` >= 96 MB (weights and temporally read caches).  Of such calls the memory-side cache (256 MB) keeps nothing until
+// the same layer comes round again, and the loads are faster where they ask for no room in it: block of 16 sequences x
+// 4096 columns (134 MB of weights) 115.7 -> 110.1 us, vanilla block 84.1 -> 80.9, X-cache step of 134 MB 71.6 -> 69.5, 40 heads
+// x 5120 columns (119 MB) 57.7 -> 55.3.  Smaller calls may find W there from the time before: 3072 columns (75 MB) 49.2 -> 50.1
+// and 69.7 -> 72.2 (vanilla), X-cache step of 68 MB 39.5 -> 41.2 (in a loop over more layers than that cache holds they gain
+// 1-3 % as well).  Smaller matrices: 1280 columns 51.7 -> 54.2.  Several batch chunks share W in L2: 72.5 -> 73.4 (24 sequences).
+bool read_once(size_t call_bytes, long rows, long e, int chunks) {
+  return chunks == 1 && rows * e * 2 >= (16L << 20) && call_bytes >= ((size_t)96 << 20);
+}
+
+template <bool DENSE>
+static void launch_product(const ProjArgs& a, int nbt, int units_per_chunk, hipStream_t st) {
+  const int chunks = (a.B + 16 * nbt - 1) / (16 * nbt);
+  dim3 grid(8u * a.csw * (((unsigned)units_per_chunk * chunks + 7) / 8)), block(512);
+  auto go = [&](auto nb) {
+    if (read_once(a.call_bytes, a.rows, a.e, chunks)) hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, false>), grid, block, 0, st, a);
+  };
+  if (nbt == 1) go(std::integral_constant<int, 1>{});
+  else if (nbt == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 4>{});
+}
+
 void launch_project_mfma(ProjArgs a, hipStream_t st) {
   const int nbt = proj_batch_tiles(a.B, a.rows, a.e, a.H);
   a.crows = proj_rows_per_split(a.rows, a.csw);
-  dim3 grid(8u * a.csw * (((unsigned)a.H * ((a.B + 16 * nbt - 1) / (16 * nbt)) + 7) / 8)), block(512);
-  if (nbt == 1) hipLaunchKernelGGL((project_mfma_kernel<1, false>), grid, block, 0, st, a);
-  else if (nbt == 2) hipLaunchKernelGGL((project_mfma_kernel<2, false>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((project_mfma_kernel<4, false>), grid, block, 0, st, a);
+  launch_product<false>(a, nbt, a.H, st);
 }
 
 // out_m = x W_m for a.nmat matrices in one launch (a.Cpart = x, a.csw from dense_row_splits).
@@ -1605,10 +1629,7 @@ void launch_dense_mfma(ProjArgs a, hipStream_t st) {
   const int nbt = proj_batch_tiles(a.B, a.rows, a.e, a.H * a.nmat);
   a.crows = proj_rows_per_split(a.rows, a.csw);
   a.mode = 2;
-  dim3 grid(8u * a.csw * (((unsigned)a.H * a.nmat * ((a.B + 16 * nbt - 1) / (16 * nbt)) + 7) / 8)), block(512);
-  if (nbt == 1) hipLaunchKernelGGL((project_mfma_kernel<1, true>), grid, block, 0, st, a);
-  else if (nbt == 2) hipLaunchKernelGGL((project_mfma_kernel<2, true>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((project_mfma_kernel<4, true>), grid, block, 0, st, a);
+  launch_product<true>(a, nbt, a.H * a.nmat, st);
 }
 
 int dense_row_splits(int H, int nmat, int rows, int e, int B) {

@@ -44,6 +44,7 @@ __device__ __forceinline__ void split_hi_lo(const float (&x)[8], bf16x8& hi, bf1
 constexpr int XQ_HEADS = 4;
 constexpr int XQ_QROW = 16 * 16 + 16;    // bytes per (head, k-step, k-group) of B operands in LDS: 16 sequences x 16 bytes + padding
 
+template <bool ONCE>
 __global__ __launch_bounds__(512) void xq_tilde_kernel(const float* q, const uint16_t* Wk, uint16_t* qt, int B,
                                                        int H, int d_k, int dm, int e, float scale, int* counters,
                                                        int ncounters) {
@@ -65,7 +66,11 @@ __global__ __launch_bounds__(512) void xq_tilde_kernel(const float* q, const uin
     const int h = min(h0 + hh, H - 1);
     const uint16_t* wrow = Wk + (size_t)(c0 + n) * e + (size_t)h * d_k + kq * 8;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) av[hh][ks] = *reinterpret_cast<const u32x4*>(wrow + min(ks, nks - 1) * 32);
+    for (int ks = 0; ks < 4; ++ks) {
+      const u32x4* const src = reinterpret_cast<const u32x4*>(wrow + min(ks, nks - 1) * 32);
+      if constexpr (ONCE) av[hh][ks] = __builtin_nontemporal_load(src);
+      else av[hh][ks] = *src;
+    }
   }
   // q of the workgroup's heads and sequences: 16 x XQ_HEADS d_k floats = nks pieces of 4 floats per thread
   {
@@ -876,10 +881,14 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
 }
 
 void launch_xq_tilde(const float* q, const void* Wk, float* qt, int B, int H, int d_k, int d_model, int e,
-                     float scale, int* counters, int ncounters, hipStream_t st) {
+                     float scale, size_t call_bytes, int* counters, int ncounters, hipStream_t st) {
   dim3 grid((H + XQ_HEADS - 1) / XQ_HEADS, (d_model + 127) / 128, (B + 15) / 16);
-  hipLaunchKernelGGL(xq_tilde_kernel, grid, dim3(512), 0, st, q, (const uint16_t*)Wk, (uint16_t*)qt, B, H, d_k, d_model,
-                     e, scale, counters, ncounters);
+  auto go = [&](auto once) {
+    hipLaunchKernelGGL(xq_tilde_kernel<decltype(once)::value>, grid, dim3(512), 0, st, q, (const uint16_t*)Wk, (uint16_t*)qt, B, H, d_k,
+                       d_model, e, scale, counters, ncounters);
+  };
+  if (read_once(call_bytes, d_model, e, (int)grid.z)) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 void launch_xscores(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
