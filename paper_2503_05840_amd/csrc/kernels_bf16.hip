@@ -287,7 +287,11 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   const bool xl = a.xcd_local != 0;
   const unsigned long long my_place = COH ? 0 : 1ull << (8 * (my_xcc() ^ (a.apart ? cs & 1 : 0)));
   unsigned long long places = 0;
-  if (!COH && xl && a.csw > 1 && tid == 0)
+  // With a.flags (an attention block's first launch: nothing has cleared any words for it) as a flag instead.
+  const bool by_flags = DENSE && a.flags != nullptr;
+  const int unit_at = (bz * nhx + hx) * a.csw, flag_id = (int)(a.launch_id << 3), place_flag = flag_id | (int)((my_xcc() ^ (a.apart ? cs & 1 : 0)));
+  if (by_flags && xl && a.csw > 1 && tid == 0) st_result(a.flags + PROJ_MAX_FLAGS + unit_at + cs, place_flag, true);
+  else if (!COH && xl && a.csw > 1 && tid == 0)
     places = __hip_atomic_fetch_add(a.places + (bz * nhx + hx), my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;
 
   const bool even = a.mode == 1;
@@ -484,6 +488,15 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   if constexpr (COH) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the merged C gives way to the sum)
 
+  // Where the unit's workgroups run, all of whom have stored that by now if they started together (else asked again below);
+  // this one's own flag is out.
+  int place = place_flag;
+  auto look_at_places = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane < a.csw) place = ld_err<true>(a.flags + PROJ_MAX_FLAGS + unit_at + lane);
+  };
+  if (by_flags && xl && a.csw > 1 && w == 0) look_at_places();
+
   // ---- sum the 8 waves, IPR of the 8 accumulator columns per pass through LDS: thread (ei, lane) ends up with
   //      accumulator element i0 + ei / NBT of batch tile ei % NBT as that lane of a wave held it ----------------
   constexpr int IPR = 8 / NBT;
@@ -568,7 +581,21 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) {
+  if (by_flags) {
+    // Arrival flags that carry the launch's id need no launch that clears them (4.6 us; a round trip to L2 more here than
+    // counting).  A workgroup stores its flag, waits for that, and looks at all of the unit's: the last to store sees them
+    // all.  Two that see them all both finish, with the same values.  The flags of where they run were stored before
+    // anything else: seen by the last as well.
+    if (w == 0) {
+      if (lane == 0 && !(xl && a.apart && (cs & 1))) st_result(a.flags + unit_at + cs, flag_id, !xl);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      int arrived = flag_id;
+      if (lane < a.csw) arrived = ld_err<true>(a.flags + unit_at + lane);
+      if (!__all((unsigned)(place ^ flag_id) < 8u)) look_at_places();
+      const bool all_here = __all(arrived == flag_id), all_placed = __all((unsigned)(place ^ flag_id) < 8u), together = __all(place == place_flag);
+      if (lane == 0) sm.is_last = all_placed && !together ? 2 : (all_here && together);
+    }
+  } else if (tid == 0) {
     int* const counter = &a.counters[bz * nhx + hx];
     // (the sum of the bytes: how many had added themselves by then)
     const bool last_apart = !COH && (int)((places * 0x0101010101010101ull) >> 56) == a.csw && places != (unsigned long long)a.csw * my_place;
@@ -615,7 +642,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         if (tid + u * NTHR < nel) emit(bl[u], col[u], sum[u], other, false);
       }
     });
-    if (tid == 0) a.counters[bz * nhx + hx] = 0;
+    if (tid == 0 && !by_flags) a.counters[bz * nhx + hx] = 0;
     return;
   }
   if (mine) {
@@ -640,7 +667,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     const int bl = v / a.d_k, j = v % a.d_k;
     emit(bl, j, sm.obuf[bl][j], sm.obuf[bl][j ^ 1], bad);
   }
-  if (tid == 0) a.counters[bz * nhx + hx] = 0;
+  if (tid == 0 && !by_flags) a.counters[bz * nhx + hx] = 0;
 }
 
 template <int NBT, bool DENSE, bool ONCE>
@@ -653,6 +680,9 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   const int slot = blockIdx.x >> 3, unit = (slot / a.csw) * 8 + (blockIdx.x & 7);
   // (the launch the error word speaks of; an earlier launch of the call has written it already)
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.err && !a.err_before) st_result(a.err - 1, (int)a.launch_id, true);
+  // (control words of the launches that follow: nothing of this launch uses them)
+  if (DENSE && a.flags && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < PROJ_BLOCK_INTS; i += 512) a.counters[i] = 0;
   if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
   project_work<NBT, false, DENSE, ONCE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);

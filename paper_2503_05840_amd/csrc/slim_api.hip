@@ -735,7 +735,9 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   StageTimer tm(o, st);
   if (fast) {
     // q, k (and v) in one launch; the new rows go straight into the caches
-    launch_zero_ints(pa.counters, CTRL_INTS, st);
+    // (flags of an earlier replay carry the id that a recorded launch repeats)
+    if (recording(st)) launch_zero_ints(pa.counters, CTRL_INTS, st);
+    pa.flags = ctrl + PROJ_FLAGS_AT;
     pa.nmat = nmat; pa.csw = dense_row_splits(H, nmat, d, d, B);
     pa.Wm[0] = (const uint16_t*)c.W_Q; pa.outm[0] = q; pa.role[0] = 1;
     pa.Wm[1] = (const uint16_t*)c.W_K; pa.outm[1] = nullptr; pa.role[1] = 2;
@@ -769,6 +771,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   if (rc) return rc;
   tm.mark();
   if (fast) {
+    pa.flags = nullptr;
     pa.Cpart = attn; pa.nmat = 1; pa.csw = dense_row_splits(H, 1, d, d, B); pa.err_before = 1; pa.places = unit_words(ctrl, true);
     pa.Wm[0] = (const uint16_t*)c.W_O; pa.outm[0] = (float*)c.y; pa.role[0] = 0;
     launch_dense_mfma(pa, st);

@@ -90,7 +90,13 @@ constexpr int PROJ_STAGED_ROWS = 1024;   // rows of W per workgroup of the singl
 // More units than this have no row splits (proj_splits_per_unit).
 constexpr int PROJ_MAX_UNITS = 128;
 constexpr int PROJ_CTRL_INTS = 3 * PROJ_MAX_UNITS;             // counters, words
-constexpr int PROJ_SECOND_WORDS = PROJ_CTRL_INTS;              // (int offset of the second set, cleared with the whole block)
+constexpr int PROJ_SECOND_WORDS = PROJ_CTRL_INTS;              // (int offset of the second set, cleared by a block's first launch)
+constexpr int PROJ_BLOCK_INTS = PROJ_SECOND_WORDS + 2 * PROJ_MAX_UNITS;
+// A block's first launch finds nothing cleared: flags tagged with the launch's id, one per workgroup (row splits times units,
+// a single round of workgroups at most), that it has arrived and, behind these, where it runs.
+constexpr int PROJ_MAX_FLAGS = 256;
+constexpr int PROJ_FLAGS_AT = 1024;                            // int offset in the control block
+static_assert(PROJ_FLAGS_AT >= PROJ_BLOCK_INTS, "the flags are not among the words that are cleared");
 
 struct FusedGeom {
   int lph, lphp, hpu;   // active lanes per head (d_k/8), lanes reserved per head, heads per unit
@@ -103,6 +109,7 @@ struct ProjArgs {
   const uint16_t* W;                  // [rows][e] bf16
   float* out; float* outpart;         // [B][e], [csw][B][proj_part_row]
   int* counters; unsigned long long* places;       // [PROJ_MAX_UNITS] each
+  int* flags;                         // dense products, nullable: [2][PROJ_MAX_FLAGS], used instead of these
   int* err; unsigned launch_id;       // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
   int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
   const int32_t* seq_lens;
