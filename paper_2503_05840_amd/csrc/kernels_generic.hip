@@ -306,16 +306,21 @@ __global__ __launch_bounds__(256) void weighted_sum_kernel(
 // merge + projection on the vector ALU:  out[b][h d_k + j] = sum_c C[b][h][c] W[c][h d_k + j] with C merged from
 // the context splits (log-sum-exp weights, 1 / l) on the fly.
 // One workgroup (4 waves) per (head and block of 64 of its columns, row split of W, 4 sequences): per 64 rows c it
-// requests its 64 x 64 block of W, merges C of its 4 sequences x 64 rows (a lane per row, the splits dealt to the
-// waves in fours) while W travels, and multiplies from LDS; row groups and waves are summed in a fixed order, row splits by
+// requests its 64 x 64 block of W and the partials of its 4 sequences x 64 rows (the splits dealt to the waves in fours),
+// merges and multiplies from LDS; row groups and waves are summed in a fixed order, row splits by
 // the last workgroup to arrive (as in the MFMA projection: write-through stores, agent-scope loads).
 // Bound by the length of this chain, not by bytes: the row splits are what fills the chip (one kernel that merged
 // to memory and one with a workgroup per 64 columns took 7.4 + 40.3 us for 4 sequences x 16 heads x 1024 rows with
-// up to 12 splits each; this one 13.2 us with up to 47, most of it round trips).
+// up to 12 splits each; this one 10.5 us with up to 47).  Everything that can be is asked for in one round trip, 16 bytes a
+// lane: with a trip for the maxima and sums first and then one per 16 splits, 4 bytes a lane, it was 13.3 us (the step 26.4
+// -> 23.6; 1 x 100 rows x 256 columns 12.5 -> 12.1, 1 x 3000 x 1024 25.7 -> 23.7); at once but 4 bytes a lane 13.8.
 // ------------------------------------------------------------------------------------------------
 constexpr int MP_ROWS = 64, MP_COLS = 64, MP_NB = 4, MP_SPLITS = 4;
 
-template <class ET>
+// R: rounds of MP_SPLITS splits per wave (nsplit <= 4 R MP_SPLITS).  Maxima, sums, W and all partials of the first 64 rows are
+// asked for at once, before it is known which splits a sequence has (what a split that does not exist left in the scratch
+// is read and not used); then the next 64 rows' behind the use of these.
+template <class ET, int R>
 __global__ __launch_bounds__(256) void merge_project_kernel(
     const float* __restrict__ Cpart, const float* __restrict__ mpart, const float* __restrict__ lpart, int nsplit,
     int own_splits, const int32_t* __restrict__ seq_lens, int T, const typename ET::elem* __restrict__ W, int rows, int e,
@@ -323,7 +328,8 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
   __shared__ float wgt[MP_NB][MERGE_MAX_SPLITS];
   __shared__ int nsp[MP_NB];
   __shared__ float cs[MP_NB][MP_ROWS];
-  __shared__ float red[4][MP_NB][MP_COLS];
+  __shared__ __align__(16) float red[4][MP_NB][MP_COLS];
+  static_assert(MP_SPLITS == 4 && MP_ROWS == 64, "lane -> split and rows");
   __shared__ int is_last;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wu = __builtin_amdgcn_readfirstlane(w);
@@ -339,6 +345,27 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) ET::four(Wc + (size_t)min(c0 + rg + 16 * i, rows - 1) * e, wv[i]);
   };
+  float mp, lp;                                         // one wave per sequence, a lane per split
+  {
+    const size_t at = ((size_t)min(b0 + w, B - 1) * nsplit + min(lane, nsplit - 1)) * H + h;
+    mp = mpart[at];
+    lp = lpart[at];
+  }
+  load_w(c_lo);
+  // this wave's share of every sequence's splits: a lane four rows c of one split, sixteen lanes the 64 rows, so that one
+  // load instruction takes four splits (clamped indices, no branches)
+  f32x4 x[R][MP_NB];
+  auto load_parts = [&](int c0) {
+    const int cl = min(c0 + idx * 4, rows - 4);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int sp = min((i * 4 + wu) * MP_SPLITS + (lane >> 4), nsplit - 1);
+#pragma unroll
+      for (int q = 0; q < MP_NB; ++q)
+        x[i][q] = *reinterpret_cast<const f32x4*>(Cpart + ((size_t)(min(b0 + q, B - 1) * nsplit + sp) * H + h) * rows + cl);
+    }
+  };
+  load_parts(c_lo);
   // splits of the four sequences (wave-uniform)
   int ns4[MP_NB];
 #pragma unroll
@@ -350,23 +377,16 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
     }
     if (q >= nb) ns4[q] = 0;
   }
-  load_w(c_lo);                                         // in flight while the weights of the splits are built
-
-  {                                                     // one wave per sequence, a lane per split
-    const int b = min(b0 + w, B - 1);
+  {
     const int ns = w == 0 ? ns4[0] : w == 1 ? ns4[1] : w == 2 ? ns4[2] : ns4[3];
-    float mp = NEG_INF, lp = 0.f;
-    if (lane < ns) {
-      mp = mpart[((size_t)b * nsplit + lane) * H + h];
-      lp = lpart[((size_t)b * nsplit + lane) * H + h];
-    }
+    if (lane >= ns) { mp = NEG_INF; lp = 0.f; }
     const float M = max_over_wave(mp);
     const float wg = (mp == NEG_INF) ? 0.f : __expf(mp - M);
     const float L = sum_over_wave(wg * lp);
     wgt[w][lane] = wg / L;
     if (lane == 0) nsp[w] = ns;
   }
-  __syncthreads();
+  lds_barrier();                                        // (LDS only: the partials stay in flight)
 
   float acc[MP_NB][4];
 #pragma unroll
@@ -374,32 +394,29 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[q][c] = 0.f;
   for (int c0 = c_lo; c0 < c_hi; c0 += MP_ROWS) {
-    // C of row c0 + lane: this wave's share of every sequence's splits, four splits of four sequences per round trip
-    // (wave-uniform bases and clamped split indices: one load instruction each, no branches)
-    float cv[MP_NB];
 #pragma unroll
-    for (int q = 0; q < MP_NB; ++q) cv[q] = 0.f;
-    const int cl = min(c0 + lane, rows - 1);
-    for (int s0 = wu * MP_SPLITS; s0 < nsplit; s0 += 4 * MP_SPLITS) {
-      float x[MP_NB][MP_SPLITS];
+    for (int q = 0; q < MP_NB; ++q) {
+      f32x4 cv = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < MP_NB; ++q)
+      for (int i = 0; i < R; ++i) {
+        const int sp = (i * 4 + wu) * MP_SPLITS + (lane >> 4);
+        const float wg = wgt[q][sp];
 #pragma unroll
-        for (int u = 0; u < MP_SPLITS; ++u)
-          x[q][u] = Cpart[((size_t)(min(b0 + q, B - 1) * nsplit + min(s0 + u, max(ns4[q] - 1, 0))) * H + h) * rows + cl];
+        for (int j = 0; j < 4; ++j) cv[j] = sp < ns4[q] ? fmaf(wg, x[i][q][j], cv[j]) : cv[j];
+      }
 #pragma unroll
-      for (int q = 0; q < MP_NB; ++q)
-#pragma unroll
-        for (int u = 0; u < MP_SPLITS; ++u) cv[q] = s0 + u < ns4[q] ? fmaf(wgt[q][s0 + u], x[q][u], cv[q]) : cv[q];
+      for (int j = 0; j < 4; ++j) {
+        cv[j] += __shfl_xor(cv[j], 16);
+        cv[j] += __shfl_xor(cv[j], 32);
+      }
+      if (lane < 16) *reinterpret_cast<f32x4*>(&red[w][q][idx * 4]) = cv;
     }
-#pragma unroll
-    for (int q = 0; q < MP_NB; ++q) red[w][q][lane] = cv[q];
-    __syncthreads();
+    lds_barrier();
     {
       const float sum = red[0][w][lane] + red[1][w][lane] + red[2][w][lane] + red[3][w][lane];
       cs[w][lane] = c0 + lane < c_hi ? (nsp[w] > 0 ? sum : NAN) : 0.f;      // (no row at all: 0 / 0)
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -408,8 +425,11 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[q][c] = fmaf(x, wv[i][c], acc[q][c]);
       }
-    if (c0 + MP_ROWS < c_hi) load_w(c0 + MP_ROWS);
-    __syncthreads();
+    if (c0 + MP_ROWS < c_hi) {
+      load_w(c0 + MP_ROWS);
+      load_parts(c0 + MP_ROWS);
+    }
+    lds_barrier();
   }
   // the four row groups of a wave, then the waves
 #pragma unroll
@@ -916,12 +936,21 @@ void launch_merge_project(int dtype, const float* Cpart, const float* mpart, con
                           float* outpart, int row_splits, int* counters, int B, hipStream_t st) {
   const int crows = ((rows + row_splits - 1) / row_splits + MP_ROWS - 1) / MP_ROWS * MP_ROWS;
   dim3 grid(H * ((d_k + MP_COLS - 1) / MP_COLS), row_splits, (B + MP_NB - 1) / MP_NB);
-  if (dtype == DT_BF16)
-    hipLaunchKernelGGL(merge_project_kernel<BF16>, grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, (int)own_splits, seq_lens, T,
-                       (const uint16_t*)W, rows, e, H, d_k, out, outpart, row_splits, crows, counters, B);
-  else
-    hipLaunchKernelGGL(merge_project_kernel<F32>, grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, (int)own_splits, seq_lens, T,
-                       (const float*)W, rows, e, H, d_k, out, outpart, row_splits, crows, counters, B);
+  auto go = [&](auto et, auto r) {
+    using ET = decltype(et);
+    hipLaunchKernelGGL((merge_project_kernel<ET, decltype(r)::value>), grid, dim3(256), 0, st, Cpart, mpart, lpart, nsplit, (int)own_splits,
+                       seq_lens, T, (const typename ET::elem*)W, rows, e, H, d_k, out, outpart, row_splits, crows, counters, B);
+  };
+  auto with_rounds = [&](auto et) {
+    const int rounds = (nsplit + 4 * MP_SPLITS - 1) / (4 * MP_SPLITS);
+    static_assert(MERGE_MAX_SPLITS <= 16 * MP_SPLITS, "four rounds");
+    if (rounds <= 1) go(et, std::integral_constant<int, 1>{});
+    else if (rounds == 2) go(et, std::integral_constant<int, 2>{});
+    else if (rounds == 3) go(et, std::integral_constant<int, 3>{});
+    else go(et, std::integral_constant<int, 4>{});
+  };
+  if (dtype == DT_BF16) with_rounds(BF16{});
+  else with_rounds(F32{});
 }
 
 void launch_project(int dtype, const float* x, const void* W, int rows, int e, float* out, int B, hipStream_t st) {
