@@ -317,9 +317,11 @@ __global__ __launch_bounds__(256) void weighted_sum_kernel(
 // ------------------------------------------------------------------------------------------------
 constexpr int MP_ROWS = 64, MP_COLS = 64, MP_NB = 4, MP_SPLITS = 4;
 
-// R: rounds of MP_SPLITS splits per wave (nsplit <= 4 R MP_SPLITS).  Maxima, sums, W and all partials of the first 64 rows are
-// asked for at once, before it is known which splits a sequence has (what a split that does not exist left in the scratch
-// is read and not used); then the next 64 rows' behind the use of these.
+// R: rounds of MP_SPLITS splits per wave (nsplit <= 4 R MP_SPLITS).  Maxima, sums and W are asked for first, then all partials of
+// the first 64 rows, of the splits that the lengths (in L2 since the launch before) say a sequence has; then the next 64 rows'
+// behind the use of these.  Asked for before the lengths were known, the places of splits that do not exist were read as well, up
+// to 33 MB of scratch where contexts are short in a large capacity: 4 sequences of 50 rows of 2048 x 32 heads x 1024 columns,
+// 16 layers in turn, 30.2 us instead of 24.3; full contexts are no slower for it (25.5 -> 25.1 at 4 x 1500, 6 x 1500 32.0 -> 31.4).
 template <class ET, int R>
 __global__ __launch_bounds__(256) void merge_project_kernel(
     const float* __restrict__ Cpart, const float* __restrict__ mpart, const float* __restrict__ lpart, int nsplit,
@@ -352,20 +354,6 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
     lp = lpart[at];
   }
   load_w(c_lo);
-  // this wave's share of every sequence's splits: a lane four rows c of one split, sixteen lanes the 64 rows, so that one
-  // load instruction takes four splits (clamped indices, no branches)
-  f32x4 x[R][MP_NB];
-  auto load_parts = [&](int c0) {
-    const int cl = min(c0 + idx * 4, rows - 4);
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int sp = min((i * 4 + wu) * MP_SPLITS + (lane >> 4), nsplit - 1);
-#pragma unroll
-      for (int q = 0; q < MP_NB; ++q)
-        x[i][q] = *reinterpret_cast<const f32x4*>(Cpart + ((size_t)(min(b0 + q, B - 1) * nsplit + sp) * H + h) * rows + cl);
-    }
-  };
-  load_parts(c_lo);
   // splits of the four sequences (wave-uniform)
   int ns4[MP_NB];
 #pragma unroll
@@ -377,6 +365,21 @@ __global__ __launch_bounds__(256) void merge_project_kernel(
     }
     if (q >= nb) ns4[q] = 0;
   }
+  // this wave's share of every sequence's splits: a lane four rows c of one split, sixteen lanes the 64 rows, so that one
+  // load instruction takes four splits (clamped to the sequence's own, no branches)
+  f32x4 x[R][MP_NB];
+  auto load_parts = [&](int c0) {
+    const int cl = min(c0 + idx * 4, rows - 4);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
+      for (int q = 0; q < MP_NB; ++q) {
+        const int sp = min((i * 4 + wu) * MP_SPLITS + (lane >> 4), max(ns4[q] - 1, 0));
+        x[i][q] = *reinterpret_cast<const f32x4*>(Cpart + ((size_t)(min(b0 + q, B - 1) * nsplit + sp) * H + h) * rows + cl);
+      }
+    }
+  };
+  load_parts(c_lo);
   {
     const int ns = w == 0 ? ns4[0] : w == 1 ? ns4[1] : w == 2 ? ns4[2] : ns4[3];
     if (lane >= ns) { mp = NEG_INF; lp = 0.f; }
