@@ -1672,15 +1672,25 @@ int proj_rows_per_split(int rows, int csw) {
   return ((rows + csw - 1) / csw + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
 }
 
-// Whether a launch's loads of W are nontemporal: a matrix of at least 16 MB that one batch chunk reads, in a call that reads
-// `call_bytes` >= 96 MB (weights and temporally read caches).  Of such calls the memory-side cache (256 MB) keeps nothing until
-// the same layer comes round again, and the loads are faster where they ask for no room in it: block of 16 sequences x
-// 4096 columns (134 MB of weights) 115.7 -> 110.1 us, vanilla block 84.1 -> 80.9, X-cache step of 134 MB 71.6 -> 69.5, 40 heads
-// x 5120 columns (119 MB) 57.7 -> 55.3.  Smaller calls may find W there from the time before: 3072 columns (75 MB) 49.2 -> 50.1
-// and 69.7 -> 72.2 (vanilla), X-cache step of 68 MB 39.5 -> 41.2 (in a loop over more layers than that cache holds they gain
-// 1-3 % as well).  Smaller matrices: 1280 columns 51.7 -> 54.2.  Several batch chunks share W in L2: 72.5 -> 73.4 (24 sequences).
-bool read_once(size_t call_bytes, long rows, long e, int chunks) {
-  return chunks == 1 && rows * e * 2 >= (16L << 20) && call_bytes >= ((size_t)96 << 20);
+// Whether a call's loads of its weight matrices are nontemporal (where one batch chunk reads a matrix): weights of at least 64 MB,
+// in a call that is known to read 96 MB of what the memory-side cache (256 MB) would keep: its weights, and an X-cache that is
+// read once.  Three such layers fill that cache, so a model's next token finds nothing of W there, and the loads are faster where
+// they ask for no room in it.  us with temporal -> nontemporal loads, layers of together at least 0.9 GB in turn; three
+// layers; one layer alone, whose weights the cache does keep and which is slower for it:
+//   block, 16 sequences x 4096 columns, rotary  114.1 -> 111.3   113.6 -> 107.6   105.2 -> 106.5
+//   block, 1 x 4096                              55.7 -> 52.7     55.0 -> 50.9     49.8 -> 51.9
+//   block, 1 x 3584                              50.4 -> 47.8     49.4 -> 47.7     45.9 -> 46.9
+//   vanilla block, 4 x 4096                      84.3 -> 80.5     89.0 -> 85.6     85.4 -> 86.7
+//   64 heads x 8192 columns, 1 x 400 rows        45.7 -> 43.4     45.8 -> 43.5     38.5 -> 42.9   (2 x 4000: 98.9 -> 98.0)
+//   X-cache, 128 heads, 8 x 4096 x 1024          71.4 -> 70.3     71.2 -> 69.4     66.0 -> 67.4   (16 x 4096: 103.1 -> 102.7)
+// Below 96 MB three layers fit (block of 2 x 3072 columns, 75 MB of weights: 50.9 -> 49.6, but 47.9 -> 49.1 and 47.4 -> 48.8).
+// Fewer weights gain nothing (X-cache, 80 heads, 8 x 4096 x 1280, 52 MB of weights: 81.9 -> 81.9, 81.6 -> 81.4, 71.5 -> 74.8), nor
+// do several batch chunks, which share W in L2 (24 sequences x 4096: 72.5 -> 73.4).  Rows that a call may have but need not use do
+// not count (X-cache, 64 heads, 400 of 4096 rows in use: 38.3 -> 39.1, 35.4 -> 36.2, 35.0 -> 39.9), nor do caches that are
+// read twice, the second time from the memory-side cache (40 heads x 5120 columns, 4 ragged sequences of 3000..6000 rows: 121.3
+// -> 129.2 with three layers or more; 2 ragged of 2500..4001 rows 58.2 -> 58.0).
+bool read_once(size_t weight_bytes, size_t cache_bytes) {
+  return weight_bytes >= ((size_t)64 << 20) && weight_bytes + cache_bytes >= ((size_t)96 << 20);
 }
 
 template <bool DENSE>
@@ -1688,7 +1698,7 @@ static void launch_product(const ProjArgs& a, int nbt, int units_per_chunk, hipS
   const int chunks = (a.B + 16 * nbt - 1) / (16 * nbt);
   dim3 grid(8u * a.csw * (((unsigned)units_per_chunk * chunks + 7) / 8)), block(512);
   auto go = [&](auto nb) {
-    if (read_once(a.call_bytes, a.rows, a.e, chunks)) hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, true>), grid, block, 0, st, a);
+    if (a.once && chunks == 1) hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, true>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, false>), grid, block, 0, st, a);
   };
   if (nbt == 1) go(std::integral_constant<int, 1>{});

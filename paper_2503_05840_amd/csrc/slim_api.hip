@@ -423,7 +423,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.out = (float*)out; pa.outpart = (float*)(ws + p.off_outpart); pa.counters = ctrl;
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = lid; pa.err_before = 1; pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-    pa.call_bytes = 2 * (size_t)d * d;                 // (the stream kernel's loads of K are nontemporal)
+    pa.once = read_once(2 * (size_t)d * d, 0);
     pa.NG = g.NG; pa.nsplit = 0; pa.mode = 0; pa.mscale = 1.0f; pa.csw = p.csw; pa.xcd_local = xcd_local;
     pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     if (const int shares = fused_by_sequence(g, B, lens != nullptr)) {
@@ -497,7 +497,7 @@ int decode_core(const void* q, const void* Kcache, const void* W_KV, void* out, 
     pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
     pa.nsplit = wide ? p.nsplit_k : p.nsplit; pa.mode = 1;
     pa.mscale = wide ? 1.0f : 1.4426950408889634f;     // (the plain kernels' maxima are natural logarithms)
-    pa.csw = p.csw; pa.call_bytes = 2 * ((size_t)B * T + d) * d; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+    pa.csw = p.csw; pa.once = read_once(2 * (size_t)d * d, 0); pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
     pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = block_id ? block_id : next_launch_id(); pa.err_before = block_id != 0;
     launch_project_mfma(pa, st);
@@ -614,12 +614,13 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     // MFMA path: q~, scores (log2 domain), weighted sum per context split, merge + projection
     int* ctrl = (int*)(ws + p.off_ctrl);
     const int csw = proj_row_splits(H, d_model, e, B);
-    const size_t call_bytes = 2 * ((size_t)B * T + 2 * (size_t)e) * d_model;
-    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, call_bytes, ctrl,
+    const bool one_pass = p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT;
+    const bool once = xcache_read_once(B, T, d_model, e, lens != nullptr, one_pass);
+    launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, once, ctrl,
                     csw > 1 ? PROJ_CTRL_INTS : 0, st);
     tm.mark();
     int nsplit = p.nsplit_x;
-    if (p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT) {
+    if (one_pass) {
       // d_model 512..1280: scores, numerators and weighted sum in one pass over X
       nsplit = p.nsplit_xf;
       launch_xfused(qt, X, xb, lens, T, H, d_model, nsplit, Cpart, mpart, lpart, B, st);
@@ -636,7 +637,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = next_launch_id(); pa.seq_lens = lens;
     pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d_model; pa.e = e;
     pa.NG = 0; pa.nsplit = nsplit; pa.mode = 1; pa.mscale = 1.0f;
-    pa.csw = csw; pa.call_bytes = call_bytes; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+    pa.csw = csw; pa.once = once; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
     pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
     launch_project_mfma(pa, st);
     tm.mark();
@@ -727,7 +728,7 @@ int attention_block(bool slim_path, const BlockCall& c, int B, int H, int T, int
   ProjArgs pa{};
   pa.Cpart = (const float*)c.x; pa.outpart = (float*)(ws + bb.off_dpart); pa.counters = ctrl;
   pa.seq_lens = lens; pa.B = B; pa.T = T; pa.H = H; pa.d_k = d_k; pa.rows = d; pa.e = d;
-  pa.nsplit = 1; pa.mscale = 1.0f; pa.call_bytes = 4 * 2 * (size_t)d * d; pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
+  pa.nsplit = 1; pa.mscale = 1.0f; pa.once = read_once(4 * 2 * (size_t)d * d, 0); pa.xcd_local = xcd_round_robin_known() && !flag_of(o, SLIM_VARIANT_VIA_MEMORY);
     pa.apart = flag_of(o, SLIM_VARIANT_APART); pa.places = unit_words(ctrl, false);
   const unsigned id = fast ? next_launch_id() : 0;     // one for all launches of the call
   pa.err = ctrl + CTRL_INTS - 1; pa.launch_id = id;

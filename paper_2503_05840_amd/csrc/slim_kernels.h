@@ -116,7 +116,7 @@ struct ProjArgs {
   int B, T, H, d_k, rows, e;
   int NG, nsplit, mode;               // mode 0: partials laid out by the stream kernel; 1: [b][nsplit]
   float mscale;                       // 1 for log2-domain maxima, log2(e) for natural-log ones
-  size_t call_bytes;                  // weights and caches the whole call reads with temporal loads (read_once)
+  bool once;                          // nontemporal loads of W where one batch chunk reads it (read_once)
   int csw, crows;                     // row splits of W across workgroups, rows per split
   // Workgroups i and j of a launch share an XCD where i % 8 == j % 8 (checked at set-up, and by the workgroups of a unit on
   // every launch): the row splits of a head meet in its L2.  0: not known, they meet at the memory side.
@@ -172,7 +172,7 @@ int proj_batch_tiles(int B, int rows, int e, int H);
 int proj_splits_per_unit(int units);
 int proj_row_splits(int H, int rows, int e, int B);
 int proj_part_row(int H, int d_k);
-bool read_once(size_t call_bytes, long rows, long e, int chunks);
+bool read_once(size_t weight_bytes, size_t cache_bytes);
 int proj_rows_per_split(int rows, int csw);
 void launch_project_mfma(ProjArgs a, hipStream_t st);
 int dense_row_splits(int H, int nmat, int rows, int e, int B);
@@ -182,10 +182,11 @@ void launch_dense_mfma(ProjArgs a, hipStream_t st);
 bool xcache_fast_ok(int dtype, int H, int d_model, int d_k);
 int xcache_splits(int B, int H, int T, int d_model);
 void launch_xq_tilde(const float* q, const void* Wk, float* qt, int B, int H, int d_k, int d_model, int e,
-                     float scale, size_t call_bytes, int* counters, int ncounters, hipStream_t st);
+                     float scale, bool once, int* counters, int ncounters, hipStream_t st);
 void launch_xscores(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
                     int d_model, float* S, int B, hipStream_t st);
 bool xfused_ok(int d_model);                 // one pass over X instead of xscores + xweighted
+bool xcache_read_once(int B, int T, int d_model, int e, bool ragged, bool one_pass);   // (read_once)
 int xfused_splits(int B, int H, int T, int d_model);
 int xfused_most_splits(int B, int H, int T, int d_model);    // bound of the splits at T and every shorter context
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
