@@ -1697,9 +1697,14 @@ template <bool DENSE>
 static void launch_product(const ProjArgs& a, int nbt, int units_per_chunk, hipStream_t st) {
   const int chunks = (a.B + 16 * nbt - 1) / (16 * nbt);
   dim3 grid(8u * a.csw * (((unsigned)units_per_chunk * chunks + 7) / 8)), block(512);
+  auto launch = [&](auto nb, auto once) {
+    hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, decltype(once)::value>), grid, block, 0, st, a);
+  };
   auto go = [&](auto nb) {
-    if (a.once && chunks == 1) hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, false>), grid, block, 0, st, a);
+    // (a block's matrices are at most 4096 columns wide: more than one batch tile always come in more than one chunk)
+    if constexpr (!DENSE || decltype(nb)::value == 1)
+      if (a.once && chunks == 1) return launch(nb, std::true_type{});
+    launch(nb, std::false_type{});
   };
   if (nbt == 1) go(std::integral_constant<int, 1>{});
   else if (nbt == 2) go(std::integral_constant<int, 2>{});

@@ -2,7 +2,7 @@
 it pays, so never rows that a ragged batch may leave unused, and no cache that is read twice."""
 import pytest
 
-from launch_rules import read_once, xcache_read_once
+from launch_rules import batch_chunks, batch_tiles, read_once, xcache_read_once
 
 
 @pytest.mark.parametrize("B,T,H,d,ragged,one_pass,want", [
@@ -25,3 +25,14 @@ def test_xcache(B, T, H, d, ragged, one_pass, want):
 ])
 def test_weights_alone(matrices, d, want):
     assert read_once(matrices * 2 * d * d, 0) == want
+
+
+def test_blocks_of_several_batch_tiles_come_in_several_chunks():
+    """(the reason why a block's products have nontemporal loads with one batch tile only)"""
+    for H in range(1, 33):                                             # what the block's fast path takes: 32 heads, 4096 columns
+        for d_k in (8, 16, 32, 64, 72, 80, 96, 104, 112, 120, 128):
+            d = H * d_k
+            if d <= 4096 and read_once(4 * 2 * d * d, 0):
+                for B in range(1, 1025):
+                    for units in (H, 2 * H, 3 * H):
+                        assert batch_tiles(B, d, d, units) == 1 or batch_chunks(B, d, d, units) > 1
