@@ -1649,13 +1649,6 @@ int proj_batch_tiles(int B, int rows, int e, int H) {
   return B <= 32 ? 2 : 4;
 }
 
-// Row splits of `units` (head, batch chunk) pairs: a unit's workgroups share an XCD, which holds 32 of them at once
-// (one per compute unit: a single round).
-int proj_splits_per_unit(int units) {
-  const int c = 32 / ((units + 7) / 8);
-  return c < 1 ? 1 : c;
-}
-
 int proj_row_splits(int H, int rows, int e, int B) {
   // one 32-row tile of W per wave (8 waves = 256 rows per workgroup) unless that makes more
   // workgroups than CUs

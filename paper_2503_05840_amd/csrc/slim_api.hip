@@ -46,6 +46,7 @@ unsigned long long* unit_words(int* ctrl, bool second) {
 // flags from the middle on, and in its last two ints the id of the latest fast-path call and the error word (= that id when a
 // wait ran out or workgroups could not meet).
 constexpr int CTRL_INTS = 4096;
+static_assert(PROJ_FLAGS_AT + 2 * PROJ_MAX_FLAGS <= CTRL_INTS / 2, "a block's flags end before the stream kernel's begin");
 
 int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 

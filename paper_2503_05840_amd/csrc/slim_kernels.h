@@ -98,6 +98,22 @@ constexpr int PROJ_MAX_FLAGS = 256;
 constexpr int PROJ_FLAGS_AT = 1024;                            // int offset in the control block
 static_assert(PROJ_FLAGS_AT >= PROJ_BLOCK_INTS, "the flags are not among the words that are cleared");
 
+// Row splits of `units` (head, batch chunk) pairs: a unit's workgroups share an XCD, which holds 32 of them at once
+// (one per compute unit: a single round).
+constexpr int proj_splits_per_unit(int units) {
+  const int c = 32 / ((units + 7) / 8);
+  return c < 1 ? 1 : c;
+}
+// Split units have a control word each, their workgroups a flag each, and a wave looks at a unit's flags a lane each.
+constexpr bool proj_splits_fit() {
+  for (int units = 1; units <= 16 * PROJ_MAX_UNITS; ++units) {
+    const int c = proj_splits_per_unit(units);
+    if (c > 1 && (units > PROJ_MAX_UNITS || units * c > PROJ_MAX_FLAGS || c > 64)) return false;
+  }
+  return true;
+}
+static_assert(proj_splits_fit(), "control words and flags of a projection whose rows of W are split");
+
 struct FusedGeom {
   int lph, lphp, hpu;   // active lanes per head (d_k/8), lanes reserved per head, heads per unit
   int G, NG, gpx;       // column units per group, groups, groups per XCD (0 = not packed)
@@ -169,7 +185,6 @@ bool probe_xcd_round_robin(unsigned* dev_buf, hipStream_t st);
 int fused_blocks_per_cu(const FusedGeom& g, bool rope);
 void launch_fused_stream(const FusedGeom& g, const FusedArgs& a, hipStream_t st);
 int proj_batch_tiles(int B, int rows, int e, int H);
-int proj_splits_per_unit(int units);
 int proj_row_splits(int H, int rows, int e, int B);
 int proj_part_row(int H, int d_k);
 bool read_once(size_t weight_bytes, size_t cache_bytes);
