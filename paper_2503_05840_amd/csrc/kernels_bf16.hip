@@ -633,8 +633,8 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (by_flags) {
-    // Arrival flags that carry the launch's id need no launch that clears them (4.6 us; a round trip to L2 more here than
-    // counting).  A workgroup stores its flag, waits for that, and looks at all of the unit's: the last to store sees them
+    // Arrival flags that carry the launch's id need no launch that clears them; this one takes longer by a round trip to L2 more
+    // than counting costs, and the call gains 0.2 to 1.3 us.  A workgroup stores its flag, waits for that, and looks at all of the unit's: the last to store sees them
     // all.  Two that see them all both finish, with the same values.  The flags of where they run were stored before
     // anything else: seen by the last as well.
     if (w == 0) {

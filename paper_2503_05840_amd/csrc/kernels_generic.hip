@@ -311,9 +311,10 @@ __global__ __launch_bounds__(256) void weighted_sum_kernel(
 // the last workgroup to arrive (as in the MFMA projection: write-through stores, agent-scope loads).
 // Bound by the length of this chain, not by bytes: the row splits are what fills the chip (one kernel that merged
 // to memory and one with a workgroup per 64 columns took 7.4 + 40.3 us for 4 sequences x 16 heads x 1024 rows with
-// up to 12 splits each; this one 10.5 us with up to 47).  Everything that can be is asked for in one round trip, 16 bytes a
+// up to 12 splits each; this one 10.2 us with up to 47).  Everything that can be is asked for in one round trip, 16 bytes a
 // lane: with a trip for the maxima and sums first and then one per 16 splits, 4 bytes a lane, it was 13.3 us (the step 26.4
-// -> 23.6; 1 x 100 rows x 256 columns 12.5 -> 12.1, 1 x 3000 x 1024 25.7 -> 23.7); at once but 4 bytes a lane 13.8.
+// -> 23.4, 1 x 3000 x 1024 25.7 -> 23.7; with a few splits the same, 12.2 at 1 x 100 rows x 256 columns); at once but 4 bytes a
+// lane 13.8.
 // ------------------------------------------------------------------------------------------------
 constexpr int MP_ROWS = 64, MP_COLS = 64, MP_NB = 4, MP_SPLITS = 4;
 

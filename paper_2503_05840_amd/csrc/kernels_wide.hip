@@ -10,11 +10,12 @@ namespace slim {
 namespace {
 
 // A wave takes 16 rows of 64 / LPHP neighbouring heads (LPHP lanes per head, 8 columns each: up to 1 KB of
-// consecutive bytes per row), all 16 loads in flight at once, sums each row over the head's lanes with DPP adds and
+// consecutive bytes per row), all 16 loads in flight at once (with rotary keys as many as the registers beside the table's
+// entries allow), sums each row over the head's lanes with DPP adds and
 // leaves with consecutive rows of a head on the head's lanes.  Bound by HBM: one load, 16 multiply-adds and the
 // reduction per 16 bytes and lane are a fifth of what the vector ALU does in the time the bytes take.  (One wave per
 // row with per-head sums through LDS, as the plain kernel does it: 67 us for 6503 rows of 5120 columns, 67 MB; this one
-// 15.4 us, 4.3 TB/s with the launch.)
+// 16.3 us, numerators included: 4.1 TB/s with the launch.)
 constexpr int KS_ROWS = 16, KS_WAVES = 4, KS_BLOCK = KS_ROWS * KS_WAVES;
 
 // NUM: leaves with numerators p = 2^(s - ref) of its 64 rows, ref = the block's largest score of the head rounded up to a
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(KS_WAVES * 64) void kscores_kernel(const float* __r
 // of the time).  All waves weigh against one reference, the largest of the split's blocks, so nothing is rescaled on the
 // way: a tile's numerators are multiplied by 2^(its block's reference - that one).
 // What bounds it: the trip of a tile of K, which comes from the memory-side cache, one tile ahead at three head tiles (two do
-// not fit the registers): 24.5 us at 40 heads x 5120 columns, 6503 rows (67 MB), where taking the numerators in every
+// not fit the registers): 24.6 us at 40 heads x 5120 columns, 6503 rows (67 MB), where taking the numerators in every
 // workgroup, 130 vector operations and 8 exponentials per tile and head tile, took 27.8.  The whole step 60.6 -> 57.7 us
 // there, 140.6 -> 128.1 at 12 ragged sequences of 300..3000 rows, 163.3 -> 156.0 at 4 x 6000 rows x 48 heads x 128; with
 // contexts of a few hundred rows it is the same (27.7 and 27.6 us at 2 x 250..500 x 40 x 96).

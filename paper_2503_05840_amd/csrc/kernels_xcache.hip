@@ -291,9 +291,10 @@ constexpr float XW_SLACK = 6.0f;
 
 // NT: head tiles of 16 per workgroup.  FULL: the weights enter the matrix product as three bf16 terms (8 + 8 + 8
 // bits: exactly the fp32 value) and their sum is taken in fp32 on the vector ALU -- K-caches whose weights are fp32, where
-// the scratch has no room for what kweighted_kernel (kernels_wide.hip) needs; otherwise rounded to bf16 once.  (FULL is 3 MFMAs where there was one; the matrix cores are idle
-// most of the time here.)  At 40 heads x 5120 columns, 6503 rows: 28.0 us, K coming from the memory-side cache, where
-// the vector-ALU kernel took 99.8; the whole step 197.8 -> 59.8 us.
+// the scratch has no room for what kweighted_kernel (kernels_wide.hip) needs (heads of 8 columns with 321 to 511 rows, say, or
+// 1100 sequences of 4300 rows and more x 8 heads of 64 columns); otherwise rounded to bf16 once.  (FULL is 3 MFMAs where there was one; the
+// matrix cores are idle most of the time here.)  At 8 sequences of 500 rows, 48 heads x 8 columns: 10.9 us, where the vector-ALU
+// kernel takes 58.4.
 template <int NT, bool FULL>
 __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const uint16_t* X, long x_bstride,
                                                         const int32_t* seq_lens, int T, int B, int H, int dm, int nsplit,

@@ -216,7 +216,7 @@ inline unsigned unit_grid(int nunits, int ninner, int colocate) {
   return colocate ? 8u * (unsigned)ninner * (unsigned)((nunits + 7) / 8) : (unsigned)nunits * (unsigned)ninner;
 }
 
-// ---- bf16 K-caches the stream kernel does not take (kernels_wide.hip; weighted sum in kernels_xcache.hip) ----
+// ---- bf16 K-caches the stream kernel does not take (kernels_wide.hip; launch_xweighted_full in kernels_xcache.hip) ----
 // [B][H][T padded to 32]: with `blocks` (kscores_block_floats) softmax numerators against a reference per head and 64
 // rows, else scores in the log2 domain (scale_log2 = log2(e) / sqrt(d_k)); then per split the weighted sum with fp32
 // weights, partials laid out [b][nsplit], maxima in the log2 domain.
