@@ -334,7 +334,8 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   unsigned long long places = 0;
   // With a.flags (an attention block's first launch: nothing has cleared any words for it) as a flag instead.
   const bool by_flags = DENSE && a.flags != nullptr;
-  const int unit_at = (bz * nhx + hx) * a.csw, flag_id = (int)(a.launch_id << 3), place_flag = flag_id | (int)((my_xcc() ^ (a.apart ? cs & 1 : 0)));
+  const int unit_at = (bz * nhx + hx) * a.csw, flag_id = (int)(a.launch_id << 3);
+  const int place_flag = DENSE ? flag_id | (int)((my_xcc() ^ (a.apart ? cs & 1 : 0))) : 0;
   if (by_flags && xl && a.csw > 1 && tid == 0) st_result(a.flags + PROJ_MAX_FLAGS + unit_at + cs, place_flag, true);
   else if (!COH && xl && a.csw > 1 && tid == 0)
     places = __hip_atomic_fetch_add(a.places + (bz * nhx + hx), my_place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + my_place;

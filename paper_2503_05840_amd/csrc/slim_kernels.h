@@ -120,19 +120,22 @@ struct FusedGeom {
   int NT, NP, grid, nparts;   // MFMA head tiles, waves per workgroup
 };
 
+// The order of the fields decides which of them a kernel loads together, so has to hold together: with another eight bytes before
+// csw the single launch of up to 16 heads kept ~390 scalars in lanes of vector registers and loaded arguments, which lie in
+// host memory, once more on its way to the result; as it is, 86.  1 x 1500 rows x 8 heads x 64 22.4 -> 19.4 us, 1 x 1500 x 16 x 128 20.4 -> 18.1,
+// 8 ragged x 2000 x 16 x 64 23.7 -> 22.6; 32 heads the same within 0.5 %, but for 17..32 heads of 64 columns: 21.9 -> 22.2 at 1 x 700.
 struct ProjArgs {
+  int* flags;                         // dense products, nullable: [2][PROJ_MAX_FLAGS], used instead of counters and places
   const float* Cpart; const float* mpart; const float* lpart;
   const uint16_t* W;                  // [rows][e] bf16
   float* out; float* outpart;         // [B][e], [csw][B][proj_part_row]
   int* counters; unsigned long long* places;       // [PROJ_MAX_UNITS] each
-  int* flags;                         // dense products, nullable: [2][PROJ_MAX_FLAGS], used instead of these
   int* err; unsigned launch_id;       // err: word raised (= launch_id) when the result cannot be had; err[-1]: launch it speaks of
   int err_before;                     // an earlier launch of this call may have raised err: then the result is NaN
   const int32_t* seq_lens;
   int B, T, H, d_k, rows, e;
   int NG, nsplit, mode;               // mode 0: partials laid out by the stream kernel; 1: [b][nsplit]
   float mscale;                       // 1 for log2-domain maxima, log2(e) for natural-log ones
-  bool once;                          // nontemporal loads of W where one batch chunk reads it (read_once)
   int csw, crows;                     // row splits of W across workgroups, rows per split
   // Workgroups i and j of a launch share an XCD where i % 8 == j % 8 (checked at set-up, and by the workgroups of a unit on
   // every launch): the row splits of a head meet in its L2.  0: not known, they meet at the memory side.
@@ -147,6 +150,7 @@ struct ProjArgs {
   uint16_t* Kc; uint16_t* Vc; long c_bstride;
   int k_banded;                       // Kc is a banded cache (see FusedArgs::k_banded)
   const float* rope; int rotate_k;
+  bool once;                          // nontemporal loads of W where one batch chunk reads it (read_once)
 };
 
 struct FusedArgs {
