@@ -10,20 +10,24 @@ namespace slim {
 namespace {
 
 // A wave takes 16 rows of 64 / LPHP neighbouring heads (LPHP lanes per head, 8 columns each: up to 1 KB of
-// consecutive bytes per row), all 16 loads in flight at once (with rotary keys as many as the registers beside the table's
-// entries allow), sums each row over the head's lanes with DPP adds and
+// consecutive bytes per row), all 16 loads in flight at once, sums each row over the head's lanes with DPP adds and
 // leaves with consecutive rows of a head on the head's lanes.  Bound by HBM: one load, 16 multiply-adds and the
 // reduction per 16 bytes and lane are a fifth of what the vector ALU does in the time the bytes take.  (One wave per
 // row with per-head sums through LDS, as the plain kernel does it: 67 us for 6503 rows of 5120 columns, 67 MB; this one
 // 16.3 us, numerators included: 4.1 TB/s with the launch.)
+// With rotary keys the table's entries of four rows travel beside the 16 rows, and where numerators follow four waves per SIMD are
+// asked for (three with heads of 8 columns, 133 registers): left to itself the compiler takes 62 to 67 registers for eight, the rows
+// alone being 64, and loads a few rows at a time (the step with 2 x 3000 rows x 40 heads x 64: 37.3 us, with these registers
+// 34.9; 1 x 700 x 40 x 128 33.8 and 31.1; before there were numerators 35.4 and 31.4).
 constexpr int KS_ROWS = 16, KS_WAVES = 4, KS_BLOCK = KS_ROWS * KS_WAVES;
+constexpr int ks_waves(int lphp, bool fixed, int otherwise) { return fixed ? (lphp == 1 ? 3 : 4) : otherwise; }
 
 // NUM: leaves with numerators p = 2^(s - ref) of its 64 rows, ref = the block's largest score of the head rounded up to a
 // whole number, and with ref and the sum of p per (block, head): the weighted sum's workgroups, one per 128 columns of K,
 // would each take every exponential again (40 times at 5120 columns).  A whole ref makes the weighted sum's change to a
 // common one a change of exponent.  Rows past the end up to the next multiple of 32 get weight 0.  Without NUM: the scores.
 template <int LPHP, bool ROPE, bool NUM>
-__global__ __launch_bounds__(KS_WAVES * 64) void kscores_kernel(const float* __restrict__ q, const uint16_t* __restrict__ K,
+__global__ __launch_bounds__(KS_WAVES * 64) __attribute__((amdgpu_waves_per_eu(ks_waves(LPHP, ROPE && NUM, 1), ks_waves(LPHP, ROPE && NUM, 8)))) void kscores_kernel(const float* __restrict__ q, const uint16_t* __restrict__ K,
                                                                 long k_bstride, const int32_t* __restrict__ seq_lens, int T,
                                                                 int H, int d, int d_k, float scale_log2,
                                                                 const float* __restrict__ rope, float* __restrict__ S,
