@@ -526,274 +526,6 @@ __global__ __launch_bounds__(512) void xweighted_kernel(const float* S, const ui
 }
 
 
-// ------------------------------------------------------------------------------------------------
-// One pass over X for 512 <= d_model <= 1280: scores, softmax numerators and the weighted sum of one
-// (sequence, context split, group of heads) in one kernel, so X leaves memory once per head group,
-// no score matrix is written, and the exponentials of a row are computed once instead of once per
-// column block.  The accumulators (32 heads x d_model fp32 = 128 KB at 1024 columns) stay in the
-// workgroup's registers for its whole row range, which is why the COLUMNS are split over the waves
-// (wave w owns columns [128 w, 128 w + 128): its slice of q~ as resident B operands, its 32 x 128 slice
-// of every row tile, its accumulator block) and the waves meet twice per 32-row tile in LDS --
-// the same exchange of numerators between column owners as in the K-cache stream kernel, but inside
-// one workgroup, with barriers:
-//   1. park the slice in LDS (row-padded), transpose it in registers for step 3, request the next tile,
-//      read the slice back in A-operand order, partial scores of the group's heads over the wave's
-//      columns on MFMA (query hi + lo), partials to LDS;  -- barrier --
-//   2. the first eight waves (four, if there are fewer than eight) sum the partials of their heads over the column
-//      owners (lane = row), keep those heads' running reference and sum of weights, write bf16 numerators and, when a
-//      reference moved, the rescale factors;  -- barrier --
-//   3. every wave rescales if a reference moved and adds P^T X on MFMA.
-// Rows are not split over the waves, so nothing is merged at the end.  A one-dimensional launch: the head
-// groups of a (sequence, context split) read the same rows and are mapped to one XCD (unit_of_workgroup).
-// Shapes: 4, 6 or 8 waves x 16 or 32 heads for d_model <= 512, 768, 1024 and 10 waves x 16 heads beyond (three waves
-// on two of the four SIMDs, hence 168 registers, which hold half the accumulators and the hi halves of q~; the lo
-// halves wait in LDS).  (Four waves that score tile k + 1 beside four that sum tile k, both MFMA phases in one barrier
-// interval: 51 us instead of 46 at 8 sequences x 128 heads x 4096 rows x 1024 columns -- the tile then crosses LDS twice
-// and its 64 KB through the L1, at 64 bytes a cycle, stand between the barriers.)
-// ------------------------------------------------------------------------------------------------
-constexpr int XF_PITCH = 272;            // bytes per parked row: 256 + 16 of padding
-constexpr int XF_RED_HS = 36;            // floats per head row of a wave's partial scores (32 rows + padding that keeps 16-byte stores)
-constexpr int XF_P_HS = 40;              // bf16 per head row of the numerators (32 rows + padding)
-
-// NW waves, each the owner of 128 columns (d_model <= 128 NW); NT head tiles of 16 per group.
-// Workgroups a compute unit holds at once: two waves of 256 registers per SIMD.  (Two of 6 waves would need 168: spills.)
-constexpr int xfused_per_cu(int NW) { return NW == 4 ? 2 : 1; }
-
-template <int NW, int NT>
-__global__ __launch_bounds__(NW * 64, 2) void xfused_kernel(const uint16_t* qt, const uint16_t* X, long x_bstride,
-                                                         const int32_t* seq_lens, int T, int B, int H, int dm, int nsplit,
-                                                         float* Cpart, float* mpart, float* lpart, int colocate) {
-  constexpr int HG = 16 * NT;                          // heads per group
-  constexpr int OWN = NW >= 8 ? 8 : 4;                 // waves that make the numerators
-  constexpr int HPL = HG / (2 * OWN);                  // heads per lane of an owner wave (lane = (row, half): 2 x 32 lanes)
-  static_assert(NT == 1 || NT == 2, "registers");
-  __shared__ __align__(16) unsigned char slot[NW][32 * XF_PITCH];
-  __shared__ __align__(16) float red[NW][HG][XF_RED_HS];
-  __shared__ __align__(16) uint16_t P_s[HG][XF_P_HS];
-  __shared__ float alpha_s[HG];
-  // With three waves per SIMD the lo halves of q~ do not fit the registers: they wait in LDS (a wave's own
-  // 4 KB, read back one operand at a time); with two waves per SIMD they stay resident.
-  constexpr bool LO_IN_LDS = NW > 8;
-  __shared__ __align__(16) u32x4 qlo[LO_IN_LDS ? NW : 1][LO_IN_LDS ? NT * 4 : 1][64];
-  // unit = (sequence, context split): its head groups read the same rows of X, from one XCD's L2
-  int unit, hg;
-  if (!unit_of_workgroup(blockIdx.x, (H + HG - 1) / HG, B * nsplit, colocate != 0, unit, hg)) return;
-  const int s = unit / B, b = unit - s * B;            // (sequences fastest: with B a multiple of 8 the splits of a sequence, which
-                                                       //  read the same q~, share an XCD as well: 49.8 -> 47 us at B = 8)
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int idx = lane & 15, rg = lane >> 4;           // column group / row group of the register tile
-  const int n = idx, kg = rg;                          // MFMA: N index (head) or M index (row), k group
-  const int ncb = dm / 128;                            // column owners: waves 0 .. ncb - 1
-  const bool has_cols = w < ncb;
-  const int len = seq_len_of(seq_lens, b, T);
-  const int rows_per = ((len + nsplit - 1) / nsplit + 31) / 32 * 32;
-  const int r_lo = s * rows_per, r_hi = min(len, r_lo + rows_per);
-  const int pid = b * nsplit + s;
-  const int ntile = r_lo < r_hi ? (r_hi - r_lo + 31) / 32 : 0;
-  const int NHT = (H + 15) / 16;
-
-  // q~ of the group's 32 heads over this wave's columns, hi + lo, resident as B operands
-  u32x4 bqh[NT][4], bql[LO_IN_LDS ? 1 : NT][4];
-  {
-    const size_t lo_off = (size_t)B * NHT * 16 * dm;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int ht = min(hg * NT + t, NHT - 1);        // (a tile past the last one repeats it; its heads are masked)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const uint16_t* src = qt + ((((size_t)b * NHT + ht) * (dm / 32) + (size_t)((has_cols ? w : 0) * 4 + ks)) * 64 + lane) * 8;
-        bqh[t][ks] = *reinterpret_cast<const u32x4*>(src);
-        if constexpr (LO_IN_LDS) qlo[w][t * 4 + ks][lane] = *reinterpret_cast<const u32x4*>(src + lo_off);
-        else bql[t][ks] = *reinterpret_cast<const u32x4*>(src + lo_off);
-      }
-    }
-  }
-  const char* Xb = reinterpret_cast<const char*>(X + (size_t)b * x_bstride + (has_cols ? w * 128 : 0) + idx * 8);
-  const unsigned pitchB = (unsigned)dm * 2u;
-  // (rows past the end re-read the last row: finite values that meet a zero weight)
-  auto load_tile = [&](u32x4 (&t)[8], int r0) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const unsigned off = __umul24((unsigned)max(min(r0 + rg * 8 + j, len - 1), 0), pitchB);
-      t[j] = *reinterpret_cast<const u32x4*>(Xb + off);
-    }
-  };
-  f32x4 acc[8][NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // softmax state of the heads this wave owns (the first OWN waves): lane (r = lane % 32, hp = lane / 32) looks after
-  // row r of heads (2 w + hp) HPL + {0 .. HPL - 1} of the group; m is the same in all 32 lanes, l is the
-  // lane's own share
-  const int r = lane & 31, hp = lane >> 5;
-  const bool owner = w < OWN;
-  float m[HPL], l[HPL];
-#pragma unroll
-  for (int i = 0; i < HPL; ++i) { m[i] = NEG_INF; l[i] = 0.f; }
-
-  u32x4 xt[1][8];                                      // (one set: it is free again as soon as the tile is parked and transposed)
-  auto tile_row = [&](int k) { return r_lo + 32 * min(k, max(ntile - 1, 0)); };
-  load_tile(xt[0], tile_row(0));
-  char* const sl = reinterpret_cast<char*>(slot[w]);
-
-  u32x4 (&cur)[8] = xt[0];
-  u32x4 am[8];                                         // the parked tile, transposed: A operands of its weighted sum
-  // 1. the slice into LDS; partial scores of the 32 heads over this wave's 128 columns
-  auto park = [&]() {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(sl + (rg * 8 + j) * XF_PITCH + idx * 16) = cur[j];
-  };
-  auto scores = [&](int k) {
-    f32x4 sp[2][NT];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) sp[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const bf16x8 a8 = *reinterpret_cast<const bf16x8*>(sl + (mt * 16 + n) * XF_PITCH + (ks * 4 + kg) * 16);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          sp[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, __builtin_bit_cast(bf16x8, bqh[t][ks]), sp[mt][t], 0, 0, 0);
-          const u32x4 lo = LO_IN_LDS ? qlo[w][t * 4 + ks][lane] : bql[t][ks];
-          sp[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, __builtin_bit_cast(bf16x8, lo), sp[mt][t], 0, 0, 0);
-        }
-        // (three waves per SIMD: keep the scheduler from fetching all operands of the tile ahead, which
-        //  would push the accumulators out of the registers)
-        if constexpr (LO_IN_LDS) __builtin_amdgcn_sched_barrier(0);
-      }
-    if (has_cols) {                                    // D: column n = head, rows kg*4 + i
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(&red[w][t * 16 + n][mt * 16 + kg * 4]) = sp[mt][t];
-    }
-  };
-  // 2. this wave's four heads: sum over the column owners, reference, numerators
-  bool moved_before = true;                            // alpha_s of this wave's heads may not be all ones (wave-uniform)
-  auto numerators = [&](int k) {
-    if (!owner) return;
-    const int r0 = r_lo + 32 * k;
-    float x[HPL];
-    bool over = false;
-#pragma unroll
-    for (int i = 0; i < HPL; ++i) {
-      const int hl = (2 * w + hp) * HPL + i;
-      float sc = 0.f;
-#pragma unroll
-      for (int w0 = 0; w0 < NW; w0 += 8) {             // (the reads of a batch are issued before the first is used)
-        constexpr int NR = NW < 8 ? NW : 8;
-        float part[NR];
-#pragma unroll
-        for (int ws = 0; ws < NR; ++ws)                // (waves without columns leave their block unwritten: read, not used)
-          part[ws] = red[min(w0 + ws, NW - 1)][hl][r];
-#pragma unroll
-        for (int ws = 0; ws < NR; ++ws) sc += w0 + ws < ncb ? part[ws] : 0.f;
-      }
-      const bool live = (hg * HG + hl < H) && (r0 + r < r_hi);
-      x[i] = live ? sc : NEG_INF;
-      over |= x[i] > m[i] + XW_SLACK;
-    }
-    // The reference moves only when the maximum has grown by more than XW_SLACK, as in xweighted_kernel: rarely, so the
-    // maximum over the rows is taken only then.
-    const bool moved = __any(over);
-    if (moved || moved_before) {
-#pragma unroll
-      for (int i = 0; i < HPL; ++i) {
-        const float tmax = max_over_32(x[i]);
-        const float mn = (tmax > m[i] + XW_SLACK) ? tmax : m[i];
-        const float alpha = (m[i] == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f(m[i] - mn);   // (nothing accumulated yet: nothing to rescale)
-        l[i] *= alpha;
-        m[i] = mn;
-        if (r == 0) alpha_s[(2 * w + hp) * HPL + i] = alpha;
-      }
-    }
-    moved_before = moved;
-#pragma unroll
-    for (int i = 0; i < HPL; ++i) {
-      const __bf16 pw = (__bf16)__builtin_amdgcn_exp2f(x[i] - (m[i] == NEG_INF ? 0.f : m[i]));
-      l[i] += (float)pw;                               // the weight as the MFMA will see it
-      P_s[(2 * w + hp) * HPL + i][r] = __builtin_bit_cast(uint16_t, pw);
-    }
-  };
-  // 3. rescale where a reference moved; P^T X for this wave's columns (the tile in am, its numerators in LDS)
-  auto weighted_sum = [&]() {
-    bf16x8 pb[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float al = alpha_s[t * 16 + n];
-      pb[t] = *reinterpret_cast<const bf16x8*>(&P_s[t * 16 + n][kg * 8]);
-      if (__any(al != 1.f)) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i][t] *= al;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bf16x8 av = __builtin_bit_cast(bf16x8, am[i]);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pb[t], acc[i][t], 0, 0, 0);
-    }
-  };
-  // (Letting the weighted sum of tile k - 1 share a barrier interval with the scores of tile k, the two waves
-  //  of a SIMD in opposite order, was measured: 68 against 58 us on the T5-11B-shaped configuration.)
-  for (int k = 0; k < ntile; ++k) {
-    park();
-    transpose8x8(cur, am);                             // (cur is parked: its registers go to the next tile,
-    // requested before the scores so that it has a whole step to arrive; past the end: the last tile again,
-    // unused)
-    load_tile(cur, tile_row(k + 1));
-    scores(k);
-    lds_barrier();
-    numerators(k);
-    lds_barrier();
-    weighted_sum();
-  }
-
-  // ---- the partial of this (sequence, split): every wave its own columns, the owners their heads' (m, l).
-  // An accumulator lane holds 32 consecutive columns of one head as eight 16-byte pieces: stored from there,
-  // every instruction writes 64 pieces into 64 different cache lines (measured: 10 of the kernel's 59 us on
-  // 8 sequences x 128 heads x 1024 columns).  So the wave's 16 x 128 block of a head tile goes through its
-  // own, now idle, slot and leaves with a head's 512 bytes on 32 consecutive lanes.
-  if (has_cols) {
-    constexpr int OP = 128 + 4;                        // floats per head row in the slot (padding: no bank conflicts)
-    static_assert(16 * OP * 4 <= 32 * XF_PITCH, "a head tile's block must fit the wave's slot");
-    float* const ob = reinterpret_cast<float*>(sl);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the wave's earlier reads of the slot are done)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {                    // accumulator row i: column group rg*4 + i of the block
-        float* d8 = ob + n * OP + (rg * 4 + i) * 8;
-        *reinterpret_cast<f32x4*>(d8) = f32x4{acc[0][t][i], acc[1][t][i], acc[2][t][i], acc[3][t][i]};
-        *reinterpret_cast<f32x4*>(d8 + 4) = f32x4{acc[4][t][i], acc[5][t][i], acc[6][t][i], acc[7][t][i]};
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS operations of one wave complete in order)
-#pragma unroll
-      for (int k2 = 0; k2 < 8; ++k2) {
-        const int hl = 2 * k2 + (lane >> 5), c4 = (lane & 31) * 4;
-        const int h = hg * HG + t * 16 + hl;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(ob + hl * OP + c4);
-        if (h < H) *reinterpret_cast<f32x4*>(Cpart + ((size_t)pid * H + h) * dm + w * 128 + c4) = v;
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < HPL; ++i) {
-    float lt = l[i];
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) lt += __shfl_xor(lt, o);
-    const int h = hg * HG + (2 * w + hp) * HPL + i;
-    if (owner && r == 0 && h < H) {
-      mpart[(size_t)pid * H + h] = m[i];
-      lpart[(size_t)pid * H + h] = lt;
-    }
-  }
-}
-
 }  // namespace
 
 // Head tiles in flight for H heads: 1, 2, 4 or 8.
@@ -818,67 +550,6 @@ int xcache_splits(int B, int H, int T, int d_model) {
   if (s > cap) s = cap;
   if (s > PROJ_MAX_PARTS) s = PROJ_MAX_PARTS;
   return s < 1 ? 1 : s;
-}
-
-bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_model <= 1280; }
-
-// Shape of the one-pass kernel: waves, and head tiles per workgroup
-static int xfused_waves(int d_model) { return d_model <= 512 ? 4 : d_model <= 768 ? 6 : d_model <= 1024 ? 8 : 10; }
-static int xfused_tiles(int H, int d_model) { return d_model <= 1024 && H > 16 ? 2 : 1; }
-
-// Context splits of the one-pass kernel: one workgroup per (split, head group, sequence).
-static long xfused_units(int B, int H, int d_model) {
-  const int hg = 16 * xfused_tiles(H, d_model);
-  return (long)B * ((H + hg - 1) / hg);
-}
-static long xfused_slots(int d_model) { return 256 * xfused_per_cu(xfused_waves(d_model)); }
-
-// At most: eight tiles of rows each, what the projection merges, and six more than fill the chip once (beyond that 0.5 %
-// of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials without bound).  Grows with T.
-int xfused_most_splits(int B, int H, int T, int d_model) {
-  const long units = xfused_units(B, H, d_model), fill = (xfused_slots(d_model) + units - 1) / units + 6;
-  const int most = (T + 255) / 256;
-  return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
-}
-
-// The count whose rounds of workgroups over the 256 compute units take the fewest steps of 32 rows, where starting a
-// workgroup, its first tile and its partial cost about four steps.  (Filling the chip with ceil(256 / units) splits made
-// 288 workgroups of 24 sequences x 2 head groups x 6 splits, two rounds of 8 steps: 50.8 us; 5 splits take one round of
-// 10: 33.6 us.)
-int xfused_splits(int B, int H, int T, int d_model) {
-  const long per = xfused_units(B, H, d_model), slots = xfused_slots(d_model);
-  const int tiles = (T + 31) / 32, most = xfused_most_splits(B, H, T, d_model);
-  int best = 1;
-  long best_cost = 0;
-  for (int s = 1; s <= most; ++s) {
-    const long rounds = (per * s + slots - 1) / slots, cost = rounds * ((tiles + s - 1) / s + 4);
-    if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
-  }
-  return best;
-}
-
-void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
-                   int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
-  const int nt = xfused_tiles(H, d_model), hg = 16 * nt;
-  const int colocate = colocate_units(B * nsplit);
-  dim3 grid(unit_grid(B * nsplit, (H + hg - 1) / hg, colocate));
-  auto go = [&](auto nw, auto tiles) {
-    hipLaunchKernelGGL((xfused_kernel<decltype(nw)::value, decltype(tiles)::value>), grid, dim3(decltype(nw)::value * 64), 0, st,
-                       (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H, d_model, nsplit, Cpart, mpart, lpart,
-                       colocate);
-  };
-  using N1 = std::integral_constant<int, 1>;
-  using N2 = std::integral_constant<int, 2>;
-  auto either = [&](auto nw) {
-    if (nt == 2) go(nw, N2{});
-    else go(nw, N1{});
-  };
-  switch (xfused_waves(d_model)) {
-    case 4: either(std::integral_constant<int, 4>{}); break;
-    case 6: either(std::integral_constant<int, 6>{}); break;
-    case 8: either(std::integral_constant<int, 8>{}); break;
-    default: go(std::integral_constant<int, 10>{}, N1{}); break;
-  }
 }
 
 // Two passes over X: the second finds X in the memory-side cache, and nontemporal weights gain nothing beside it (64 heads x 8 x

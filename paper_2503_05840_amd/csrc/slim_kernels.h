@@ -204,7 +204,7 @@ void launch_xq_tilde(const float* q, const void* Wk, float* qt, int B, int H, in
                      float scale, bool once, int* counters, int ncounters, hipStream_t st);
 void launch_xscores(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
                     int d_model, float* S, int B, hipStream_t st);
-bool xfused_ok(int d_model);                 // one pass over X instead of xscores + xweighted
+bool xfused_ok(int d_model);                 // (kernels_xfused.hip) one pass over X instead of xscores + xweighted
 bool xcache_read_once(int B, int T, int d_model, int e, bool ragged, bool one_pass);   // (read_once)
 int xfused_splits(int B, int H, int T, int d_model);
 int xfused_most_splits(int B, int H, int T, int d_model);    // bound of the splits at T and every shorter context
