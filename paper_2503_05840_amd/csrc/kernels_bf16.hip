@@ -104,8 +104,7 @@ __device__ void build_tile_prefix(int* prefix, int* lens_s, const int32_t* lens,
       const int b = b0 + lane;
       const int len = b < B ? seq_len_of(lens, b, T) : 0;
       int v = (len + TILE_ROWS - 1) / TILE_ROWS;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
+      for (int o = 1; o < 64 && o < B; o <<= 1) {
         const int up = __shfl_up(v, o);
         v += (lane >= o) ? up : 0;
       }
@@ -764,9 +763,16 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
 // following seven rows advance by the one-position rotation (table row 1), kept in registers.
 constexpr float SOFTMAX_SLACK = 6.0f;
 
+// The lane, made where it is asked for: the compiler cannot keep it, or what follows from it, through the stream.
+__device__ __forceinline__ int fresh_lane() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
+
 // LPHP: lanes reserved per head: 16, 8, 4 or 2 (heads of up to 128, 64, 32 or 16 columns).  At compile time, because the
 // divisions by it and what follows from them cost registers: with a run-time value for the two narrow classes, layers of 17
-// to 32 such heads had 84 bytes of scratch per lane (108 with rotary keys) where the others have 56..60 (80..88), and took
+// to 32 such heads had 84 bytes of scratch per lane (108 with rotary keys) where the others had 56..60 (80..88; now none has any), and took
 // 26.2 us at 1 x 4096 rows x 32 heads x 32 (now 25.8), 40.3 at 4 x 5000 with rotary keys (now 38.1).  BYSEQ: the by-sequence partition (a.by_sequence != 0), which has no merge of the
 // waves and never runs the projection; an instantiation of its own keeps each partition's code out of the
 // other's registers.
@@ -778,8 +784,8 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   static_assert(NP == 8 && NS == 2 && PD == 2, "the step structure and the thread mappings below assume these");
   __shared__ int prefix[FUSED_MAX_B + 1];
   __shared__ int lens_s[FUSED_MAX_B];               // rows per sequence
-  __shared__ float marr[NP][NT][16];
-  __shared__ float larr[NP][NT][16];
+  __shared__ __align__(16) float marr[NT][16][NP];  // (a head's eight waves side by side: two 16-byte reads)
+  __shared__ __align__(16) float larr[NT][16][NP];
   // Per wave: NS landing slots of 8 KB for K tiles.  By-context partition: the end-of-share merge of
   // the waves goes through the (then idle) slots, which is why the array is a little larger than
   // the slots.  By-sequence partition: the other waves keep streaming; a wave writes its result
@@ -862,13 +868,11 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   const bool pub_lane = col_active && (li == 0);    // one lane per head publishes its row group
   const int ucol0 = u * a.hpu * a.d_k;
   const int uwc = min(a.hpu * a.d_k, a.d - ucol0);  // columns of this unit
-  int ocol[4];                                      // first unit-local column of accumulator row r, or -1
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int mi = rg * 4 + r;                      // column group (the A operand's M index)
+  // first unit-local column of column group mi (the A operand's M index), or -1
+  auto col_of_group = [&](int mi) {
     const int h2 = mi / lphp, l2 = mi % lphp;
-    ocol[r] = (l2 < a.lph && h2 < a.hpu && h2 * a.d_k + l2 * 8 < uwc) ? h2 * a.d_k + l2 * 8 : -1;
-  }
+    return (l2 < a.lph && h2 < a.hpu && h2 * a.d_k + l2 * 8 < uwc) ? h2 * a.d_k + l2 * 8 : -1;
+  };
 
   // A tile in its LDS slot: row r, 16-byte chunk c (8 columns) at byte r * ROW_PITCH + c * 16, with one
   // chunk of padding per row (17 chunks), so that all three access patterns are free of bank conflicts
@@ -967,28 +971,37 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   // End of a share in the by-context partition, all threads: sum the waves' accumulators
   // out of mbuf[wave][head][col] (one thread per four columns of a head) and write the group's
   // partial for this sequence.
-  auto write_partial = [&](int pid) {
-    const int oc4 = (tid & 31) * 4, oh0 = tid >> 5;  // four columns of heads oh0, oh0 + 16
+  // (ln: the lane, see fresh_lane)
+  auto write_partial = [&](int pid, int ln) {
+    if (u == 0 && wu == NP - 1 && ln < a.H) {         // (first: this workgroup is not to be later than the others for it)
+      const f32x4* const mw = reinterpret_cast<const f32x4*>(marr[ln >> 4][ln & 15]);
+      const f32x4* const lw = reinterpret_cast<const f32x4*>(larr[ln >> 4][ln & 15]);
+      const f32x4 m0 = mw[0], m1 = mw[1], l0 = lw[0], l1 = lw[1];
+      float mall = NEG_INF, l = 0.f;
+#pragma unroll
+      for (int ww = 0; ww < NP; ++ww) {
+        mall = fmaxf(mall, ww < 4 ? m0[ww & 3] : m1[ww & 3]);
+        l += ww < 4 ? l0[ww & 3] : l1[ww & 3];
+      }
+      st_result(a.mpart + (size_t)pid * a.H + ln, mall, fuse);
+      st_result(a.lpart + (size_t)pid * a.H + ln, l, fuse);
+    }
+    const int oc4 = (ln & 31) * 4, oh0 = wu * 2 + (ln >> 5);         // four columns of heads oh0, oh0 + 16
     if (oc4 < uwc) {
+      f32x4 part[HP / 16][NP];
+#pragma unroll
+      for (int jj = 0; jj < HP / 16; ++jj)
+#pragma unroll
+        for (int ww = 0; ww < NP; ++ww)
+          part[jj][ww] = *reinterpret_cast<const f32x4*>(mbuf + ((size_t)ww * HP + oh0 + 16 * jj) * MERGE_PITCH + oc4);
 #pragma unroll
       for (int jj = 0; jj < HP / 16; ++jj) {
         const int h = oh0 + 16 * jj;
         f32x4 osum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ww = 0; ww < NP; ++ww) osum += *reinterpret_cast<const f32x4*>(mbuf + ((size_t)ww * HP + h) * MERGE_PITCH + oc4);
+        for (int ww = 0; ww < NP; ++ww) osum += part[jj][ww];
         if (h < a.H) st_result4(a.Cpart + ((size_t)pid * a.H + h) * a.d + ucol0 + oc4, osum, fuse);
       }
-    }
-    if (u == 0 && tid < a.H) {
-      const int t = tid >> 4, nn = tid & 15;
-      float mall = NEG_INF, l = 0.f;
-#pragma unroll
-      for (int ww = 0; ww < NP; ++ww) {
-        mall = fmaxf(mall, marr[ww][t][nn]);
-        l += larr[ww][t][nn];
-      }
-      st_result(a.mpart + (size_t)pid * a.H + tid, mall, fuse);
-      st_result(a.lpart + (size_t)pid * a.H + tid, l, fuse);
     }
   };
 
@@ -1384,26 +1397,28 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
         // wave's (idle) slot t and leaves with a head's columns on consecutive lanes.
         constexpr int OP = 128 + 4;                     // floats per head row in the slot (padding: no bank conflicts)
         static_assert(16 * OP * 4 <= SLOT_PITCH && NT <= NS, "a head tile's block must fit one slot");
+        const int ln = fresh_lane(), nl = ln & 15, kl = ln >> 4;       // (as below: what waits for this in scratch delays the loads in flight)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          float* const ob = reinterpret_cast<float*>(myslots + t * SLOT_PITCH) + n * OP;
+          float* const ob = reinterpret_cast<float*>(myslots + t * SLOT_PITCH) + nl * OP;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            if (ocol[r] < 0) continue;
-            *reinterpret_cast<f32x4*>(ob + ocol[r]) = f32x4{acc[0][t][r], acc[1][t][r], acc[2][t][r], acc[3][t][r]};
-            *reinterpret_cast<f32x4*>(ob + ocol[r] + 4) = f32x4{acc[4][t][r], acc[5][t][r], acc[6][t][r], acc[7][t][r]};
+            const int oc = col_of_group(kl * 4 + r);
+            if (oc < 0) continue;
+            *reinterpret_cast<f32x4*>(ob + oc) = f32x4{acc[0][t][r], acc[1][t][r], acc[2][t][r], acc[3][t][r]};
+            *reinterpret_cast<f32x4*>(ob + oc + 4) = f32x4{acc[4][t][r], acc[5][t][r], acc[6][t][r], acc[7][t][r]};
           }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS operations of one wave complete in order)
         {
           // head hl of the block on lanes 32 (hl % 2) .. +31, four columns per lane; two heads per instruction
-          const int c4 = (lane & 31) * 4;
-          const float* src = reinterpret_cast<const float*>(myslots) + (lane >> 5) * OP + c4;
-          float* dst = a.Cpart + ((size_t)sg.pid * a.H + (lane >> 5)) * a.d + ucol0 + c4;
+          const int c4 = (ln & 31) * 4;
+          const float* src = reinterpret_cast<const float*>(myslots) + (ln >> 5) * OP + c4;
+          float* dst = a.Cpart + ((size_t)sg.pid * a.H + (ln >> 5)) * a.d + ucol0 + c4;
           const int nh = min(a.H, HP);
 #pragma unroll 1
-          for (int hl = lane >> 5; hl < nh; hl += 2) {
+          for (int hl = ln >> 5; hl < nh; hl += 2) {
             const int t = hl >> 4;
             const f32x4 v = *reinterpret_cast<const f32x4*>(src + (t * (SLOT_PITCH / 4 - 16 * OP)));
             if (c4 < uwc) st_result4(dst, v, fuse);
@@ -1414,8 +1429,8 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the next share parks its tiles in these slots)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const int h = t * 16 + n;
-          if (u == 0 && kg == 0 && h < a.H) {
+          const int h = t * 16 + nl;
+          if (u == 0 && kl == 0 && h < a.H) {
             st_result(a.mpart + (size_t)sg.pid * a.H + h, m[t], fuse);
             st_result(a.lpart + (size_t)sg.pid * a.H + h, accl[t][0], fuse);
           }
@@ -1424,38 +1439,50 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       }
       // ---- by context: merge the waves and write one partial (every wave of the workgroup walks the
       //      same shares, so all of them meet at these barriers) -------------------------------------
-      __syncthreads();                                // every slot is idle from here on
-      if (kg == 0) {
+      // What depends on the lane is made here, from a lane number made here, as in the by-sequence partial above: made before the
+      // stream, it waited in scratch (60 bytes a lane, 88 with rotary keys), a round trip for each piece that is fetched back, and a kernel
+      // with scratch starts later as well.  Without any: 1 x 16384 rows x 32 heads x 128 51.8 -> 43.7 us, 1 x 200 22.9 -> 19.7,
+      // 8 ragged x 5000 x 32 x 96 with rotary keys 66.6 -> 59.9, 16 ragged x 32768 (banded) 370 -> 351; 64 x 1500 x 20 x 64, 12
+      // bytes before, 70.6 -> 69.1.  (Barriers for LDS only: __syncthreads() would also wait for the requests past the end and,
+      // between shares, for the partial's write-through stores, whose arrival only the flag at the end of the launch depends on.)
+      const int ln = fresh_lane(), nl = ln & 15, kl = ln >> 4;
+      if (kl == 0) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) marr[p][t][n] = m[t];
+        for (int t = 0; t < NT; ++t) marr[t][nl][p] = m[t];
       }
-      __syncthreads();
+      lds_barrier();                                  // every slot is idle from here on
       {
         // accumulators -> mbuf[wave][head][col], in MFMA layout, scaled to the maximum over the waves
+        f32x4 mw[NT][2];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) mw[t][i] = *reinterpret_cast<const f32x4*>(&marr[t][nl][i * 4]);
         float wsc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           float mall = NEG_INF;
 #pragma unroll
-          for (int ww = 0; ww < NP; ++ww) mall = fmaxf(mall, marr[ww][t][n]);
-          wsc[t] = (m[t] == NEG_INF) ? 0.f : exp2f(m[t] - mall);
-          if (kg == 0) larr[p][t][n] = accl[t][0] * wsc[t];   // every accumulator row holds the same sum
+          for (int ww = 0; ww < NP; ++ww) mall = fmaxf(mall, mw[t][ww >> 2][ww & 3]);
+          wsc[t] = (m[t] == NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(m[t] - mall);
+          if (kl == 0) larr[t][nl][p] = accl[t][0] * wsc[t];   // every accumulator row holds the same sum
         }
-        float* mine = mbuf + (size_t)p * HP * MERGE_PITCH + n * MERGE_PITCH;
+        float* mine = mbuf + (size_t)p * HP * MERGE_PITCH + nl * MERGE_PITCH;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          if (ocol[r] < 0) continue;
+          const int oc = col_of_group(kl * 4 + r);
+          if (oc < 0) continue;
 #pragma unroll
           for (int t = 0; t < NT; ++t) {
-            f32x4* dst = reinterpret_cast<f32x4*>(mine + t * 16 * MERGE_PITCH + ocol[r]);
+            f32x4* dst = reinterpret_cast<f32x4*>(mine + t * 16 * MERGE_PITCH + oc);
             dst[0] = f32x4{acc[0][t][r], acc[1][t][r], acc[2][t][r], acc[3][t][r]} * wsc[t];
             dst[1] = f32x4{acc[4][t][r], acc[5][t][r], acc[6][t][r], acc[7][t][r]} * wsc[t];
           }
         }
       }
-      __syncthreads();
-      write_partial(sg.pid);
-      __syncthreads();                                // the slots are reused by the next share
+      lds_barrier();
+      write_partial(sg.pid, ln);
+      lds_barrier();                                  // the slots are reused by the next share
     }
   }
   if (!fuse) return;

@@ -47,6 +47,9 @@ def disassembly(symbol, folder):
     return _output(LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", "--disassemble-symbols=" + symbol, _file_with(symbol, folder))
 
 
+def notes(symbol, folder):
+    return _output(LLVM + "llvm-readelf", "--notes", _file_with(symbol, folder))
+
+
 def vector_registers(symbol, folder):
-    notes = _output(LLVM + "llvm-readelf", "--notes", _file_with(symbol, folder))
-    return int(re.search(r"\.name:\s+%s\n(?:(?!\.name:).*\n)*?.*\.vgpr_count:\s+(\d+)" % re.escape(symbol), notes).group(1))
+    return int(re.search(r"\.name:\s+%s\n(?:(?!\.name:).*\n)*?.*\.vgpr_count:\s+(\d+)" % re.escape(symbol), notes(symbol, folder)).group(1))

@@ -1,0 +1,21 @@
+"""No instantiation of the stream kernel uses scratch memory, counted in the built library: 60 bytes a lane of it (addresses for the merge of the
+waves, made before the stream) cost a launch 3 to 8 us."""
+import re
+
+import pytest
+
+import built_code
+
+KERNEL = "_ZN4slim12_GLOBAL__N_119fused_stream_kernelILi%dELb%dELi%dELb%dEEEvNS_9FusedArgsE"
+
+
+@pytest.mark.skipif(not built_code.PRESENT, reason="no disassembler")
+def test_stream_kernels_have_no_scratch(tmp_path):
+    notes = built_code.notes(KERNEL % (2, 0, 16, 0), tmp_path)
+    for tiles in (1, 2):
+        for rotary in (0, 1):
+            for lanes in (2, 4, 8, 16):
+                for by_sequence in (0, 1):
+                    name = KERNEL % (tiles, rotary, lanes, by_sequence)
+                    size = re.search(r"\.name:\s+%s\n(?:(?!\.name:).*\n)*?.*\.private_segment_fixed_size:\s+(\d+)" % re.escape(name), notes)
+                    assert size and int(size.group(1)) == 0, name
