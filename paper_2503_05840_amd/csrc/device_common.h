@@ -70,6 +70,13 @@ __device__ __forceinline__ float sum_over_wave(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The lane, made where it is asked for: the compiler cannot keep it, or what follows from it, through the stream.
+__device__ __forceinline__ int fresh_lane() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
+
 // 8 rows x 8 bf16 columns per lane  ->  8 operands (one per column), each 8 rows of that column.
 __device__ __forceinline__ void transpose8x8(const u32x4 (&kt)[8], u32x4 (&a)[8]) {
 #pragma unroll

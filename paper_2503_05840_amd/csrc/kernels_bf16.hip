@@ -763,13 +763,6 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
 // following seven rows advance by the one-position rotation (table row 1), kept in registers.
 constexpr float SOFTMAX_SLACK = 6.0f;
 
-// The lane, made where it is asked for: the compiler cannot keep it, or what follows from it, through the stream.
-__device__ __forceinline__ int fresh_lane() {
-  int ln;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-  return ln;
-}
-
 // LPHP: lanes reserved per head: 16, 8, 4 or 2 (heads of up to 128, 64, 32 or 16 columns).  At compile time, because the
 // divisions by it and what follows from them cost registers: with a run-time value for the two narrow classes, layers of 17
 // to 32 such heads had 84 bytes of scratch per lane (108 with rotary keys) where the others had 56..60 (80..88; now none has any), and took
