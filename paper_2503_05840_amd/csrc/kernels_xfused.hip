@@ -475,7 +475,7 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
 
 bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_model <= 1280; }
 
-// Head tiles per workgroup
+// Head tiles per workgroup.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
 static int xfused_tiles(int H, int d_model) { return H > 16 && d_model <= 1024 ? 2 : 1; }
 
 // Context splits of the one-pass kernel: one workgroup per (split, head group, sequence).
@@ -521,8 +521,9 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
                          dim3(XF_NW * 64), 0, st, (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H, d_model, nsplit,
                          Cpart, mpart, lpart, colocate);
     };
-    if (nt == 2) with(std::integral_constant<int, 2>{});
-    else with(std::integral_constant<int, 1>{});
+    if constexpr (decltype(cbf)::value + decltype(half)::value < 3)       // (wider rows: 16 heads a group, xfused_tiles)
+      if (nt == 2) return with(std::integral_constant<int, 2>{});
+    with(std::integral_constant<int, 1>{});
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
