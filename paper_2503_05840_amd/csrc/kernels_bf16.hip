@@ -418,6 +418,33 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     if (lg > 0) f(std::integral_constant<int, 1>{});
     else f(std::integral_constant<int, 2>{});
   };
+  // A launch of its own makes the merged C of a tile's rows in B-operand layout, a lane eight rows c of sequence n.  Up to four
+  // sequences: from four partials per round trip, the first four of a tile asked for ahead -- behind the maxima and sums for the first tile,
+  // behind the products of the one before for the others -- because a trip is what takes the time there (X-cache of 1 x 4096 rows x 32 heads x
+  // 1024 columns 34.5 -> 32.6 us, 1 x 4096 x 128 heads 46.2 -> 44.3, wide K-cache of 2 x 4001 x 40 heads x 128 56.2 -> 55.5).  More
+  // sequences: one or two at a time, since there the lines of the partials do, 16 for 16 sequences, and what is fetched beyond
+  // the last partial costs (24 x 1500 x 20 heads x 1280 48.1 us, with four per trip 49.6; 8 x 4096 x 64 heads x 768 44.1 and 45.7).
+  constexpr bool IN_TILE = !COH && !DENSE && NBT == 1;
+  constexpr int QMOST = 4;
+  const bool few = IN_TILE && nb <= 4;
+  f32x4 pt[IN_TILE ? QMOST : 1][2];
+  int pn0 = 0, pnn = 0, most = 0;                     // this lane's sequence: first partial, how many; the most of any lane
+  auto ask_parts = [&](auto Q_, int ct, int p) {
+    constexpr int Q = decltype(Q_)::value;
+    const int c = min(c_lo + ct * TILE_ROWS + kg * 8, a.rows - 8);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const float* src = a.Cpart + ((size_t)(pn0 + min(p + q, max(pnn - 1, 0))) * a.H + h) * a.rows + c;
+      pt[q][0] = *reinterpret_cast<const f32x4*>(src);
+      pt[q][1] = *reinterpret_cast<const f32x4*>(src + 4);
+    }
+  };
+  // (a partial that does not exist is a repeated load of one that does: one, two or four per trip by how many there are)
+  auto with_parts = [&](auto&& f) {
+    if (most <= 1) f(std::integral_constant<int, 1>{});
+    else if (most == 2) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, QMOST>{});
+  };
   if constexpr (!DENSE) {
     // ---- merge weights for head h: one wave per sequence, one lane per partial; the first partials
     //      themselves are asked for behind the maxima and sums ----------------------------------------
@@ -431,6 +458,13 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         mp[i] = ld_part<COH>(a.mpart + (size_t)(first_part(bl) + lane) * a.H + h);
         lp[i] = ld_part<COH>(a.lpart + (size_t)(first_part(bl) + lane) * a.H + h);
       }
+    }
+    if (few) {
+      const int bl = min(n, nb - 1);
+      pn0 = even ? (bbase + bl) * a.nsplit : sm.pid0s[bl];
+      pnn = even ? min(a.nsplit, PROJ_MAX_PARTS) : sm.nps[bl];
+      most = even ? pnn : __builtin_amdgcn_readfirstlane((int)max_over_wave((float)pnn));
+      if (w < ntile) with_parts([&](auto Q_) { ask_parts(Q_, w, 0); });
     }
     const bool fetched = COH && seq0 < nb && lane0 < rows4;
     if constexpr (COH)
@@ -483,6 +517,31 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         const int at = ((ct * 4 + kg) * 16 + n) * 8;
         bhi[t] = *reinterpret_cast<const bf16x8*>(cs_hi + at);
         blo[t] = *reinterpret_cast<const bf16x8*>(cs_lo + at);
+      }
+    } else if (few) {
+      float cn[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) cn[j] = 0.f;
+      with_parts([&](auto Q_) {
+        constexpr int Q = decltype(Q_)::value;
+        for (int p = 0; p < most; p += Q) {
+          if (p > 0) ask_parts(Q_, ct, p);
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            const float wgt = p + q < pnn ? sm.wpid[min(n, nb - 1)][p + q] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) cn[j] = p + q < pnn ? fmaf(wgt, pt[q][j >> 2][j & 3], cn[j]) : cn[j];
+          }
+        }
+        if (more) ask_parts(Q_, ct + NW, 0);
+      });
+      const bool live = n < nb && c0 + kg * 8 < c_hi;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float v = live ? cn[j] : 0.f;
+        const __bf16 hi = (__bf16)v;
+        bhi[0][j] = hi;
+        blo[0][j] = (__bf16)(v - (float)hi);
       }
     } else {
       const int c = c0 + kg * 8;
