@@ -22,6 +22,15 @@ __device__ __forceinline__ int seq_len_of(const int32_t* lens, int b, int T) {
   return n < 0 ? 0 : (n > T ? T : n);
 }
 
+// Partials that a later launch reads, stored through the L2s to the memory side: what is left dirty there is written back between the
+// launches, and the next one starts that much later (4 us after 9 MB).  For whole lines only: pieces of 16 bytes took 12 %
+// longer, and the partials of the by-sequence stream and of the wide path's weighted sum, which leave while others still stream or in such
+// pieces, 1-3 %.  (The s_nops: a store of more than 64 bits still reads its data registers in the wait states after it issues, and the compiler,
+// which pads its own stores, is free to overwrite the inputs of an asm statement with the very next vector instruction.)
+__device__ __forceinline__ void store_through(float* p, f32x4 v) {
+  asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+
 // Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for its
 // global loads (__syncthreads() would also drain the tiles that are being prefetched from HBM).
 __device__ __forceinline__ void lds_barrier() {
