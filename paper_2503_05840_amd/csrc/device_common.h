@@ -59,6 +59,17 @@ __device__ __forceinline__ float max_over_32(float v) {
   return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
+// sum over the 32 lanes that share lane / 32, the same bits as a __shfl_xor butterfly from 1 to 16
+__device__ __forceinline__ float sum_over_32(float v) {
+  v = dpp_add<0xB1>(v);
+  v = dpp_add<0x4E>(v);
+  v = dpp_add<0x141>(v);
+  v = dpp_add<0x140>(v);
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
 // max / sum over the whole wave, the same in every lane: DPP inside the 16-lane rows, register swaps across them (a
 // __shfl_xor butterfly goes through LDS six times, a tenth of a microsecond each)
 __device__ __forceinline__ float max_over_wave(float v) {
@@ -84,6 +95,16 @@ __device__ __forceinline__ int fresh_lane() {
   int ln;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
   return ln;
+}
+
+// v of the lanes l, l^16, l^32, l^48 added up, the same in all four and the same bits as a __shfl_xor butterfly over 16 and 32: each
+// sum has the same two terms
+__device__ __forceinline__ float sum_over_row_groups(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // 8 rows x 8 bf16 columns per lane  ->  8 operands (one per column), each 8 rows of that column.

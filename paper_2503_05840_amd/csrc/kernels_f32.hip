@@ -200,9 +200,7 @@ __global__ __launch_bounds__(512) void f32_stream_kernel(const float* __restrict
         if (h < H && c < d) store_through(Cpart + (pid * H + h) * d + c, v);
       }
     }
-    float lt = l[t];
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) lt += __shfl_xor(lt, o);
+    const float lt = sum_over_32(l[t]);
     const int h2 = t * 16 + 2 * w + half;
     if (row == 0 && h2 < H) {
       mpart[pid * H + h2] = m[t];
