@@ -242,6 +242,15 @@ def slim_read_probe(buf) -> None:
         raise SlimError(rc, "slim_read_probe")
 
 
+def _current_stream(torch):
+    """Handle of the current device's current stream.  torch.cuda.current_stream() makes a Stream object for it, 2.8 us of the 13 that a
+    small call spends on the host; the raw handle takes 0.2."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())
+
+
 def _opts(dtype, seq_lens, seq_lens_host, t_stride, workspace, variant, stage_ms=None, rope_table=None, wait_budget_us=0,
           k_layout=0):
     import torch
@@ -256,7 +265,7 @@ def _opts(dtype, seq_lens, seq_lens_host, t_stride, workspace, variant, stage_ms
     if workspace is not None:
         o.workspace = workspace.data_ptr()
         o.workspace_bytes = workspace.numel() * workspace.element_size()
-    o.stream = torch.cuda.current_stream().cuda_stream
+    o.stream = _current_stream(torch)
     o.variant = int(variant)
     if stage_ms is not None:      # a ctypes float array of MAX_STAGES entries, filled by the call
         o.stage_ms = ctypes.cast(stage_ms, ctypes.POINTER(ctypes.c_float))
