@@ -178,7 +178,8 @@ __device__ __forceinline__ void ld_part8(const float* const (&p)[8], unsigned o0
 // (matrix, head) column blocks.  The result leaves as fp32, or -- the new token's rows -- rotated to
 // the append position and/or stored into the caches (ProjArgs::role).
 // ONCE: W is read once per launch and is large: its loads ask to be let go of first (nontemporal).
-template <int NBT, bool COH, bool DENSE, bool ONCE, class Hook>
+// FEW: up to four sequences in a launch of its own.
+template <int NBT, bool COH, bool DENSE, bool ONCE, bool FEW, class Hook>
 __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, int bz, const int* prefix,
                                              ProjShared<NBT>& sm, float* red, Hook&& after_w_issue) {
   const int mtx = DENSE ? hx / a.H : 0;
@@ -418,16 +419,15 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
     if (lg > 0) f(std::integral_constant<int, 1>{});
     else f(std::integral_constant<int, 2>{});
   };
-  // A launch of its own makes the merged C of a tile's rows in B-operand layout, a lane eight rows c of sequence n.  Up to four
-  // sequences: from four partials per round trip, the first four of a tile asked for ahead -- behind the maxima and sums for the first tile,
-  // behind the products of the one before for the others -- because a trip is what takes the time there (X-cache of 1 x 4096 rows x 32 heads x
+  // A launch of its own makes the merged C of a tile's rows in B-operand layout, a lane eight rows c of sequence n.  FEW: from
+  // four partials per round trip, the first four of a tile asked for ahead -- behind the maxima and sums for the first tile, behind
+  // the products of the one before for the others -- because a trip is what takes the time there (X-cache of 1 x 4096 rows x 32 heads x
   // 1024 columns 34.5 -> 32.6 us, 1 x 4096 x 128 heads 46.2 -> 44.3, wide K-cache of 2 x 4001 x 40 heads x 128 56.2 -> 55.5).  More
   // sequences: one or two at a time, since there the lines of the partials do, 16 for 16 sequences, and what is fetched beyond
   // the last partial costs (24 x 1500 x 20 heads x 1280 48.1 us, with four per trip 49.6; 8 x 4096 x 64 heads x 768 44.1 and 45.7).
-  constexpr bool IN_TILE = !COH && !DENSE && NBT == 1;
+  // In a kernel of its own, because the others paid for what they do not run: 64 x 448 rows x 6 heads x 64 22.4 -> 22.2 us.
   constexpr int QMOST = 4;
-  const bool few = IN_TILE && nb <= 4;
-  f32x4 pt[IN_TILE ? QMOST : 1][2];
+  f32x4 pt[FEW ? QMOST : 1][2];
   int pn0 = 0, pnn = 0, most = 0;                     // this lane's sequence: first partial, how many; the most of any lane
   auto ask_parts = [&](auto Q_, int ct, int p) {
     constexpr int Q = decltype(Q_)::value;
@@ -459,7 +459,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         lp[i] = ld_part<COH>(a.lpart + (size_t)(first_part(bl) + lane) * a.H + h);
       }
     }
-    if (few) {
+    if constexpr (FEW) {
       const int bl = min(n, nb - 1);
       pn0 = even ? (bbase + bl) * a.nsplit : sm.pid0s[bl];
       pnn = even ? min(a.nsplit, PROJ_MAX_PARTS) : sm.nps[bl];
@@ -518,7 +518,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
         bhi[t] = *reinterpret_cast<const bf16x8*>(cs_hi + at);
         blo[t] = *reinterpret_cast<const bf16x8*>(cs_lo + at);
       }
-    } else if (few) {
+    } else if constexpr (FEW) {
       float cn[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) cn[j] = 0.f;
@@ -777,7 +777,7 @@ __device__ __forceinline__ void project_work(const ProjArgs& a, int hx, int cs, 
   if (tid == 0 && !by_flags) a.counters[bz * nhx + hx] = 0;
 }
 
-template <int NBT, bool DENSE, bool ONCE>
+template <int NBT, bool DENSE, bool ONCE, bool FEW>
 __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   __shared__ int prefix[FUSED_MAX_B + 1];
   __shared__ ProjShared<NBT> sm;
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(512) void project_mfma_kernel(const ProjArgs a) {
   if (DENSE && a.flags && blockIdx.x == 0)
     for (int i = threadIdx.x; i < PROJ_BLOCK_INTS; i += 512) a.counters[i] = 0;
   if (unit >= nhx * ((a.B + 16 * NBT - 1) / (16 * NBT))) return;
-  project_work<NBT, false, DENSE, ONCE>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
+  project_work<NBT, false, DENSE, ONCE, FEW>(a, unit % nhx, slot % a.csw, unit / nhx, prefix, sm, red, [&]() {
     if (!DENSE && a.mode == 0) build_tile_prefix(prefix, nullptr, a.seq_lens, a.B, a.T);
     return true;
   });
@@ -1052,8 +1052,10 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
         f32x4 osum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ww = 0; ww < NP; ++ww) osum += part[jj][ww];
-        // (through the L2s also where a launch of its own reads them: 32 ragged x 1000 rows x 32 heads x 128 80.7 -> 78.6 us)
-        if (h < a.H) st_result4(a.Cpart + ((size_t)pid * a.H + h) * a.d + ucol0 + oc4, osum, true);
+        // (Through the L2s also where a launch of its own reads them, for two head tiles: 32 ragged x 1000 rows x 32 heads x 128
+        // 80.6 -> 78.4 us.  The partials of up to 16 heads are small, and the way to memory is the longer one: 96 x 448 x 8 heads x
+        // 64 31.7 -> 32.0 us, 24 x 1500 x 12 heads 31.8 -> 32.3.)
+        if (h < a.H) st_result4(a.Cpart + ((size_t)pid * a.H + h) * a.d + ucol0 + oc4, osum, NT == 2 || fuse);
       }
     }
   };
@@ -1552,7 +1554,7 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
   if (phead >= a.proj.H) return;
   // (everything of the stream phase is over in this workgroup: its LDS is reused)
   ProjShared<1>& psm = *reinterpret_cast<ProjShared<1>*>(sbuf);
-  project_work<1, true, false, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
+  project_work<1, true, false, false, false>(a.proj, phead, psplit, 0, prefix, psm, red, [&]() {
     // Every workgroup's partials must be out: all arrival flags carry this launch's id.  False: the workgroups of this head
     // are to meet in an XCD's L2, and do not run on one XCD.
     bool together = true;
@@ -1772,7 +1774,12 @@ static void launch_product(const ProjArgs& a, int nbt, int units_per_chunk, hipS
   const int chunks = (a.B + 16 * nbt - 1) / (16 * nbt);
   dim3 grid(8u * a.csw * (((unsigned)units_per_chunk * chunks + 7) / 8)), block(512);
   auto launch = [&](auto nb, auto once) {
-    hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, decltype(once)::value>), grid, block, 0, st, a);
+    if constexpr (!DENSE && decltype(nb)::value == 1)
+      if (a.B <= 4) {                                  // (FEW: project_work)
+        hipLaunchKernelGGL((project_mfma_kernel<1, false, decltype(once)::value, true>), grid, block, 0, st, a);
+        return;
+      }
+    hipLaunchKernelGGL((project_mfma_kernel<decltype(nb)::value, DENSE, decltype(once)::value, false>), grid, block, 0, st, a);
   };
   auto go = [&](auto nb) {
     // (a block's matrices are at most 4096 columns wide: more than one batch tile always come in more than one chunk)
