@@ -29,7 +29,7 @@ __host__ __device__ inline int fs_part_pitch(int d) { return d / 16 + 1; }      
 //      running maximum, rescale factors
 //   3. MFMA: M = columns (lane idx holds columns 4 idx .. +3 of a 64-column block, one MFMA per column of the
 //      four), N = heads, K = 4 rows per instruction
-// (CI = 4 with two head tiles and rotary keys does not fit 256 registers: 48 bytes of scratch per lane.)
+// (CI = 4 with two head tiles and rotary keys does not fit 256 registers: 52 bytes of scratch per lane.)
 template <int CI, int NT, bool ROPE>
 __global__ __launch_bounds__(512) void f32_stream_kernel(const float* __restrict__ q, const float* __restrict__ K, long k_bstride,
                                                          const int32_t* __restrict__ seq_lens, int T, int H, int d, int d_k,
