@@ -95,7 +95,7 @@ __device__ __forceinline__ unsigned my_xcc() { return __builtin_amdgcn_s_getreg(
 
 // Tiles of 32 rows: prefix[b] = number of tiles of sequences 0..b-1; lens_s[b] (if given) = rows of
 // sequence b.  The first wave takes 64 sequences at a time, one per lane (one memory round trip per 64
-// sequences instead of one per sequence), and adds them up with a scan over the lanes.
+// sequences instead of one per sequence), and adds them up with a scan over the lanes (prefix_over_wave).
 __device__ void build_tile_prefix(int* prefix, int* lens_s, const int32_t* lens, int B, int T) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
@@ -103,16 +103,12 @@ __device__ void build_tile_prefix(int* prefix, int* lens_s, const int32_t* lens,
     for (int b0 = 0; b0 < B; b0 += 64) {
       const int b = b0 + lane;
       const int len = b < B ? seq_len_of(lens, b, T) : 0;
-      int v = (len + TILE_ROWS - 1) / TILE_ROWS;
-      for (int o = 1; o < 64 && o < B; o <<= 1) {
-        const int up = __shfl_up(v, o);
-        v += (lane >= o) ? up : 0;
-      }
+      const int v = prefix_over_wave((len + TILE_ROWS - 1) / TILE_ROWS);
       if (b < B) {
         prefix[b + 1] = carry + v;
         if (lens_s) lens_s[b] = len;
       }
-      carry += __shfl(v, 63);
+      carry += __builtin_amdgcn_readlane(v, 63);
     }
     if (lane == 0) prefix[0] = 0;
   }
