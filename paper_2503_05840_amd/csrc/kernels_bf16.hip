@@ -1448,7 +1448,9 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
         // wave's (idle) slot t and leaves with a head's columns on consecutive lanes.
         constexpr int OP = 128 + 4;                     // floats per head row in the slot (padding: no bank conflicts)
         static_assert(16 * OP * 4 <= SLOT_PITCH && NT <= NS, "a head tile's block must fit one slot");
-        const int ln = fresh_lane(), nl = ln & 15, kl = ln >> 4;       // (as below: what waits for this in scratch delays the loads in flight)
+        // (Two head tiles: the lane made here, as below, because what waits for this in scratch delays the loads in flight.  One tile has
+        // registers for it: 243 ragged x 165 rows x 16 heads x 72 57.0 us, with the lane made here 58.3.)
+        const int ln = NT == 1 ? lane : fresh_lane(), nl = ln & 15, kl = ln >> 4;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
