@@ -6,6 +6,7 @@
 #include "device_common.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace slim {
 namespace {
@@ -486,26 +487,37 @@ static long xfused_units(int B, int H, int d_model) {
 }
 static long xfused_slots(int H, int d_model) { return 256 * (d_model <= 512 ? xf_per_cu(1, 0, xfused_tiles(H, d_model)) : 1); }   // workgroups at once
 
-// At most: eight tiles of rows each, what the projection merges, and six more than fill the chip once (beyond that 0.5 %
-// of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials without bound).  Grows with T.
+// At most: one per started 128 rows of T (a split may hold fewer: lengths below T, whole tiles), what the projection merges, and six more
+// than fill the chip once (beyond that 0.5 % of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials without bound).
+// Grows with T, and the workspace's partials with it.
 int xfused_most_splits(int B, int H, int T, int d_model) {
   const long units = xfused_units(B, H, d_model), fill = (xfused_slots(H, d_model) + units - 1) / units + 6;
   const int most = (T + 127) / 128;
   return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
 }
 
-// The count whose rounds of workgroups over the compute units take the least time, in tenths of a step of 32 rows (1.6 us): starting
-// a workgroup, its first tile and its last cost about four steps; a split's partials 0.4 steps per MB (written here, read by
-// the projection) and a tenth more (a round trip of the merge).  Without the partials' share 8 sequences x 32 heads x 4096 rows x
-// 1024 columns took 47.9 us in 32 splits and take 44.2 in 16.
+// Rounds of workgroups over the compute units with s splits: per XCD where the units are dealt to the XCDs (launch_xfused), else over all.
+static long xfused_rounds(int B, int H, int d_model, int s) {
+  const long slots = xfused_slots(H, d_model), units = (long)B * s, groups = xfused_units(1, H, d_model);
+  if (colocate_units(B * s)) return ((units + 7) / 8 * groups + slots / 8 - 1) / (slots / 8);
+  return (units * groups + slots - 1) / slots;
+}
+
+// The count that takes the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37 per head tile and 37
+// more; starting a workgroup, its first tile and its last, 1900 a round.  Whatever the splits, X comes at 120 per MB; the two overlap, but
+// not fully (the root of the squares).  A split costs 88 (a round trip of the merge) and 465 per MB of its partials (written here, read by
+// the projection).  Fitted to 840 shapes of the range (B up to 96, 6 to 128 heads, all widths, 200 to 8000 rows), 0.5 % slower than their best counts in
+// the mean; with one price for steps of every width, 1.5 %, because narrow rows and few heads were cut too fine (64 x 1500 rows x 16
+// heads x 512 columns 44.2 us, now 43.2) and others too coarsely, or into a second round on an XCD (27 x 1500 x 40 x 1280 83.7, now 69.1).
 int xfused_splits(int B, int H, int T, int d_model) {
-  const long per = xfused_units(B, H, d_model), slots = xfused_slots(H, d_model);
   const int tiles = (T + 31) / 32, most = xfused_most_splits(B, H, T, d_model);
-  const long partial = 4L * B * H * d_model;           // bytes of a split's partials
+  const int ksteps = (d_model / 128 + 1) / 2 * 2;      // (CBF * 4 + HALF * 2 of launch_xfused)
+  const double step = 700 + 37.0 * ksteps * (xfused_tiles(H, d_model) + 1), rows = 120e-6 * 2 * B * T * d_model;
+  const double split = 88 + 465e-6 * 4 * B * H * d_model;
   int best = 1;
-  long best_cost = 0;
+  double best_cost = 0;
   for (int s = 1; s <= most; ++s) {
-    const long rounds = (per * s + slots - 1) / slots, cost = 10 * rounds * ((tiles + s - 1) / s + 4) + 4 * s * partial / (1 << 20) + s;
+    const double work = xfused_rounds(B, H, d_model, s) * ((tiles + s - 1) / s * step + 1900), cost = sqrt(work * work + rows * rows) + s * split;
     if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
   }
   return best;

@@ -34,3 +34,9 @@ def read_once(weight_bytes, cache_bytes):
 def xcache_read_once(B, T, d_model, e, ragged, one_pass):
     i, b = ctypes.c_int, ctypes.c_bool
     return _rule("_ZN4slim16xcache_read_onceEiiiibb", b, i, i, i, i, b, b)(B, T, d_model, e, ragged, one_pass)
+
+
+def one_pass_splits(B, H, T, d_model):
+    """Context splits of the one-pass X-cache kernel, and the most that any context up to T takes."""
+    i = ctypes.c_int
+    return tuple(_rule("_ZN4slim%sEiiii" % name, i, i, i, i, i)(B, H, T, d_model) for name in ("13xfused_splits", "18xfused_most_splits"))

@@ -1,0 +1,32 @@
+"""Into how many context splits the one-pass X-cache kernel cuts a call: counts within 2 % of the best one that was measured, over widths and head
+counts whose steps cost a quarter to all of the longest, and batches that an even share of the compute units does not hold."""
+import pytest
+
+from launch_rules import one_pass_splits
+
+
+@pytest.mark.parametrize("B,H,T,d_model,best", [
+    (64, 16, 1500, 512, (5, 6, 7)),                # narrow steps, the memory's rate: more than fill the chip once only add partials
+    (27, 16, 1500, 512, (6, 7, 8, 9, 10)),
+    (32, 16, 1500, 1024, (5, 6)),
+    (12, 24, 1500, 896, (10, 12)),                 # two head tiles
+    (13, 32, 1500, 640, (12,)),
+    (2, 128, 2290, 640, (16, 18, 20)),
+    (27, 40, 1500, 1280, (2,)),                    # three would take two rounds on some XCDs
+    (7, 40, 1500, 1152, (10,)),
+    (40, 128, 1500, 768, (3,)),                    # more than one round in any case
+    (36, 128, 1355, 1024, (2, 3)),
+    (8, 128, 4096, 1024, (8,)),
+    (24, 20, 1500, 1280, (5,)),
+])
+def test_counts_that_were_measured(B, H, T, d_model, best):
+    assert one_pass_splits(B, H, T, d_model)[0] in best
+
+
+@pytest.mark.parametrize("d_model", range(512, 1281, 128))
+def test_counts_stay_within_the_workspace(d_model):
+    for B in (1, 3, 8, 31, 64, 300):
+        for H in (1, 16, 17, 40, 128):
+            for T in (1, 31, 128, 129, 1500, 4096, 70000):
+                splits, most = one_pass_splits(B, H, T, d_model)
+                assert 1 <= splits <= most <= 64
