@@ -330,6 +330,12 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     if constexpr (NT == 2 || CBF == 1) fence();
   };
   constexpr int END = NBLK - 1;                        // the last block
+  // EARLY: registers that were parked are asked for again at once, not when the block's other work is done.  What decides there is how many
+  // bytes are on their way, and a register waits for its next request empty: 16 heads a group, two blocks: 32 x 1500 rows x 16 heads x 1024
+  // 42.4 -> 41.3 us, 96 x 16 x 1024 80.8 -> 78.6, 64 x 16 x 768 53.4 -> 53.1, small batches the same; 32 heads a group, one block: 76 ragged x 1500 x
+  // 24 x 512 49.6 -> 43.9, 40 x 1000 x 32 x 512 33.6 -> 32.8.  Not where the matrix instructions decide (32 heads and two blocks: 8 x 4096 x
+  // 128 x 1024 63.7 -> 64.8) nor where two workgroups share a compute unit (16 heads and one block: 4 x 1500 x 16 x 512 23.8 -> 24.2).
+  constexpr bool EARLY = NT == 1 ? NBLK == 2 : NBLK == 1;
   if (ntile > 0) {
     aim(0);
 #pragma unroll
@@ -349,7 +355,7 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
 #pragma unroll
     for (int blk = 0; blk < (NBLK == 1 ? 1 : END); ++blk) park(blk, 0, 8);
     aim(2);
-    if constexpr (NBLK > 1) request(0, 0, 8);
+    if constexpr (NBLK > 1 || EARLY) request(0, 0, 8);
     lds_barrier();
     auto last = [&]() {
       numerators(ntile - 1);
@@ -373,12 +379,14 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
         read_a(1);
         fence();
         if constexpr (NBLK > 1) park(END, 0, 2);
-        if constexpr (NBLK != 2) request(NBLK == 1 ? 0 : 1, 0, 4);
+        if constexpr (EARLY && NBLK == 2) request(END, 0, 2);
+        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 0, 4);
         score(0);
         paced();
         read_a(2);
         if constexpr (NBLK > 1) park(END, 2, 4);
-        if constexpr (NBLK != 2) request(NBLK == 1 ? 0 : 1, 4, 8);
+        if constexpr (EARLY && NBLK == 2) request(END, 2, 4);
+        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 4, 8);
         score(1);
         paced();
         rescale_all();
@@ -387,7 +395,9 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
           read_rows(blk, 0);
           if (blk > 0) park(blk - 1, 0, 4);
           if (blk == 0 && NBLK > 1) park(END, 4, 8);
+          if (blk == 0 && NBLK == 2 && EARLY) request(END, 4, 8);
           if (blk == (END > 0 ? 1 : 0)) aim(k + 3);
+          if (blk == 1 && EARLY) request(0, 0, 4);
           sum_block(blk);
           paced();
           const int ks0 = blk == 0 ? 2 : blk * 4, ks1 = blk == 0 ? 4 : min(blk * 4 + 4, KS);
@@ -398,15 +408,18 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
               turn_rows(blk, 0);
               read_rows(blk, 1);
               if (blk > 0) park(blk - 1, 4, 6);
+              if (blk == 1 && EARLY) request(0, 4, 6);
             }
             if (ks == ks0 + 1) {
               turn_rows(blk, 1);
               if (blk > 0) park(blk - 1, 6, 8);
+              if (blk == 1 && EARLY) request(0, 6, 8);
               if (NBLK == 1) park(0, 0, 8);
+              if (NBLK == 1 && EARLY) request(0, 0, 8);
             }
-            if (blk == 0 && NBLK > 1) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
+            if (blk == 0 && NBLK > 1 && !EARLY) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
             // (the first block's registers are free once it is parked, behind the second block's first k-steps)
-            if (blk == 1) {
+            if (blk == 1 && !EARLY) {
               if (ks1 - ks0 == 4 && ks >= ks1 - 2) request(0, (ks - ks1 + 2) * 4, (ks - ks1 + 2) * 4 + 4);
               if (ks1 - ks0 == 2 && ks == ks1 - 1) request(0, 0, 8);
             }
