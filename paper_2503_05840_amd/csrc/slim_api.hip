@@ -67,8 +67,10 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
     p.nsplit_x = xcache_splits(B, H, T, width);
     at_least((size_t)B * p.nsplit_x);
     if (xfused_ok(width)) {
-      p.nsplit_xf = xfused_splits(B, H, T, width);
-      at_least((size_t)B * xfused_most_splits(B, H, T, width));
+      // (Room for a split per started 256 rows, or for as many as the other passes take: what a workspace has always had.  More splits of
+      // few rows pay only where a batch is small, and there the others' partials are more.)
+      at_least((size_t)B * std::min(xfused_most_splits(B, H, T, width), (T + 255) / 256));
+      p.nsplit_xf = (int)std::min<size_t>(xfused_splits(B, H, T, width), nparts / B);
     }
   } else {
     // vanilla kernel: workgroups of four waves, a wave per group of heads; about eight workgroups per
