@@ -52,4 +52,4 @@ def notes(symbol, folder):
 
 
 def vector_registers(symbol, folder):
-    return int(re.search(r"\.name:\s+%s\n(?:(?!\.name:).*\n)*?.*\.vgpr_count:\s+(\d+)" % re.escape(symbol), notes(symbol, folder)).group(1))
+    return int(re.search(r"\.name:\s+%s\n(?:(?!\s*\.name:).*\n)*?.*\.vgpr_count:\s+(\d+)" % re.escape(symbol), notes(symbol, folder)).group(1))
