@@ -148,8 +148,7 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) a8[ks & 1][mt] = *reinterpret_cast<const bf16x8*>(sc_at + mt * 16 * PITCH + ks * 64);
   };
-  auto score = [&](int ks) {
-    if (!ALL && !ks_has(ks)) return;
+  auto products = [&](int ks) {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -158,6 +157,18 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int t = 0; t < NT; ++t) sp[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8[ks & 1][mt], __builtin_bit_cast(bf16x8, bql[t][ks]), sp[mt][t], 0, 0, 0);
+  };
+  auto score = [&](int ks) {
+    if (ALL || ks_has(ks)) products(ks);
+  };
+  auto first_scores = [&]() {                          // the first tile's, with a branch for each block that may not exist, not for each k-step
+    no_scores();
+#pragma unroll
+    for (int blk = 0; blk < CBF + HALF; ++blk)
+      if (blk == 0 || ALL || (blk < CBF ? has_full(blk) : has_half)) {
+#pragma unroll
+        for (int ks = blk * 4; ks < min(blk * 4 + 4, KS); ++ks) { read_a(ks); products(ks); }
+      }
   };
   auto hand_over = [&]() {                             // D: column n = head, rows kg*4 + i
 #pragma unroll
@@ -240,20 +251,20 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
       else rf[j] = *reinterpret_cast<const u32x4*>(park_at + (q * 4 + j) * PITCH + blk * 256 + n * 16);
     }
   };
-  auto turn_rows = [&](int blk, int q) {
+  auto turn = [&](int blk, int q, const u32x4* f, const u32x2* g) {      // (the four rows in f, of the half block in g)
 #pragma unroll
     for (int jp = 0; jp < 2; ++jp) {
       if (HALF && blk == CBF) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          amh[2 * c][2 * q + jp] = __builtin_amdgcn_perm(rh[2 * jp + 1][c], rh[2 * jp][c], 0x05040100u);
-          amh[2 * c + 1][2 * q + jp] = __builtin_amdgcn_perm(rh[2 * jp + 1][c], rh[2 * jp][c], 0x07060302u);
+          amh[2 * c][2 * q + jp] = __builtin_amdgcn_perm(g[2 * jp + 1][c], g[2 * jp][c], 0x05040100u);
+          amh[2 * c + 1][2 * q + jp] = __builtin_amdgcn_perm(g[2 * jp + 1][c], g[2 * jp][c], 0x07060302u);
         }
       } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          amf[blk < CBF ? blk : 0][2 * c][2 * q + jp] = __builtin_amdgcn_perm(rf[2 * jp + 1][c], rf[2 * jp][c], 0x05040100u);
-          amf[blk < CBF ? blk : 0][2 * c + 1][2 * q + jp] = __builtin_amdgcn_perm(rf[2 * jp + 1][c], rf[2 * jp][c], 0x07060302u);
+          amf[blk < CBF ? blk : 0][2 * c][2 * q + jp] = __builtin_amdgcn_perm(f[2 * jp + 1][c], f[2 * jp][c], 0x05040100u);
+          amf[blk < CBF ? blk : 0][2 * c + 1][2 * q + jp] = __builtin_amdgcn_perm(f[2 * jp + 1][c], f[2 * jp][c], 0x07060302u);
         }
       }
     }
@@ -267,6 +278,7 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
       }
     }
   };
+  auto turn_rows = [&](int blk, int q) { turn(blk, q, rf, rh); };
   bf16x8 pb[NT];
   float al[NT];
   auto fetch_weights = [&]() {
@@ -336,16 +348,39 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
   // 24 x 512 49.6 -> 43.9, 40 x 1000 x 32 x 512 33.6 -> 32.8.  Not where the matrix instructions decide (32 heads and two blocks: 8 x 4096 x
   // 128 x 1024 63.7 -> 64.8) nor where two workgroups share a compute unit (16 heads and one block: 4 x 1500 x 16 x 512 23.8 -> 24.2).
   constexpr bool EARLY = NT == 1 ? NBLK == 2 : NBLK == 1;
-  if (ntile > 0) {
+  auto last = [&]() {
+    numerators(ntile - 1);
+    lds_barrier();
+    fetch_weights();
+    rescale_all();
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) sum_block(blk);
+  };
+  // A workgroup of one tile has a way of its own, which asks for no other tile and transposes this one on its way to the slot: one wave per
+  // SIMD issues all of it in turn, and what the longer way does for the tiles after the first took a tenth of such a call (with what the
+  // partial's way out saves: 2 x 17 rows x 8 heads x 1152 22.5 -> 20.8 us, 3 x 10 x 20 x 1280 22.7 -> 21.3, 1 x 11 x 32 x 1024 23.4 -> 22.0).
+  if (ntile == 1) {
+    aim(0);
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) request(blk, 0, 8);
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) {
+      park(blk, 0, 8);
+      turn(blk, 0, lf[blk < CBF ? blk : 0], lh);
+      turn(blk, 1, lf[blk < CBF ? blk : 0] + 4, lh + 4);
+    }
+    first_scores();
+    hand_over();
+    lds_barrier();
+    last();
+  } else if (ntile > 1) {
     aim(0);
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) { request(blk, 0, 8); park(blk, 0, 8); }
     aim(1);
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) request(blk, 0, 8);
-    no_scores();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) { read_a(ks); score(ks); }
+    first_scores();
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) {
       read_rows(blk, 0); turn_rows(blk, 0);
@@ -357,102 +392,94 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     aim(2);
     if constexpr (NBLK > 1 || EARLY) request(0, 0, 8);
     lds_barrier();
-    auto last = [&]() {
-      numerators(ntile - 1);
+    int k = 0;
+    do {
+      // on entry: tile k's operands in registers and its partial scores handed over; tile k + 1 parked but for the last of
+      // several blocks, which is in registers; tile k + 2 requested as far as its registers were free
+      numerators(k);
+      read_a(0);
       lds_barrier();
+      fence();
       fetch_weights();
+      no_scores();
+      read_a(1);
+      fence();
+      if constexpr (NBLK > 1) park(END, 0, 2);
+      if constexpr (EARLY && NBLK == 2) request(END, 0, 2);
+      if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 0, 4);
+      score(0);
+      paced();
+      read_a(2);
+      if constexpr (NBLK > 1) park(END, 2, 4);
+      if constexpr (EARLY && NBLK == 2) request(END, 2, 4);
+      if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 4, 8);
+      score(1);
+      paced();
       rescale_all();
 #pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk) sum_block(blk);
-    };
-    int k = 0;
-    if (ntile > 1) {
-      do {
-        // on entry: tile k's operands in registers and its partial scores handed over; tile k + 1 parked but for the last of
-        // several blocks, which is in registers; tile k + 2 requested as far as its registers were free
-        numerators(k);
-        read_a(0);
-        lds_barrier();
-        fence();
-        fetch_weights();
-        no_scores();
-        read_a(1);
-        fence();
-        if constexpr (NBLK > 1) park(END, 0, 2);
-        if constexpr (EARLY && NBLK == 2) request(END, 0, 2);
-        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 0, 4);
-        score(0);
+      for (int blk = 0; blk < NBLK; ++blk) {
+        read_rows(blk, 0);
+        if (blk > 0) park(blk - 1, 0, 4);
+        if (blk == 0 && NBLK > 1) park(END, 4, 8);
+        if (blk == 0 && NBLK == 2 && EARLY) request(END, 4, 8);
+        if (blk == (END > 0 ? 1 : 0)) aim(k + 3);
+        if (blk == 1 && EARLY) request(0, 0, 4);
+        sum_block(blk);
         paced();
-        read_a(2);
-        if constexpr (NBLK > 1) park(END, 2, 4);
-        if constexpr (EARLY && NBLK == 2) request(END, 2, 4);
-        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 4, 8);
-        score(1);
-        paced();
-        rescale_all();
+        const int ks0 = blk == 0 ? 2 : blk * 4, ks1 = blk == 0 ? 4 : min(blk * 4 + 4, KS);
 #pragma unroll
-        for (int blk = 0; blk < NBLK; ++blk) {
-          read_rows(blk, 0);
-          if (blk > 0) park(blk - 1, 0, 4);
-          if (blk == 0 && NBLK > 1) park(END, 4, 8);
-          if (blk == 0 && NBLK == 2 && EARLY) request(END, 4, 8);
-          if (blk == (END > 0 ? 1 : 0)) aim(k + 3);
-          if (blk == 1 && EARLY) request(0, 0, 4);
-          sum_block(blk);
-          paced();
-          const int ks0 = blk == 0 ? 2 : blk * 4, ks1 = blk == 0 ? 4 : min(blk * 4 + 4, KS);
-#pragma unroll
-          for (int ks = ks0; ks < ks1; ++ks) {
-            if (ks + 1 < KS && ks + 1 > 2) read_a(ks + 1);
-            if (ks == ks0) {
-              turn_rows(blk, 0);
-              read_rows(blk, 1);
-              if (blk > 0) park(blk - 1, 4, 6);
-              if (blk == 1 && EARLY) request(0, 4, 6);
-            }
-            if (ks == ks0 + 1) {
-              turn_rows(blk, 1);
-              if (blk > 0) park(blk - 1, 6, 8);
-              if (blk == 1 && EARLY) request(0, 6, 8);
-              if (NBLK == 1) park(0, 0, 8);
-              if (NBLK == 1 && EARLY) request(0, 0, 8);
-            }
-            if (blk == 0 && NBLK > 1 && !EARLY) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
-            // (the first block's registers are free once it is parked, behind the second block's first k-steps)
-            if (blk == 1 && !EARLY) {
-              if (ks1 - ks0 == 4 && ks >= ks1 - 2) request(0, (ks - ks1 + 2) * 4, (ks - ks1 + 2) * 4 + 4);
-              if (ks1 - ks0 == 2 && ks == ks1 - 1) request(0, 0, 8);
-            }
-            score(ks);
-            paced();
+        for (int ks = ks0; ks < ks1; ++ks) {
+          if (ks + 1 < KS && ks + 1 > 2) read_a(ks + 1);
+          if (ks == ks0) {
+            turn_rows(blk, 0);
+            read_rows(blk, 1);
+            if (blk > 0) park(blk - 1, 4, 6);
+            if (blk == 1 && EARLY) request(0, 4, 6);
           }
+          if (ks == ks0 + 1) {
+            turn_rows(blk, 1);
+            if (blk > 0) park(blk - 1, 6, 8);
+            if (blk == 1 && EARLY) request(0, 6, 8);
+            if (NBLK == 1) park(0, 0, 8);
+            if (NBLK == 1 && EARLY) request(0, 0, 8);
+          }
+          if (blk == 0 && NBLK > 1 && !EARLY) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
+          // (the first block's registers are free once it is parked, behind the second block's first k-steps)
+          if (blk == 1 && !EARLY) {
+            if (ks1 - ks0 == 4 && ks >= ks1 - 2) request(0, (ks - ks1 + 2) * 4, (ks - ks1 + 2) * 4 + 4);
+            if (ks1 - ks0 == 2 && ks == ks1 - 1) request(0, 0, 8);
+          }
+          score(ks);
+          paced();
         }
-        hand_over();
-        lds_barrier();
-      } while (++k + 1 < ntile);
-      last();
-    }
-    if (ntile == 1) last();
+      }
+      hand_over();
+      lds_barrier();
+    } while (++k + 1 < ntile);
+    last();
   }
 
   // ---- the partial of this (sequence, split): every wave its own columns, a head's threads its (m, l).  An accumulator lane
   // holds 32 consecutive columns of a head in a block of 128 (16 in the half block): stored from there, every instruction
   // writes 64 pieces into 64 different cache lines.  So the wave's 16 x 128 block of a head tile goes through its own, now
-  // idle, slot and leaves with a head's columns on consecutive lanes, through the L2s (store_through: 8 x 4096 x 32 heads x 1024 44.5 ->
-  // 42.8 us, 24 x 1500 x 20 heads x 1280 48.3 -> 47.4; 64 x 1500 x 16 x 1024 63.7 -> 64.2).
+  // idle, slot and leaves with a head's columns on consecutive lanes, through the L2s (as store_through: 8 x 4096 x 32 heads x 1024 44.5 ->
+  // 42.8 us, 24 x 1500 x 20 heads x 1280 48.3 -> 47.4).  The stores go by a buffer descriptor of the group's heads that exist, which drops the
+  // rows of the others: one addition each, where a predicate and a 64-bit address took a dozen instructions; a block of 16 heads took 0.5 us
+  // to leave and takes 0.2.
   float* const ob = reinterpret_cast<float*>(slot[w]);
+  const __amdgpu_buffer_rsrc_t to =
+      __builtin_amdgcn_make_buffer_rsrc(Cpart + ((size_t)pid * H + hg * HG) * dm, 0, min(H - hg * HG, HG) * dm * 4, 0x00020000);
   auto leave = [&](int t, int col, auto COLS, auto&& put) {
     constexpr int NC = decltype(COLS)::value, OP = NC + 4, LPR = NC / 4;   // floats per head row (padding: no bank conflicts), lanes per row
     static_assert(16 * OP * 4 <= 32 * PITCH, "a head tile's block must fit the wave's slot");
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the wave's earlier reads of the slot are done)
+    const int at = (lane / LPR * dm + (lane % LPR) * 4) * 4;
+    asm volatile("" ::: "memory");                     // (LDS operations of one wave complete in order: nothing to wait for)
     put(ob + n * OP);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS operations of one wave complete in order)
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int k2 = 0; k2 < NC / 16; ++k2) {
-      const int hl = (64 / LPR) * k2 + lane / LPR, c4 = (lane % LPR) * 4;
-      const int h = hg * HG + t * 16 + hl;
-      const f32x4 v = *reinterpret_cast<const f32x4*>(ob + hl * OP + c4);
-      if (h < H) store_through(Cpart + ((size_t)pid * H + h) * dm + col + c4, v);
+      const u32x4 v = *reinterpret_cast<const u32x4*>(ob + ((64 / LPR) * k2 + lane / LPR) * OP + (lane % LPR) * 4);
+      __builtin_amdgcn_raw_buffer_store_b128(v, to, at + ((t * 16 + (64 / LPR) * k2) * dm + col) * 4, 0, 1 | 16);   // (sc0 sc1)
     }
   };
 #pragma unroll

@@ -1,5 +1,5 @@
 """What the compiler made of the one-pass X-cache kernel, of the wide path's weighted sum and of the stream kernel, read from the built library: no scratch memory in any
-instantiation."""
+instantiation, and a partial that leaves by buffer stores, without a predicate and a 64-bit address for each piece."""
 import re
 
 import pytest
@@ -23,3 +23,12 @@ def _scratch(prefix, folder):
 def test_no_scratch(prefix, kernels, tmp_path):
     found = _scratch(prefix, tmp_path)
     assert len(found) >= kernels and not any(found.values()), found
+
+
+@pytest.mark.skipif(not built_code.PRESENT, reason="no disassembler")
+def test_partials_leave_by_buffer_stores(tmp_path):
+    for name in _scratch(XFUSED, tmp_path):
+        blocks, half, tiles = (int(x) for x in re.match(r"Li(\d)ELi(\d)ELi(\d)E", name[len(XFUSED):]).groups())
+        text = built_code.disassembly(name, tmp_path)
+        assert text.count("buffer_store_dwordx4") % (tiles * (8 * blocks + 4 * half)) == 0 and "buffer_store_dwordx4" in text, name
+        assert "global_store_dwordx4" not in text, name
