@@ -59,7 +59,7 @@ constexpr int xf_per_cu(int CBF, int HALF, int NT) { return CBF == 1 && HALF + N
 template <int CBF, int HALF, int NT, bool ALL>
 __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_kernel(const uint16_t* qt, const uint16_t* X, long x_bstride,
                                                                const int32_t* seq_lens, int T, int B, int H, int dm, int nsplit,
-                                                               float* Cpart, float* mpart, float* lpart, int colocate) {
+                                                               float* Cpart, float* mpart, float* lpart, int colocate, int through) {
   constexpr int HG = 16 * NT;                          // heads per group
   constexpr int KS = CBF * 4 + HALF * 2;               // k-steps of 32 columns per wave
   constexpr int PITCH = xf_pitch(CBF, HALF);
@@ -462,10 +462,9 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
   // ---- the partial of this (sequence, split): every wave its own columns, a head's threads its (m, l).  An accumulator lane
   // holds 32 consecutive columns of a head in a block of 128 (16 in the half block): stored from there, every instruction
   // writes 64 pieces into 64 different cache lines.  So the wave's 16 x 128 block of a head tile goes through its own, now
-  // idle, slot and leaves with a head's columns on consecutive lanes, through the L2s (as store_through: 8 x 4096 x 32 heads x 1024 44.5 ->
-  // 42.8 us, 24 x 1500 x 20 heads x 1280 48.3 -> 47.4).  The stores go by a buffer descriptor of the group's heads that exist, which drops the
-  // rows of the others: one addition each, where a predicate and a 64-bit address took a dozen instructions; a block of 16 heads took 0.5 us
-  // to leave and takes 0.2.
+  // idle, slot and leaves with a head's columns on consecutive lanes, through the L2s where xfused_through says so.  The stores go by a
+  // buffer descriptor of the group's heads that exist, which drops the rows of the others: one addition each, where a predicate and a 64-bit
+  // address took a dozen instructions; a block of 16 heads took 0.5 us to leave and takes 0.2.
   float* const ob = reinterpret_cast<float*>(slot[w]);
   const __amdgpu_buffer_rsrc_t to =
       __builtin_amdgcn_make_buffer_rsrc(Cpart + ((size_t)pid * H + hg * HG) * dm, 0, min(H - hg * HG, HG) * dm * 4, 0x00020000);
@@ -476,11 +475,15 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     asm volatile("" ::: "memory");                     // (LDS operations of one wave complete in order: nothing to wait for)
     put(ob + n * OP);
     asm volatile("" ::: "memory");
+    auto rows = [&](auto POLICY) {
 #pragma unroll
-    for (int k2 = 0; k2 < NC / 16; ++k2) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(ob + ((64 / LPR) * k2 + lane / LPR) * OP + (lane % LPR) * 4);
-      __builtin_amdgcn_raw_buffer_store_b128(v, to, at + ((t * 16 + (64 / LPR) * k2) * dm + col) * 4, 0, 1 | 16);   // (sc0 sc1)
-    }
+      for (int k2 = 0; k2 < NC / 16; ++k2) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(ob + ((64 / LPR) * k2 + lane / LPR) * OP + (lane % LPR) * 4);
+        __builtin_amdgcn_raw_buffer_store_b128(v, to, at + ((t * 16 + (64 / LPR) * k2) * dm + col) * 4, 0, decltype(POLICY)::value);
+      }
+    };
+    if (through) rows(std::integral_constant<int, 1 | 16>{});            // (sc0 sc1)
+    else rows(std::integral_constant<int, 0>{});
   };
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -563,6 +566,11 @@ int xfused_splits(int B, int H, int T, int d_model) {
   return best;
 }
 
+// Whether that many bytes of partials leave through the L2s (store_through).  What is left dirty there is written back between the launches, 0.4 us for
+// 5 MB, 1.2 for 40; what goes to memory takes the longer way, 0.3 us of the launch's end whatever it is.  264 shapes: up to 1.8 MB 0.25 us a call faster
+// without (1 x 14 rows x 24 heads x 896 23.2 -> 22.9), from 2.6 MB 0.2 to 1.2 slower (8 x 4096 x 32 heads x 1024 42.8 and 44.5).
+bool xfused_through(size_t bytes) { return bytes >= ((size_t)9 << 18); }
+
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
                    int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
   const int nt = xfused_tiles(H, d_model), hg = 16 * nt;
@@ -572,7 +580,7 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
     auto with = [&](auto tiles) {
       hipLaunchKernelGGL((xfused_kernel<decltype(cbf)::value, decltype(half)::value, decltype(tiles)::value, decltype(all)::value>), grid,
                          dim3(XF_NW * 64), 0, st, (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H, d_model, nsplit,
-                         Cpart, mpart, lpart, colocate);
+                         Cpart, mpart, lpart, colocate, xfused_through(sizeof(float) * B * nsplit * H * d_model));
     };
     if constexpr (decltype(cbf)::value + decltype(half)::value < 3)       // (wider rows: 16 heads a group, xfused_tiles)
       if (nt == 2) return with(std::integral_constant<int, 2>{});

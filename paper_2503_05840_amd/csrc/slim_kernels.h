@@ -208,6 +208,7 @@ bool xfused_ok(int d_model);                 // (kernels_xfused.hip) one pass ov
 bool xcache_read_once(int B, int T, int d_model, int e, bool ragged, bool one_pass);   // (read_once)
 int xfused_splits(int B, int H, int T, int d_model);
 int xfused_most_splits(int B, int H, int T, int d_model);    // bound of the splits at T and every shorter context
+bool xfused_through(size_t bytes);           // whether that many bytes of partials leave through the L2s
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
                    int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 void launch_xweighted(const float* S, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,

@@ -40,3 +40,8 @@ def one_pass_splits(B, H, T, d_model):
     """Context splits of the one-pass X-cache kernel, and the most that any context up to T takes."""
     i = ctypes.c_int
     return tuple(_rule("_ZN4slim%sEiiii" % name, i, i, i, i, i)(B, H, T, d_model) for name in ("13xfused_splits", "18xfused_most_splits"))
+
+
+def one_pass_through(nbytes):
+    """Whether that many bytes of the one-pass X-cache kernel's partials leave through the L2s."""
+    return _rule("_ZN4slim14xfused_throughEm", ctypes.c_bool, ctypes.c_size_t)(nbytes)
