@@ -520,47 +520,53 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
 
 bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_model <= 1280; }
 
-// Head tiles per workgroup.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
+// Head tiles of a workgroup.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
 static int xfused_tiles(int H, int d_model) { return H > 16 && d_model <= 1024 ? 2 : 1; }
+static long xfused_groups(int H, int tiles) { return (H + 16 * tiles - 1) / (16 * tiles); }
+static int xfused_log_slots(int d_model, int tiles) { return d_model <= 512 && xf_per_cu(1, 0, tiles) == 2 ? 9 : 8; }   // workgroups at once: 256 or 512
 
-// Context splits of the one-pass kernel: one workgroup per (split, head group, sequence).
-static long xfused_units(int B, int H, int d_model) {
-  const int hg = 16 * xfused_tiles(H, d_model);
-  return (long)B * ((H + hg - 1) / hg);
-}
-static long xfused_slots(int H, int d_model) { return 256 * (d_model <= 512 ? xf_per_cu(1, 0, xfused_tiles(H, d_model)) : 1); }   // workgroups at once
-
-// At most: one per started 128 rows of T (a split may hold fewer: lengths below T, whole tiles), what the projection merges, and six more
-// than fill the chip once (beyond that 0.5 % of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials without bound).
-// Grows with T, and the workspace's partials with it.
+// Context splits, at most: one per started 128 rows of T (a split may hold fewer: lengths below T, whole tiles), what the projection merges,
+// and six more than fill the chip once (beyond that 0.5 % of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials
+// without bound).  Grows with T.
 int xfused_most_splits(int B, int H, int T, int d_model) {
-  const long units = xfused_units(B, H, d_model), fill = (xfused_slots(H, d_model) + units - 1) / units + 6;
+  const int tiles = xfused_tiles(H, d_model);
+  const long units = B * xfused_groups(H, tiles), fill = ((1 << xfused_log_slots(d_model, tiles)) + units - 1) / units + 6;
   const int most = (T + 127) / 128;
   return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
 }
 
-// Rounds of workgroups over the compute units with s splits: per XCD where the units are dealt to the XCDs (launch_xfused), else over all.
-static long xfused_rounds(int B, int H, int d_model, int s) {
-  const long slots = xfused_slots(H, d_model), units = (long)B * s, groups = xfused_units(1, H, d_model);
-  if (colocate_units(B * s)) return ((units + 7) / 8 * groups + slots / 8 - 1) / (slots / 8);
-  return (units * groups + slots - 1) / slots;
+// Rounds of workgroups over 2^log_slots with s splits: per XCD where the units are dealt to the XCDs (launch_xfused), else over all.
+static long xfused_rounds(int B, long groups, int log_slots, int s) {
+  const long units = (long)B * s;
+  if (colocate_units(B * s)) return ((units + 7) / 8 * groups + (1 << (log_slots - 3)) - 1) >> (log_slots - 3);
+  return (units * groups + (1 << log_slots) - 1) >> log_slots;
 }
 
-// The count that takes the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37 per head tile and 37
-// more; starting a workgroup, its first tile and its last, 1900 a round.  Whatever the splits, X comes at 120 per MB; the two overlap, but
-// not fully (the root of the squares).  A split costs 88 (a round trip of the merge) and 465 per MB of its partials (written here, read by
-// the projection).  Fitted to 840 shapes of the range (B up to 96, 6 to 128 heads, all widths, 200 to 8000 rows), 0.5 % slower than their best counts in
-// the mean; with one price for steps of every width, 1.5 %, because narrow rows and few heads were cut too fine (64 x 1500 rows x 16
-// heads x 512 columns 44.2 us, now 43.2) and others too coarsely, or into a second round on an XCD (27 x 1500 x 40 x 1280 83.7, now 69.1).
-int xfused_splits(int B, int H, int T, int d_model) {
-  const int tiles = (T + 31) / 32, most = xfused_most_splits(B, H, T, d_model);
-  const int ksteps = (d_model / 128 + 1) / 2 * 2;      // (CBF * 4 + HALF * 2 of launch_xfused)
-  const double step = 700 + 37.0 * ksteps * (xfused_tiles(H, d_model) + 1), rows = 120e-6 * 2 * B * T * d_model;
-  const double split = 88 + 465e-6 * 4 * B * H * d_model;
+// The context splits that take the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37
+// per head tile and 37 more; starting a workgroup, its first tile and its last, 1900 a round.  Whatever the splits, X comes at 120 per MB; the
+// two overlap, but not fully (the root of the squares).  A split costs 88 (a round trip of the merge) and 465 per MB of its partials
+// (written here, read by the projection).  Fitted to 840 shapes of the range (B up to 96, 6 to 128 heads, all widths, 200 to 8000 rows), 0.5 % slower
+// than their best counts in the mean; with one price for steps of every width, 1.5 %, because narrow rows and few heads were cut too fine (64 x 1500
+// rows x 16 heads x 512 columns 44.2 us, now 43.2) and others too coarsely, or into a second round on an XCD (27 x 1500 x 40 x 1280 83.7, now 69.1).
+//
+// Ragged batches: the lengths are the device's, so half of T is taken for their mean.  Where there is more than one round the workgroups take
+// their turns as others end, and the time is the load of a slot and most of the longest workgroup: priced as full rounds of the longest, batches of
+// many sequences were cut too coarsely (55 sequences of 100..7576 rows x 40 heads x 512 columns 154 us, now 117; 44 x 100..2655 x 128 x 768 149 and 119;
+// 121 such shapes 2.4 % slower than their best counts, now 1.6 %).
+int xfused_splits(int B, int H, int T, int d_model, bool ragged, int most) {
+  const double share = ragged ? 0.5 : 1.0;
+  const int tiles = (T + 31) / 32, ksteps = (d_model / 128 + 1) / 2 * 2;   // (CBF * 4 + HALF * 2 of launch_xfused)
+  const int nt = xfused_tiles(H, d_model), log_slots = xfused_log_slots(d_model, nt);
+  const long groups = xfused_groups(H, nt);
+  const double rows = 120e-6 * 2 * B * T * d_model * share, split = 88 + 465e-6 * 4 * B * H * d_model;
+  const double per_slot = (double)B * groups / (1 << log_slots), step = 700 + 37.0 * ksteps * (nt + 1);
   int best = 1;
   double best_cost = 0;
   for (int s = 1; s <= most; ++s) {
-    const double work = xfused_rounds(B, H, d_model, s) * ((tiles + s - 1) / s * step + 1900), cost = sqrt(work * work + rows * rows) + s * split;
+    const long rounds = xfused_rounds(B, groups, log_slots, s);
+    const double longest = (tiles + s - 1) / s * step + 1900, load = per_slot * (share * tiles * step + 1900 * s);
+    const double work = ragged && rounds > 1 ? std::min(rounds * longest, load + 0.8 * longest) : rounds * longest;
+    const double cost = sqrt(work * work + rows * rows) + s * split;
     if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
   }
   return best;
@@ -573,9 +579,9 @@ bool xfused_through(size_t bytes) { return bytes >= ((size_t)9 << 18); }
 
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
                    int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
-  const int nt = xfused_tiles(H, d_model), hg = 16 * nt;
+  const int nt = xfused_tiles(H, d_model);
   const int colocate = colocate_units(B * nsplit);
-  dim3 grid(unit_grid(B * nsplit, (H + hg - 1) / hg, colocate));
+  dim3 grid(unit_grid(B * nsplit, (int)xfused_groups(H, nt), colocate));
   auto go = [&](auto cbf, auto half, auto all) {
     auto with = [&](auto tiles) {
       hipLaunchKernelGGL((xfused_kernel<decltype(cbf)::value, decltype(half)::value, decltype(tiles)::value, decltype(all)::value>), grid,

@@ -36,10 +36,11 @@ def xcache_read_once(B, T, d_model, e, ragged, one_pass):
     return _rule("_ZN4slim16xcache_read_onceEiiiibb", b, i, i, i, i, b, b)(B, T, d_model, e, ragged, one_pass)
 
 
-def one_pass_splits(B, H, T, d_model):
+def one_pass_splits(B, H, T, d_model, ragged=False):
     """Context splits of the one-pass X-cache kernel, and the most that any context up to T takes."""
-    i = ctypes.c_int
-    return tuple(_rule("_ZN4slim%sEiiii" % name, i, i, i, i, i)(B, H, T, d_model) for name in ("13xfused_splits", "18xfused_most_splits"))
+    i, b = ctypes.c_int, ctypes.c_bool
+    most = _rule("_ZN4slim18xfused_most_splitsEiiii", i, i, i, i, i)(B, H, T, d_model)
+    return _rule("_ZN4slim13xfused_splitsEiiiibi", i, i, i, i, i, b, i)(B, H, T, d_model, ragged, most), most
 
 
 def one_pass_through(nbytes):

@@ -30,3 +30,15 @@ def test_counts_stay_within_the_workspace(d_model):
             for T in (1, 31, 128, 129, 1500, 4096, 70000):
                 splits, most = one_pass_splits(B, H, T, d_model)
                 assert 1 <= splits <= most <= 64
+
+
+@pytest.mark.parametrize("B,H,T,d_model,best", [   # lengths from 100 to T
+    (44, 128, 2655, 768, (2, 3, 4)),               # one split: 149 us, these 119 to 120
+    (58, 128, 4437, 512, (3, 4, 5)),               # one: 187, these 155 to 157
+    (53, 40, 3637, 640, (5, 6)),                   # two: 111, these 93 to 94
+    (53, 20, 2515, 1280, (5,)),                    # two: 99, five 87
+    (92, 40, 1661, 1024, (3,)),                    # one: 116, three 106
+    (16, 64, 4694, 512, (8,)),                     # one round of workgroups, as if all had T rows
+])
+def test_counts_of_ragged_batches_that_were_measured(B, H, T, d_model, best):
+    assert one_pass_splits(B, H, T, d_model, ragged=True)[0] in best
