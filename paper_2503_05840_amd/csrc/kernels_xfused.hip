@@ -520,8 +520,8 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
 
 bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_model <= 1280; }
 
-// Head tiles of a workgroup.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
-static int xfused_tiles(int H, int d_model) { return H > 16 && d_model <= 1024 ? 2 : 1; }
+// Head tiles of a workgroup, at most.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
+static int xfused_most_tiles(int H, int d_model) { return H > 16 && d_model <= 1024 ? 2 : 1; }
 static long xfused_groups(int H, int tiles) { return (H + 16 * tiles - 1) / (16 * tiles); }
 static int xfused_log_slots(int d_model, int tiles) { return d_model <= 512 && xf_per_cu(1, 0, tiles) == 2 ? 9 : 8; }   // workgroups at once: 256 or 512
 
@@ -529,7 +529,7 @@ static int xfused_log_slots(int d_model, int tiles) { return d_model <= 512 && x
 // and six more than fill the chip once (beyond that 0.5 % of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials
 // without bound).  Grows with T.
 int xfused_most_splits(int B, int H, int T, int d_model) {
-  const int tiles = xfused_tiles(H, d_model);
+  const int tiles = xfused_most_tiles(H, d_model);
   const long units = B * xfused_groups(H, tiles), fill = ((1 << xfused_log_slots(d_model, tiles)) + units - 1) / units + 6;
   const int most = (T + 127) / 128;
   return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
@@ -542,7 +542,7 @@ static long xfused_rounds(int B, long groups, int log_slots, int s) {
   return (units * groups + (1 << log_slots) - 1) >> log_slots;
 }
 
-// The context splits that take the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37
+// Head tiles and context splits: what takes the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37
 // per head tile and 37 more; starting a workgroup, its first tile and its last, 1900 a round.  Whatever the splits, X comes at 120 per MB; the
 // two overlap, but not fully (the root of the squares).  A split costs 88 (a round trip of the merge) and 465 per MB of its partials
 // (written here, read by the projection).  Fitted to 840 shapes of the range (B up to 96, 6 to 128 heads, all widths, 200 to 8000 rows), 0.5 % slower
@@ -551,23 +551,31 @@ static long xfused_rounds(int B, long groups, int log_slots, int s) {
 //
 // Ragged batches: the lengths are the device's, so half of T is taken for their mean.  Where there is more than one round the workgroups take
 // their turns as others end, and the time is the load of a slot and most of the longest workgroup: priced as full rounds of the longest, batches of
-// many sequences were cut too coarsely (55 sequences of 100..7576 rows x 40 heads x 512 columns 154 us, now 117; 44 x 100..2655 x 128 x 768 149 and 119;
+// many sequences were cut too coarsely (55 sequences of 100..7576 rows x 40 heads x 512 columns 154 us, now 122; 44 x 100..2655 x 128 x 768 149 and 120;
 // 121 such shapes 2.4 % slower than their best counts, now 1.6 %).
-int xfused_splits(int B, int H, int T, int d_model, bool ragged, int most) {
+//
+// Layers of more than 16 heads take groups of 16 where all of these fit the chip at once and cost less: their steps are shorter, and X, which
+// the groups share in an XCD's L2, is not what bounds so few rows.  (With 32 heads a group half of the chip stood idle: 2 x 490 rows x 32 heads x 1024
+// 27.8 -> 24.9 us, 6 x 14 x 64 x 1024 23.8 -> 21.9, 1 x 2998 x 64 x 640 30.7 -> 28.4.  Where they do not fit it is the other way: 18 x 2145 x 128
+// heads x 640 65.7 us, in groups of 16 84.9.  227 shapes: 0.2 % slower than the better of the two, always 32 heads a group 6 %.)
+XFusedCut xfused_cut(int B, int H, int T, int d_model, bool ragged, int most) {
   const double share = ragged ? 0.5 : 1.0;
   const int tiles = (T + 31) / 32, ksteps = (d_model / 128 + 1) / 2 * 2;   // (CBF * 4 + HALF * 2 of launch_xfused)
-  const int nt = xfused_tiles(H, d_model), log_slots = xfused_log_slots(d_model, nt);
-  const long groups = xfused_groups(H, nt);
   const double rows = 120e-6 * 2 * B * T * d_model * share, split = 88 + 465e-6 * 4 * B * H * d_model;
-  const double per_slot = (double)B * groups / (1 << log_slots), step = 700 + 37.0 * ksteps * (nt + 1);
-  int best = 1;
+  XFusedCut best{0, 1};
   double best_cost = 0;
-  for (int s = 1; s <= most; ++s) {
-    const long rounds = xfused_rounds(B, groups, log_slots, s);
-    const double longest = (tiles + s - 1) / s * step + 1900, load = per_slot * (share * tiles * step + 1900 * s);
-    const double work = ragged && rounds > 1 ? std::min(rounds * longest, load + 0.8 * longest) : rounds * longest;
-    const double cost = sqrt(work * work + rows * rows) + s * split;
-    if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
+  for (int nt = xfused_most_tiles(H, d_model); nt >= 1; --nt) {
+    const long groups = xfused_groups(H, nt);
+    const int log_slots = xfused_log_slots(d_model, nt);
+    const double per_slot = (double)B * groups / (1 << log_slots), step = 700 + 37.0 * ksteps * (nt + 1);
+    for (int s = 1; s <= most; ++s) {
+      if (nt < xfused_most_tiles(H, d_model) && xfused_rounds(B, groups, 8, s) > 1) break;
+      const long rounds = xfused_rounds(B, groups, log_slots, s);
+      const double longest = (tiles + s - 1) / s * step + 1900, load = per_slot * (share * tiles * step + 1900 * s);
+      const double work = ragged && rounds > 1 ? std::min(rounds * longest, load + 0.8 * longest) : rounds * longest;
+      const double cost = sqrt(work * work + rows * rows) + s * split;
+      if (!best.tiles || cost < best_cost) { best = {nt, s}; best_cost = cost; }
+    }
   }
   return best;
 }
@@ -578,8 +586,8 @@ int xfused_splits(int B, int H, int T, int d_model, bool ragged, int most) {
 bool xfused_through(size_t bytes) { return bytes >= ((size_t)9 << 18); }
 
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
-                   int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
-  const int nt = xfused_tiles(H, d_model);
+                   XFusedCut cut, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
+  const int nt = cut.tiles, nsplit = cut.splits;
   const int colocate = colocate_units(B * nsplit);
   dim3 grid(unit_grid(B * nsplit, (int)xfused_groups(H, nt), colocate));
   auto go = [&](auto cbf, auto half, auto all) {
@@ -588,7 +596,7 @@ void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t
                          dim3(XF_NW * 64), 0, st, (const uint16_t*)qt, (const uint16_t*)X, x_bstride, seq_lens, T, B, H, d_model, nsplit,
                          Cpart, mpart, lpart, colocate, xfused_through(sizeof(float) * B * nsplit * H * d_model));
     };
-    if constexpr (decltype(cbf)::value + decltype(half)::value < 3)       // (wider rows: 16 heads a group, xfused_tiles)
+    if constexpr (decltype(cbf)::value + decltype(half)::value < 3)       // (wider rows: 16 heads a group, xfused_most_tiles)
       if (nt == 2) return with(std::integral_constant<int, 2>{});
     with(std::integral_constant<int, 1>{});
   };

@@ -626,8 +626,9 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     int nsplit = p.nsplit_x;
     if (one_pass) {
       // d_model 512..1280: scores, numerators and weighted sum in one pass over X
-      nsplit = xfused_splits(B, H, T, d_model, lens != nullptr, p.most_xf);
-      launch_xfused(qt, X, xb, lens, T, H, d_model, nsplit, Cpart, mpart, lpart, B, st);
+      const XFusedCut cut = xfused_cut(B, H, T, d_model, lens != nullptr, p.most_xf);
+      nsplit = cut.splits;
+      launch_xfused(qt, X, xb, lens, T, H, d_model, cut, Cpart, mpart, lpart, B, st);
       tm.mark();
     } else {
       launch_xscores(qt, X, xb, lens, T, H, d_model, S, B, st);

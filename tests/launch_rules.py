@@ -36,11 +36,20 @@ def xcache_read_once(B, T, d_model, e, ragged, one_pass):
     return _rule("_ZN4slim16xcache_read_onceEiiiibb", b, i, i, i, i, b, b)(B, T, d_model, e, ragged, one_pass)
 
 
-def one_pass_splits(B, H, T, d_model, ragged=False):
-    """Context splits of the one-pass X-cache kernel, and the most that any context up to T takes."""
+class _Cut(ctypes.Structure):
+    _fields_ = [("tiles", ctypes.c_int), ("splits", ctypes.c_int)]
+
+
+def one_pass_cut(B, H, T, d_model, ragged=False):
+    """Head tiles of a workgroup of the one-pass X-cache kernel, context splits, and the most that any context up to T takes."""
     i, b = ctypes.c_int, ctypes.c_bool
     most = _rule("_ZN4slim18xfused_most_splitsEiiii", i, i, i, i, i)(B, H, T, d_model)
-    return _rule("_ZN4slim13xfused_splitsEiiiibi", i, i, i, i, i, b, i)(B, H, T, d_model, ragged, most), most
+    cut = _rule("_ZN4slim10xfused_cutEiiiibi", _Cut, i, i, i, i, b, i)(B, H, T, d_model, ragged, most)
+    return cut.tiles, cut.splits, most
+
+
+def one_pass_splits(B, H, T, d_model, ragged=False):
+    return one_pass_cut(B, H, T, d_model, ragged)[1:]
 
 
 def one_pass_through(nbytes):

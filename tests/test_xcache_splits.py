@@ -2,7 +2,7 @@
 counts whose steps cost a quarter to all of the longest, and batches that an even share of the compute units does not hold."""
 import pytest
 
-from launch_rules import one_pass_splits
+from launch_rules import one_pass_cut, one_pass_splits
 
 
 @pytest.mark.parametrize("B,H,T,d_model,best", [
@@ -10,8 +10,8 @@ from launch_rules import one_pass_splits
     (27, 16, 1500, 512, (6, 7, 8, 9, 10)),
     (32, 16, 1500, 1024, (5, 6)),
     (12, 24, 1500, 896, (10, 12)),                 # two head tiles
-    (13, 32, 1500, 640, (12,)),
-    (2, 128, 2290, 640, (16, 18, 20)),
+    (13, 32, 1500, 640, (8, 9)),                   # one head tile in a workgroup (below), as the next: 31.2 us, 12 splits of two tiles 32.5
+    (2, 128, 2290, 640, (11, 12, 13, 14, 15)),     # 32 to 33 us, 15 splits of two tiles 34.2
     (27, 40, 1500, 1280, (2,)),                    # three would take two rounds on some XCDs
     (7, 40, 1500, 1152, (10,)),
     (40, 128, 1500, 768, (3,)),                    # more than one round in any case
@@ -42,3 +42,19 @@ def test_counts_stay_within_the_workspace(d_model):
 ])
 def test_counts_of_ragged_batches_that_were_measured(B, H, T, d_model, best):
     assert one_pass_splits(B, H, T, d_model, ragged=True)[0] in best
+
+
+@pytest.mark.parametrize("B,H,T,d_model,tiles", [  # us with one head tile and with two
+    (2, 32, 490, 1024, 1),                         # 24.9, 27.8
+    (6, 64, 14, 1024, 1),                          # 21.9, 23.8
+    (1, 64, 2998, 640, 1),                         # 28.4, 30.7
+    (7, 64, 1654, 896, 1),                         # 33.6, 35.9
+    (18, 128, 2145, 640, 2),                       # 84.9, 65.7
+    (81, 64, 686, 512, 2),                         # 59.2, 55.3: two workgroups of one tile on a compute unit
+    (80, 128, 1405, 512, 2),                       # 141.1, 136.4
+    (8, 128, 4096, 1024, 2),
+    (24, 20, 1500, 1280, 1),                       # (two do not fit)
+    (8, 16, 4096, 1024, 1),
+])
+def test_head_tiles_that_were_measured(B, H, T, d_model, tiles):
+    assert one_pass_cut(B, H, T, d_model)[0] == tiles
