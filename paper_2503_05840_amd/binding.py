@@ -7,6 +7,7 @@ CPU fallback: if the built library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -242,13 +243,17 @@ def slim_read_probe(buf) -> None:
         raise SlimError(rc, "slim_read_probe")
 
 
+@functools.lru_cache(maxsize=None)
 def _current_stream(torch):
-    """Handle of the current device's current stream.  torch.cuda.current_stream() makes a Stream object for it, 2.8 us of the 13 that a
-    small call spends on the host; the raw handle takes 0.2."""
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None or not torch.cuda.is_initialized():
+    """A function that returns the handle of the current device's current stream.  torch.cuda.current_stream() makes a Stream object for it, 2.8 us of
+    the 13 that a small call spends on the host; the raw handle, where this torch has both functions that it takes, 0.2."""
+    raw, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+    def public():
         return torch.cuda.current_stream().cuda_stream
-    return raw(torch._C._cuda_getDevice())
+    if raw is None or device is None:
+        return public
+    return lambda: raw(device()) if torch.cuda.is_initialized() else public()
 
 
 def _opts(dtype, seq_lens, seq_lens_host, t_stride, workspace, variant, stage_ms=None, rope_table=None, wait_budget_us=0,
@@ -265,7 +270,7 @@ def _opts(dtype, seq_lens, seq_lens_host, t_stride, workspace, variant, stage_ms
     if workspace is not None:
         o.workspace = workspace.data_ptr()
         o.workspace_bytes = workspace.numel() * workspace.element_size()
-    o.stream = _current_stream(torch)
+    o.stream = _current_stream(torch)()
     o.variant = int(variant)
     if stage_ms is not None:      # a ctypes float array of MAX_STAGES entries, filled by the call
         o.stage_ms = ctypes.cast(stage_ms, ctypes.POINTER(ctypes.c_float))
