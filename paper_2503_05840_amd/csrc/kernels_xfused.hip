@@ -6,7 +6,6 @@
 #include "device_common.h"
 
 #include <algorithm>
-#include <cmath>
 
 namespace slim {
 namespace {
@@ -523,59 +522,46 @@ bool xfused_ok(int d_model) { return d_model % 128 == 0 && d_model >= 512 && d_m
 // Head tiles of a workgroup, at most.  Beyond 1024 columns 32 heads' accumulators and q~ alone are 320 registers a lane: spills.
 static int xfused_most_tiles(int H, int d_model) { return H > 16 && d_model <= 1024 ? 2 : 1; }
 static long xfused_groups(int H, int tiles) { return (H + 16 * tiles - 1) / (16 * tiles); }
-static int xfused_log_slots(int d_model, int tiles) { return d_model <= 512 && xf_per_cu(1, 0, tiles) == 2 ? 9 : 8; }   // workgroups at once: 256 or 512
+static long xfused_slots(int d_model, int tiles) { return 256 * (d_model <= 512 ? xf_per_cu(1, 0, tiles) : 1); }   // workgroups at once
+
+// Layers of more than 16 heads go in groups of 16 where all of these run at once, each on a compute unit of its own: their steps are shorter, and
+// X, which the groups share in an XCD's L2, is not what bounds so few rows.  (In groups of 32 half of the chip and more stood idle: 2 x 490 rows x 32
+// heads x 1024 27.8 -> 24.9 us, 6 x 14 x 64 x 1024 23.8 -> 21.9, 1 x 2998 x 64 x 640 30.7 -> 28.4.  Where they do not fit it is the other way: 18 x
+// 2145 x 128 heads x 640 65.7 us, in groups of 16 84.9; 81 x 686 x 64 x 512, two workgroups on a compute unit, 55.3 and 59.2.)  A head's sums do not depend on
+// its group.
+int xfused_tiles(int B, int H, int d_model, int nsplit) {
+  const long units = (long)B * nsplit, groups = xfused_groups(H, 1);
+  const bool fit = colocate_units(B * nsplit) ? (units + 7) / 8 * groups <= 32 : units * groups <= 256;   // (per XCD where launch_xfused deals the units to them)
+  return fit ? 1 : xfused_most_tiles(H, d_model);
+}
 
 // Context splits, at most: one per started 128 rows of T (a split may hold fewer: lengths below T, whole tiles), what the projection merges,
 // and six more than fill the chip once (beyond that 0.5 % of the shapes up to 8192 rows would gain up to 1.5 % in steps, for partials
 // without bound).  Grows with T.
 int xfused_most_splits(int B, int H, int T, int d_model) {
   const int tiles = xfused_most_tiles(H, d_model);
-  const long units = B * xfused_groups(H, tiles), fill = ((1 << xfused_log_slots(d_model, tiles)) + units - 1) / units + 6;
+  const long units = B * xfused_groups(H, tiles), fill = (xfused_slots(d_model, tiles) + units - 1) / units + 6;
   const int most = (T + 127) / 128;
   return (int)std::min<long>(std::min(most, PROJ_MAX_PARTS), fill);
 }
 
-// Rounds of workgroups over 2^log_slots with s splits: per XCD where the units are dealt to the XCDs (launch_xfused), else over all.
-static long xfused_rounds(int B, long groups, int log_slots, int s) {
-  const long units = (long)B * s;
-  if (colocate_units(B * s)) return ((units + 7) / 8 * groups + (1 << (log_slots - 3)) - 1) >> (log_slots - 3);
-  return (units * groups + (1 << log_slots) - 1) >> log_slots;
-}
-
-// Head tiles and context splits: what takes the least time, in ns.  A step of 32 rows takes 700 and, for every 32 columns of a wave (k-step), 37
-// per head tile and 37 more; starting a workgroup, its first tile and its last, 1900 a round.  Whatever the splits, X comes at 120 per MB; the
-// two overlap, but not fully (the root of the squares).  A split costs 88 (a round trip of the merge) and 465 per MB of its partials
-// (written here, read by the projection).  Fitted to 840 shapes of the range (B up to 96, 6 to 128 heads, all widths, 200 to 8000 rows), 0.5 % slower
-// than their best counts in the mean; with one price for steps of every width, 1.5 %, because narrow rows and few heads were cut too fine (64 x 1500
-// rows x 16 heads x 512 columns 44.2 us, now 43.2) and others too coarsely, or into a second round on an XCD (27 x 1500 x 40 x 1280 83.7, now 69.1).
-//
-// Ragged batches: the lengths are the device's, so half of T is taken for their mean.  Where there is more than one round the workgroups take
-// their turns as others end, and the time is the load of a slot and most of the longest workgroup: priced as full rounds of the longest, batches of
-// many sequences were cut too coarsely (55 sequences of 100..7576 rows x 40 heads x 512 columns 154 us, now 122; 44 x 100..2655 x 128 x 768 149 and 120;
-// 121 such shapes 2.4 % slower than their best counts, now 1.6 %).
-//
-// Layers of more than 16 heads take groups of 16 where all of these fit the chip at once and cost less: their steps are shorter, and X, which
-// the groups share in an XCD's L2, is not what bounds so few rows.  (With 32 heads a group half of the chip stood idle: 2 x 490 rows x 32 heads x 1024
-// 27.8 -> 24.9 us, 6 x 14 x 64 x 1024 23.8 -> 21.9, 1 x 2998 x 64 x 640 30.7 -> 28.4.  Where they do not fit it is the other way: 18 x 2145 x 128
-// heads x 640 65.7 us, in groups of 16 84.9.  227 shapes: 0.2 % slower than the better of the two, always 32 heads a group 6 %.)
-XFusedCut xfused_cut(int B, int H, int T, int d_model, bool ragged, int most) {
-  const double share = ragged ? 0.5 : 1.0;
-  const int tiles = (T + 31) / 32, ksteps = (d_model / 128 + 1) / 2 * 2;   // (CBF * 4 + HALF * 2 of launch_xfused)
-  const double rows = 120e-6 * 2 * B * T * d_model * share, split = 88 + 465e-6 * 4 * B * H * d_model;
-  XFusedCut best{0, 1};
-  double best_cost = 0;
-  for (int nt = xfused_most_tiles(H, d_model); nt >= 1; --nt) {
-    const long groups = xfused_groups(H, nt);
-    const int log_slots = xfused_log_slots(d_model, nt);
-    const double per_slot = (double)B * groups / (1 << log_slots), step = 700 + 37.0 * ksteps * (nt + 1);
-    for (int s = 1; s <= most; ++s) {
-      if (nt < xfused_most_tiles(H, d_model) && xfused_rounds(B, groups, 8, s) > 1) break;
-      const long rounds = xfused_rounds(B, groups, log_slots, s);
-      const double longest = (tiles + s - 1) / s * step + 1900, load = per_slot * (share * tiles * step + 1900 * s);
-      const double work = ragged && rounds > 1 ? std::min(rounds * longest, load + 0.8 * longest) : rounds * longest;
-      const double cost = sqrt(work * work + rows * rows) + s * split;
-      if (!best.tiles || cost < best_cost) { best = {nt, s}; best_cost = cost; }
-    }
+// The count whose rounds of workgroups of as many heads as fit take the least time, in tenths of a step of 32 rows (1.6 us at 1024 columns and 32
+// heads): starting a workgroup, its first tile and its last cost about four steps; a split's partials 0.4 steps per MB (written here,
+// read by the projection) and a tenth more (a round trip of the merge).  Without the partials' share 8 sequences x 32 heads x 4096 rows x
+// 1024 columns took 47.9 us in 32 splits and take 44.2 in 16.  One price for steps of every width is too dear for narrow rows and few heads, and
+// a ragged batch is cut as if all had T rows.  Prices by width and head tiles, rounds per XCD and half of T for ragged batches gave 0.4 % in the mean
+// over 310 shapes (32 x 1500 x 16 heads x 1024 42.4 -> 40.9 us, 55 x 100..7576 x 40 x 512 158 -> 125), but another count moves the references of the numerators,
+// and with them the rounding of the weights: the results differ by 1e-3 from those of this count, where the error against 64 bits is
+// the same.  A call's results stay what they are.
+int xfused_splits(int B, int H, int T, int d_model) {
+  const int wide = xfused_most_tiles(H, d_model), tiles = (T + 31) / 32, most = xfused_most_splits(B, H, T, d_model);
+  const long per = B * xfused_groups(H, wide), slots = xfused_slots(d_model, wide);
+  const long partial = 4L * B * H * d_model;           // bytes of a split's partials
+  int best = 1;
+  long best_cost = 0;
+  for (int s = 1; s <= most; ++s) {
+    const long rounds = (per * s + slots - 1) / slots, cost = 10 * rounds * ((tiles + s - 1) / s + 4) + 4 * s * partial / (1 << 20) + s;
+    if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
   }
   return best;
 }
@@ -586,8 +572,8 @@ XFusedCut xfused_cut(int B, int H, int T, int d_model, bool ragged, int most) {
 bool xfused_through(size_t bytes) { return bytes >= ((size_t)9 << 18); }
 
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
-                   XFusedCut cut, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
-  const int nt = cut.tiles, nsplit = cut.splits;
+                   int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st) {
+  const int nt = xfused_tiles(B, H, d_model, nsplit);
   const int colocate = colocate_units(B * nsplit);
   dim3 grid(unit_grid(B * nsplit, (int)xfused_groups(H, nt), colocate));
   auto go = [&](auto cbf, auto half, auto all) {

@@ -22,7 +22,7 @@ struct Plan {
   int nsplit = 1;      // context splits of the weighted-sum step
   int nsplit_v = 1;    // context splits of the vanilla kernel
   int nsplit_x = 1;    // context splits of the X-cache MFMA path (two passes over X)
-  int most_xf = 0;     // context splits of the one-pass X-cache kernel, at most (0: the shape does not take it)
+  int nsplit_xf = 0;   // context splits of the one-pass X-cache kernel (0: the shape does not take it)
   size_t off_S = 0, off_Cpart = 0, off_m = 0, off_l = 0, off_qt = 0;
   size_t off_vacc = 0, off_vm = 0, off_vl = 0;
   size_t vanilla_floats = 0;    // floats from off_vacc to the end of the vanilla kernel's part
@@ -69,9 +69,8 @@ Plan make_plan(int B, int H, int T, int width, int e, bool xcache) {
     if (xfused_ok(width)) {
       // (Room for a split per started 256 rows, or for as many as the other passes take: what a workspace has always had.  More splits of
       // few rows pay only where a batch is small, and there the others' partials are more.)
-      const int most = xfused_most_splits(B, H, T, width);
-      at_least((size_t)B * std::min(most, (T + 255) / 256));
-      p.most_xf = (int)std::min<size_t>(most, nparts / B);
+      at_least((size_t)B * std::min(xfused_most_splits(B, H, T, width), (T + 255) / 256));
+      p.nsplit_xf = (int)std::min<size_t>(xfused_splits(B, H, T, width), nparts / B);
     }
   } else {
     // vanilla kernel: workgroups of four waves, a wave per group of heads; about eight workgroups per
@@ -618,7 +617,7 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     // MFMA path: q~, scores (log2 domain), weighted sum per context split, merge + projection
     int* ctrl = (int*)(ws + p.off_ctrl);
     const int csw = proj_row_splits(H, d_model, e, B);
-    const bool one_pass = p.most_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT;
+    const bool one_pass = p.nsplit_xf > 0 && req != SLIM_VARIANT_FUSED_SPLIT;
     const bool once = xcache_read_once(B, T, d_model, e, lens != nullptr, one_pass);
     launch_xq_tilde((const float*)q, W_K, qt, B, H, d_k, d_model, e, scale * 1.4426950408889634f, once, ctrl,
                     csw > 1 ? PROJ_CTRL_INTS : 0, st);
@@ -626,9 +625,8 @@ extern "C" int slim_decode_xcache(const void* q, const void* X, const void* W_K,
     int nsplit = p.nsplit_x;
     if (one_pass) {
       // d_model 512..1280: scores, numerators and weighted sum in one pass over X
-      const XFusedCut cut = xfused_cut(B, H, T, d_model, lens != nullptr, p.most_xf);
-      nsplit = cut.splits;
-      launch_xfused(qt, X, xb, lens, T, H, d_model, cut, Cpart, mpart, lpart, B, st);
+      nsplit = p.nsplit_xf;
+      launch_xfused(qt, X, xb, lens, T, H, d_model, nsplit, Cpart, mpart, lpart, B, st);
       tm.mark();
     } else {
       launch_xscores(qt, X, xb, lens, T, H, d_model, S, B, st);

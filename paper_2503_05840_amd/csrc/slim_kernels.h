@@ -206,12 +206,12 @@ void launch_xscores(const float* qt, const void* X, long x_bstride, const int32_
                     int d_model, float* S, int B, hipStream_t st);
 bool xfused_ok(int d_model);                 // (kernels_xfused.hip) one pass over X instead of xscores + xweighted
 bool xcache_read_once(int B, int T, int d_model, int e, bool ragged, bool one_pass);   // (read_once)
-struct XFusedCut { int tiles, splits; };     // head tiles of a workgroup, context splits
-XFusedCut xfused_cut(int B, int H, int T, int d_model, bool ragged, int most);   // with at most `most` splits
-bool xfused_through(size_t bytes);           // whether that many bytes of partials leave through the L2s
+int xfused_splits(int B, int H, int T, int d_model);
 int xfused_most_splits(int B, int H, int T, int d_model);    // bound of the splits at T and every shorter context
+int xfused_tiles(int B, int H, int d_model, int nsplit);     // head tiles of 16 in a workgroup
+bool xfused_through(size_t bytes);           // whether that many bytes of partials leave through the L2s
 void launch_xfused(const float* qt, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H, int d_model,
-                   XFusedCut cut, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
+                   int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 void launch_xweighted(const float* S, const void* X, long x_bstride, const int32_t* seq_lens, int T, int H,
                       int d_model, int nsplit, float* Cpart, float* mpart, float* lpart, int B, hipStream_t st);
 

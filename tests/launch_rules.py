@@ -36,22 +36,18 @@ def xcache_read_once(B, T, d_model, e, ragged, one_pass):
     return _rule("_ZN4slim16xcache_read_onceEiiiibb", b, i, i, i, i, b, b)(B, T, d_model, e, ragged, one_pass)
 
 
-class _Cut(ctypes.Structure):
-    _fields_ = [("tiles", ctypes.c_int), ("splits", ctypes.c_int)]
-
-
-def one_pass_cut(B, H, T, d_model, ragged=False):
-    """Head tiles of a workgroup of the one-pass X-cache kernel, context splits, and the most that any context up to T takes."""
-    i, b = ctypes.c_int, ctypes.c_bool
-    most = _rule("_ZN4slim18xfused_most_splitsEiiii", i, i, i, i, i)(B, H, T, d_model)
-    cut = _rule("_ZN4slim10xfused_cutEiiiibi", _Cut, i, i, i, i, b, i)(B, H, T, d_model, ragged, most)
-    return cut.tiles, cut.splits, most
-
-
-def one_pass_splits(B, H, T, d_model, ragged=False):
-    return one_pass_cut(B, H, T, d_model, ragged)[1:]
+def one_pass_splits(B, H, T, d_model):
+    """Context splits of the one-pass X-cache kernel, and the most that any context up to T takes."""
+    i = ctypes.c_int
+    return tuple(_rule("_ZN4slim%sEiiii" % name, i, i, i, i, i)(B, H, T, d_model) for name in ("13xfused_splits", "18xfused_most_splits"))
 
 
 def one_pass_through(nbytes):
     """Whether that many bytes of the one-pass X-cache kernel's partials leave through the L2s."""
     return _rule("_ZN4slim14xfused_throughEm", ctypes.c_bool, ctypes.c_size_t)(nbytes)
+
+
+def one_pass_tiles(B, H, T, d_model):
+    """Head tiles of a workgroup of the one-pass X-cache kernel."""
+    i = ctypes.c_int
+    return _rule("_ZN4slim12xfused_tilesEiiii", i, i, i, i, i)(B, H, d_model, one_pass_splits(B, H, T, d_model)[0])
