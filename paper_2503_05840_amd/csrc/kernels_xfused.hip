@@ -160,13 +160,16 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
   auto score = [&](int ks) {
     if (ALL || ks_has(ks)) products(ks);
   };
-  auto first_scores = [&]() {                          // the first tile's, with a branch for each block that may not exist, not for each k-step
+  // The first tile's: a branch for each block that may not exist, not for each k-step.  (Two head tiles: for each k-step, and one way for every
+  // number of tiles, below.  Their small batches go in groups of 16, and with either change the compiler moves more registers in the loop: 36 x
+  // 7172 rows x 64 heads x 640 139.3 -> 144.3 us, 22 x 3777 x 128 x 1024 125.9 -> 130.7.)
+  auto first_scores = [&]() {
     no_scores();
 #pragma unroll
     for (int blk = 0; blk < CBF + HALF; ++blk)
-      if (blk == 0 || ALL || (blk < CBF ? has_full(blk) : has_half)) {
+      if (NT == 2 || blk == 0 || ALL || (blk < CBF ? has_full(blk) : has_half)) {
 #pragma unroll
-        for (int ks = blk * 4; ks < min(blk * 4 + 4, KS); ++ks) { read_a(ks); products(ks); }
+        for (int ks = blk * 4; ks < min(blk * 4 + 4, KS); ++ks) { read_a(ks); if (NT == 2) score(ks); else products(ks); }
       }
   };
   auto hand_over = [&]() {                             // D: column n = head, rows kg*4 + i
@@ -357,8 +360,8 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
   };
   // A workgroup of one tile has a way of its own, which asks for no other tile and transposes this one on its way to the slot: one wave per
   // SIMD issues all of it in turn, and what the longer way does for the tiles after the first took a tenth of such a call (with what the
-  // partial's way out saves: 2 x 17 rows x 8 heads x 1152 22.5 -> 20.8 us, 3 x 10 x 20 x 1280 22.7 -> 21.3, 1 x 11 x 32 x 1024 23.4 -> 22.0).
-  if (ntile == 1) {
+  // partial's way out saves: 2 x 17 rows x 8 heads x 1152 22.5 -> 20.8 us, 3 x 10 x 20 x 1280 22.7 -> 21.3).
+  if (NT == 1 && ntile == 1) {
     aim(0);
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) request(blk, 0, 8);
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     hand_over();
     lds_barrier();
     last();
-  } else if (ntile > 1) {
+  } else if (ntile > 0) {
     aim(0);
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) { request(blk, 0, 8); park(blk, 0, 8); }
@@ -392,70 +395,73 @@ __global__ __launch_bounds__(XF_NW * 64, xf_per_cu(CBF, HALF, NT)) void xfused_k
     if constexpr (NBLK > 1 || EARLY) request(0, 0, 8);
     lds_barrier();
     int k = 0;
-    do {
-      // on entry: tile k's operands in registers and its partial scores handed over; tile k + 1 parked but for the last of
-      // several blocks, which is in registers; tile k + 2 requested as far as its registers were free
-      numerators(k);
-      read_a(0);
-      lds_barrier();
-      fence();
-      fetch_weights();
-      no_scores();
-      read_a(1);
-      fence();
-      if constexpr (NBLK > 1) park(END, 0, 2);
-      if constexpr (EARLY && NBLK == 2) request(END, 0, 2);
-      if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 0, 4);
-      score(0);
-      paced();
-      read_a(2);
-      if constexpr (NBLK > 1) park(END, 2, 4);
-      if constexpr (EARLY && NBLK == 2) request(END, 2, 4);
-      if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 4, 8);
-      score(1);
-      paced();
-      rescale_all();
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk) {
-        read_rows(blk, 0);
-        if (blk > 0) park(blk - 1, 0, 4);
-        if (blk == 0 && NBLK > 1) park(END, 4, 8);
-        if (blk == 0 && NBLK == 2 && EARLY) request(END, 4, 8);
-        if (blk == (END > 0 ? 1 : 0)) aim(k + 3);
-        if (blk == 1 && EARLY) request(0, 0, 4);
-        sum_block(blk);
+    if (ntile > 1) {
+      do {
+        // on entry: tile k's operands in registers and its partial scores handed over; tile k + 1 parked but for the last of
+        // several blocks, which is in registers; tile k + 2 requested as far as its registers were free
+        numerators(k);
+        read_a(0);
+        lds_barrier();
+        fence();
+        fetch_weights();
+        no_scores();
+        read_a(1);
+        fence();
+        if constexpr (NBLK > 1) park(END, 0, 2);
+        if constexpr (EARLY && NBLK == 2) request(END, 0, 2);
+        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 0, 4);
+        score(0);
         paced();
-        const int ks0 = blk == 0 ? 2 : blk * 4, ks1 = blk == 0 ? 4 : min(blk * 4 + 4, KS);
+        read_a(2);
+        if constexpr (NBLK > 1) park(END, 2, 4);
+        if constexpr (EARLY && NBLK == 2) request(END, 2, 4);
+        if constexpr (NBLK != 2 && !(NBLK == 1 && EARLY)) request(NBLK == 1 ? 0 : 1, 4, 8);
+        score(1);
+        paced();
+        rescale_all();
 #pragma unroll
-        for (int ks = ks0; ks < ks1; ++ks) {
-          if (ks + 1 < KS && ks + 1 > 2) read_a(ks + 1);
-          if (ks == ks0) {
-            turn_rows(blk, 0);
-            read_rows(blk, 1);
-            if (blk > 0) park(blk - 1, 4, 6);
-            if (blk == 1 && EARLY) request(0, 4, 6);
-          }
-          if (ks == ks0 + 1) {
-            turn_rows(blk, 1);
-            if (blk > 0) park(blk - 1, 6, 8);
-            if (blk == 1 && EARLY) request(0, 6, 8);
-            if (NBLK == 1) park(0, 0, 8);
-            if (NBLK == 1 && EARLY) request(0, 0, 8);
-          }
-          if (blk == 0 && NBLK > 1 && !EARLY) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
-          // (the first block's registers are free once it is parked, behind the second block's first k-steps)
-          if (blk == 1 && !EARLY) {
-            if (ks1 - ks0 == 4 && ks >= ks1 - 2) request(0, (ks - ks1 + 2) * 4, (ks - ks1 + 2) * 4 + 4);
-            if (ks1 - ks0 == 2 && ks == ks1 - 1) request(0, 0, 8);
-          }
-          score(ks);
+        for (int blk = 0; blk < NBLK; ++blk) {
+          read_rows(blk, 0);
+          if (blk > 0) park(blk - 1, 0, 4);
+          if (blk == 0 && NBLK > 1) park(END, 4, 8);
+          if (blk == 0 && NBLK == 2 && EARLY) request(END, 4, 8);
+          if (blk == (END > 0 ? 1 : 0)) aim(k + 3);
+          if (blk == 1 && EARLY) request(0, 0, 4);
+          sum_block(blk);
           paced();
+          const int ks0 = blk == 0 ? 2 : blk * 4, ks1 = blk == 0 ? 4 : min(blk * 4 + 4, KS);
+#pragma unroll
+          for (int ks = ks0; ks < ks1; ++ks) {
+            if (ks + 1 < KS && ks + 1 > 2) read_a(ks + 1);
+            if (ks == ks0) {
+              turn_rows(blk, 0);
+              read_rows(blk, 1);
+              if (blk > 0) park(blk - 1, 4, 6);
+              if (blk == 1 && EARLY) request(0, 4, 6);
+            }
+            if (ks == ks0 + 1) {
+              turn_rows(blk, 1);
+              if (blk > 0) park(blk - 1, 6, 8);
+              if (blk == 1 && EARLY) request(0, 6, 8);
+              if (NBLK == 1) park(0, 0, 8);
+              if (NBLK == 1 && EARLY) request(0, 0, 8);
+            }
+            if (blk == 0 && NBLK > 1 && !EARLY) request(END, (ks - ks0) * 4, (ks - ks0) * 4 + 4);
+            // (the first block's registers are free once it is parked, behind the second block's first k-steps)
+            if (blk == 1 && !EARLY) {
+              if (ks1 - ks0 == 4 && ks >= ks1 - 2) request(0, (ks - ks1 + 2) * 4, (ks - ks1 + 2) * 4 + 4);
+              if (ks1 - ks0 == 2 && ks == ks1 - 1) request(0, 0, 8);
+            }
+            score(ks);
+            paced();
+          }
         }
-      }
-      hand_over();
-      lds_barrier();
-    } while (++k + 1 < ntile);
-    last();
+        hand_over();
+        lds_barrier();
+      } while (++k + 1 < ntile);
+      last();
+    }
+    if (NT > 1 && ntile == 1) last();
   }
 
   // ---- the partial of this (sequence, split): every wave its own columns, a head's threads its (m, l).  An accumulator lane
