@@ -23,9 +23,9 @@ __device__ __forceinline__ int seq_len_of(const int32_t* lens, int b, int T) {
 }
 
 // Partials that a later launch reads, stored through the L2s to the memory side: what is left dirty there is written back between the
-// launches, and the next one starts that much later (4 us after 9 MB).  For whole lines only: pieces of 16 bytes took 12 %
-// longer, and the partials of the by-sequence stream and of the wide path's weighted sum, which leave while others still stream or in such
-// pieces, 1-3 %.  (The s_nops: a store of more than 64 bits still reads its data registers in the wait states after it issues, and the compiler,
+// launches, and the next one starts that much later (4 us after 9 MB).  For instructions that store runs of 256 bytes and more (they need not
+// begin or end with a line: fp32 rows of 40 columns, units of heads of 80): pieces of 16 bytes took 12 % longer, and the partials of the
+// by-sequence stream and of the wide path's weighted sum, which leave while others still stream or in such pieces, 1-3 %.  (The s_nops: a store of more than 64 bits still reads its data registers in the wait states after it issues, and the compiler,
 // which pads its own stores, is free to overwrite the inputs of an asm statement with the very next vector instruction.)
 __device__ __forceinline__ void store_through(float* p, f32x4 v) {
   asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");

@@ -86,8 +86,7 @@ __device__ __forceinline__ void st_result(int* p, int v, bool write_through) {
 }
 
 __device__ __forceinline__ void st_result4(float* p, f32x4 v, bool write_through) {
-  // (s_nops: see st_exch)
-  if (write_through) asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+  if (write_through) store_through(p, v);
   else *reinterpret_cast<f32x4*>(p) = v;
 }
 
@@ -1048,9 +1047,10 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
         f32x4 osum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ww = 0; ww < NP; ++ww) osum += part[jj][ww];
-        // (Through the L2s also where a launch of its own reads them, for two head tiles: 32 ragged x 1000 rows x 32 heads x 128
-        // 80.6 -> 78.4 us.  The partials of up to 16 heads are small, and the way to memory is the longer one: 96 x 448 x 8 heads x
-        // 64 31.7 -> 32.0 us, 24 x 1500 x 12 heads 31.8 -> 32.3.)
+        // (Through the L2s also where a launch of its own reads them, for two head tiles: 0.2 us of a call slower up to 7 MB of partials, the
+        // same up to 12, 0.6 to 3 us faster from there (80 shapes; units that share lines, heads of 40 or 80 columns, no other than whole lines).
+        // For one tile, up to 10 MB, the way to memory is the longer one: 0.3 to 1.8 us (129 shapes).  A choice by the bytes when the kernel runs
+        // costs its calls 0.5 to 1 %, more than it gives.)
         if (h < a.H) st_result4(a.Cpart + ((size_t)pid * a.H + h) * a.d + ucol0 + oc4, osum, NT == 2 || fuse);
       }
     }
