@@ -1493,8 +1493,8 @@ __global__ __launch_bounds__(FUSED_WAVES * 64) void fused_stream_kernel(const Fu
       // ---- by context: merge the waves and write one partial (every wave of the workgroup walks the
       //      same shares, so all of them meet at these barriers) -------------------------------------
       // What depends on the lane is made here, from a lane number made here, as in the by-sequence partial above: made before the
-      // stream, it waited in scratch (60 bytes a lane, 88 with rotary keys), a round trip for each piece that is fetched back, and a kernel
-      // with scratch starts later as well.  Without any: 1 x 16384 rows x 32 heads x 128 51.8 -> 43.7 us, 1 x 200 22.9 -> 19.7,
+      // stream, it waited in scratch (60 bytes a lane, 88 with rotary keys), a round trip for each piece that is fetched
+      // back.  Without any, and with what else is said here: 1 x 16384 rows x 32 heads x 128 51.8 -> 43.7 us, 1 x 200 22.9 -> 19.7,
       // 8 ragged x 5000 x 32 x 96 with rotary keys 66.6 -> 59.9, 16 ragged x 32768 (banded) 370 -> 351; 64 x 1500 x 20 x 64, 12
       // bytes before, 70.6 -> 69.1.  (Barriers for LDS only: __syncthreads() would also wait for the requests past the end and,
       // between shares, for the partial's write-through stores, whose arrival only the flag at the end of the launch depends on.)

@@ -49,8 +49,8 @@ constexpr int xf_per_cu(int CBF, int HALF, int NT) { return CBF == 1 && HALF + N
 // (1600 cycles), 16 LDS writes (20 each), 38 reads, 64 transpositions, 16 requests -- and the numerators, during which the
 // matrix cores wait: 3400 cycles a tile.  Eight waves of 128 columns (two per SIMD, two phases of latency behind three barriers'
 // worth of LDS round trips, partial scores of eight owners) took 4900; the registers for this order of a step are not there
-// with two waves per SIMD.  8 sequences x 128 heads x 4096 rows x 1024 columns: 45.6 -> 40.9 us, the call 69.3 -> 64.5;
-// 24 x 1500 x 20 heads x 1280 51.9 -> 48.1, 4 x 1000 x 64 heads x 768 37.3 -> 29.9, 4 x 1500 x 8 heads x 512 27.3 -> 24.1.
+// with two waves per SIMD.  8 sequences x 128 heads x 4096 rows x 1024 columns: 45.6 -> 39.5 us, the call 69.3 -> 63.0;
+// 24 x 1500 x 20 heads x 1280 51.9 -> 46.9, 4 x 1000 x 64 heads x 768 37.3 -> 29.9, 4 x 1500 x 8 heads x 512 27.3 -> 24.1.
 // Tried on it: the numerators beside the weighted sum (3800 cycles: the parking then crowds into that phase), tiles touched
 // two steps ahead so that they come from L2 (5 us slower: 64 lines an instruction), and requests and parking in one place
 // each instead of spread over the matrix instructions (4900 cycles).
